@@ -15,6 +15,7 @@ _SO = os.path.join(_HERE, "libprunetrain.so")
 _lib = None
 
 PT_OK = 0
+ERR_WORKSPACE, ERR_UNSUPPORTED = -3, -4
 STATUS = {0: "PT_OK", -1: "PT_ERR_NULL", -2: "PT_ERR_SHAPE", -3: "PT_ERR_WORKSPACE", -4: "PT_ERR_UNSUPPORTED",
           -5: "PT_ERR_LAUNCH", -6: "PT_ERR_EMPTY"}
 LASSO_OUT, LASSO_IN = 1, 2
@@ -362,6 +363,11 @@ def layer_lasso(w, out_norm, in_norm, dw, K, RS, Cc, w_cpitch, flags) -> LayerLa
 
 def _array(items, typ):
     return items if isinstance(items, C.Array) else (typ * max(1, len(items)))(*items)
+
+
+def part_of(jobs: C.Array, first: int, end: int) -> C.Array:
+    """jobs[first:end] as an array that shares its memory."""
+    return (jobs._type_ * (end - first)).from_buffer(jobs, first * C.sizeof(jobs._type_))
 
 
 def group_norms_batched_workspace_bytes(layers) -> int:

@@ -1,0 +1,190 @@
+"""Host side of the harness without a GPU: tensors live in host memory, streams and events are stand-ins, and every
+library call that would launch something is recorded instead.  Queries (workspaces, plans) go to the real library."""
+import contextlib
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_1901_09290_amd import binding as B
+from paper_1901_09290_amd import harness as hz
+from paper_1901_09290_amd import workloads as wl
+
+
+def _pointers(v, out):
+    """Every address in a call's argument: plain integers, void pointers, fields of structures, elements of arrays."""
+    if isinstance(v, (int, C.c_void_p)):
+        out.append(v if isinstance(v, int) else v.value)
+    elif isinstance(v, C.Array):
+        for e in v:
+            _pointers(e, out)
+    elif isinstance(v, C.Structure):
+        for name, typ in v._fields_:
+            if typ is C.c_void_p:
+                out.append(getattr(v, name))
+
+
+class _Recorder:
+    """Stands in for the loaded library: launching calls are noted as (name, addresses) and answered by `status`."""
+
+    def __init__(self, real):
+        self.real, self.calls, self.status = real, [], lambda name, args: 0
+
+    def __getattr__(self, name):
+        if name.endswith("_bytes") or name.endswith("_plan") and name != "pt_compact_plan" or name.startswith("pt_last"):
+            return getattr(self.real, name)
+
+        def call(*args):
+            seen = []
+            for a in args:
+                _pointers(a, seen)
+            self.calls.append((name, seen))
+            return self.status(name, args)
+        return call
+
+    def seen(self, prefix=""):
+        return {p for name, ps in self.calls if name.startswith(prefix) for p in ps}
+
+
+class _Stream:
+    cuda_stream = 0
+
+    def wait_stream(self, other):
+        pass
+
+    def wait_event(self, event):
+        pass
+
+
+class _Event:
+    def record(self, stream=None):
+        pass
+
+    def synchronize(self):
+        pass
+
+
+@pytest.fixture
+def recorded(monkeypatch):
+    rec = _Recorder(B.lib())
+    monkeypatch.setattr(B, "lib", lambda: rec)
+    monkeypatch.setattr(B, "_raw_stream", lambda: 0)
+    monkeypatch.setattr(hz, "DEV", "cpu")
+    main = _Stream()
+    monkeypatch.setattr(torch.cuda, "Stream", _Stream)
+    monkeypatch.setattr(torch.cuda, "Event", _Event)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: main)
+    monkeypatch.setattr(torch.cuda, "stream", lambda s: contextlib.nullcontext())
+    return rec
+
+
+def residual_block(N=2):
+    """A first layer, a residual block with a shortcut convolution and a strided layer behind it."""
+    return [
+        wl.ConvSpec("first", N, 16, 16, 3, 24, 3, 3, 1, 1, None, 0, first=True),
+        wl.ConvSpec("b_a", N, 16, 16, 24, 16, 1, 1, 1, 0, 0, 1),
+        wl.ConvSpec("b_b", N, 16, 16, 16, 16, 3, 3, 1, 1, 1, 2),
+        wl.ConvSpec("b_c", N, 16, 16, 16, 40, 1, 1, 1, 0, 2, 3),
+        wl.ConvSpec("b_proj", N, 16, 16, 24, 40, 1, 1, 1, 0, 0, 3),
+        wl.ConvSpec("last", N, 16, 16, 40, 33, 3, 3, 2, 1, 3, None),
+    ]
+
+
+TENSORS = ("x", "dy", "w_master", "w_bf16", "w_crsk", "y", "dx", "dw", "out_norm", "in_norm")
+
+
+@pytest.mark.parametrize("grouped", [True, False])
+@pytest.mark.parametrize("overlap,fuse", [(True, True), (True, False), (False, False)])
+def test_network_reads_the_layers_tensors_at_every_call(recorded, monkeypatch, grouped, overlap, fuse):
+    """Every tensor of every layer is replaced between two iterations: the second one must hand the library the new
+    tensors and none of the old ones, whose memory may belong to something else by then."""
+    if not grouped:
+        monkeypatch.setattr(hz, "WGRAD_GROUP_MAX_BYTES", 0)
+    net = hz.Network(hz.build_network(residual_block(), seed=1))
+    assert net.fork == {1: 4} and net.grouped == grouped and len(net.groups) == (3 if grouped else 6)
+    net.overlap_wgrad, net.fuse_lasso = overlap, fuse
+
+    def iteration():
+        net.train_step(1e-3)
+        net.regulariser_value()
+        net.optimizer_step(1e-3, 0.1, 0.9, 0.0)
+
+    iteration()
+    old = {(i, a): getattr(l, a) for i, l in enumerate(net.layers) for a in TENSORS}
+    assert {t.data_ptr() for t in old.values() if t is not None} <= recorded.seen()
+    for (i, a), t in old.items():
+        if t is not None:
+            setattr(net.layers[i], a, t.clone())
+    net.layers[1].lasso_flags = 0
+    recorded.calls.clear()
+    iteration()
+    seen = recorded.seen()
+    assert not {k for k, t in old.items() if t is not None and t.data_ptr() in seen}
+    assert {getattr(net.layers[i], a).data_ptr() for (i, a), t in old.items() if t is not None} <= seen
+    if overlap:
+        assert [j.flags for j in net.wgrad_jobs] == [l.lasso_flags for l in reversed(net.layers)]
+
+
+def test_network_enlarges_a_weight_gradient_workspace(recorded):
+    """A tensor may be replaced by one that is aligned worse and whose plan needs more partial sums: the call's refusal
+    for want of workspace is answered with a larger one, any other status is passed on."""
+    net = hz.Network(hz.build_network(residual_block(), seed=1))
+    sizes = [w.numel() for w in net.ws_sides]
+    refused = []
+
+    def status(name, args):
+        if name == "pt_conv_bwd_weight_batched" and not refused:
+            refused.append(args[5])
+            return B.ERR_WORKSPACE
+        return 0
+    recorded.status = status
+    net.train_step(1e-3)
+    calls = [ps for name, ps in recorded.calls if name == "pt_conv_bwd_weight_batched"]
+    assert refused == sizes and len(calls) == len(net.groups) + 1
+    recorded.status = lambda name, args: B.ERR_UNSUPPORTED if name == "pt_conv_bwd_weight_batched" else 0
+    with pytest.raises(B.PruneTrainError) as e:
+        net.train_step(1e-3)
+    assert e.value.status == B.ERR_UNSUPPORTED
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("grouped", [True, False])
+def test_train_step_after_tensors_were_replaced_against_oracle(monkeypatch, grouped):
+    """The next batch arrives in other tensors, the gradients are wanted elsewhere, and one input is only 8-byte aligned:
+    the second step's outputs against the oracle, and the first step's tensors left as they were."""
+    import oracle
+    from gpu_util import CONV_TOL, host_bf16, rel_err
+    if not grouped:
+        monkeypatch.setattr(hz, "WGRAD_GROUP_MAX_BYTES", 0)
+    specs = residual_block(N=8)
+    rng = np.random.Generator(np.random.PCG64(21))
+    batches = [[wl.conv_tensors(s, rng) for s in specs] for _ in range(2)]
+    net = hz.Network([hz.ConvLayer(s, host=t) for s, t in zip(specs, batches[0])])
+    assert net.grouped == grouped
+    lam = 1e-2
+    net.train_step(lam)
+    torch.cuda.synchronize()
+    first = [(l.x, l.dy, l.dw, l.dw.clone(), l.y, l.y.clone()) for l in net.layers]
+    for l, t in zip(net.layers, batches[1]):
+        l.x, l.dy = hz._to_dev_bf16(t["x"], l.xp), hz._to_dev_bf16(t["dy"], l.yp)
+        l.dw, l.y = torch.zeros_like(l.dw), torch.zeros_like(l.y)
+        if l.dx is not None:
+            l.dx = torch.zeros_like(l.dx)
+    x = net.layers[-1].x
+    apart = torch.zeros(x.numel() + 4, dtype=x.dtype, device=x.device)[4:].view(x.shape)
+    apart.copy_(x)
+    net.layers[-1].x = apart
+    assert apart.data_ptr() % 16 == 8
+    net.train_step(lam)
+    torch.cuda.synchronize()
+    for l, t, w in zip(net.layers, batches[1], (b["w"] for b in batches[0])):
+        s, o = l.spec, oracle.shape_of(l.spec)
+        ron, rin = oracle.group_norms(w)
+        assert rel_err(host_bf16(l.y, s.K), oracle.conv_fwd(o, t["x"], w)) <= CONV_TOL, s
+        if l.dx is not None:
+            assert rel_err(host_bf16(l.dx, s.C), oracle.conv_bwd_data(o, t["dy"], w)) <= CONV_TOL, s
+        ref = oracle.group_lasso_grad(w, ron, rin, lam, l.lasso_flags, oracle.conv_bwd_weight(o, t["x"], t["dy"]))
+        assert rel_err(l.dw.cpu().numpy()[..., : s.C], ref) <= CONV_TOL, s
+    for _, _, dw, dw0, y, y0 in first:
+        assert torch.equal(dw, dw0) and torch.equal(y, y0)
