@@ -401,7 +401,7 @@ int32_t pt_compact_nhwc_batched(const pt_gather_nhwc* jobs, int32_t n_jobs, void
 
 /* Compaction straight from a plan: the gathers of pt_compact_weights / _vector / _nhwc with the survivor counts read on
  * the DEVICE (the scalars pt_compact_plan wrote), so that a reconfiguration enqueues its gathers behind its plan without
- * the host having seen the counts, and the job table of a network is built once.  Per job:
+ * the host having seen the counts.  Per job:
  *   PT_PLANNED_WEIGHTS  src fp32 [K][RS][cpitch]; out fp32 [K'][RS][P'], rows of P' = round_up(C', 8) elements
  *   PT_PLANNED_NHWC     src bf16 [rows][cpitch];  out bf16 [rows][P'], channels C' .. P'-1 written as zero
  *   PT_PLANNED_VECTOR   src [K] of elem_bytes (1, 2, 4 or 8); out [K']

@@ -809,8 +809,9 @@ extern "C" int32_t pt_compact_weights_batched(const pt_gather_weights* jobs, int
 }
 
 // The gathers of all three kinds with the counts read on the device: grids are sized for nothing pruned and the kernels
-// stop at the counts.  Reading the counts back first costs a reconfiguration of ResNet-50 about 270 us of idle GPU (the
-// copy, the host's wake-up, 370 job structs and their launches) in front of 350 us of gathers.
+// stop at the counts.  Reading the counts back first leaves the GPU idle in front of the gathers for the copy, the host's
+// wake-up and the jobs' preparation: a sweep of the pruned ResNet-50 takes 647 us that way, 377 us this way (the first one
+// of a model, host data cold: 1216 and 1045 us).
 extern "C" int32_t pt_compact_planned(const pt_planned_gather* jobs, int32_t n_jobs, void* stream) {
     if (n_jobs < 0) return PT_ERR_SHAPE;
     if (n_jobs == 0) return PT_OK;

@@ -148,6 +148,72 @@ def test_network_enlarges_a_weight_gradient_workspace(recorded):
     assert e.value.status == B.ERR_UNSUPPORTED
 
 
+def _reconfig_model(with_activations=True):
+    specs = [
+        wl.ConvSpec("m0", 1, 6, 6, 3, 30, 3, 3, 1, 1, None, 0, first=True),
+        wl.ConvSpec("m1", 1, 6, 6, 30, 37, 1, 1, 1, 0, 0, 1),
+        wl.ConvSpec("m2", 1, 6, 6, 37, 30, 3, 3, 1, 1, 1, 0),
+        wl.ConvSpec("m3", 1, 6, 6, 30, 9, 1, 1, 1, 0, 0, None),
+    ]
+    edges = [wl.Edge("e0", 30, [0, 2], [1, 3]), wl.Edge("e1", 37, [1], [2])]
+    rng = np.random.Generator(np.random.PCG64(5))
+    weights = wl.network_weights(specs, edges, wl.zeroed_channel_sets(edges, 0.3, rng), rng)
+    model = hz.ReconfigModel(specs, edges, weights, seed=2, with_activations=with_activations)
+    model.counts.copy_(torch.tensor([20, 25], dtype=torch.int32))   # as the recorded plan would leave them
+    return model
+
+
+@pytest.mark.parametrize("with_activations", [True, False])
+def test_compaction_reads_the_models_tensors_at_every_call(recorded, monkeypatch, with_activations):
+    """The gathers of compact() after every tensor was replaced (some behind the same tensor object): job by job what the
+    calls for single jobs make of the tensors the model holds now."""
+    zeros = torch.zeros
+    monkeypatch.setattr(torch, "zeros", lambda *a, pin_memory=False, **kw: zeros(*a, **kw))
+    m = _reconfig_model(with_activations)
+    tables = []
+
+    def status(name, args):
+        if name == "pt_compact_planned":
+            tables.append([bytes(j) for j in args[0][: args[1]]])
+        return 0
+    recorded.status = status
+
+    def expected():
+        small, acts = [], []
+        for i, s in enumerate(m.specs):
+            ik, nk = (None, None) if s.out_edge is None else (m.idx[s.out_edge], m.counts[s.out_edge:])
+            ic, nc = (None, None) if s.in_edge is None else (m.idx[s.in_edge], m.counts[s.in_edge:])
+            for src, dst in ((m.w[i], m.w_out[i]), (m.mom[i], m.mom_out[i])):
+                small.append(B.planned_weights(src, s.K, s.R * s.S, s.C, hz.pitch8(s.C), ik, nk, ic, nc, dst))
+            if ik is not None:
+                small += [B.planned_vector(v, 4, s.K, ik, nk, o) for v, o in zip(m.bn[i], m.bn_out[i])]
+            if m.act and ic is not None:
+                acts.append(B.planned_nhwc(m.act[i], s.N * s.H * s.W, s.C, hz.pitch8(s.C), ic, nc, m.act_out[i]))
+        # (fields a kind does not read may hold anything)
+        return [sorted(map(_planned_fields, map(bytes, jobs))) for jobs in ([acts] if acts else []) + [small]]
+
+    for again in range(3):
+        tables.clear()
+        m.compact()
+        assert [sorted(map(_planned_fields, t)) for t in tables] == expected()
+        assert m.new_counts.tolist() == [20, 25]
+        if again == 0:      # every tensor is another one
+            for name in ("w", "mom", "act", "w_out", "mom_out", "act_out", "idx"):
+                setattr(m, name, [t.clone() for t in getattr(m, name)])
+            m.bn, m.bn_out, m.counts = [[v.clone() for v in vs] for vs in m.bn], [[v.clone() for v in vs] for vs in m.bn_out], m.counts.clone()
+        else:               # the same objects, other memory
+            for t in (*m.w, *m.act_out, *m.bn[0], *m.idx):
+                t.data = t.data.clone()
+
+
+def _planned_fields(job):
+    j = B.PlannedGather.from_buffer_copy(job)
+    used = {B.PLANNED_WEIGHTS: ("src", "out", "idxK", "nK_dev", "idxC", "nC_dev", "K", "RS", "C", "cpitch"),
+            B.PLANNED_NHWC: ("src", "out", "idxC", "nC_dev", "rows", "C", "cpitch"),
+            B.PLANNED_VECTOR: ("src", "out", "idxK", "nK_dev", "K", "elem_bytes")}[j.kind]
+    return (j.kind, *((getattr(j, f) or 0) for f in used))
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("grouped", [True, False])
 def test_train_step_after_tensors_were_replaced_against_oracle(monkeypatch, grouped):
