@@ -206,6 +206,24 @@ def test_compaction_reads_the_models_tensors_at_every_call(recorded, monkeypatch
                 t.data = t.data.clone()
 
 
+def test_compaction_of_activations_that_do_not_stream(recorded, monkeypatch):
+    """The planned gathers refuse an activation (as they do one that is not 16-byte aligned): compact() takes the calls with
+    the counts on the host.  Another refusal is passed on."""
+    zeros = torch.zeros
+    monkeypatch.setattr(torch, "zeros", lambda *a, pin_memory=False, **kw: zeros(*a, **kw))
+    m = _reconfig_model()
+    recorded.status = lambda name, args: B.ERR_UNSUPPORTED if name == "pt_compact_planned" else 0
+    m.compact()
+    assert [name for name, _ in recorded.calls] == ["pt_compact_planned", "pt_compact_nhwc_batched", "pt_compact_weights_batched",
+                                                    "pt_compact_vector_batched"]
+    assert {t.data_ptr() for t in m.act[1:] + m.act_out[1:]} <= recorded.seen("pt_compact_nhwc_batched")
+    assert {t.data_ptr() for t in m.w + m.mom + m.w_out + m.mom_out} <= recorded.seen("pt_compact_weights_batched")
+    assert m.new_counts.tolist() == [20, 25]
+    recorded.status = lambda name, args: -2 if name == "pt_compact_planned" else 0
+    with pytest.raises(B.PruneTrainError):
+        m.compact()
+
+
 def _planned_fields(job):
     j = B.PlannedGather.from_buffer_copy(job)
     used = {B.PLANNED_WEIGHTS: ("src", "out", "idxK", "nK_dev", "idxC", "nC_dev", "K", "RS", "C", "cpitch"),
@@ -254,3 +272,30 @@ def test_train_step_after_tensors_were_replaced_against_oracle(monkeypatch, grou
         assert rel_err(l.dw.cpu().numpy()[..., : s.C], ref) <= CONV_TOL, s
     for _, _, dw, dw0, y, y0 in first:
         assert torch.equal(dw, dw0) and torch.equal(y, y0)
+
+
+@pytest.mark.gpu
+def test_sweep_with_a_misaligned_activation():
+    """One saved activation starts 2 bytes off a 16-byte boundary: the sweep takes it, and every output equals plain
+    indexing."""
+    m = _reconfig_model()
+    a = m.act[2]
+    m.act[2] = torch.zeros(a.numel() + 1, dtype=a.dtype, device=a.device)[1:].view(a.shape)
+    m.act[2].copy_(a)
+    m.sweep(1e-6)
+    torch.cuda.synchronize()
+    kept = [m.idx[e][: int(n)].long() for e, n in enumerate(m.new_counts)]
+    assert [k.numel() for k in kept] == [21, 26]
+    for i, s in enumerate(m.specs):
+        ik = torch.arange(s.K, device=a.device) if s.out_edge is None else kept[s.out_edge]
+        ic = torch.arange(s.C, device=a.device) if s.in_edge is None else kept[s.in_edge]
+        pitch = hz.pitch8(ic.numel())
+        for src, out in ((m.w[i], m.w_out[i]), (m.mom[i], m.mom_out[i])):
+            got = out.reshape(-1)[: ik.numel() * s.R * s.S * pitch].view(ik.numel(), s.R, s.S, pitch)
+            assert torch.equal(got[..., : ic.numel()], src[ik][..., ic])
+        if s.in_edge is not None:
+            got = m.act_out[i].reshape(-1)[: s.N * s.H * s.W * pitch].view(s.N, s.H, s.W, pitch)
+            assert torch.equal(got[..., : ic.numel()], m.act[i][..., ic])
+        if s.out_edge is not None:
+            for v, o in zip(m.bn[i], m.bn_out[i]):
+                assert torch.equal(o[: ik.numel()], v[ik])
