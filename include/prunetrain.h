@@ -426,6 +426,11 @@ typedef struct pt_planned_gather {
 } pt_planned_gather;
 int32_t pt_compact_planned(const pt_planned_gather* jobs, int32_t n_jobs, void* stream);
 
+/* As pt_compact_planned, but the call writes nothing at all when one of counts[0 .. n_counts) (DEVICE) is 0: an edge with
+ * no survivors is not a layout, and the caller who reads the counts back finds its outputs as they were. */
+int32_t pt_compact_planned_guarded(const pt_planned_gather* jobs, int32_t n_jobs, const int32_t* counts, int32_t n_counts,
+                                   void* stream);
+
 /* ---- channel gating pieces and the paper's other zeroing rule: Sec. 4.1, 4.2 ----------------------------- */
 
 /* Channel scatter, the inverse of pt_compact_nhwc (the scatter layer of channel gating, Sec. 4.2):

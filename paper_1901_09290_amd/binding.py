@@ -38,7 +38,7 @@ EXPORTS = [
     "pt_group_lasso_penalty_batched", "pt_lasso_set_coeff", "pt_compact_nhwc_batched",
     "pt_scatter_nhwc", "pt_group_maxabs", "pt_apply_zero", "pt_sgd_momentum_lasso_batched",
     "pt_zero_groups_batched", "pt_reconcile_plan_batched", "pt_compact_vector_batched", "pt_compact_weights_batched",
-    "pt_compact_planned", "pt_conv_bwd_data_crsk_batched",
+    "pt_compact_planned", "pt_compact_planned_guarded", "pt_conv_bwd_data_crsk_batched",
     "pt_conv_bwd_weight_batched_workspace_bytes", "pt_conv_bwd_weight_batched",
     "pt_bn_workspace_bytes", "pt_bn_fwd", "pt_bn_bwd", "pt_plan_layer_removal",
     "pt_conv_fwd_stats_workspace_bytes", "pt_conv_fwd_stats", "pt_bn_fwd_from_sums",
@@ -198,6 +198,7 @@ def lib() -> C.CDLL:
             "pt_conv_bwd_weight_batched_workspace_bytes": [C.POINTER(LayerWgrad), i32, i32, C.POINTER(sz)],
             "pt_conv_bwd_weight_batched": [C.POINTER(LayerWgrad), i32, f32, i32, vp, sz, vp],
             "pt_compact_planned": [C.POINTER(PlannedGather), i32, vp],
+            "pt_compact_planned_guarded": [C.POINTER(PlannedGather), i32, vp, i32, vp],
             "pt_plan_layer_removal": [C.POINTER(RemovalEdge), i32, i32, vp, vp],
             "pt_conv_fwd_stats_workspace_bytes": [dp, C.POINTER(sz), C.POINTER(i32)],
             "pt_conv_fwd_stats": [dp, vp, vp, vp, vp, sz, vp],
@@ -517,6 +518,13 @@ def planned_jobs(n: int):
 def compact_planned(jobs, stream=None) -> None:
     arr = _array(jobs, PlannedGather)
     _ck("pt_compact_planned", lib().pt_compact_planned(arr, len(jobs), _stream(stream)))
+
+
+def compact_planned_guarded(jobs, counts, stream=None) -> None:
+    """counts: int32 device tensor; one that is 0 keeps the call from writing anything."""
+    arr = _array(jobs, PlannedGather)
+    _ck("pt_compact_planned_guarded",
+        lib().pt_compact_planned_guarded(arr, len(jobs), _ptr(counts), counts.numel(), _stream(stream)))
 
 
 def layer_crsk(w, wt, K, RS, Cc, w_cpitch) -> LayerCrsk:

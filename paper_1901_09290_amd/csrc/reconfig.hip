@@ -145,8 +145,21 @@ struct GatherJob {
     int x_cpitch, Cp, out_cpitch, ppc;  // ppc: pixels per run
     int chunk0, pad;                    // first run of this tensor in the global sequence
 };
+// Survivor counts that must all be positive for a launch to write anything (none: n = 0).  Every wave decides for itself,
+// from one load where there are at most 64, so that the decision needs no barrier.
+struct CountGuard {
+    const int* counts;
+    int n, pad;
+};
+__device__ __forceinline__ bool some_empty(const CountGuard& g) {
+    bool empty = false;
+    for (int i = (int)threadIdx.x & 63; i < g.n; i += 64) empty = empty || g.counts[i] <= 0;
+    return __ballot(empty) != 0ull;
+}
+
 struct GatherJobs {
     GatherJob j[kMaxGatherJobs];
+    CountGuard guard;
     int n, total_chunks;
 };
 
@@ -192,6 +205,10 @@ __global__ __launch_bounds__(kGatherThreads) void k_compact_nhwc_lds(const Gathe
 
     int g = blockIdx.x;
     if (g < total) issue(g, 0);
+    if (jobs.guard.n && some_empty(jobs.guard)) {  // (behind the first run's loads, whose latency covers the counts')
+        __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));  // nothing may land in LDS after the workgroup has gone
+        return;
+    }
     for (int it = 0; g < total; g += gridDim.x, ++it) {
         const int buf = it & 1;
         const bool more = g + (int)gridDim.x < total;
@@ -326,10 +343,12 @@ struct VecJob {
 };
 struct VecJobs {
     VecJob j[kMaxVecJobs];
+    CountGuard guard;
     int first[(kMaxVecJobs + 63) / 64 * 64];  // first workgroup of each job
     int n;
 };
 __global__ __launch_bounds__(256) void k_compact_vector_multi(const VecJobs jobs) {
+    if (jobs.guard.n && some_empty(jobs.guard)) return;
     const int ji = job_of_block(jobs.first, blockIdx.x);
     const VecJob& jb = jobs.j[ji];
     const int t = (blockIdx.x - jobs.first[ji]) * 256 + threadIdx.x;
@@ -355,12 +374,14 @@ struct WJob {
 };
 struct WJobs {
     WJob j[kMaxWJobs];
+    CountGuard guard;
     int first[(kMaxWJobs + 63) / 64 * 64];  // first workgroup of each job
     int n;
 };
 // A workgroup gathers `rows_per_blk` consecutive output rows (k', rs) of one tensor; a thread produces 4
 // consecutive c' of a row.
 __global__ __launch_bounds__(256) void k_compact_weights_multi(const WJobs jobs) {
+    if (jobs.guard.n && some_empty(jobs.guard)) return;
     const int ji = job_of_block(jobs.first, blockIdx.x);
     const WJob& jb = jobs.j[ji];
     const int Cp = jb.nC_dev ? *jb.nC_dev : jb.Cp;
@@ -620,6 +641,7 @@ extern "C" int32_t pt_compact_nhwc(const uint16_t* x, int64_t pixels, int32_t C,
     hipStream_t st = (hipStream_t)stream;
     if (!gather_streams(x, x_cpitch, Cp, out, out_cpitch)) return gather_elementwise(x, pixels, x_cpitch, idx, Cp, out, out_cpitch, st);
     GatherJobs t;
+    t.guard = CountGuard{};
     t.n = 0;
     t.total_chunks = 0;
     const int32_t r2 = add_gather_job(t, x, pixels, x_cpitch, idx, Cp, out, out_cpitch, st);
@@ -638,6 +660,7 @@ extern "C" int32_t pt_compact_nhwc_batched(const pt_gather_nhwc* jobs, int32_t n
     }
     hipStream_t st = (hipStream_t)stream;
     GatherJobs t;
+    t.guard = CountGuard{};
     t.n = 0;
     t.total_chunks = 0;
     for (int i = 0; i < n_jobs; ++i) {
@@ -735,6 +758,7 @@ extern "C" int32_t pt_compact_vector_batched(const pt_gather_vector* jobs, int32
         if (j.n_keep > 0 && (!j.v || !j.idx || !j.out)) return PT_ERR_NULL;
     }
     VecJobs t;
+    t.guard = CountGuard{};
     t.n = 0;
     int blocks = 0;
     auto flush = [&]() -> int32_t {
@@ -778,6 +802,7 @@ extern "C" int32_t pt_compact_weights_batched(const pt_gather_weights* jobs, int
         if ((int64_t)j.Kp * j.RS > 0x7fffffff) return PT_ERR_UNSUPPORTED;
     }
     WJobs t;
+    t.guard = CountGuard{};
     t.n = 0;
     int64_t blocks = 0;
     auto flush = [&]() -> int32_t {
@@ -812,10 +837,12 @@ extern "C" int32_t pt_compact_weights_batched(const pt_gather_weights* jobs, int
 // stop at the counts.  Reading the counts back first leaves the GPU idle in front of the gathers for the copy, the host's
 // wake-up and the jobs' preparation: a sweep of the pruned ResNet-50 takes 647 us that way, 377 us this way (the first one
 // of a model, host data cold: 1216 and 1045 us).
-extern "C" int32_t pt_compact_planned(const pt_planned_gather* jobs, int32_t n_jobs, void* stream) {
-    if (n_jobs < 0) return PT_ERR_SHAPE;
+extern "C" int32_t pt_compact_planned_guarded(const pt_planned_gather* jobs, int32_t n_jobs, const int32_t* counts,
+                                              int32_t n_counts, void* stream) {
+    if (n_jobs < 0 || n_counts < 0) return PT_ERR_SHAPE;
     if (n_jobs == 0) return PT_OK;
-    if (!jobs) return PT_ERR_NULL;
+    if (!jobs || (n_counts > 0 && !counts)) return PT_ERR_NULL;
+    const CountGuard guard{counts, n_counts, 0};
     for (int i = 0; i < n_jobs; ++i) {
         const pt_planned_gather& j = jobs[i];
         if (j.kind == PT_PLANNED_WEIGHTS) {
@@ -837,6 +864,7 @@ extern "C" int32_t pt_compact_planned(const pt_planned_gather* jobs, int32_t n_j
     hipStream_t st = (hipStream_t)stream;
     int32_t rc = PT_OK;
     GatherJobs g;
+    g.guard = guard;
     g.n = g.total_chunks = 0;
     for (int i = 0; i < n_jobs && rc == PT_OK; ++i) {
         const pt_planned_gather& j = jobs[i];
@@ -846,6 +874,7 @@ extern "C" int32_t pt_compact_planned(const pt_planned_gather* jobs, int32_t n_j
     if (rc == PT_OK) rc = launch_gather_jobs(g, st);
     if (rc != PT_OK) return rc;
     WJobs t;
+    t.guard = guard;
     t.n = 0;
     int64_t blocks = 0;
     auto flush_w = [&]() -> int32_t {
@@ -869,6 +898,7 @@ extern "C" int32_t pt_compact_planned(const pt_planned_gather* jobs, int32_t n_j
     }
     if (rc == PT_OK) rc = flush_w();
     VecJobs v;
+    v.guard = guard;
     v.n = 0;
     int vblocks = 0;
     auto flush_v = [&]() -> int32_t {
@@ -888,6 +918,10 @@ extern "C" int32_t pt_compact_planned(const pt_planned_gather* jobs, int32_t n_j
         vblocks += (j.K + 255) / 256;
     }
     return rc == PT_OK ? flush_v() : rc;
+}
+
+extern "C" int32_t pt_compact_planned(const pt_planned_gather* jobs, int32_t n_jobs, void* stream) {
+    return pt_compact_planned_guarded(jobs, n_jobs, nullptr, 0, stream);
 }
 
 // ---- channel scatter, max-abs criterion, zeroing of flagged groups -------------------------------------

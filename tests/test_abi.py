@@ -179,6 +179,14 @@ def test_planned_compaction_validates_on_the_host(lib):
     assert call(job(kind=2, elem_bytes=3)) == -4 and call(job(kind=3)) == -4
 
 
+def test_guarded_compaction_validates_on_the_host(lib):
+    call = lambda jobs, n, counts, n_counts: lib.pt_compact_planned_guarded(jobs, n, counts, n_counts, None)
+    job = (B.PlannedGather * 1)(B.PlannedGather(4096, 4096, 4096, 4096, 4096, 4096, 4, 8, 1, 8, 7, 0, 4))
+    assert call(None, 0, None, 0) == 0 and call(None, 1, None, 0) == -1
+    assert call(job, 1, 4096, -1) == -2 and call(job, 1, None, 3) == -1
+    assert call(job, 1, 4096, 3) == -2      # the jobs are checked as in the plain call
+
+
 def test_batched_gradient_calls_validate_on_the_host(lib):
     d = B.conv_desc(4, 16, 16, 16, 16, 3, 3, 1, 1)
     job = lambda **kw: B.LayerWgrad(**{**dict(d=d, x=4096, dy=4096, dw=4096, w=4096, out_norm=4096, in_norm=4096, flags=3), **kw})

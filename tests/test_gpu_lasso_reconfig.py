@@ -653,3 +653,50 @@ def test_planned_compaction_reads_the_counts_on_the_device(C, keep_n):
         assert torch.equal(out.view(-1)[:n].view(src.shape[0], RS, op)[..., :keep_n], src[..., sel])
         assert (out.view(-1)[n:] == 3.0).all()
     assert torch.equal(vo[:keep_n], v[sel]) and (vo[keep_n:] == 7).all()
+
+
+@pytest.mark.parametrize("n_counts,zero_at", [(1, 0), (1, None), (64, 63), (65, 64), (130, 127), (130, None), (0, None)])
+def test_guarded_compaction_writes_all_or_nothing(n_counts, zero_at):
+    """One count of 0 anywhere (before, at and past the 64 that one load covers) keeps all three kinds of gather from
+    writing; with none the call is the plain one."""
+    from gpu_util import DEV
+    C, RS, pixels = 72, 3, 700           # several runs of the streaming gather
+    idx = torch.arange(0, C, 2, dtype=torch.int32, device=DEV)
+    n_dev = torch.tensor([idx.numel()], dtype=torch.int32, device=DEV)
+    counts = torch.full((n_counts,), 5, dtype=torch.int32, device=DEV)
+    if zero_at is not None:
+        counts[zero_at] = 0
+    x = torch.randn((pixels, C), device=DEV).to(torch.bfloat16)
+    w, v = torch.randn((C, RS, C), device=DEV), torch.randn(C, device=DEV)
+    src = (x, w, v)
+
+    def outputs(run):
+        out = [torch.full_like(t, 3.0) for t in src]
+        run([B.planned_nhwc(x, pixels, C, C, idx, n_dev, out[0]), B.planned_weights(w, C, RS, C, C, idx, n_dev, idx, n_dev, out[1]),
+             B.planned_vector(v, 4, C, idx, n_dev, out[2])])
+        torch.cuda.synchronize()
+        return out
+    plain = outputs(B.compact_planned)
+    guarded = outputs(lambda jobs: B.compact_planned_guarded(jobs, counts))
+    for a, b in zip(plain, guarded):
+        assert not (a == 3.0).all()
+        assert (b == 3.0).all() if zero_at is not None else torch.equal(a, b)
+
+
+def test_sweep_refused_for_an_empty_edge_leaves_the_outputs():
+    """An edge all of whose groups are zero: the sweep raises, and no compacted tensor has been touched."""
+    from paper_1901_09290_amd import harness as hz
+    specs = [wl.ConvSpec("s0", 2, 8, 8, 3, 24, 3, 3, 1, 1, None, 0, first=True), wl.ConvSpec("s1", 2, 8, 8, 24, 40, 1, 1, 1, 0, 0, 1),
+             wl.ConvSpec("s2", 2, 8, 8, 40, 16, 1, 1, 1, 0, 1, None)]
+    edges = [wl.Edge("e0", 24, [0], [1]), wl.Edge("e1", 40, [1], [2])]
+    rng = np.random.Generator(np.random.PCG64(3))
+    weights = wl.network_weights(specs, edges, [np.arange(5, dtype=np.int32), np.arange(40, dtype=np.int32)], rng)
+    m = hz.ReconfigModel(specs, edges, weights, seed=4)
+    outs = m.w_out + m.mom_out + m.act_out + [v for vs in m.bn_out for v in vs]
+    for t in outs:
+        t.fill_(3.0)
+    with pytest.raises(B.PruneTrainError) as e:
+        m.sweep(1e-6)
+    torch.cuda.synchronize()
+    assert e.value.status == -2 and m.new_counts.tolist() == [19, 0]
+    assert all((t == 3.0).all() for t in outs)

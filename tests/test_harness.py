@@ -173,7 +173,7 @@ def test_compaction_reads_the_models_tensors_at_every_call(recorded, monkeypatch
     tables = []
 
     def status(name, args):
-        if name == "pt_compact_planned":
+        if name == "pt_compact_planned_guarded":
             tables.append([bytes(j) for j in args[0][: args[1]]])
         return 0
     recorded.status = status
@@ -194,7 +194,9 @@ def test_compaction_reads_the_models_tensors_at_every_call(recorded, monkeypatch
 
     for again in range(3):
         tables.clear()
+        recorded.calls.clear()
         m.compact()
+        assert all(m.counts.data_ptr() in ps for _, ps in recorded.calls)   # the counts that must be positive
         assert [sorted(map(_planned_fields, t)) for t in tables] == expected()
         assert m.new_counts.tolist() == [20, 25]
         if again == 0:      # every tensor is another one
@@ -212,16 +214,34 @@ def test_compaction_of_activations_that_do_not_stream(recorded, monkeypatch):
     zeros = torch.zeros
     monkeypatch.setattr(torch, "zeros", lambda *a, pin_memory=False, **kw: zeros(*a, **kw))
     m = _reconfig_model()
-    recorded.status = lambda name, args: B.ERR_UNSUPPORTED if name == "pt_compact_planned" else 0
+    recorded.status = lambda name, args: B.ERR_UNSUPPORTED if name == "pt_compact_planned_guarded" else 0
     m.compact()
-    assert [name for name, _ in recorded.calls] == ["pt_compact_planned", "pt_compact_nhwc_batched", "pt_compact_weights_batched",
-                                                    "pt_compact_vector_batched"]
+    assert [name for name, _ in recorded.calls] == ["pt_compact_planned_guarded", "pt_compact_nhwc_batched",
+                                                    "pt_compact_weights_batched", "pt_compact_vector_batched"]
     assert {t.data_ptr() for t in m.act[1:] + m.act_out[1:]} <= recorded.seen("pt_compact_nhwc_batched")
     assert {t.data_ptr() for t in m.w + m.mom + m.w_out + m.mom_out} <= recorded.seen("pt_compact_weights_batched")
     assert m.new_counts.tolist() == [20, 25]
-    recorded.status = lambda name, args: -2 if name == "pt_compact_planned" else 0
+    recorded.status = lambda name, args: -2 if name == "pt_compact_planned_guarded" else 0
     with pytest.raises(B.PruneTrainError):
         m.compact()
+
+
+def test_edge_without_survivors_is_refused_on_either_route(recorded, monkeypatch):
+    """The counts that come back hold a 0: the planned gathers (which write nothing then) end in the error that the calls
+    with the counts on the host return.  A model with an edge of no layer, whose count is nobody's business, takes those."""
+    zeros = torch.zeros
+    monkeypatch.setattr(torch, "zeros", lambda *a, pin_memory=False, **kw: zeros(*a, **kw))
+    m = _reconfig_model()
+    m.counts[1] = 0
+    with pytest.raises(B.PruneTrainError) as e:
+        m.compact()
+    assert e.value.status == -2 and {name for name, _ in recorded.calls} == {"pt_compact_planned_guarded"}
+    m = _reconfig_model()
+    m = hz.ReconfigModel(m.specs, m.edges + [wl.Edge("unused", 8, [0], [])], [w.numpy()[..., : s.C] for w, s in zip(m.w, m.specs)], 2)
+    m.counts.copy_(torch.tensor([20, 25, 0], dtype=torch.int32))
+    recorded.calls.clear()
+    m.compact()
+    assert m.new_counts.tolist() == [20, 25, 0] and "pt_compact_planned_guarded" not in {name for name, _ in recorded.calls}
 
 
 def _planned_fields(job):
