@@ -2402,6 +2402,7 @@ struct StemWgradArgs {
 };
 constexpr int kSwTH = 2, kSwTW = 64;
 constexpr int kSwSlots = 256;                 // one workgroup of 16 waves per CU
+constexpr int kSwPairsFrom = 17;              // tiles from which a workgroup takes at least two
 constexpr int kSwSlabRow = 64 * 32;           // floats per filter row in a slab
 
 template <int STRIDE>
@@ -2584,7 +2585,14 @@ inline void plan_stem_wgrad(StemWgradArgs& a, int* slabs) {
     const int64_t tiles = (int64_t)a.N * a.tiles_p * a.tiles_q;
     a.tiles = (int)tiles;
     // Tiles per workgroup: a pair (one for each wave group) takes 1.2 us, a slab 0.03 us to write and add up (fitted to 7 x 7
-    // filters on 96 x 96 to 224 x 224 at batch 8 to 64: 192 tiles as 96 slabs 11 us, as 192 slabs 15 us).
+    // filters on 96 x 96 to 224 x 224 at batch 8 to 64: 192 tiles as 96 slabs 11 us, as 192 slabs 15 us).  The smallest
+    // problems keep a tile and a slab for each workgroup, the plan that callers were told of them: within 0.2 us there (10 tiles
+    // 7.35 against 7.16 us in pairs), 1 us at 64 tiles.
+    if (tiles < kSwPairsFrom) {
+        a.run = 1;
+        *slabs = (int)tiles;
+        return;
+    }
     const int64_t least = (tiles + kSwSlots - 1) / kSwSlots;
     float best = 1e30f;
     for (int64_t run = (least + 1) & ~1ll; run <= tiles + 1; run += 2) {
