@@ -226,7 +226,7 @@ def _ptr(t) -> Optional[int]:
 _raw_stream = None  # () -> handle of the current device's current stream, set at the first call that needs it
 
 
-def _stream(stream) -> Optional[int]:
+def _stream(stream=None) -> Optional[int]:
     """The raw handle of `stream`, or of the current stream.  Every call of an eager step comes through here: building a
     torch.cuda.Stream object to read its handle takes 2.8 us, as long as the launch itself; the raw query takes 0.1 us."""
     global _raw_stream
@@ -278,9 +278,25 @@ def _ws(ws):
     return (None, 0) if ws is None else (ws.data_ptr(), ws.numel() * ws.element_size())
 
 
+raw_workspace, raw_stream = _ws, _stream   # for the *_at forms
+
 def conv_fwd(d: ConvDesc, x, w, y, ws=None, stream=None) -> None:
     p, n = _ws(ws)
     _ck("pt_conv_fwd", lib().pt_conv_fwd(C.byref(d), _ptr(x), _ptr(w), _ptr(y), p, n, _stream(stream)))
+
+
+def conv_fwd_at(d: ConvDesc, x: int, w: int, y: int, ws, stream: Optional[int]) -> None:
+    """conv_fwd for a caller that has the addresses at hand; ws: (address, bytes)."""
+    rc = lib().pt_conv_fwd(C.byref(d), x, w, y, ws[0], ws[1], stream)
+    if rc:
+        raise PruneTrainError("pt_conv_fwd", rc)
+
+
+def conv_bwd_data_crsk_at(d: ConvDesc, dy: int, wt: int, dx: int, stream: Optional[int]) -> None:
+    """conv_bwd_data_crsk for a caller that has the addresses at hand."""
+    rc = lib().pt_conv_bwd_data_crsk(C.byref(d), dy, wt, dx, stream)
+    if rc:
+        raise PruneTrainError("pt_conv_bwd_data_crsk", rc)
 
 
 def conv_fwd_jobs(descs: Sequence[ConvDesc], xs, ws, ys):
