@@ -92,29 +92,34 @@ __global__ __launch_bounds__(kBnThreads) void k_bn_sums(const uint16_t* __restri
             }
         }
     }
-    float a[8], b[8];
+    // A thread keeps kBnSumRows sums of each kind, one for each row of a batch, and adds them as a tree at the end: of n rows
+    // the longest chain of additions is n / 8 + 3 with no instruction more per row (200704 x 256, 98 rows a thread: relative
+    // error of invstd 3.0e-7 with one sum, 3.2e-8 with eight; forward and backward 146.3 and 147.2 us).
+    float a[kBnSumRows][8], b[kBnSumRows][8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) a[e] = 0.f, b[e] = 0.f;
+    for (int u = 0; u < kBnSumRows; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a[u][e] = b[u][e] = 0.f;
     const int64_t r0 = (int64_t)blockIdx.x * g.rows_per_block;
     const int64_t r1 = min(g.pixels, r0 + g.rows_per_block);
     if (live) {
-        auto add = [&](const uint4& xq, const uint4& gq) {
+        auto add = [&](int u, const uint4& xq, const uint4& gq) {
             float xv[8];
             unpack8(xq, xv);
             if (MODE == 0) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float d = xv[e] - c0[e];
-                    a[e] += d;
-                    b[e] += d * d;
+                    a[u][e] += d;
+                    b[u][e] += d * d;
                 }
             } else {
                 float gv[8];
                 unpack8(gq, gv);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    a[e] += gv[e];
-                    b[e] += gv[e] * ((xv[e] - c0[e]) * c1[e]);
+                    a[u][e] += gv[e];
+                    b[u][e] += gv[e] * ((xv[e] - c0[e]) * c1[e]);
                 }
             }
         };
@@ -132,20 +137,30 @@ __global__ __launch_bounds__(kBnThreads) void k_bn_sums(const uint16_t* __restri
             px += kBnSumRows * sx;
             if (MODE == 1) pg += kBnSumRows * sg;
 #pragma unroll
-            for (int u = 0; u < kBnSumRows; ++u) add(xq[u], MODE == 1 ? gq[u] : xq[u]);
+            for (int u = 0; u < kBnSumRows; ++u) add(u, xq[u], MODE == 1 ? gq[u] : xq[u]);
         }
-        for (; n > 0; --n) {
-            const uint4 xq = *reinterpret_cast<const uint4*>(px);
-            const uint4 gq = MODE == 1 ? *reinterpret_cast<const uint4*>(pg) : xq;
-            add(xq, gq);
-            px += sx;
-            if (MODE == 1) pg += sg;
+#pragma unroll
+        for (int u = 0; u < kBnSumRows - 1; ++u) {  // the rows left over
+            if (u < n) {
+                const uint4 xq = *reinterpret_cast<const uint4*>(px + u * sx);
+                const uint4 gq = MODE == 1 ? *reinterpret_cast<const uint4*>(pg + u * sg) : xq;
+                add(u, xq, gq);
+            }
         }
     }
 #pragma unroll
+    for (int w = 1; w < kBnSumRows; w *= 2)
+#pragma unroll
+        for (int u = 0; u + w < kBnSumRows; u += 2 * w)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                a[u][e] += a[u + w][e];
+                b[u][e] += b[u + w][e];
+            }
+#pragma unroll
     for (int e = 0; e < 8; ++e) {
-        red[0][tid * 8 + e] = a[e];
-        red[1][tid * 8 + e] = b[e];
+        red[0][tid * 8 + e] = a[0][e];
+        red[1][tid * 8 + e] = b[0][e];
     }
     __syncthreads();
     // row groups added in ty order: thread f owns channel f

@@ -125,6 +125,26 @@ def test_bn_is_run_to_run_identical_and_full_size():
         assert torch.equal(a, b)
 
 
+def test_bn_sums_have_short_chains():
+    """The first row that a thread meets is 1, the 97 behind it 2^-25 each, less than half a unit in the last place of 1: one
+    sum that takes them all loses them all (2.9e-6).  With eight sums, one for every eighth row, the chain is 12 additions
+    for the batches of eight, 1 for the rows left over, 3 for the tree over the sums, 7 for the row groups of a workgroup,
+    then fp64 and one rounding; for positive terms the relative error is at most that many half units."""
+    from gpu_util import DEV, workspace
+    pixels, C, ranges, groups = 64 * 56 * 56, 256, 256, 8
+    dy = torch.full((pixels, C), 2.0 ** -25, dtype=torch.bfloat16, device=DEV)
+    dy.view(ranges, pixels // ranges, C)[:, :groups] = 1.0
+    x = torch.zeros_like(dy)
+    ones, out = torch.ones(C, device=DEV), [torch.zeros(C, device=DEV) for _ in range(2)]
+    ws = workspace(B.bn_workspace_bytes(pixels, C))
+    B.bn_bwd(x, dy, pixels, C, C, C, ones, ones, ones, torch.empty_like(x), C, out[0], out[1], ws)
+    torch.cuda.synchronize()
+    exact = ranges * groups + (pixels - ranges * groups) * 2.0 ** -25
+    err = float((out[1].double() - exact).abs().max()) / exact
+    assert err <= (12 + 1 + 3 + 7 + 1) * 2.0 ** -24, err
+    assert float((out[0].double() + exact).abs().max()) / exact <= (12 + 1 + 3 + 7 + 1) * 2.0 ** -24   # xhat = -1
+
+
 FUSED = [
     # N  H   W   C    K   R st pad
     (2, 12, 12, 64, 64, 3, 1, 1),
