@@ -103,10 +103,11 @@ inline IgemmArgs make_bwd_data_args(const pt_conv_desc* d, const BwdClass& c, in
     return a;
 }
 
-// Small dense channel counts (an image-like input): fold the S taps of a filter row into one run.
+// Small dense channel counts (an image-like input): fold the S taps of a filter row into one run (of at most the eight
+// blocks that a table of tails has bytes for).
 inline void igemm_fold(IgemmArgs& a) {
     if (a.fold || !(a.CredP < 64 && a.TS > 1 && a.ts_step == 1 && a.apitch == a.CredP && a.bpitch == a.CredP &&
-                    a.b_ts_stride == 1 && a.TR * a.TS <= 64))
+                    a.b_ts_stride == 1 && a.TR * a.TS <= 64 && a.TS * a.CredP <= 512))
         return;
     a.fold = 1;
     a.TSm = a.TS;

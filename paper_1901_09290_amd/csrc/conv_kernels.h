@@ -163,7 +163,7 @@ inline void set_tail_tables(IgemmArgs& a) {
         return;
     }
     const int per = (int)(a.Cfold.d >> 3);  // chunks per run
-    const int nblk = (a.CredP + 63) >> 6;   // <= 7
+    const int nblk = (a.CredP + 63) >> 6;   // <= 8: igemm_fold sees to it
     for (int c = 0; c < nblk * 8; ++c)
         if (c % per == tail_chunk) a.tail_kv |= 1ull << c;
 }
@@ -466,11 +466,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
         const int h0 = (int)gi * a.h_mul + a.h_add, w0 = (int)gj * a.w_mul + a.w_add;
         a_off[j] = (uint32_t)(((int)n * a.srcH + h0) * a.srcW + w0) * (uint32_t)a.apitch + (uint32_t)kvoff;
         // validity is separable: one bit per filter column, replicated for every valid filter row
-        uint32_t colbits = 0;
-        for (int t = 0; t < a.TSm; ++t) colbits |= ((unsigned)(w0 + t * a.ts_step) < (unsigned)a.srcW ? 1u : 0u) << t;
+        uint64_t colbits = 0;
+        for (int t = 0; t < a.TSm; ++t) colbits |= (uint64_t)((unsigned)(w0 + t * a.ts_step) < (unsigned)a.srcW) << t;
         uint64_t mask = 0;
         for (int r = 0; r < a.TR; ++r)
-            if ((unsigned)(h0 + r * a.tr_step) < (unsigned)a.srcH) mask |= (uint64_t)colbits << (r * a.TSm);
+            if ((unsigned)(h0 + r * a.tr_step) < (unsigned)a.srcH) mask |= colbits << (r * a.TSm);
         a_mask[j] = mask;
     }
     const uint32_t b_rowlen = (uint32_t)a.b_taps * a.bpitch;

@@ -107,6 +107,15 @@ def test_ragged_channel_counts_with_zero_padding_vouched(case):
     _check_full(spec, 400 + sum(case), pitch8(spec.C), pitch8(spec.K), pitch8(spec.C), pad_zero=True)
 
 
+@pytest.mark.parametrize("R,S,pad", [(1, 33, 16), (1, 40, 20), (1, 64, 31), (2, 32, 16), (40, 1, 20), (1, 9, 4), (1, 65, 32)])
+@pytest.mark.parametrize("C,K", [(64, 40), (12, 24), (56, 16)])
+def test_long_filters(R, S, pad, C, K):
+    """Filter rows past the 32 taps of a 32-bit mask, runs of folded taps past the eight blocks of the table of tails (NaN in
+    the channel padding), and more taps than the direct kernel has bits for."""
+    from gpu_util import pitch8
+    _check_full(wl.ConvSpec("t", 1, 45, 47, C, K, R, S, 1, pad, None, None), 700 + R + S + C, pitch8(C), pitch8(K), pitch8(C))
+
+
 MANY_TILES = [
     # launches with more tiles than the chip holds workgroups at once (650 - 770 pixel tiles, all whole), in both
     # pipeline depths of the direct kernel and with one, two, four and nine reduction steps per tile
