@@ -424,7 +424,9 @@ __device__ __forceinline__ void wait_vmcnt() {
 // TAIL = some run of channels ends inside an 8-chunk whose remaining elements are undefined.
 // STATS = also reduce the stored outputs to per-channel sums and sums of squares (see IgemmArgs::stats).
 // AV = the caller has established that every tap of every row lies inside the source image (no validity tests).
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool RAGGED, bool TAIL = RAGGED, bool STATS = false, bool AV = false>
+// FOLD = the problem may be a folded one (without AV; the branch for it costs the others 22.2 -> 23.1 us on 14 x 14 x 256 -> 256,
+// 3 x 3, batch 64: the loads no longer share a block with the step's LDS reads and MFMAs).
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool RAGGED, bool TAIL, bool STATS, bool AV, bool FOLD>
 __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN problems) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
     const IgemmArgs a = problems.a[blockIdx.y];  // (a copy: the fields then live in scalar registers as kernel arguments do)
@@ -457,7 +459,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
     // per-lane row constants: element offset of tap (0,0) + chunk, and a bit per tap: tap inside the image.
     // Rows past the end of the problem are clamped to the last row: their results are never stored.
     uint32_t a_off[LA];
-    uint64_t a_mask[LA];  // bit (r * TSm + s): tap (r, s) of this row lies inside the image
+    int skip_lo[LA], skip_hi[LA];  // bit r * TSm + s: tap (r, s) of this row lies outside the image (hi: from the 33rd tap on)
 #pragma unroll
     for (int j = 0; j < LA; ++j) {
         const int m = min(m0 + (wave + NW * j) * 8 + lrow, a.M - 1);
@@ -471,7 +473,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
         uint64_t mask = 0;
         for (int r = 0; r < a.TR; ++r)
             if ((unsigned)(h0 + r * a.tr_step) < (unsigned)a.srcH) mask |= colbits << (r * a.TSm);
-        a_mask[j] = mask;
+        skip_lo[j] = (int)~(uint32_t)mask;
+        skip_hi[j] = (int)~(uint32_t)(mask >> 32);
     }
     const uint32_t b_rowlen = (uint32_t)a.b_taps * a.bpitch;
     uint32_t b_off[LB];
@@ -497,10 +500,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
 #pragma unroll
     for (int j = 0; j < LB; ++j) b_v[j] = b_off[j] * 2u;
 
-    // The next step to issue, kept as running scalar offsets: a step adds one of three constants (next 64 channels, next
-    // filter column, next filter row).  Which lanes read zeros changes with the tap only, so it is worked out once per tap.
-    // (Recomputing both from the tap and block every step cost 0.9 % of ResNet-50's forward pass, 1278 -> 1267 us, and 0.7 % of
-    // the whole step, 3419 -> 3395 us.)
+    // With taps outside the image the next step to issue is kept as running scalar offsets, to which a step adds one of three
+    // constants (next 64 channels, next filter column, next filter row), and which lanes read zeros, which changes with the
+    // tap only, is worked out once per tap: recomputing both in every step takes 23.1 us instead of 22.8 for 14 x 14 x 256 ->
+    // 256, 3 x 3, batch 64, the test alone in every step 24.0.  With none outside (mostly 1 x 1 layers of few steps) there is
+    // no test, and what the constants take ahead of the first load is not won back: 28 x 28 x 512 -> 128 12.96 us with them,
+    // 12.70 with the offsets from tap and block.
     const int nblk = (a.CredP + BK - 1) / BK;
     const int ts_a = a.ts_step * a.apitch * 2, ts_b = a.b_ts_stride * a.bpitch * 2, back = (nblk - 1) * BK * 2;
     const int col_a = ts_a - back, col_b = ts_b - back;
@@ -508,61 +513,59 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
     const int row_b = a.b_tr_stride * a.bpitch * 2 - (a.TS - 1) * ts_b - back;
     uint32_t s_a = (uint32_t)(-a.a_smin * 2), s_b = (uint32_t)(a.b_tap0 * a.bpitch * 2);
     int blk = nblk, col = a.TS;          // blocks left of this tap, columns left of this filter row
+    int tap = 0, f_cb = 0;               // tap (folded mode: the first one of its filter row) and channel base
+    int i_tr = 0, i_ts = 0, i_cb = 0;    // AV: tap and channel base
     int c_cb = 0;                        // channel base of the next step to compute (uniform)
-    int f_cb = 0, f_tap = 0;             // folded mode: channel base and first tap of the filter row
-    uint32_t a_now[LA];                  // a_v or the out-of-range offset
-    auto next_tap = [&]() {
-        if constexpr (!AV) {
+    const uint32_t past = RAGGED && (nblk - 1) * BK + kvoff >= a.Cred ? kBufOut : 0u;  // in a tap's last block
+    uint32_t a_now[LA];                  // a_v, or kBufOut in lanes that read zeros: the tap's bit sign-extended, and an OR
+    auto set_tap = [&](int t) {
 #pragma unroll
-            for (int j = 0; j < LA; ++j) {
-                a_now[j] = (a_mask[j] & 1u) ? a_v[j] : kBufOut;
-                a_mask[j] >>= 1;
-            }
-        }
+        for (int j = 0; j < LA; ++j)
+            a_now[j] = AV ? a_v[j] : a_v[j] | (uint32_t)__builtin_amdgcn_sbfe(t & 32 ? skip_hi[j] : skip_lo[j], t & 31, 1);
     };
-#pragma unroll
-    for (int j = 0; j < LA; ++j) a_now[j] = a_v[j];
-    if (!a.fold) next_tap();
+    set_tap(0);
 
     auto issue = [&](int stage) {
         uint8_t* sbase = smem_b + stage * STAGE_BYTES;
-        uint32_t va[LA], vb[LB];
-#pragma unroll
-        for (int j = 0; j < LA; ++j) va[j] = a_now[j];
-#pragma unroll
-        for (int j = 0; j < LB; ++j) vb[j] = b_v[j];
-        if constexpr (!AV) {
-            if (a.fold) {  // uniform: the tap depends on the lane's chunk
-                const int tapbit = f_tap + (int)fdiv((uint32_t)(f_cb + kvoff), a.Cfold);
-#pragma unroll
-                for (int j = 0; j < LA; ++j) va[j] = (f_cb + kvoff < a.Cred && ((a_mask[j] >> tapbit) & 1u)) ? a_v[j] : kBufOut;
+        uint32_t sa, sb;
+        bool last;
+        if constexpr (AV) {
+            sa = (uint32_t)(((i_tr * a.tr_step * a.srcW + i_ts * a.ts_step) * a.apitch + i_cb - a.a_smin) * 2);
+            sb = (uint32_t)(((a.b_tap0 + i_tr * a.b_tr_stride + i_ts * a.b_ts_stride) * a.bpitch + i_cb) * 2);
+            last = i_cb + BK >= a.CredP;
+        } else {
+            sa = s_a;
+            sb = s_b;
+            last = blk == 1;
+            // (uniform) folded: the tap depends on the lane's chunk; past the last chunk it means nothing
+            if constexpr (FOLD) {
+                if (a.fold) set_tap(tap + (int)fdiv((uint32_t)(f_cb + kvoff), a.Cfold));
             }
         }
-        if constexpr (RAGGED) {
-            if (blk == 1) {  // uniform: the last block of the tap
-                const bool ok = (nblk - 1) * BK + kvoff < a.Cred;
-#pragma unroll
-                for (int j = 0; j < LA; ++j) va[j] = ok ? va[j] : kBufOut;
-#pragma unroll
-                for (int j = 0; j < LB; ++j) vb[j] = ok ? vb[j] : kBufOut;
-            }
-        }
+        const uint32_t zero = RAGGED ? past & (last ? ~0u : 0u) : 0u;
 #pragma unroll
         for (int j = 0; j < LA; ++j)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_srd, (lds_void_ptr)(sbase + (wave + NW * j) * 1024), 16, va[j], s_a, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_srd, (lds_void_ptr)(sbase + (wave + NW * j) * 1024), 16, a_now[j] | zero, sa, 0, 0);
 #pragma unroll
         for (int j = 0; j < LB; ++j)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(b_srd, (lds_void_ptr)(sbase + BM * 128 + (wave + NW * j) * 1024), 16, vb[j], s_b, 0, 0);
-        // (selects, not branches: the counters stay in scalar registers)
-        const bool last = blk == 1, last_col = col == 1;
-        s_a += (uint32_t)(last ? (last_col ? row_a : col_a) : BK * 2);
-        s_b += (uint32_t)(last ? (last_col ? row_b : col_b) : BK * 2);
-        blk = last ? nblk : blk - 1;
-        col = last ? (last_col ? a.TS : col - 1) : col;
-        if constexpr (!AV) {
-            f_tap += last ? a.TSm : 0;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(b_srd, (lds_void_ptr)(sbase + BM * 128 + (wave + NW * j) * 1024), 16,
+                                                     b_v[j] | zero, sb, 0, 0);
+        if constexpr (AV) {
+            i_cb += BK;
+            if (i_cb >= a.CredP) {
+                i_cb = 0;
+                if (++i_ts == a.TS) { i_ts = 0; ++i_tr; }
+            }
+        } else {
+            // (selects, not branches: the counters stay in scalar registers)
+            const bool last_col = col == 1;
+            s_a += (uint32_t)(last ? (last_col ? row_a : col_a) : BK * 2);
+            s_b += (uint32_t)(last ? (last_col ? row_b : col_b) : BK * 2);
+            blk = last ? nblk : blk - 1;
+            col = last ? (last_col ? a.TS : col - 1) : col;
+            tap += last ? (FOLD && a.fold ? a.TSm : 1) : 0;
             f_cb = last ? 0 : f_cb + BK;
-            if (last && !a.fold) next_tap();
+            if (last) set_tap(tap);
         }
     };
     // ---- MFMA state ---------------------------------------------------------------------------
@@ -861,12 +864,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
 // What the host has decided for one problem of the direct kernel: which instantiation, and its launch shape.
 typedef void (*igemm_dl_kern_t)(const IgemmArgsN);
 struct IgemmDlPlan {
-    igemm_dl_kern_t kern;
-    LdsOptIn* opt_in;
-    // the same instantiation with the tap validity tests (== kern unless the problem is free of them): what a group of
-    // problems falls back to when only some of them could do without
-    igemm_dl_kern_t kern_tests;
-    LdsOptIn* opt_in_tests;
+    // [0] the instantiation for this problem, [1] the same with the tap validity tests, [2] with the folded mode as well: what
+    // a group of problems falls back to when only some of them could do without
+    igemm_dl_kern_t kern[3];
+    LdsOptIn* opt_in[3];
     size_t lds, lds_used;
     int threads;
 };
@@ -876,19 +877,12 @@ struct IgemmDlPlan {
 inline hipError_t launch_igemm_dl_planned(const IgemmArgs* as, const IgemmDlPlan* ps, int n, hipStream_t st) {
     bool done[kIgemmMaxProblems] = {false, false, false, false};
     if (n > kIgemmMaxProblems) return hipErrorInvalidValue;
-    IgemmDlPlan local[kIgemmMaxProblems];
-    bool same = true, same_tests = true;
-    for (int i = 1; i < n; ++i) {
-        same = same && ps[i].kern == ps[0].kern;
-        same_tests = same_tests && ps[i].kern_tests == ps[0].kern_tests;
-    }
-    if (!same && same_tests) {  // one launch with the validity tests rather than two without and with
-        for (int i = 0; i < n; ++i) {
-            local[i] = ps[i];
-            local[i].kern = ps[i].kern_tests;
-            local[i].opt_in = ps[i].opt_in_tests;
-        }
-        ps = local;
+    // one launch of a more general instantiation rather than two of their own
+    int level = 0;
+    for (int l = 2; l >= 0; --l) {
+        bool same = true;
+        for (int i = 1; i < n; ++i) same = same && ps[i].kern[l] == ps[0].kern[l];
+        if (same) level = l;
     }
     for (int i = 0; i < n; ++i) {
         if (done[i]) continue;
@@ -896,7 +890,7 @@ inline hipError_t launch_igemm_dl_planned(const IgemmArgs* as, const IgemmDlPlan
         int cnt = 0, gx = 0;
         size_t lds_used = 0;
         for (int j = i; j < n; ++j) {
-            if (done[j] || ps[j].kern != ps[i].kern) continue;
+            if (done[j] || ps[j].kern[level] != ps[i].kern[level]) continue;
             done[j] = true;
             // longest workgroups first: the launch ends on short ones
             int at = cnt++;
@@ -905,10 +899,11 @@ inline hipError_t launch_igemm_dl_planned(const IgemmArgs* as, const IgemmDlPlan
             gx = as[j].grid_x > gx ? as[j].grid_x : gx;
             lds_used = ps[j].lds_used > lds_used ? ps[j].lds_used : lds_used;
         }
-        if (hipError_t e = ps[i].opt_in->ensure(reinterpret_cast<const void*>(ps[i].kern), ps[i].lds); e != hipSuccess) return e;
+        const igemm_dl_kern_t kern = ps[i].kern[level];
+        if (hipError_t e = ps[i].opt_in[level]->ensure(reinterpret_cast<const void*>(kern), ps[i].lds); e != hipSuccess) return e;
         // (several problems: a width that is a multiple of the 8 XCDs keeps every problem's tile -> XCD assignment)
         const unsigned gxr = cnt > 1 ? (unsigned)((gx + 7) / 8 * 8) : (unsigned)gx;
-        hipLaunchKernelGGL(ps[i].kern, dim3(gxr, (unsigned)cnt), dim3((unsigned)ps[i].threads), lds_used, st, m);
+        hipLaunchKernelGGL(kern, dim3(gxr, (unsigned)cnt), dim3((unsigned)ps[i].threads), lds_used, st, m);
     }
     return hipSuccess;
 }
@@ -950,22 +945,27 @@ inline hipError_t plan_igemm_dl_cfg(IgemmArgs& a, IgemmDlPlan& plan) {
     a.a_all_valid = inside(h_first, h_last, a.srcH) && inside(h_first + rr, h_last + rr, a.srcH) &&
                     inside(w_first, w_last, a.srcW) && inside(w_first + ss, w_last + ss, a.srcW);
     const bool av = a.a_all_valid && variant != 2;
-    typedef igemm_dl_kern_t kern_t;
-    const kern_t kerns[2][5] = {{k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, false, false>,
-                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, false, false>,
-                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, true, false, false>,
-                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, true, false>,
-                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, true, false>},
-                                {k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, false, true>,
-                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, false, true>,
-                                 nullptr,
-                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, true, true>,
-                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, true, true>}};
-    static LdsOptIn opt_in[2][5];
-    plan.kern = kerns[av ? 1 : 0][variant];
-    plan.opt_in = &opt_in[av ? 1 : 0][variant];
-    plan.kern_tests = kerns[0][variant];
-    plan.opt_in_tests = &opt_in[0][variant];
+    static const igemm_dl_kern_t kerns[3][5] = {{k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, false, false, false>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, false, false, false>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, true, false, false, false>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, true, false, false>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, true, false, false>},
+                                                {k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, false, true, false>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, false, true, false>,
+                                                 nullptr,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, true, true, false>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, true, true, false>},
+                                                {k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, false, false, true>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, false, false, true>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, true, false, false, true>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, true, false, true>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, true, false, true>}};
+    static LdsOptIn opt_in[3][5];
+    const int tests = a.fold ? 2 : 0, rows[3] = {av ? 1 : tests, tests, 2};
+    for (int l = 0; l < 3; ++l) {
+        plan.kern[l] = kerns[rows[l]][variant];
+        plan.opt_in[l] = &opt_in[rows[l]][variant];
+    }
     plan.lds = lds;
     plan.threads = NT;
     const int64_t tiles = ceil_div(a.M, BM) * a.tiles_n;
@@ -1179,8 +1179,10 @@ inline hipError_t plan_igemm_small_cfg(IgemmArgs& a, IgemmDlPlan& plan) {
     // neighbouring tiles, which share an XCD and its L2, should share the larger operand
     a.m_fast = (int64_t)a.Nout * a.b_taps * a.bpitch > (int64_t)a.M * a.CredP;
     static LdsOptIn opt_in;
-    plan.kern = plan.kern_tests = k_igemm_small<BM, BN, NB, STAGES>;
-    plan.opt_in = plan.opt_in_tests = &opt_in;
+    for (int l = 0; l < 3; ++l) {
+        plan.kern[l] = k_igemm_small<BM, BN, NB, STAGES>;
+        plan.opt_in[l] = &opt_in;
+    }
     plan.lds = plan.lds_used = lds;
     plan.threads = 512;
     const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;

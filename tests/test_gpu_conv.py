@@ -233,6 +233,11 @@ BATCHED_FWD = [
     [(2, 14, 14, 64, 64, 3, 1, 1), (2, 14, 14, 64, 256, 1, 1, 0), (2, 14, 14, 64, 64, 1, 1, 0)],   # three problems, mixed shapes
     [(2, 18, 18, 3, 16, 7, 2, 3), (2, 12, 12, 24, 40, 3, 1, 1)],               # an image-like first layer beside a 3 x 3 layer
     [(2, 9, 9, 16, 24, 1, 1, 0)] * 5,                                          # more problems than one launch holds
+    # 128 x 128 tiles of different instantiations that share a launch of the more general one: with and without taps outside
+    # the image, then with folded filter rows as well, and one folded problem beside one without any test
+    [(4, 56, 56, 72, 384, 3, 1, 1), (4, 56, 56, 72, 384, 1, 1, 0)],
+    [(4, 56, 56, 72, 384, 1, 1, 0), (4, 56, 56, 24, 384, 3, 1, 1), (4, 56, 56, 72, 384, 3, 1, 1)],
+    [(4, 56, 56, 24, 384, 3, 1, 1), (4, 56, 56, 72, 384, 1, 2, 0), (4, 56, 56, 72, 1536, 1, 2, 0)],
 ]
 
 
