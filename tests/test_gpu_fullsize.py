@@ -159,14 +159,18 @@ def test_cfg4_pruned_shapes_batch2_whole_tensors():
         _check_layer_whole(_at_batch(spec, 2), seed=3500 + i)
 
 
-@pytest.mark.parametrize("norms_head,branches", [(11, True), (None, True), (None, False)],
-                         ids=["norms_split_over_two_streams", "norms_before_forward", "shortcuts_on_the_main_stream"])
-def test_cfg2_resnet32_train_step_on_side_streams_against_oracle(norms_head, branches, monkeypatch):
+@pytest.mark.parametrize("norms_head,branches,grouped", [
+    (11, True, False), (None, True, False), (None, False, False), (11, True, True), (None, True, True), (None, False, True),
+], ids=["norms_split_over_two_streams", "norms_before_forward", "shortcuts_on_the_main_stream", "groups_norms_split",
+        "groups", "groups_shortcuts_by_themselves"])
+def test_cfg2_resnet32_train_step_on_side_streams_against_oracle(norms_head, branches, grouped, monkeypatch):
     """Network.train_step as the benchmark runs it (norms split over two streams or all ahead of the forward pass,
     k-innermost filter copies, the input gradients of the blocks' shortcut convolutions on a side stream or in line, weight
     gradients with the regulariser folded in on four side streams, zero padding vouched for) on the whole ResNet-32
     stack at batch 128: every layer's norms, y, dx and dw against the oracle.  Then the weights change (one optimizer
-    step) and a second step must see the new weights everywhere, the k-innermost copies of the first layers too."""
+    step) and a second step must see the new weights everywhere, the k-innermost copies of the first layers too.
+    Grouped: as a network of this size runs by itself, the weight gradients in three calls on one side stream and the
+    shortcuts' input gradients in one call with their neighbours'; the benchmark's networks are above that limit."""
     from gpu_util import CONV_TOL, F32_TOL, host_bf16, rel_err
     from paper_1901_09290_amd import harness as hz
     specs, _ = wl.resnet32_layers(N=128)
@@ -174,8 +178,12 @@ def test_cfg2_resnet32_train_step_on_side_streams_against_oracle(norms_head, bra
     host = [wl.conv_tensors(s, rng) for s in specs]
     if norms_head is not None:
         monkeypatch.setattr(hz, "NORMS_HEAD_LAYERS", norms_head)
+    if not grouped:
+        monkeypatch.setattr(hz, "WGRAD_GROUP_MAX_BYTES", 0)
     net = hz.Network([hz.ConvLayer(s, host=t) for s, t in zip(specs, host)])
     assert net.overlap_wgrad and net.fuse_lasso and (net.norm_jobs_tail is not None) == (norms_head is not None)
+    assert net.grouped == grouped and len(net.sides) == (1 if grouped else 4)
+    assert len(net.groups) == (3 if grouped else len(specs)) and net.wgrad_workgroups == (0 if grouped else hz.WGRAD_WORKGROUPS)
     # the two stride-2 stages have a shortcut convolution each, forking where their first block starts
     names = [s.name for s in specs]
     assert net.overlap_branches and {names[j]: names[i] for j, i in net.fork.items()} == {
@@ -287,7 +295,8 @@ def test_cfg5_resnet50_reconfiguration_sweep(seed):
 # ---------------------------------------------------------------------------------------------- #
 # HIP graph: replays equal the eager launches
 # ---------------------------------------------------------------------------------------------- #
-def test_hip_graph_replays_equal_eager():
+@pytest.mark.parametrize("grouped", [True, False])
+def test_hip_graph_replays_equal_eager(grouped, monkeypatch):
     """The benchmark replays captured launch sequences.  Capture a training step of a small network
     (stride-2, ragged and folded layers) plus the sweep's detection; replay it several times with eager
     work and synchronisation in between; every replay must reproduce the eager results bit for bit."""
@@ -306,8 +315,10 @@ def test_hip_graph_replays_equal_eager():
     ]
     edges = [wl.Edge("e0", 24, [0], [1]), wl.Edge("e1", 40, [1], [2]), wl.Edge("e2", 72, [2], [3, 4, 7]),
              wl.Edge("e3", 32, [4], [5]), wl.Edge("e4", 32, [5], [6]), wl.Edge("e5", 96, [6, 7], [])]
+    if not grouped:     # weight gradients one by one on four side streams, as in a network of the benchmark's size
+        monkeypatch.setattr(hz, "WGRAD_GROUP_MAX_BYTES", 0)
     net = hz.Network(hz.build_network(specs, seed=5))
-    assert net.fork == {4: 7} and net.overlap_branches and net.batch_branches_fwd
+    assert net.grouped == grouped and net.fork == {4: 7} and net.overlap_branches and net.batch_branches_fwd
     rng = np.random.Generator(np.random.PCG64(5))
     zero_sets = wl.zeroed_channel_sets(edges, 0.25, rng)
     model = hz.ReconfigModel(specs, edges, wl.network_weights(specs, edges, zero_sets, rng), seed=6)
