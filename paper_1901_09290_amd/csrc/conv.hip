@@ -829,9 +829,11 @@ static int32_t plan_wgrad_batched(const pt_layer_wgrad* layers, int n, float lam
         out[i].p = plan_wgrad_tiles(&l.d, out[i].vec);
         total += (float)out[i].p.tiles_m * out[i].p.tiles_n * out[i].p.iters_total * wgrad_step_us(out[i].p);
     }
+    const bool alone = n == 1 && !workgroups;  // one layer with the chip to itself: planned as pt_conv_bwd_weight plans it
+    if (alone && !out[0].stem) out[0].p = plan_wgrad(out[0].d, out[0].vec);
     float best_us = 1e30f;
     int best = 1;
-    for (int rounds = 1; rounds <= (workgroups ? 1 : 4); ++rounds) {
+    for (int rounds = 1; !alone && rounds <= (workgroups ? 1 : 4); ++rounds) {
         const float piece = total / (float)(rounds * slots);
         float longest = 0.f, part = 0.f;
         for (int i = 0; i < n; ++i) {
@@ -850,7 +852,7 @@ static int32_t plan_wgrad_batched(const pt_layer_wgrad* layers, int n, float lam
     }
     size_t off = 0;
     for (int i = 0; i < n; ++i) {
-        if (!out[i].stem) {
+        if (!out[i].stem && !alone) {
             WgradPlan& p = out[i].p;
             const float piece = total / (float)(best * slots);
             if (n == 1 && workgroups)  // (two of the smaller workgroups find room on a CU beside others)

@@ -209,6 +209,18 @@ def test_batched_gradient_calls_validate_on_the_host(lib):
     assert f(ok, ptrs(4096, 4098), ok) == -2
 
 
+@pytest.mark.parametrize("shape", [(64, 28, 371, 115, 1), (64, 14, 256, 256, 3), (64, 56, 64, 64, 3), (8, 7, 512, 512, 3),
+                                   (4, 16, 16, 16, 3), (2, 9, 45, 38, 3), (64, 56, 64, 256, 1)])
+def test_batched_gradient_call_of_one_layer_takes_the_single_calls_plan(lib, shape):
+    """The same layer in pt_conv_bwd_weight and alone in pt_conv_bwd_weight_batched: as many splits, so as much workspace."""
+    N, H, Cc, K, R = shape
+    p8 = lambda n: (n + 7) // 8 * 8
+    d = B.conv_desc(N, H, H, Cc, K, R, R, 1, R // 2, p8(Cc), p8(K), p8(Cc))
+    info = B.conv_bwd_weight_plan(d, True)
+    need = 0 if info.splits == 1 else (info.splits * K * R * R * p8(Cc) * 4 + 255) // 256 * 256
+    assert B.conv_bwd_weight_batched_workspace_bytes([B.LayerWgrad(d=d, x=4096, dy=4096, dw=4096)]) == need
+
+
 def test_crsk_calls_validate_on_the_host(lib):
     fake = 256
     assert lib.pt_weights_to_crsk_batched(None, 0, None) == 0
