@@ -62,15 +62,19 @@ def short(name: str) -> str:
     return n.replace("pt::", "")
 
 
-MAIN_FAMILIES = ("k_igemm_dl", "k_wgrad_dl", "k_igemm", "k_wgrad", "k_stem_fwd", "k_stem_wgrad", "k_conv3x3_res")
+# Kernels of the convolution calls and the family each is counted under (a digit behind the name is part of the variant).
+FAMILIES = {"k_igemm_dl": "k_igemm_dl", "k_igemm_small": "k_igemm_small", "k_igemm": "k_igemm", "k_conv3x3_res": "k_conv3x3_res",
+            "k_stem_fwd": "k_stem_fwd", "k_stem_wgrad": "k_stem_wgrad", "k_wgrad_dl": "k_wgrad_dl",
+            "k_wgrad_dl_multi": "k_wgrad_dl_multi", "k_wgrad": "k_wgrad", "k_wgrad_reduce": "k_wgrad_reduce",
+            "k_wgrad_reduce_multi": "k_wgrad_reduce", "k_stem_wgrad_reduce": "k_wgrad_reduce", "k_zero_class": "k_zero_class",
+            "k_transpose_w": "k_transpose_w", "k_transpose_w_multi": "k_transpose_w", "k_tile_stats": "k_tile_stats"}
+# ... and those of them that run the matrix cores
+MAIN_FAMILIES = ("k_igemm_dl", "k_igemm_small", "k_wgrad_dl", "k_wgrad_dl_multi", "k_igemm", "k_wgrad", "k_stem_fwd",
+                 "k_stem_wgrad", "k_conv3x3_res")
 
 
 def family(n: str) -> Optional[str]:
-    for f in ("k_igemm_dl", "k_igemm", "k_conv3x3_res", "k_stem_fwd", "k_stem_wgrad_reduce", "k_stem_wgrad", "k_wgrad_dl", "k_wgrad_reduce", "k_wgrad",
-              "k_zero_class"):
-        if n.startswith(f + "<") or n == f or n.startswith(f + "4"):
-            return "k_wgrad_reduce" if f in ("k_wgrad_reduce", "k_stem_wgrad_reduce") else f
-    return None
+    return FAMILIES.get(re.match(r"\w*", n).group().rstrip("0123456789"))
 
 
 def load_trace(path: str) -> List[dict]:
@@ -266,10 +270,10 @@ def cmd_traffic(a) -> None:
         k[2] += sum(r["c"].get("FETCH_SIZE", 0) for r in f) * ff
         k[3] += sum(r["c"].get("WRITE_SIZE", 0) for r in w) * wf
         k[4] += c["bytes"]
-    o.append("%-66s %8s %15s %15s" % ("kernel", "launches", "fetch_MB/launch", "write_MB/launch"))
+    o.append("%-72s %8s %15s %15s" % ("kernel", "launches", "fetch_MB/launch", "write_MB/launch"))
     for n in sorted(agg, key=lambda n: -(agg[n][1] + agg[n][2])):
         c = agg[n]
-        o.append("%-66s %8d %15.2f %15.2f" % (n[:66], c[0], c[1] / c[0] / 1e6, c[2] / c[0] / 1e6))
+        o.append("%-72s %8d %15.2f %15.2f" % (n[:72], c[0], c[1] / c[0] / 1e6, c[2] / c[0] / 1e6))
     o.append("")
     k = per_kind["wgrad"]
     if k[0]:
@@ -279,7 +283,7 @@ def cmd_traffic(a) -> None:
                  % (k[4] / k[0] / 1e6, (k[2] + k[3]) / k[4]))
     k = per_kind["igemm"]
     if k[0]:
-        o.append("per k_igemm_dl launch (conv_fwd and conv_bwd_data calls, %d launches, the first layer's k_stem_fwd, the early 3x3 layers' k_conv3x3_res and the zero fill of empty parity classes included): fetch %.1f MB + write %.1f MB = %.1f MB of HBM traffic"
+        o.append("per k_igemm_dl launch (conv_fwd and conv_bwd_data calls, %d launches, k_igemm_small, the first layer's k_stem_fwd, the early 3x3 layers' k_conv3x3_res and the zero fill of empty parity classes included): fetch %.1f MB + write %.1f MB = %.1f MB of HBM traffic"
                  % (k[1], k[2] / k[1] / 1e6, k[3] / k[1] / 1e6, (k[2] + k[3]) / k[1] / 1e6))
         o.append("algorithmic bytes per launch: %.1f MB  -> traffic / algorithmic = %.2f" % (k[4] / k[1] / 1e6, (k[2] + k[3]) / k[4]))
     _write(a.out, o)
@@ -317,15 +321,15 @@ def cmd_mfma(a) -> None:
     o.append("busy% = MfmaUtil = SQ_VALU_MFMA_BUSY_CYCLES summed over the SIMDs / (GRBM_GUI_ACTIVE x number of SIMDs): the share of the kernel's")
     o.append("cycles in which a SIMD's matrix core was executing, averaged over the launches with their durations as weights.")
     o.append("")
-    o.append("%-7s %-52s %6s %8s %9s %9s %5s %7s %6s %6s" % ("width", "kernel", "calls", "avg_us", "alg_GF", "mfma_GF", "pad", "TF/s", "%peak", "busy%"))
+    o.append("%-7s %-72s %6s %8s %9s %9s %5s %7s %6s %6s" % ("width", "kernel", "calls", "avg_us", "alg_GF", "mfma_GF", "pad", "TF/s", "%peak", "busy%"))
     keys = sorted(agg, key=lambda k: (k[0], -agg[k]["us"]))
     tot = collections.defaultdict(lambda: collections.defaultdict(float))
     for key in keys:
         g = agg[key]
         mf = g.get("SQ_INSTS_VALU_MFMA_MOPS_BF16", 0.0) * MFMA_FLOP_PER_MOP
         busy = g["util_us"] / g["us"] / 100
-        o.append("%-7s %-52s %6d %8.2f %9.2f %9.2f %5.2f %7.0f %6.1f %6.1f" % (
-            key[0], key[1][:52], g["n"], g["us"] / g["n"], g["flops"] / g["n"] / 1e9, mf / g["n"] / 1e9,
+        o.append("%-7s %-72s %6d %8.2f %9.2f %9.2f %5.2f %7.0f %6.1f %6.1f" % (
+            key[0], key[1][:72], g["n"], g["us"] / g["n"], g["flops"] / g["n"] / 1e9, mf / g["n"] / 1e9,
             mf / max(1.0, g["flops"]), mf / g["us"] / 1e6, 100 * mf / (g["us"] * 1e-6) / peak, 100 * busy))
         t = tot[(key[0], family(key[1]))]
         for k, v in g.items():
@@ -335,7 +339,7 @@ def cmd_mfma(a) -> None:
         g = tot[key]
         mf = g.get("SQ_INSTS_VALU_MFMA_MOPS_BF16", 0.0) * MFMA_FLOP_PER_MOP
         busy = g["util_us"] / g["us"] / 100
-        o.append("%-7s %-12s all instantiations: %5d launches, %8.1f us; executed %.1f TFLOP/s on the matrix cores = %.1f%% of the bf16 peak (algorithmic %.1f TFLOP/s); MFMA busy %.1f%%" % (
+        o.append("%-7s %-14s all instantiations: %5d launches, %8.1f us; executed %.1f TFLOP/s on the matrix cores = %.1f%% of the bf16 peak (algorithmic %.1f TFLOP/s); MFMA busy %.1f%%" % (
             key[0], key[1], g["n"], g["us"], mf / g["us"] / 1e6, 100 * mf / (g["us"] * 1e-6) / peak, g["flops"] / g["us"] / 1e6, 100 * busy))
     _write(a.out, o)
 
@@ -351,7 +355,7 @@ def cmd_step(a) -> None:
     o.append("  python3 -m paper_1901_09290_amd.profile_report step --stats <out>/..._kernel_stats.csv --bench <out>/bench.json --out <this file>")
     o.append("durations in microseconds; the run holds the timed graph replays of the step plus the per-phase and per-family timing passes of bench.py")
     o.append("")
-    o.append("%-66s %7s %11s %9s %9s %9s %6s" % ("kernel", "calls", "total_us", "avg_us", "min_us", "max_us", "pct"))
+    o.append("%-72s %7s %11s %9s %9s %9s %6s" % ("kernel", "calls", "total_us", "avg_us", "min_us", "max_us", "pct"))
     tot, calls = collections.defaultdict(float), collections.defaultdict(int)
     for r in rows:
         n = short(r["Name"])
@@ -361,7 +365,7 @@ def cmd_step(a) -> None:
             calls[f] += int(r["Calls"])
         if float(r["Percentage"]) < 0.05:
             continue
-        o.append("%-66s %7d %11.1f %9.2f %9.2f %9.2f %6.2f" % (n[:66], int(r["Calls"]), float(r["TotalDurationNs"]) / 1e3,
+        o.append("%-72s %7d %11.1f %9.2f %9.2f %9.2f %6.2f" % (n[:72], int(r["Calls"]), float(r["TotalDurationNs"]) / 1e3,
                  float(r["AverageNs"]) / 1e3, float(r["MinNs"]) / 1e3, float(r["MaxNs"]) / 1e3, float(r["Percentage"])))
     o.append("")
     rl = bench["roofline"]
@@ -375,6 +379,9 @@ def cmd_step(a) -> None:
         o.append("  k_wgrad_dl (all instantiations): %d launches, %.1f us total, %.2f us average; k_wgrad_reduce: %d launches, %.2f us average"
                  % (calls["k_wgrad_dl"], tot["k_wgrad_dl"], tot["k_wgrad_dl"] / calls["k_wgrad_dl"], calls["k_wgrad_reduce"],
                     tot["k_wgrad_reduce"] / max(1, calls["k_wgrad_reduce"])))
+    for f in sorted(tot):
+        if f not in ("k_igemm_dl", "k_wgrad_dl", "k_wgrad_reduce"):
+            o.append("  %s: %d launches, %.1f us total, %.2f us average" % (f, calls[f], tot[f], tot[f] / calls[f]))
     o.append("")
     o.append("bench.py line of the same run (value, step time, roofline):")
     o.append(json.dumps({k: bench[k] for k in ("value", "unit", "ms_per_step", "roofline")}))

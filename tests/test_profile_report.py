@@ -3,6 +3,7 @@ byte counters by the copy probe, and the figures derived from them (no GPU, synt
 import csv
 import json
 import os
+import re
 
 import pytest
 
@@ -70,6 +71,21 @@ def test_trace_splits_into_the_manifests_calls(tmp_path):
     assert [len(s) for s in segs] == [1, 4, 2] * 3
     assert all(pr.family(r["name"]) == "k_igemm_dl" for r in segs[1])
     assert [pr.family(r["name"]) for r in segs[2]] == ["k_wgrad_dl", "k_wgrad_reduce"]
+
+
+def test_every_kernel_of_the_convolution_calls_has_a_family():
+    """The kernels in the convolution sources, by their declarations: a new one has to be given a family, or its time would
+    be left out of the tables.  Variants with template arguments or a digit behind the name fall under the kernel's own."""
+    csrc, kernels = os.path.join(os.path.dirname(pr.__file__), "csrc"), set()
+    for name in ("conv.hip", "conv_kernels.h"):
+        text = open(os.path.join(csrc, name)).read()
+        kernels |= set(re.findall(r"__global__[^;{]*?\bvoid\s+(k_\w+)|__global__[^;{]*?\)\s*void\s+(k_\w+)", text))
+    kernels = {k for pair in kernels for k in pair if k}
+    assert len(kernels) >= 15 and kernels == set(pr.FAMILIES)
+    assert set(pr.MAIN_FAMILIES) <= set(pr.FAMILIES.values())
+    assert pr.family("k_igemm_small<64, 64, 1, 3>") == "k_igemm_small" and pr.family("k_wgrad_reduce4<true>") == "k_wgrad_reduce"
+    assert pr.family("k_wgrad_dl_multi") == "k_wgrad_dl_multi" and pr.family("k_wgrad_reduce_multi") == "k_wgrad_reduce"
+    assert pr.family("k_bn_sums<0>") is None and pr.family("at::native::x") is None
 
 
 def test_missing_marker_triple_is_an_error(tmp_path):
