@@ -23,6 +23,7 @@
 // costs one partially filled 8-vector per tap; lanes beyond C are masked to zero on load.  32-wide
 // accumulator blocks that lie wholly outside the logical output are skipped.
 #include <algorithm>
+#include <exception>
 #include <vector>
 
 #include "conv_kernels.h"
@@ -810,7 +811,11 @@ static int32_t plan_wgrad_batched(const pt_layer_wgrad* layers, int n, float lam
                                   std::vector<WgradLayer>& out, size_t* bytes, bool query) {
     if (workgroups < 0) return PT_ERR_SHAPE;
     const int slots = workgroups ? workgroups : kWgSlots;
-    out.resize((size_t)n);
+    try {
+        out.resize((size_t)n);
+    } catch (const std::exception&) {  // (no memory for the plan: no exception leaves a C entry point)
+        return PT_ERR_UNSUPPORTED;
+    }
     float total = 0.f;
     for (int i = 0; i < n; ++i) {
         const pt_layer_wgrad& l = layers[i];

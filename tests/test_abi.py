@@ -3,6 +3,8 @@ host-side argument validation answers with status codes before anything is enque
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -219,6 +221,18 @@ def test_batched_gradient_call_of_one_layer_takes_the_single_calls_plan(lib, sha
     info = B.conv_bwd_weight_plan(d, True)
     need = 0 if info.splits == 1 else (info.splits * K * R * R * p8(Cc) * 4 + 255) // 256 * 256
     assert B.conv_bwd_weight_batched_workspace_bytes([B.LayerWgrad(d=d, x=4096, dy=4096, dw=4096)]) == need
+
+
+def test_batched_gradient_call_reports_a_plan_that_does_not_fit_memory():
+    """More layers than the address space has room to plan: a status, not an exception that ends the process (the layers
+    themselves are not looked at before)."""
+    code = ("import ctypes as C, resource\n"
+            "from paper_1901_09290_amd import binding as B\n"
+            "f, n = B.lib().pt_conv_bwd_weight_batched_workspace_bytes, C.c_size_t(0)\n"
+            "f.argtypes = None\n"
+            "resource.setrlimit(resource.RLIMIT_AS, (16 << 30, 16 << 30))\n"
+            "assert f(C.c_void_p(4096), C.c_int32(1 << 30), C.c_int32(0), C.byref(n)) == -4\n")
+    assert subprocess.run([sys.executable, "-c", code], cwd=ROOT).returncode == 0
 
 
 def test_crsk_calls_validate_on_the_host(lib):
