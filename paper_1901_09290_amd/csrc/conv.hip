@@ -465,7 +465,8 @@ static int32_t bwd_data_one(const pt_conv_desc* d, const uint16_t* dy, const uin
 }
 
 // Per-channel sums and sums of squares of 128 output pixels (blockIdx.x) x 64 channels (blockIdx.y), laid out as
-// IgemmArgs::stats: 8 channels a lane, four rows a thread, the 32 threads of a channel added in a fixed order.
+// IgemmArgs::stats: 8 channels a lane, four rows a thread, the 32 threads of a channel added as a tree (a chain of 3 + 5
+// additions, as short as that of the convolution kernels' epilogue).
 __global__ __launch_bounds__(256) void k_tile_stats(const uint16_t* __restrict__ y, int64_t pixels, int K, int ypitch,
                                                     float* __restrict__ stats) {
     __shared__ float red[2][32][65];
@@ -493,10 +494,14 @@ __global__ __launch_bounds__(256) void k_tile_stats(const uint16_t* __restrict__
     __syncthreads();
     if (threadIdx.x >= 128) return;
     const int c = threadIdx.x & 63, which = threadIdx.x >> 6, k = blockIdx.y * 64 + c;
-    float t = 0.f;
+    float t[32];
 #pragma unroll
-    for (int r = 0; r < 32; ++r) t += red[which][r][c];
-    if (k < K) stats[((size_t)which * gridDim.x + blockIdx.x) * K + k] = t;
+    for (int r = 0; r < 32; ++r) t[r] = red[which][r][c];
+#pragma unroll
+    for (int n = 16; n > 0; n /= 2)
+#pragma unroll
+        for (int r = 0; r < n; ++r) t[r] += t[r + n];
+    if (k < K) stats[((size_t)which * gridDim.x + blockIdx.x) * K + k] = t[0];
 }
 
 // Forward convolution with the statistics epilogue: only the direct kernel has it.

@@ -158,6 +158,30 @@ FUSED = [
 ]
 
 
+def test_statistics_of_small_tiles_have_short_chains():
+    """Sums of a small layer's output, taken tile by tile of 128 pixels: every 32nd pixel 1, the others 2^-25 (the weights are
+    the unit matrix in the middle of a 3 x 3 filter, so y = x, and the layer is one that takes small tiles).  The 32 partial sums of a channel added one by one lose all but the first (9e-7); added as
+    trees the chain is 2 + 5 additions, and a term of its own may be added to each of the four rows' sums."""
+    from gpu_util import DEV, dev_bf16, empty_bf16, workspace
+    N, H, C = 2, 16, 128
+    spec = wl.ConvSpec("t", N, H, H, C, C, 3, 3, 1, 1, None, None)
+    w = np.zeros((C, 3, 3, C), dtype=np.float32)
+    w[:, 1, 1] = np.eye(C)
+    x = np.full((N * H * H, C), 2.0 ** -25, dtype=np.float32)
+    x[::32] = 1.0
+    d = B.desc_of(spec, C, C, C, B.CONV_PAD_ZERO)
+    nbytes, n_partial = B.conv_fwd_stats_workspace(d)
+    sums, y = workspace(nbytes), empty_bf16((N * H * H, C), fill=0)
+    xd, wd = dev_bf16(x), dev_bf16(w)
+    B.conv_fwd_stats(d, xd, wd, y, sums)
+    torch.cuda.synchronize()
+    assert n_partial == 4 and torch.equal(y, xd)
+    got = sums.view(torch.float32)[: 2 * n_partial * C].view(2, n_partial, C).double()
+    for which, tiny in enumerate((2.0 ** -25, 2.0 ** -50)):
+        exact = 4 + 124 * tiny
+        assert float((got[which] - exact).abs().max()) <= (3 + 5) * 2.0 ** -24 * exact
+
+
 @pytest.mark.parametrize("case", FUSED, ids=lambda c: "x".join(map(str, c)))
 def test_conv_with_statistics_epilogue_feeds_the_normalisation(case):
     """pt_conv_fwd_stats + pt_bn_fwd_from_sums against the oracle's convolution, rounded to bf16 as stored, followed
