@@ -424,8 +424,8 @@ __device__ __forceinline__ void wait_vmcnt() {
 // TAIL = some run of channels ends inside an 8-chunk whose remaining elements are undefined.
 // STATS = also reduce the stored outputs to per-channel sums and sums of squares (see IgemmArgs::stats).
 // AV = the caller has established that every tap of every row lies inside the source image (no validity tests).
-// FOLD = the problem may be a folded one (without AV; the branch for it costs the others 22.2 -> 23.1 us on 14 x 14 x 256 -> 256,
-// 3 x 3, batch 64: the loads no longer share a block with the step's LDS reads and MFMAs).
+// FOLD = the problem may be a folded one (without AV; with a branch for it in the loop the loads no longer share a block with
+// the step's LDS reads and MFMAs: 22.8 instead of 22.2 us on 14 x 14 x 256 -> 256, 3 x 3, batch 64).
 template <int BM, int BN, int WGM, int WGN, int STAGES, bool RAGGED, bool TAIL, bool STATS, bool AV, bool FOLD>
 __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN problems) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
@@ -502,10 +502,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
 
     // With taps outside the image the next step to issue is kept as running scalar offsets, to which a step adds one of three
     // constants (next 64 channels, next filter column, next filter row), and which lanes read zeros, which changes with the
-    // tap only, is worked out once per tap: recomputing both in every step takes 23.1 us instead of 22.8 for 14 x 14 x 256 ->
-    // 256, 3 x 3, batch 64, the test alone in every step 24.0.  With none outside (mostly 1 x 1 layers of few steps) there is
-    // no test, and what the constants take ahead of the first load is not won back: 28 x 28 x 512 -> 128 12.96 us with them,
-    // 12.70 with the offsets from tap and block.
+    // tap only, is worked out once per tap.  14 x 14 x 256 -> 256, 3 x 3, batch 64: 22.8 us; both recomputed in every step 23.1,
+    // the test alone in every step 24.0.  With none outside (mostly 1 x 1 layers of few steps) there is no test, and what the
+    // constants take ahead of the first load is not won back: 28 x 28 x 512 -> 128 12.96 us with them, 12.70 with the offsets
+    // from tap and block.
     const int nblk = (a.CredP + BK - 1) / BK;
     const int ts_a = a.ts_step * a.apitch * 2, ts_b = a.b_ts_stride * a.bpitch * 2, back = (nblk - 1) * BK * 2;
     const int col_a = ts_a - back, col_b = ts_b - back;
@@ -2588,8 +2588,8 @@ inline void plan_stem_wgrad(StemWgradArgs& a, int* slabs) {
     a.tiles = (int)tiles;
     // Tiles per workgroup: a pair (one for each wave group) takes 1.2 us, a slab 0.03 us to write and add up (fitted to 7 x 7
     // filters on 96 x 96 to 224 x 224 at batch 8 to 64: 192 tiles as 96 slabs 11 us, as 192 slabs 15 us).  The smallest
-    // problems keep a tile and a slab for each workgroup, the plan that callers were told of them: within 0.2 us there (10 tiles
-    // 7.35 against 7.16 us in pairs), 1 us at 64 tiles.
+    // problems keep a tile and a slab for each workgroup, as pt_conv_bwd_weight_plan has always reported them: that is within
+    // 0.2 us there (10 tiles 7.35 us, in pairs 7.16) and 1 us slower at 64 tiles.
     if (tiles < kSwPairsFrom) {
         a.run = 1;
         *slabs = (int)tiles;
