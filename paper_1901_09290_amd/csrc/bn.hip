@@ -66,6 +66,11 @@ __device__ __forceinline__ void unpack8(const uint4& v, float (&f)[8]) {
     }
 }
 
+__device__ __forceinline__ float half_of(const uint4& v, int e) {
+    const uint32_t w = e < 2 ? v.x : e < 4 ? v.y : e < 6 ? v.z : v.w;
+    return __uint_as_float(e & 1 ? w & 0xffff0000u : w << 16);
+}
+
 // MODE 0: a = sum (x - pivot), b = sum (x - pivot)^2.   MODE 1: a = sum dy, b = sum dy * xhat.
 // partial layout: [2][nblocks][C].
 template <int MODE>
@@ -92,36 +97,21 @@ __global__ __launch_bounds__(kBnThreads) void k_bn_sums(const uint16_t* __restri
             }
         }
     }
-    // A thread keeps kBnSumRows sums of each kind, one for each row of a batch, and adds them as a tree at the end: of n rows
-    // the longest chain of additions is n / 8 + 3 with no instruction more per row (200704 x 256, 98 rows a thread: relative
-    // error of invstd 3.0e-7 with one sum, 3.2e-8 with eight; forward and backward 146.3 and 147.2 us).
-    float a[kBnSumRows][8], b[kBnSumRows][8];
+    // Neither sum is one chain of additions over a thread's rows.  a: a batch is summed by itself, in two chains of four, and then
+    // added, which is no instruction more.  b: four running sums, for the rows 0 and 4, 1 and 5, ... of the batches, so that
+    // every product stays part of an FMA.  Relative error of invstd for 200704 x 256 (98 rows a thread): 3.0e-7 row by row,
+    // 4.0e-8 this way, as with 1024 ranges; forward and backward 137.8 and 138.3 us (3136 x 115: 20.1 and 20.3).
+    float a[8], b[4][8];
 #pragma unroll
-    for (int u = 0; u < kBnSumRows; ++u)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) a[u][e] = b[u][e] = 0.f;
+    for (int e = 0; e < 8; ++e) a[e] = b[0][e] = b[1][e] = b[2][e] = b[3][e] = 0.f;
     const int64_t r0 = (int64_t)blockIdx.x * g.rows_per_block;
     const int64_t r1 = min(g.pixels, r0 + g.rows_per_block);
     if (live) {
-        auto add = [&](int u, const uint4& xq, const uint4& gq) {
-            float xv[8];
-            unpack8(xq, xv);
-            if (MODE == 0) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float d = xv[e] - c0[e];
-                    a[u][e] += d;
-                    b[u][e] += d * d;
-                }
-            } else {
-                float gv[8];
-                unpack8(gq, gv);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    a[u][e] += gv[e];
-                    b[u][e] += gv[e] * ((xv[e] - c0[e]) * c1[e]);
-                }
-            }
+        // element e of a row: f0 is a term of a, f0 * f1 one of b
+        auto factors = [&](const uint4& xq, const uint4& gq, int e, float& f0, float& f1) {
+            const float d = half_of(xq, e) - c0[e];
+            f0 = MODE == 0 ? d : half_of(gq, e);
+            f1 = MODE == 0 ? d : d * c1[e];
         };
         const uint16_t* px = x + (r0 + ty) * xpitch + tx * 8;
         const uint16_t* pg = MODE == 1 ? dy + (r0 + ty) * dypitch + tx * 8 : nullptr;
@@ -136,39 +126,70 @@ __global__ __launch_bounds__(kBnThreads) void k_bn_sums(const uint16_t* __restri
             }
             px += kBnSumRows * sx;
             if (MODE == 1) pg += kBnSumRows * sg;
+            float ta[2][8];
 #pragma unroll
-            for (int u = 0; u < kBnSumRows; ++u) add(u, xq[u], MODE == 1 ? gq[u] : xq[u]);
-        }
+            for (int u = 0; u < kBnSumRows; ++u) {  // (row by row: the first ones while the last are still on their way)
 #pragma unroll
-        for (int u = 0; u < kBnSumRows - 1; ++u) {  // the rows left over
-            if (u < n) {
-                const uint4 xq = *reinterpret_cast<const uint4*>(px + u * sx);
-                const uint4 gq = MODE == 1 ? *reinterpret_cast<const uint4*>(pg + u * sg) : xq;
-                add(u, xq, gq);
+                for (int e = 0; e < 8; ++e) {
+                    float f0, f1;
+                    factors(xq[u], MODE == 1 ? gq[u] : xq[u], e, f0, f1);
+                    ta[u / 4][e] = u % 4 ? ta[u / 4][e] + f0 : f0;
+                    b[u % 4][e] += f0 * f1;
+                }
             }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a[e] += ta[0][e] + ta[1][e];
         }
-    }
+        if (n > 0) {  // the rows left over, summed by themselves as well
+            float ra[8], rb[8];
 #pragma unroll
-    for (int w = 1; w < kBnSumRows; w *= 2)
+            for (int e = 0; e < 8; ++e) ra[e] = 0.f, rb[e] = 0.f;
+            for (; n > 0; --n) {
+                const uint4 xq = *reinterpret_cast<const uint4*>(px);
+                const uint4 gq = MODE == 1 ? *reinterpret_cast<const uint4*>(pg) : xq;
 #pragma unroll
-        for (int u = 0; u + w < kBnSumRows; u += 2 * w)
+                for (int e = 0; e < 8; ++e) {
+                    float f0, f1;
+                    factors(xq, gq, e, f0, f1);
+                    ra[e] += f0;
+                    rb[e] += f0 * f1;
+                }
+                px += sx;
+                if (MODE == 1) pg += sg;
+            }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                a[u][e] += a[u + w][e];
-                b[u][e] += b[u + w][e];
+                a[e] += ra[e];
+                b[0][e] += rb[e];
             }
+        }
+    }
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        red[0][tid * 8 + e] = a[0][e];
-        red[1][tid * 8 + e] = b[0][e];
+        red[0][tid * 8 + e] = a[e];
+        red[1][tid * 8 + e] = (b[0][e] + b[1][e]) + (b[2][e] + b[3][e]);
     }
     __syncthreads();
-    // row groups added in ty order: thread f owns channel f
+    // row groups added in a fixed order (many of them in four chains): thread f owns channel f
+    const int row = g.cv * 8;
     for (int f = tid; f < g.C; f += kBnThreads) {
         float s0 = 0.f, s1 = 0.f;
-        for (int y = 0; y < g.ty; ++y) {
-            s0 += red[0][y * g.cv * 8 + f];
-            s1 += red[1][y * g.cv * 8 + f];
+        int y = 0;
+        if (g.ty >= 8) {
+            float t0[4] = {0.f, 0.f, 0.f, 0.f}, t1[4] = {0.f, 0.f, 0.f, 0.f};
+            for (; y + 4 <= g.ty; y += 4) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    t0[u] += red[0][(y + u) * row + f];
+                    t1[u] += red[1][(y + u) * row + f];
+                }
+            }
+            s0 = (t0[0] + t0[1]) + (t0[2] + t0[3]);
+            s1 = (t1[0] + t1[1]) + (t1[2] + t1[3]);
+        }
+        for (; y < g.ty; ++y) {
+            s0 += red[0][y * row + f];
+            s1 += red[1][y * row + f];
         }
         partial[(size_t)blockIdx.x * g.C + f] = s0;
         partial[((size_t)g.nblocks + blockIdx.x) * g.C + f] = s1;

@@ -127,9 +127,10 @@ def test_bn_is_run_to_run_identical_and_full_size():
 
 def test_bn_sums_have_short_chains():
     """The first row that a thread meets is 1, the 97 behind it 2^-25 each, less than half a unit in the last place of 1: one
-    sum that takes them all loses them all (2.9e-6).  With eight sums, one for every eighth row, the chain is 12 additions
-    for the batches of eight, 1 for the rows left over, 3 for the tree over the sums, 7 for the row groups of a workgroup,
-    then fp64 and one rounding; for positive terms the relative error is at most that many half units."""
+    sum that takes them all loses them all (2.9e-6).  The plain sum's chain is 3 + 1 additions for a batch of eight rows, 12
+    for the batches, 1 for the rows left over; that of the products 25 in each of four sums, 2 for the four, 1 for the rows
+    left over; then 4 for the row groups of a workgroup, fp64 and one rounding.  For positive terms the relative error is at
+    most that many half units."""
     from gpu_util import DEV, workspace
     pixels, C, ranges, groups = 64 * 56 * 56, 256, 256, 8
     dy = torch.full((pixels, C), 2.0 ** -25, dtype=torch.bfloat16, device=DEV)
@@ -141,8 +142,8 @@ def test_bn_sums_have_short_chains():
     torch.cuda.synchronize()
     exact = ranges * groups + (pixels - ranges * groups) * 2.0 ** -25
     err = float((out[1].double() - exact).abs().max()) / exact
-    assert err <= (12 + 1 + 3 + 7 + 1) * 2.0 ** -24, err
-    assert float((out[0].double() + exact).abs().max()) / exact <= (12 + 1 + 3 + 7 + 1) * 2.0 ** -24   # xhat = -1
+    assert err <= (3 + 1 + 12 + 1 + 4 + 1) * 2.0 ** -24, err
+    assert float((out[0].double() + exact).abs().max()) / exact <= (25 + 2 + 1 + 4 + 1) * 2.0 ** -24   # xhat = -1
 
 
 FUSED = [
