@@ -392,6 +392,12 @@ def part_of(jobs: C.Array, first: int, end: int) -> C.Array:
     return (jobs._type_ * (end - first)).from_buffer(jobs, first * C.sizeof(jobs._type_))
 
 
+def addresses_of(jobs: C.Array, field: str) -> np.ndarray:
+    """One pointer field of every job of a table, as a writable column."""
+    typ = jobs._type_
+    return np.frombuffer(jobs, dtype=np.uint64).reshape(len(jobs), C.sizeof(typ) // 8)[:, getattr(typ, field).offset // 8]
+
+
 def group_norms_batched_workspace_bytes(layers) -> int:
     arr = _array(layers, LayerWeights)
     n = C.c_size_t(0)

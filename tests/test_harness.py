@@ -208,6 +208,27 @@ def test_compaction_reads_the_models_tensors_at_every_call(recorded, monkeypatch
                 t.data = t.data.clone()
 
 
+@pytest.mark.parametrize("how", ["detect", "detect_separate", "detect_per_call"])
+def test_detection_writes_the_plan_that_the_compaction_reads(recorded, monkeypatch, how):
+    """Weights, survivor lists, counts and keep masks replaced between two sweeps: the second one reads and writes the new
+    ones (a list that the plan did not write would be read as indices by the gathers)."""
+    zeros = torch.zeros
+    monkeypatch.setattr(torch, "zeros", lambda *a, pin_memory=False, **kw: zeros(*a, **kw))
+    m = _reconfig_model()
+
+    def tensors():
+        return [*m.w, *m.idx, *m.keep, m.counts]
+    getattr(m, how)(1e-6)
+    old = tensors()
+    assert {t.data_ptr() for t in old} <= recorded.seen()
+    m.w, m.idx, m.keep, m.counts = ([t.clone() for t in m.w], [t.clone() for t in m.idx], [t.clone() for t in m.keep],
+                                    m.counts.clone())
+    recorded.calls.clear()
+    getattr(m, how)(1e-6)
+    assert {t.data_ptr() for t in tensors()} <= recorded.seen()
+    assert not {t.data_ptr() for t in old} & recorded.seen()
+
+
 def test_compaction_of_activations_that_do_not_stream(recorded, monkeypatch):
     """The planned gathers refuse an activation (as they do one that is not 16-byte aligned): compact() takes the calls with
     the counts on the host.  Another refusal is passed on."""
