@@ -204,8 +204,10 @@ int32_t pt_conv_bwd_weight_lasso(const pt_conv_desc* d, const uint16_t* x, const
  * that a layer's pixel axis is split over workgroups (and its partial sums written, read and added) only as far as that
  * takes, and a launch's fixed cost is paid once for all of them.  The weight gradients of a backward pass are independent
  * of each other and nothing in it waits for them: a caller hands over those of several layers at once, when the last of
- * their dy is final.  `layers`: HOST array, device pointers inside; any n >= 0.  The sums are combined in an order that
- * depends on all shapes of the call: the same call gives the same bits, a call with other layers beside it need not.
+ * their dy is final.  `layers`: HOST array, device pointers inside; any n >= 0 (a plan that host memory has no room for:
+ * PT_ERR_UNSUPPORTED).  The sums are combined in an order that depends on all shapes of the call: the same call gives the
+ * same bits, a call with other layers beside it need not; one layer with workgroups = 0 is planned as by pt_conv_bwd_weight.
+ * The plan, and so the workspace, depends on the alignment of x and dy: the query takes the call's own pointers.
  * workgroups: how many workgroups of the chip to plan for, 0 = one per CU; fewer where other kernels run beside the call
  * (they then find room on the chip, and fewer partial sums are written). */
 typedef struct pt_layer_wgrad {
