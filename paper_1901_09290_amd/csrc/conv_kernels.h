@@ -81,16 +81,21 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb) {
     return xcd * per + min(xcd, rem) + q;
 }
 
-// floor(m / d) through a host-made magic number (exact for m * d < 2^32); d == 1 has magic 0.
+// floor(m / d) through a host-made magic number (exact for m * d < 2^32); d == 1, whose magic number has 33 bits, has
+// magic 0 and passes m through the mask `one` (no branch: a workgroup's first load waits for these divisions).
 struct FastDiv {
-    uint32_t d, magic;
+    uint32_t d, magic, one;
 };
-inline FastDiv make_fastdiv(uint32_t d) { return FastDiv{d, d == 1 ? 0u : make_magic(d)}; }
-__device__ __forceinline__ uint32_t fdiv(uint32_t m, FastDiv f) { return f.d == 1 ? m : __umulhi(m, f.magic); }
+inline FastDiv make_fastdiv(uint32_t d) { return FastDiv{d, d == 1 ? 0u : make_magic(d), d == 1 ? ~0u : 0u}; }
+__device__ __forceinline__ uint32_t fdiv(uint32_t m, FastDiv f) { return __umulhi(m, f.magic) + (m & f.one); }
 
 // ------------------------------------------------------------------------------------------- //
 // forward / input-gradient implicit GEMM
 // ------------------------------------------------------------------------------------------- //
+// Byte offset of grid point m = (n * gH + gi) * gW + gj in a tensor: m * point + (m / gW) * row + n * image + origin (mod 2^32).
+struct RowOffsets {
+    uint32_t point, row, image, origin;
+};
 struct IgemmArgs {
     const uint16_t* A;  // gathered activations (x or dy)
     const uint16_t* B;  // weights, [Nout][b_taps][bpitch], reduction channel innermost
@@ -135,12 +140,17 @@ struct IgemmArgs {
     // every row, a reduction step's offset minus a_smin is non-negative for every step (both in elements; the
     // buffer's base address absorbs the two shifts).  a_all_valid: no tap of any row ever leaves the source image.
     int a_guard, a_smin, a_all_valid;
-    // Direct kernel: wave priority outside the reduction loop (inside it is 2).  0 for a launch that runs alone; the
+    // Direct kernel: the raised wave priority of the reduction loop also outside it.  Off for a launch that runs alone; the
     // input gradient, which is meant to run beside weight gradients of other layers, keeps its set-up and its stores
     // ahead of them too.
     int edge_prio;
     int grid_x;  // direct kernel: workgroups (tiles) of this problem inside a launch that may hold several problems
     int m_fast;  // small tiles: consecutive tiles run along the pixels (and share weights), not along the outputs
+    // Direct kernels: the above, ready for use in a workgroup's set-up (make_igemm_offsets).
+    FastDiv t_div;  // tiles along the fast axis; magic == one == 0: too many tiles for it
+    RowOffsets src, dst;
+    int ch_mul, ch_add, cw_mul, cw_add;  // taps inside the source image: rows [gi * ch_mul + ch_add, + srcH), columns alike
+    uint64_t tap_rep;                    // bit r * TSm for every filter row r
 };
 
 // The direct kernel takes up to four problems per launch, one per blockIdx.y (the stride-parity classes of a strided
@@ -421,6 +431,33 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
+__device__ __forceinline__ int tile_div(int tile, FastDiv f) {
+    return f.magic | f.one ? (int)fdiv((uint32_t)tile, f) : tile / (int)f.d;  // uniform
+}
+__device__ __forceinline__ uint32_t swap_lane_pair(uint32_t v) {  // lanes 2i and 2i + 1 trade values
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, true);
+}
+// The taps of grid point (gi, gj) that read outside the source image: a bit r * TSm + s each, set (bits past the last tap
+// too).  The taps inside are an interval of filter rows times an interval of columns: the column bits, repeated in every
+// row by a multiplication, cut to the rows' bits.
+struct TapSkip {
+    int lo, hi;
+};
+__device__ __forceinline__ TapSkip tap_skip(const IgemmArgs& a, int gi, int gj) {
+    const int r = gi * a.ch_mul + a.ch_add, s = gj * a.cw_mul + a.cw_add;
+    const int r0 = min(max(r, 0), a.TR) * a.TSm, r1 = min(max(r + a.srcH, 0), a.TR) * a.TSm;
+    const int s0 = min(max(s, 0), a.TSm), s1 = min(max(s + a.srcW, 0), a.TSm);
+    if (a.TR * a.TSm < 32)  // uniform
+        return {(int)~(((1u << s1) - (1u << s0)) * (uint32_t)a.tap_rep & ((1u << r1) - (1u << r0))), -1};
+    auto below = [](int n) { return n > 63 ? ~0ull : (1ull << n) - 1; };
+    const uint64_t valid = (below(s1) & ~below(s0)) * a.tap_rep & (below(r1) & ~below(r0));
+    return {(int)~(uint32_t)valid, (int)~(uint32_t)(valid >> 32)};
+}
+#ifndef PT_AUX
+#define PT_AUX 0
+#endif
+constexpr int kStoreAux = PT_AUX;
+
 // TAIL = some run of channels ends inside an 8-chunk whose remaining elements are undefined.
 // STATS = also reduce the stored outputs to per-channel sums and sums of squares (see IgemmArgs::stats).
 // AV = the caller has established that every tap of every row lies inside the source image (no validity tests).
@@ -430,9 +467,7 @@ template <int BM, int BN, int WGM, int WGN, int STAGES, bool RAGGED, bool TAIL, 
 __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN problems) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
     const IgemmArgs a = problems.a[blockIdx.y];  // (a copy: the fields then live in scalar registers as kernel arguments do)
-    if (blockIdx.x >= (unsigned)a.grid_x) return;  // the whole workgroup: the launch is as wide as its largest problem
-    if (a.edge_prio == 2) __builtin_amdgcn_s_setprio(2);
-    else if (a.edge_prio == 1) __builtin_amdgcn_s_setprio(1);
+    if (a.edge_prio) __builtin_amdgcn_s_setprio(2);
     constexpr int NW = WGM * WGN, BK = 64;
     constexpr int GA = BM / 8, GB = BN / 8;    // 8-row groups = wave-level loads per stage
     constexpr int LA = GA / NW, LB = GB / NW;  // loads per lane per stage
@@ -447,8 +482,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tile = xcd_remap(blockIdx.x, a.grid_x);
-    const int n0 = (tile % a.tiles_n) * BN;
-    const int m0 = (tile / a.tiles_n) * BM;
+    const int tile_m = tile_div(tile, a.t_div);
+    const int n0 = (tile - tile_m * a.tiles_n) * BN, m0 = tile_m * BM;
 
     // A reduction step is (filter tap, block of 64 reduction channels): the same for every lane, so the
     // tap offsets and the channel base live in scalar registers.
@@ -456,33 +491,29 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
     const int kv = (lane & 7) ^ ((((wave & 1) << 2) | (lane >> 4)));  // logical 8-element chunk this lane fetches
     const int kvoff = kv * 8;
 
-    // per-lane row constants: element offset of tap (0,0) + chunk, and a bit per tap: tap inside the image.
+    // per-lane row constants: byte offset of tap (0,0) + chunk, and a bit per tap: tap outside the image.
     // Rows past the end of the problem are clamped to the last row: their results are never stored.
-    uint32_t a_off[LA];
+    // A workgroup waits for all of this before its first load (two WGs of eight waves on a CU: about 3 ns an instruction),
+    // so what does not depend on the lane is made on the host and nothing here branches or loops: 28 x 28 x 128 -> 128,
+    // 3 x 3, batch 64: 1.4 us from a workgroup's start to its first load with a loop over the taps and divisions.
+    uint32_t a_v[LA], b_v[LB];
     int skip_lo[LA], skip_hi[LA];  // bit r * TSm + s: tap (r, s) of this row lies outside the image (hi: from the 33rd tap on)
 #pragma unroll
     for (int j = 0; j < LA; ++j) {
-        const int m = min(m0 + (wave + NW * j) * 8 + lrow, a.M - 1);
-        const uint32_t row = fdiv((uint32_t)m, a.gW), gj = m - row * a.gW.d;
-        const uint32_t n = fdiv(row, a.gH), gi = row - n * a.gH.d;
-        const int h0 = (int)gi * a.h_mul + a.h_add, w0 = (int)gj * a.w_mul + a.w_add;
-        a_off[j] = (uint32_t)(((int)n * a.srcH + h0) * a.srcW + w0) * (uint32_t)a.apitch + (uint32_t)kvoff;
-        // validity is separable: one bit per filter column, replicated for every valid filter row
-        uint64_t colbits = 0;
-        for (int t = 0; t < a.TSm; ++t) colbits |= (uint64_t)((unsigned)(w0 + t * a.ts_step) < (unsigned)a.srcW) << t;
-        uint64_t mask = 0;
-        for (int r = 0; r < a.TR; ++r)
-            if ((unsigned)(h0 + r * a.tr_step) < (unsigned)a.srcH) mask |= colbits << (r * a.TSm);
-        skip_lo[j] = (int)~(uint32_t)mask;
-        skip_hi[j] = (int)~(uint32_t)(mask >> 32);
+        const uint32_t m = (uint32_t)min(m0 + (wave + NW * j) * 8 + lrow, a.M - 1);
+        const uint32_t row = fdiv(m, a.gW), n = fdiv(row, a.gH);
+        a_v[j] = m * a.src.point + row * a.src.row + n * a.src.image + a.src.origin + (uint32_t)kvoff * 2u;
+        if constexpr (!AV) {
+            const TapSkip t = tap_skip(a, (int)(row - n * a.gH.d), (int)(m - row * a.gW.d));
+            skip_lo[j] = t.lo;
+            skip_hi[j] = t.hi;
+        }
     }
-    const uint32_t b_rowlen = (uint32_t)a.b_taps * a.bpitch;
-    uint32_t b_off[LB];
+    const uint32_t b_rowbytes = (uint32_t)a.b_taps * a.bpitch * 2u;
 #pragma unroll
-    for (int j = 0; j < LB; ++j) {
-        const int nrow = min(n0 + (wave + NW * j) * 8 + lrow, a.Nout - 1);
-        b_off[j] = (uint32_t)nrow * b_rowlen + (uint32_t)kvoff;
-    }
+    for (int j = 0; j < LB; ++j)
+        b_v[j] = (uint32_t)min(n0 + (wave + NW * j) * 8 + lrow, a.Nout - 1) * b_rowbytes + (uint32_t)kvoff * 2u;
+    if (blockIdx.x >= (unsigned)a.grid_x) return;  // the whole workgroup: the launch is as wide as its largest problem
     // Both operands are fetched with buffer loads: the per-lane part of an address (row, 8-element chunk) is a
     // constant byte offset (voffset), the part that changes from step to step (filter tap, channel block) is the same
     // for every lane and travels in a scalar register (soffset), and a lane that must read zeros (tap outside the
@@ -494,11 +525,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
     const __amdgpu_buffer_rsrc_t a_srd = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t*>(a.A) + ((int64_t)a.a_smin - a.a_guard), 0, kBufRecords, kBufFlags);
     const __amdgpu_buffer_rsrc_t b_srd = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.B), 0, kBufRecords, kBufFlags);
-    uint32_t a_v[LA], b_v[LB];
-#pragma unroll
-    for (int j = 0; j < LA; ++j) a_v[j] = (a_off[j] + (uint32_t)a.a_guard) * 2u;
-#pragma unroll
-    for (int j = 0; j < LB; ++j) b_v[j] = b_off[j] * 2u;
 
     // With taps outside the image the next step to issue is kept as running scalar offsets, to which a step adds one of three
     // constants (next 64 channels, next filter column, next filter row), and which lanes read zeros, which changes with the
@@ -682,8 +708,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
     __builtin_amdgcn_s_setprio(2);
     if (all_live) main_loop(std::false_type{});
     else main_loop(std::true_type{});
-    if (a.edge_prio == 0) __builtin_amdgcn_s_setprio(0);
-    else if (a.edge_prio == 1) __builtin_amdgcn_s_setprio(1);
+    if (!a.edge_prio) __builtin_amdgcn_s_setprio(0);
 
     // ---- epilogue: registers -> global.  A lane holds, per 32x32 block, channels 8g + 4*(lane/32) + {0..3}
     // (g = 0..3) of pixel lane%32.  Swapping the upper half-wave of the g-even registers with the lower
@@ -695,31 +720,25 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
     // many partial-line write requests; a store-only probe of the two patterns differs by 15-25 %).
     const bool pair_store = a.d_vec16 && a.zf_h * a.zf_w == 1 && (a.Nout % 8 == 0 || a.pad_zero);  // uniform
     if (pair_store) {
-        const int hi = lane >> 5;
+        // Buffer stores: 32-bit offsets, and what must not be written passes an offset out of range (no branches).
+        const __amdgpu_buffer_rsrc_t d_srd = __builtin_amdgcn_make_buffer_rsrc(a.D, 0, kBufRecords, kBufFlags);
         const bool odd = (l32 & 1) != 0;
+        const int ch0 = n0 + wn * WTN + (odd ? 16 : 0) + 8 * (lane >> 5);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm) {
-            const int m = m0 + wm * WTM + tm * 32 + l32;
-            int64_t dpix;
-            if (a.d_linear) {
-                dpix = (int64_t)m * a.dpitch;
-            } else {
-                const uint32_t mm = (uint32_t)min(m, a.M - 1);
-                const uint32_t row = fdiv(mm, a.gW), gj = mm - row * a.gW.d;
-                const uint32_t n = fdiv(row, a.gH), gi = row - n * a.gH.d;
-                const int dh = (int)gi * a.d_hmul + a.d_hadd, dw = (int)gj * a.d_wmul + a.d_wadd;
-                dpix = (((int64_t)n * a.DH + dh) * a.DW + dw) * a.dpitch;
+            const uint32_t m = (uint32_t)(m0 + wm * WTM + tm * 32 + (l32 & ~1));  // this lane stores to pixels m and m + 1
+            uint32_t at0 = m * a.dst.point + a.dst.origin, at1 = at0 + a.dst.point;
+            if (!a.d_linear) {  // uniform
+                const uint32_t row0 = fdiv(m, a.gW), row1 = fdiv(m + 1, a.gW);
+                at0 += row0 * a.dst.row + fdiv(row0, a.gH) * a.dst.image;
+                at1 += row1 * a.dst.row + fdiv(row1, a.gH) * a.dst.image;
             }
-            const int64_t dother = ((int64_t)__shfl_xor((int)(dpix >> 32), 1, 64) << 32) |
-                                   (uint32_t)__shfl_xor((int)(uint32_t)dpix, 1, 64);
-            const int64_t dp0 = odd ? dother : dpix, dp1 = odd ? dpix : dother;  // pixels (m & ~1), (m & ~1) + 1
-            const bool ok0 = (m & ~1) < a.M, ok1 = (m | 1) < a.M;
+            const bool ok0 = m < (uint32_t)a.M, ok1 = m + 1 < (uint32_t)a.M;
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) {
-                const int chb = n0 + wn * WTN + tn * 32;
-                if (chb >= a.Nout) continue;  // wave-uniform
+                if (n0 + wn * WTN + tn * 32 >= a.Nout) continue;  // wave-uniform
                 const f32x16& c = acc[tn][tm];
-                uint32_t v[2][4];  // this lane's chunk of each register pair: channels chb + 16 gp + 8 hi + {0..7}
+                uint32_t v[2][4];  // this lane's chunk of each register pair: channels 16 gp + 8 (lane / 32) + {0..7} of the block
 #pragma unroll
                 for (int gp = 0; gp < 2; ++gp) {
                     const uint32_t p0 = cvt_pk_bf16(c[8 * gp + 0], c[8 * gp + 1]), q0 = cvt_pk_bf16(c[8 * gp + 2], c[8 * gp + 3]);
@@ -728,25 +747,22 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
                     const auto qs = __builtin_amdgcn_permlane32_swap(q0, q1, false, false);
                     v[gp][0] = ps[0]; v[gp][1] = qs[0]; v[gp][2] = ps[1]; v[gp][3] = qs[1];
                 }
-                uint32_t s0[4], s1[4];
+                u32x4 o0, o1;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const uint32_t give = odd ? v[0][e] : v[1][e];
-                    const uint32_t got = (uint32_t)__shfl_xor((int)give, 1, 64);
-                    s0[e] = odd ? got : v[0][e];
-                    s1[e] = odd ? v[1][e] : got;
+                    const uint32_t got = swap_lane_pair(odd ? v[0][e] : v[1][e]);
+                    o0[e] = odd ? got : v[0][e];
+                    o1[e] = odd ? v[1][e] : got;
                 }
-                const int ch = chb + (odd ? 16 : 0) + 8 * hi;
-                if (ch < a.Nout) {
-                    uint4 o0 = make_uint4(s0[0], s0[1], s0[2], s0[3]), o1 = make_uint4(s1[0], s1[1], s1[2], s1[3]);
-                    if (ch + 7 >= a.Nout) {  // last chunk of a zero-padded tensor: zeros in its padding
-                        const Mask8 k = make_mask8(a.Nout - ch);
-                        o0 = mask8(o0, true, k);
-                        o1 = mask8(o1, true, k);
-                    }
-                    if (ok0) *reinterpret_cast<uint4*>(a.D + dp0 + ch) = o0;
-                    if (ok1) *reinterpret_cast<uint4*>(a.D + dp1 + ch) = o1;
+                const int ch = ch0 + tn * 32;
+                if (a.Nout % 8 != 0 && ch + 7 >= a.Nout) {  // last chunk of a zero-padded tensor: zeros in its padding
+                    const Mask8 k = make_mask8(a.Nout - ch);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o0[e] &= k.m[e], o1[e] &= k.m[e];
                 }
+                const uint32_t at = (uint32_t)ch * 2u;
+                __builtin_amdgcn_raw_buffer_store_b128(o0, d_srd, ok0 && ch < a.Nout ? at0 + at : kBufOut, 0, kStoreAux);
+                __builtin_amdgcn_raw_buffer_store_b128(o1, d_srd, ok1 && ch < a.Nout ? at1 + at : kBufOut, 0, kStoreAux);
             }
         }
     } else {
@@ -848,7 +864,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
             }
         }
         __syncthreads();
-        const int tile_m = m0 / BM;
         for (int t = tid; t < 2 * BN; t += 64 * NW) {
             const int q = t / BN, chl = t - q * BN;
             if (n0 + chl >= a.Nout) continue;
@@ -906,6 +921,29 @@ inline hipError_t launch_igemm_dl_planned(const IgemmArgs* as, const IgemmDlPlan
         hipLaunchKernelGGL(kern, dim3(gxr, (unsigned)cnt), dim3((unsigned)ps[i].threads), lds_used, st, m);
     }
     return hipSuccess;
+}
+
+// Offsets, tap intervals and tile division of the direct kernels, from the problem's geometry; `fast` = tiles along the axis
+// that consecutive tiles run along.
+inline void make_igemm_offsets(IgemmArgs& a, int fast) {
+    a.t_div = make_fastdiv((uint32_t)fast);
+    if ((int64_t)a.grid_x * fast > 0xffffffffll) a.t_div.magic = a.t_div.one = 0;
+    auto offsets = [&](int64_t point, int64_t row, int64_t image, int64_t origin) {  // of one step in j, i, n; in elements
+        return RowOffsets{(uint32_t)(point * 2), (uint32_t)((row - a.gW.d * point) * 2), (uint32_t)((image - a.gH.d * row) * 2),
+                          (uint32_t)(origin * 2)};
+    };
+    const int64_t ap = a.apitch, dp = a.dpitch;
+    a.src = offsets(a.w_mul * ap, a.h_mul * a.srcW * ap, (int64_t)a.srcH * a.srcW * ap,
+                    ((int64_t)a.h_add * a.srcW + a.w_add) * ap + a.a_guard);
+    a.dst = offsets(a.d_wmul * dp, (int64_t)a.d_hmul * a.DW * dp, (int64_t)a.DH * a.DW * dp, ((int64_t)a.d_hadd * a.DW + a.d_wadd) * dp);
+    // tap t reads source row h0 + t * step (step = +-1): inside for t in [-h0, -h0 + srcH) or [h0 - srcH + 1, h0 + 1)
+    const bool hup = a.tr_step > 0, wup = a.ts_step > 0;
+    a.ch_mul = hup ? -a.h_mul : a.h_mul;
+    a.ch_add = hup ? -a.h_add : a.h_add - a.srcH + 1;
+    a.cw_mul = wup ? -a.w_mul : a.w_mul;
+    a.cw_add = wup ? -a.w_add : a.w_add - a.srcW + 1;
+    a.tap_rep = 0;
+    for (int r = 0; r < a.TR && r * a.TSm < 64; ++r) a.tap_rep |= 1ull << (r * a.TSm);
 }
 
 // Buffer addressing of the gathered operand (see k_igemm_dl): shifts that make both address parts non-negative; false if a
@@ -971,6 +1009,7 @@ inline hipError_t plan_igemm_dl_cfg(IgemmArgs& a, IgemmDlPlan& plan) {
     const int64_t tiles = ceil_div(a.M, BM) * a.tiles_n;
     if (tiles > 0x7fffffff) return hipErrorInvalidValue;
     a.grid_x = (int)tiles;
+    make_igemm_offsets(a, a.tiles_n);
     // A reduction of fewer steps than the pipeline has stages touches only the first nk stage buffers (and the
     // statistics epilogue a few KB of the first): the launch asks for no more LDS than that, which leaves room on the
     // CU for workgroups of kernels running beside it (train step at pruned widths -0.6 %, full -0.2 %).
@@ -997,7 +1036,7 @@ template <int BM, int BN, int NB, int STAGES>
 __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problems) {
 #if defined(__HIP_DEVICE_COMPILE__)
     const IgemmArgs a = problems.a[blockIdx.y];
-    if (blockIdx.x >= (unsigned)a.grid_x) return;
+    if (a.edge_prio) __builtin_amdgcn_s_setprio(2);
     constexpr int NW = 8, WT = (BM / 32) * (BN / 32), KS = NW / WT;  // waves over the tile, parts of the reduction
     constexpr int LPW = (BM + BN) / 64;                             // loads per wave and step
     constexpr int SUB = (BM + BN) * 128, STAGE = NB * SUB;
@@ -1011,16 +1050,8 @@ __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problem
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tile = xcd_remap(blockIdx.x, a.grid_x);
-    int tm_i, tn_i;
-    if (a.m_fast) {
-        tn_i = tile / a.tiles_m;
-        tm_i = tile - tn_i * a.tiles_m;
-    } else {
-        tm_i = tile / a.tiles_n;
-        tn_i = tile - tm_i * a.tiles_n;
-    }
-    const int m0 = tm_i * BM, n0 = tn_i * BN;
-    if (a.edge_prio == 2) __builtin_amdgcn_s_setprio(2);
+    const int slow = tile_div(tile, a.t_div), fast = tile - slow * (int)a.t_div.d;
+    const int m0 = (a.m_fast ? fast : slow) * BM, n0 = (a.m_fast ? slow : fast) * BN;
 
     // Loads as in k_igemm_dl: per-lane constants in voffset, running scalar offsets in soffset, one bit per tap and
     // lane.  A wave's load j is of one operand: the roles are scalar selects, and both operands take the same instructions.
@@ -1035,17 +1066,10 @@ __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problem
         const int g = wave + NW * j;  // 8-row group of the step: the first BM / 8 are pixels
         kvoff[j] = ((lane & 7) ^ (((g & 1) << 2) | (lane >> 4))) * 8;
         if (g < BM / 8) {  // uniform
-            const int m = min(m0 + g * 8 + lrow, a.M - 1);
-            const uint32_t row = fdiv((uint32_t)m, a.gW), gj = m - row * a.gW.d;
-            const uint32_t n = fdiv(row, a.gH), gi = row - n * a.gH.d;
-            const int h0 = (int)gi * a.h_mul + a.h_add, w0 = (int)gj * a.w_mul + a.w_add;
-            voff[j] = ((uint32_t)(((int)n * a.srcH + h0) * a.srcW + w0) * (uint32_t)a.apitch + (uint32_t)(kvoff[j] + a.a_guard)) * 2u;
-            uint32_t colbits = 0;
-            for (int t = 0; t < a.TSm; ++t) colbits |= ((unsigned)(w0 + t * a.ts_step) < (unsigned)a.srcW ? 1u : 0u) << t;
-            uint32_t valid = 0;
-            for (int r = 0; r < a.TR; ++r)
-                if ((unsigned)(h0 + r * a.tr_step) < (unsigned)a.srcH) valid |= colbits << (r * a.TSm);
-            skip[j] = (int)~valid;
+            const uint32_t m = (uint32_t)min(m0 + g * 8 + lrow, a.M - 1);
+            const uint32_t row = fdiv(m, a.gW), n = fdiv(row, a.gH);
+            voff[j] = m * a.src.point + row * a.src.row + n * a.src.image + a.src.origin + (uint32_t)kvoff[j] * 2u;
+            skip[j] = tap_skip(a, (int)(row - n * a.gH.d), (int)(m - row * a.gW.d)).lo;
         } else {
             const int nrow = min(n0 + (g - BM / 8) * 8 + lrow, a.Nout - 1);
             voff[j] = ((uint32_t)nrow * ((uint32_t)a.b_taps * a.bpitch) + (uint32_t)kvoff[j]) * 2u;
@@ -1094,6 +1118,7 @@ __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problem
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 
+    if (blockIdx.x >= (unsigned)a.grid_x) return;  // the whole workgroup
     const int nst = (a.nk + NB - 1) / NB;
 #pragma unroll
     for (int s = 0; s < STAGES - 1; ++s) issue(s);
@@ -1188,6 +1213,7 @@ inline hipError_t plan_igemm_small_cfg(IgemmArgs& a, IgemmDlPlan& plan) {
     const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
     if (tiles > 0x7fffffff) return hipErrorInvalidValue;
     a.grid_x = (int)tiles;
+    make_igemm_offsets(a, a.m_fast ? a.tiles_m : a.tiles_n);
     return hipSuccess;
 }
 
