@@ -115,16 +115,16 @@ inline void igemm_fold(IgemmArgs& a) {
 }
 
 // Which kernel takes the problems of a call that fill less than one round of 128 x 128 tiles (`as`: one problem, or the
-// stride-parity classes of an input gradient, which share a launch).  Estimated times in us, fitted to 160 ResNet-50 shapes
-// at batch 8 to 32 and pruned widths at batch 10 (chosen: 1311 us in all, the best of the three for each: 1308): a round is
-// `steps` steps of t1 (one workgroup on the CU) or t2 (two), and f1 or f2 for set-up and stores.  0 = k_igemm_dl at
-// 128 x 64, 1 = k_igemm_small at 64 x 64, 2 = at 32 x 32.  (7 x 7 324 -> 263 channels 3 x 3 at batch 10: 24 / 17 / 12 us;
-// 12 x 12 512 -> 512 3 x 3 stride 2 at batch 32: 28 / 21 / 33 us; 1024 -> 256 1 x 1: 8.3 / 10.4 / 16.4 us.)
+// stride-parity classes of an input gradient, which share a launch).  Estimated times in us, least squares over 150 ResNet-50
+// shapes at batch 1 to 100, 96 to 224 pixels, published and pruned widths (chosen: 977 us in all, the best of the three for
+// each: 976, always one of them: 1199, 1131, 1930): up to 256 workgroups take `steps` steps of t1 and f1 for set-up and
+// stores, up to 512 (two on a CU, or one after the other) t2 and f2.  0 = k_igemm_dl at 128 x 64, 1 = k_igemm_small at
+// 64 x 64, 2 = at 32 x 32.
 inline int pick_igemm_kernel(const IgemmArgs* as, int n) {
     struct Est { int bm, bn, nb; float t1, t2, f1, f2; };
-    constexpr Est est[3] = {{128, 64, 1, 0.32f, 0.39f, 0.0f, 0.9f},
-                            {64, 64, 1, 0.22f, 0.29f, 0.1f, 1.1f},
-                            {32, 32, 4, 0.48f, 0.77f, 0.2f, 1.5f}};
+    constexpr Est est[3] = {{128, 64, 1, 0.30f, 0.52f, 0.54f, 1.05f},
+                            {64, 64, 1, 0.22f, 0.38f, 0.78f, 1.72f},
+                            {32, 32, 4, 0.50f, 0.98f, 1.05f, 4.39f}};
     int best = 0;
     float best_us = 1e30f;
     for (int k = 0; k < 3; ++k) {
@@ -176,7 +176,7 @@ inline hipError_t launch_igemm(IgemmArgs& a, bool vec, hipStream_t st, IgemmDlPl
     IgemmDlPlan own;
     IgemmDlPlan& p = plan ? *plan : own;
     hipError_t e;
-    if (kernel == 2) e = plan_igemm_small_cfg<32, 32, 4, 2>(a, p);
+    if (kernel == 2) e = plan_igemm_small_cfg<32, 32, 4, 3>(a, p);
     else if (kernel == 1) e = plan_igemm_small_cfg<64, 64, 1, 3>(a, p);
     // very many pixel tiles and a narrow output (the stem): tall tiles, so half as many workgroups pay set-up and fill
     else if (a.Nout <= 64 && tiles128 >= 4096 && !a.stats) e = plan_igemm_dl_cfg<256, 64, 4, 2, 2>(a, p);

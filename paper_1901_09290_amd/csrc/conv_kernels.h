@@ -1029,9 +1029,12 @@ inline hipError_t plan_igemm_dl_cfg(IgemmArgs& a, IgemmDlPlan& plan) {
 // Same arguments, addressing and LDS layout as k_igemm_dl (one 64-channel step = BM + BN rows of 128 bytes, chunks XOR-ed
 // with the row), every geometry in one instantiation: a bit per tap (at most 31 of them) is tested per load.  No TAIL
 // (undefined channel padding), no statistics.
-// Bound by the operands' way from L2 to LDS: 64 x 64 tiles move half as much per flop as 32 x 32 and need 0.22 - 0.29 us a
-// step (48 KB of LDS, three workgroups on the CU; two steps a stage in 64 KB took 0.55 - 0.78 us for the two), 32 x 32 tiles
-// 0.48 - 0.77 us for four steps (three stages of them, one workgroup on the CU: slower by up to 1.8 times).
+// Bound by the chain of a step: wait, barrier, fragment reads, two MFMAs or four.  The fragments are read ahead of the issue of
+// a later stage's loads, some 25 instructions that would otherwise stand between the barrier and the reads (7 x 7
+// 324 -> 263, 3 x 3, batch 10: 13.4 -> 11.2 us with the third stage; 14 x 14 655 -> 207, 1 x 1: 7.0 -> 6.4 us).  64 x 64 tiles
+// move half as much per flop as 32 x 32 and need 0.22 us a step with three stages (48 KB, three workgroups on the CU; five
+// and eight stages: 0.1 us longer for each, the longer body is fetched once more); 32 x 32 tiles, few and with long
+// reductions, 0.50 us for four steps with three stages (96 KB, one workgroup; two stages: 0.70 us, four: as three).
 template <int BM, int BN, int NB, int STAGES>
 __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problems) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -1084,10 +1087,10 @@ __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problem
     }
     int blk = nblk, col = a.TS, f_cb = 0, left = a.nk;
     const int tap_bits = a.fold ? a.TSm : 1;  // taps done with a step's last block (folded: a filter row)
-    auto issue = [&](int stage) {
+    auto issue = [&](int at) {  // at: byte offset of the stage
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            uint8_t* sbase = smem_b + stage * STAGE + b * SUB;
+            uint8_t* sbase = smem_b + at + b * SUB;
             const bool last = blk == 1, last_col = col == 1;
 #pragma unroll
             for (int j = 0; j < LPW; ++j) {
@@ -1121,14 +1124,14 @@ __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problem
     if (blockIdx.x >= (unsigned)a.grid_x) return;  // the whole workgroup
     const int nst = (a.nk + NB - 1) / NB;
 #pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s) issue(s);
+    for (int s = 0; s < STAGES - 1; ++s) issue(s * STAGE);
     for (int st0 = 0; st0 < nst; st0 += STAGES) {
 #pragma unroll
         for (int s = 0; s < STAGES; ++s) {
             if (st0 + s < nst) {
                 wait_vmcnt<(STAGES - 2) * LPW * NB>();
                 barrier_nofence();
-                issue((s + STAGES - 1) % STAGES);  // (past the end: zeros into a stage nobody multiplies)
+                // fragments first: the loads of a later stage are sent out while these are on their way
                 const uint8_t* base = smem_b + s * STAGE;
                 bf16x8 fa[PER], fb[PER];
 #pragma unroll
@@ -1137,6 +1140,7 @@ __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problem
                     fb[q] = *reinterpret_cast<const bf16x8*>(base + b_row + off);
                     fa[q] = *reinterpret_cast<const bf16x8*>(base + a_row + off);
                 }
+                issue((s + STAGES - 1) % STAGES * STAGE);  // (past the end: zeros into a stage nobody multiplies)
 #pragma unroll
                 for (int q = 0; q < PER; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[q], fa[q], acc, 0, 0, 0);
             }
@@ -1151,44 +1155,53 @@ __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problem
         *reinterpret_cast<float4*>(red + (kg * BM + wm * 32 + l32) * RP + wn * 32 + 8 * g + 4 * kc0) =
             make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
     __syncthreads();
-    for (int t = tid; t < BM * BN / 8; t += 512) {
-        const int px = t / (BN / 8), ch = n0 + (t - px * (BN / 8)) * 8, m = m0 + px;
-        if (m >= a.M || ch >= a.Nout) continue;
-        const float* src = red + px * RP + (ch - n0);
-        float v[8];
+    // every thread adds and stores E consecutive channels of one pixel (32 x 32: all 512 of them, not 128 with eight each)
+    constexpr int E = BM * BN / 512, TPP = BN / E;
+    static_assert(E == 2 || E == 8, "elements per thread");
+    const int px = tid / TPP, chl = (tid % TPP) * E, ch = n0 + chl, m = m0 + px;
+    const float* src = red + px * RP + chl;
+    float v[E];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = src[e];
+    for (int e = 0; e < E; ++e) v[e] = src[e];
 #pragma unroll
-        for (int g = 1; g < KS; ++g)
+    for (int g = 1; g < KS; ++g)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] += src[g * BM * RP + e];
-        uint4 o = make_uint4(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]), cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7]));
-        int64_t dpix = (int64_t)m * a.dpitch;
-        int cell_h = 1, cell_w = 1;
-        if (!a.d_linear) {
-            const uint32_t row = fdiv((uint32_t)m, a.gW), gj = m - row * a.gW.d;
-            const uint32_t n = fdiv(row, a.gH), gi = row - n * a.gH.d;
-            const int dh = (int)gi * a.d_hmul + a.d_hadd, dw = (int)gj * a.d_wmul + a.d_wadd;
-            dpix = (((int64_t)n * a.DH + dh) * a.DW + dw) * a.dpitch;
-            cell_h = min(a.zf_h, a.DH - dh);
-            cell_w = min(a.zf_w, a.DW - dw);
+        for (int e = 0; e < E; ++e) v[e] += src[g * BM * RP + e];
+    uint32_t at = (uint32_t)m * a.dst.point + a.dst.origin + (uint32_t)ch * 2u;
+    int cell_h = 1, cell_w = 1;
+    if (!a.d_linear) {  // uniform
+        const uint32_t row = fdiv((uint32_t)m, a.gW), n = fdiv(row, a.gH);
+        at += row * a.dst.row + n * a.dst.image;
+        cell_h = min(a.zf_h, a.DH - ((int)(row - n * a.gH.d) * a.d_hmul + a.d_hadd));
+        cell_w = min(a.zf_w, a.DW - ((int)(m - row * a.gW.d) * a.d_wmul + a.d_wadd));
+    }
+    typedef uint32_t vec_t __attribute__((ext_vector_type(E / 2)));
+    vec_t o;
+    uint16_t* dst = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(a.D) + at);
+    if (m >= a.M || ch >= (a.pad_zero ? (int)((a.Nout + 7) & ~7) : a.Nout)) return;
+    if (a.zf_h * a.zf_w > 1) {  // uniform: clear the other pixels of the cell (vector stores only)
+#pragma unroll
+        for (int e = 0; e < E / 2; ++e) o[e] = 0u;
+        for (int zh = 0; zh < cell_h; ++zh)
+            for (int zw = zh == 0 ? 1 : 0; zw < cell_w; ++zw)
+                *reinterpret_cast<vec_t*>(dst + ((int64_t)zh * a.DW + zw) * a.dpitch) = o;
+    }
+#pragma unroll
+    for (int e = 0; e < E / 2; ++e) o[e] = cvt_pk_bf16(v[2 * e], v[2 * e + 1]);
+    // whole chunks of eight channels, of a zero-padded tensor also the last one (zeros in its padding), as vectors
+    if (a.d_vec16 && ((ch | 7) < a.Nout || (a.pad_zero && (ch | 7) < a.dpitch))) {
+        if (ch + E > a.Nout) {
+#pragma unroll
+            for (int e = 0; e < E / 2; ++e) {
+                const int k = a.Nout - ch - 2 * e;
+                o[e] &= k >= 2 ? 0xffffffffu : k == 1 ? 0xffffu : 0u;
+            }
         }
-        uint16_t* dst = a.D + dpix + ch;
-        if (a.zf_h * a.zf_w > 1) {  // uniform: clear the other pixels of the cell (vector stores only)
-            for (int zh = 0; zh < cell_h; ++zh)
-                for (int zw = zh == 0 ? 1 : 0; zw < cell_w; ++zw)
-                    *reinterpret_cast<uint4*>(dst + ((int64_t)zh * a.DW + zw) * a.dpitch) = make_uint4(0u, 0u, 0u, 0u);
-        }
-        if (a.d_vec16 && ch + 7 < a.Nout) {
-            *reinterpret_cast<uint4*>(dst) = o;
-        } else if (a.d_vec16 && a.pad_zero && ch + 8 <= a.dpitch) {
-            *reinterpret_cast<uint4*>(dst) = mask8(o, true, make_mask8(a.Nout - ch));
-        } else {
-            const uint32_t w[4] = {o.x, o.y, o.z, o.w};
+        *reinterpret_cast<vec_t*>(dst) = o;
+    } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (ch + e < a.Nout) dst[e] = (uint16_t)(w[e >> 1] >> ((e & 1) * 16));
-        }
+        for (int e = 0; e < E; ++e)
+            if (ch + e < a.Nout) dst[e] = (uint16_t)(o[e >> 1] >> ((e & 1) * 16));
     }
 #endif
 }
