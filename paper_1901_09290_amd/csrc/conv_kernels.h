@@ -2195,6 +2195,7 @@ struct Res3Args {
     int nbx, nby;                            // blocks of 8 columns and of 4 rows per tile
     uint32_t pw_magic;                       // divides by the patch's width (fast_div)
     int tiles_x, tiles_y, tiles, run;
+    FastDiv x_div, y_div, bx_div;            // by tiles_x, tiles_y, nbx
 };
 constexpr int kR3TH = 4, kR3MaxNB = 7, kR3Waves = 8, kR3PatchPixels = (kR3TH + 2) * (8 * kR3MaxNB + 2);
 constexpr int kR3WRow = 9 * 128 + 16, kR3WBytes = 64 * kR3WRow;
@@ -2214,6 +2215,7 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
     constexpr int WSLOTS = kR3WRow / 16;                       // 16-byte slots per weight row (73, the last one padding)
     constexpr int NWL = 64 * WSLOTS / 64, WL = (NWL + 7) / 8;  // wave-level loads of the weights, per wave
     constexpr int NPL = (kR3PatchSlots + 63) / 64, PL = (NPL + 7) / 8;
+    constexpr int NKB = KB1 ? 2 : 1;  // accumulator blocks
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_b[];
     uint8_t* wl = smem_b;
     uint8_t* pbuf = smem_b + kR3WBytes;
@@ -2255,9 +2257,10 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
     }
     const uint32_t in_bytes = (uint32_t)(a.H * a.W * a.ip) * 2u, out_bytes = (uint32_t)(a.H * a.W * a.op) * 2u;
     auto decode = [&](int tile, int& tx, int& ty, int& img) {
-        tx = tile % a.tiles_x;
-        ty = (tile / a.tiles_x) % a.tiles_y;
-        img = tile / (a.tiles_x * a.tiles_y);
+        const int row = (int)fdiv((uint32_t)tile, a.x_div);
+        img = (int)fdiv((uint32_t)row, a.y_div);
+        tx = tile - row * a.tiles_x;
+        ty = row - img * a.tiles_y;
     };
     auto issue = [&](int tile, int buf) {
         int tx, ty, img;
@@ -2279,7 +2282,7 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
 
     // ---- MFMA state -----------------------------------------------------------------------------------------------
     const int l32 = lane & 31, h = lane >> 5;
-    const int by = wave / a.nbx, bx = wave - by * a.nbx;
+    const int by = (int)fdiv((uint32_t)wave, a.bx_div), bx = wave - by * a.nbx;
     const int pr0 = by * kR3TH + (l32 >> 3), pc0 = bx * 8 + (l32 & 7);  // this lane's output pixel inside the tile
     const bool active = by < a.nby;
     uint32_t pb[9], pk[9];  // per tap: byte offset of the pixel under it in a patch, and its chunk swizzle (<< 4)
@@ -2297,21 +2300,21 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
     for (int tile = first; tile < last; ++tile, buf ^= 1) {
         const bool more = tile + 1 < last;  // uniform
         // the patch of this tile (and at first the weights) has landed; this wave's stores of the previous tile, which
-        // were issued after those loads, may still be in flight (every active wave issues exactly four)
-        if (active && tile != first) wait_vmcnt<4>();
+        // were issued after those loads, may still be in flight (every active wave issues exactly 2 * NKB)
+        if (active && tile != first) wait_vmcnt<2 * NKB>();
         else wait_vmcnt<0>();
         barrier_nofence();
         if (more) issue(tile + 1, buf ^ 1);
         // the loads stay here, ahead of the multiply and of the stores: the wait at the top of the next tile counts on
-        // the stores being the last four memory instructions of the wave, and the loads need the multiply's time to land
+        // the stores being the last memory instructions of the wave, and the loads need the multiply's time to land
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         if (active) {
             int tx, ty, img;
             decode(tile, tx, ty, img);
-            f32x16 acc[2];
+            f32x16 acc[NKB];
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+            for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[kb][v] = 0.f;
             const uint8_t* pp = pbuf + buf * kR3PatchBytes;
@@ -2339,7 +2342,7 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
             const bool ok0 = row_ok && (ow & ~1) < a.W, ok1 = row_ok && (ow | 1) < a.W;
             const uint32_t pix0 = (uint32_t)((oh * a.W + (ow & ~1)) * a.op) * 2u;
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
+            for (int kb = 0; kb < NKB; ++kb) {
                 const int ch = kb * 32 + chl;
                 const f32x16& c = acc[kb];
                 uint32_t v[2][4];
@@ -2354,8 +2357,7 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
                 uint32_t s0[4], s1[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const uint32_t give = odd ? v[0][e] : v[1][e];
-                    const uint32_t got = (uint32_t)__shfl_xor((int)give, 1, 64);
+                    const uint32_t got = swap_lane_pair(odd ? v[0][e] : v[1][e]);
                     s0[e] = odd ? got : v[0][e];
                     s1[e] = odd ? v[1][e] : got;
                 }
@@ -2402,6 +2404,9 @@ inline hipError_t launch_conv3x3_res(Res3Args& a, bool flip, hipStream_t st) {
     if (tiles <= 0 || tiles > 0x3fffffff) return hipErrorInvalidValue;
     a.tiles = (int)tiles;
     a.run = (int)((tiles + kR3Slots - 1) / kR3Slots);
+    a.x_div = make_fastdiv((uint32_t)a.tiles_x);
+    a.y_div = make_fastdiv((uint32_t)a.tiles_y);
+    a.bx_div = make_fastdiv((uint32_t)a.nbx);
     const unsigned grid = (unsigned)((tiles + a.run - 1) / a.run);
     typedef void (*kern_t)(const Res3Args);
     static const kern_t kerns[2][4][2] = {
