@@ -42,7 +42,7 @@ inline IgemmArgs make_fwd_args(const pt_conv_desc* d, const uint16_t* x, const u
     a.pad_zero = (d->flags & PT_CONV_PAD_ZERO) != 0;
     a.zf_h = a.zf_w = 1;
     a.M = d->N * d->P * d->Q;
-    a.gW = make_fastdiv((uint32_t)d->Q); a.gH = make_fastdiv((uint32_t)d->P);
+    a.gW = make_fastdiv((int64_t)d->Q); a.gH = make_fastdiv((int64_t)d->P);
     a.srcH = d->H; a.srcW = d->W; a.apitch = d->x_cpitch;
     a.h_mul = d->stride_h; a.h_add = -d->pad_h; a.w_mul = d->stride_w; a.w_add = -d->pad_w;
     a.tr_step = 1; a.ts_step = 1; a.TR = d->R; a.TS = d->S;
@@ -51,7 +51,7 @@ inline IgemmArgs make_fwd_args(const pt_conv_desc* d, const uint16_t* x, const u
     a.bpitch = d->w_cpitch; a.Nout = d->K;
     a.DH = d->P; a.DW = d->Q; a.d_hmul = 1; a.d_hadd = 0; a.d_wmul = 1; a.d_wadd = 0; a.dpitch = d->y_cpitch;
     a.d_linear = 1;
-    a.fold = 0; a.TSm = d->S; a.Creal = d->C; a.Cfold = make_fastdiv((uint32_t)a.CredP);
+    a.fold = 0; a.TSm = d->S; a.Creal = d->C; a.Cfold = make_fastdiv((int64_t)a.CredP);
     a.d_vec = (d->y_cpitch % 4 == 0) && (((uintptr_t)y & 7) == 0);
     a.d_vec16 = (d->y_cpitch % 8 == 0) && aligned16(y);
     return a;
@@ -82,7 +82,7 @@ inline IgemmArgs make_bwd_data_args(const pt_conv_desc* d, const BwdClass& c, in
     a.pad_zero = (d->flags & PT_CONV_PAD_ZERO) != 0;  // the k-innermost weight copy always has zero padding
     a.zf_h = a.zf_w = 1;
     a.M = d->N * c.gH * c.gW;
-    a.gW = make_fastdiv((uint32_t)c.gW); a.gH = make_fastdiv((uint32_t)c.gH);
+    a.gW = make_fastdiv((int64_t)c.gW); a.gH = make_fastdiv((int64_t)c.gH);
     a.srcH = d->P; a.srcW = d->Q; a.apitch = d->y_cpitch;
     a.h_mul = 1; a.h_add = (ca + d->pad_h - c.r0) / d->stride_h;
     a.w_mul = 1; a.w_add = (cb + d->pad_w - c.s0) / d->stride_w;
@@ -93,7 +93,7 @@ inline IgemmArgs make_bwd_data_args(const pt_conv_desc* d, const BwdClass& c, in
     a.DH = d->H; a.DW = d->W; a.d_hmul = d->stride_h; a.d_hadd = ca; a.d_wmul = d->stride_w; a.d_wadd = cb;
     a.dpitch = d->x_cpitch;
     a.d_linear = (d->stride_h == 1 && d->stride_w == 1);
-    a.fold = 0; a.TSm = c.TS; a.Creal = d->K; a.Cfold = make_fastdiv((uint32_t)kpitch);
+    a.fold = 0; a.TSm = c.TS; a.Creal = d->K; a.Cfold = make_fastdiv((int64_t)kpitch);
     a.d_vec = (d->x_cpitch % 4 == 0) && (((uintptr_t)dx & 7) == 0);
     a.d_vec16 = (d->x_cpitch % 8 == 0) && aligned16(dx);
     a.edge_prio = 1;
@@ -109,7 +109,7 @@ inline void igemm_fold(IgemmArgs& a) {
     a.fold = 1;
     a.TSm = a.TS;
     a.Creal = a.Cred;
-    a.Cfold = make_fastdiv((uint32_t)a.CredP);
+    a.Cfold = make_fastdiv((int64_t)a.CredP);
     a.Cred = a.CredP = a.TS * a.CredP;
     a.TS = 1;
 }
@@ -223,6 +223,9 @@ inline float wgrad_step_us(const WgradPlan& p) {
 }
 
 inline WgradPlan plan_wgrad_tiles(const pt_conv_desc* d, bool dl) {
+    // the direct kernel addresses the 128 rows of an output tile with 31 bits
+    const int64_t row = (int64_t)d->R * d->S * (round_up(d->C, 8) > d->w_cpitch ? round_up(d->C, 8) : d->w_cpitch);
+    dl = dl && row <= (1 << 22);
     WgradPlan p;
     p.dl = dl;
     p.CP = (int)round_up(d->C, 8);
@@ -349,7 +352,7 @@ inline WgradArgs make_wgrad_args(const pt_conv_desc* d, const WgradPlan& p, cons
     WgradArgs a{};
     a.X = x; a.DY = dy;
     a.pixels = d->N * d->P * d->Q;
-    a.Q = make_fastdiv((uint32_t)d->Q); a.P = make_fastdiv((uint32_t)d->P);
+    a.Q = make_fastdiv((int64_t)d->Q); a.P = make_fastdiv((int64_t)d->P);
     a.H = d->H; a.W = d->W; a.xpitch = d->x_cpitch; a.ypitch = d->y_cpitch;
     a.stride_h = d->stride_h; a.stride_w = d->stride_w; a.pad_h = d->pad_h; a.pad_w = d->pad_w;
     a.S = d->S; a.RS = d->R * d->S; a.C = d->C; a.CP = p.CP; a.KP = p.KP; a.Mtot = p.Mtot; a.K = d->K;
@@ -366,6 +369,13 @@ inline WgradArgs make_wgrad_args(const pt_conv_desc* d, const WgradPlan& p, cons
     a.OUT = a.direct ? dw : (float*)ws;
     a.out_row_pitch = p.Mtot;
     a.o_vec = (d->w_cpitch % 4 == 0) && aligned16(dw);
+    if (p.dl) {
+        a.ntile_div = make_fastdiv((int64_t)p.tiles_m * p.tiles_n);
+        a.tn_div = make_fastdiv(p.tiles_n);
+        a.tap_div = make_fastdiv(p.tiles_per_tap);
+        a.S_div = make_fastdiv((int64_t)d->S);
+        a.CP_div = make_fastdiv((int64_t)p.CP);
+    }
     return a;
 }
 

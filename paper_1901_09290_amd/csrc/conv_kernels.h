@@ -81,13 +81,18 @@ __device__ __forceinline__ int xcd_remap(int bid, int nb) {
     return xcd * per + min(xcd, rem) + q;
 }
 
-// floor(m / d) through a host-made magic number (exact for m * d < 2^32); d == 1, whose magic number has 33 bits, has
-// magic 0 and passes m through the mask `one` (no branch: a workgroup's first load waits for these divisions).
+// floor(m / d) for 0 <= m < 2^31 through a host-made reciprocal: with l = ceil(log2 d) and magic = ceil(2^(31 + l) / d) (at
+// most 32 bits) the error magic * d - 2^(31 + l) is below 2^l, so m * magic / 2^(31 + l) is off by less than 1 / d.  No
+// branch and no special divisor: a workgroup's first load waits for these divisions.
 struct FastDiv {
-    uint32_t d, magic, one;
+    uint32_t d, magic, shift;
 };
-inline FastDiv make_fastdiv(uint32_t d) { return FastDiv{d, d == 1 ? 0u : make_magic(d), d == 1 ? ~0u : 0u}; }
-__device__ __forceinline__ uint32_t fdiv(uint32_t m, FastDiv f) { return __umulhi(m, f.magic) + (m & f.one); }
+inline FastDiv make_fastdiv(int64_t d) {
+    uint32_t l = 0;
+    while ((1ll << l) < d) ++l;
+    return FastDiv{(uint32_t)d, (uint32_t)(((1ull << (31 + l)) + (uint64_t)d - 1) / (uint64_t)d), l};
+}
+__device__ __forceinline__ uint32_t fdiv(uint32_t m, FastDiv f) { return __umulhi(2 * m, f.magic) >> f.shift; }
 
 // ------------------------------------------------------------------------------------------- //
 // forward / input-gradient implicit GEMM
@@ -147,7 +152,7 @@ struct IgemmArgs {
     int grid_x;  // direct kernel: workgroups (tiles) of this problem inside a launch that may hold several problems
     int m_fast;  // small tiles: consecutive tiles run along the pixels (and share weights), not along the outputs
     // Direct kernels: the above, ready for use in a workgroup's set-up (make_igemm_offsets).
-    FastDiv t_div;  // tiles along the fast axis; magic == one == 0: too many tiles for it
+    FastDiv t_div;  // tiles along the axis that consecutive tiles run along
     RowOffsets src, dst;
     int ch_mul, ch_add, cw_mul, cw_add;  // taps inside the source image: rows [gi * ch_mul + ch_add, + srcH), columns alike
     uint64_t tap_rep;                    // bit r * TSm for every filter row r
@@ -431,9 +436,6 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
-__device__ __forceinline__ int tile_div(int tile, FastDiv f) {
-    return f.magic | f.one ? (int)fdiv((uint32_t)tile, f) : tile / (int)f.d;  // uniform
-}
 __device__ __forceinline__ uint32_t swap_lane_pair(uint32_t v) {  // lanes 2i and 2i + 1 trade values
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, true);
 }
@@ -482,7 +484,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tile = xcd_remap(blockIdx.x, a.grid_x);
-    const int tile_m = tile_div(tile, a.t_div);
+    const int tile_m = (int)fdiv((uint32_t)tile, a.t_div);
     const int n0 = (tile - tile_m * a.tiles_n) * BN, m0 = tile_m * BM;
 
     // A reduction step is (filter tap, block of 64 reduction channels): the same for every lane, so the
@@ -926,8 +928,7 @@ inline hipError_t launch_igemm_dl_planned(const IgemmArgs* as, const IgemmDlPlan
 // Offsets, tap intervals and tile division of the direct kernels, from the problem's geometry; `fast` = tiles along the axis
 // that consecutive tiles run along.
 inline void make_igemm_offsets(IgemmArgs& a, int fast) {
-    a.t_div = make_fastdiv((uint32_t)fast);
-    if ((int64_t)a.grid_x * fast > 0xffffffffll) a.t_div.magic = a.t_div.one = 0;
+    a.t_div = make_fastdiv(fast);
     auto offsets = [&](int64_t point, int64_t row, int64_t image, int64_t origin) {  // of one step in j, i, n; in elements
         return RowOffsets{(uint32_t)(point * 2), (uint32_t)((row - a.gW.d * point) * 2), (uint32_t)((image - a.gH.d * row) * 2),
                           (uint32_t)(origin * 2)};
@@ -1053,7 +1054,7 @@ __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problem
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tile = xcd_remap(blockIdx.x, a.grid_x);
-    const int slow = tile_div(tile, a.t_div), fast = tile - slow * (int)a.t_div.d;
+    const int slow = (int)fdiv((uint32_t)tile, a.t_div), fast = tile - slow * (int)a.t_div.d;
     const int m0 = (a.m_fast ? fast : slow) * BM, n0 = (a.m_fast ? slow : fast) * BN;
 
     // Loads as in k_igemm_dl: per-lane constants in voffset, running scalar offsets in soffset, one bit per tap and
@@ -1494,6 +1495,7 @@ struct WgradArgs {
     int wpitch;
     int direct;          // 1: write dw layout directly (splits == 1)
     int o_vec;
+    FastDiv ntile_div, tn_div, tap_div, S_div, CP_div;  // direct kernel: by tiles_m * tiles_n, tiles_n, tiles_per_tap, S, CP
 };
 
 template <int BM, int BN, int BK, int WGM, int WGN, int MINB, bool VEC>
@@ -1720,6 +1722,10 @@ __device__ __forceinline__ bf16x8 join_halves(s16x4 lo, s16x4 hi) {
 // an output grid equal to the input grid ('same'-padded filters): buffer loads whose moving part is a scalar; 2 = the
 // same where no tap ever leaves the image (1 x 1 filters): no per-lane work at all in a reduction step.
 // `lin`: which workgroup of the problem this is, in split-major (split, tile) order.
+#ifndef PT_WGAUX
+#define PT_WGAUX 0
+#endif
+constexpr int kWgStoreAux = PT_WGAUX;
 template <int BM, int BN, int BKP, int WGM, int WGN, int STAGES, int KSPLIT, int XMODE, bool AHEAD>
 __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin, uint8_t* smem_b) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
@@ -1742,15 +1748,15 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = wave / NWT, wave_t = wave - kg * NWT;  // wave group, wave inside the group
     const int ntile = a.tiles_m * a.tiles_n;
-    const int split = lin / ntile;
+    const int split = (int)fdiv((uint32_t)lin, a.ntile_div);
     const int tile = lin - split * ntile;
-    const int n0 = (tile % a.tiles_n) * BN;        // k origin
-    const int mt = tile / a.tiles_n;               // (tap, channel block)
+    const int mt = (int)fdiv((uint32_t)tile, a.tn_div);  // (tap, channel block)
+    const int n0 = (tile - mt * a.tiles_n) * BN;   // k origin
     // tile row block: one filter tap (CP channels), or in folded mode one filter row (S*CP contiguous elements)
-    const int tb = mt / a.tiles_per_tap;
+    const int tb = (int)fdiv((uint32_t)mt, a.tap_div);
     const int cb = (mt - tb * a.tiles_per_tap) * BM;
     const int run = a.fold ? a.S * a.CP : a.CP;
-    const int fr = a.fold ? tb : tb / a.S;
+    const int fr = a.fold ? tb : (int)fdiv((uint32_t)tb, a.S_div);
     const int it0 = split * a.iters_per_split;
     const int it1 = min(a.iters_total, it0 + a.iters_per_split);
 
@@ -1776,7 +1782,7 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
     const int xr = lane / CPRX, xpc = lane % CPRX;
     const int xlc = (unit_logical(xpc >> 1, wave * RPLX + xr, RBX) << 1) | (xpc & 1);
     const int xc = min(cb + xlc * 8, run - 8);     // clamp: chunks past the run are never stored
-    const int fs = a.fold ? xc / a.CP : tb - fr * a.S;   // filter column of this lane's chunk
+    const int fs = a.fold ? (int)fdiv((uint32_t)xc, a.CP_div) : tb - fr * a.S;   // filter column of this lane's chunk
     const int fs_addr = a.fold ? 0 : fs;           // folded: the column offset is part of xc
     const int yr = lane / CPRY, ypc = lane % CPRY;
     const int ylc = (unit_logical(ypc >> 1, wave * RPLY + yr, RBY) << 1) | (ypc & 1);
@@ -2055,62 +2061,53 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
     // ---- epilogue: the MFMA's row operand is dy, so a lane holds input channel (column) lane%32 of the 32x32 block
     // and output channels (rows) 8g + 4*(lane/32) + {0..3}: a store instruction writes, for one output channel per
     // half-wave, 32 consecutive input channels = 128 contiguous bytes of dw (or of the partial slab).
-    float* out = a.OUT + (a.direct ? 0 : (int64_t)split * a.K * a.out_row_pitch);
-    const int hi4 = (lane >> 5) * 4;
+    // Buffer stores on a descriptor of the tile's rows: 32-bit offsets, and what must not be written (output channels past
+    // the last one, input channels past the run) is out of range, so the 16 * TM * TN stores are that many instructions and
+    // an addition each (1.75 us of a workgroup's life with a 64-bit address and a branch per store, 0.8 us so).
+    const int row_pitch = a.direct ? a.RS * a.wpitch : a.out_row_pitch, tap_pitch = a.direct ? a.wpitch : a.CP;
+    const int64_t first = (int64_t)n0 * row_pitch + (a.direct ? 0 : (int64_t)split * a.K * a.out_row_pitch);
+    const uint32_t tile_bytes = (uint32_t)(min(a.K - n0, BN) * row_pitch) * 4u;  // <= 2^31 (plan_wgrad_tiles)
+    const __amdgpu_buffer_rsrc_t o_srd = __builtin_amdgcn_make_buffer_rsrc(a.OUT + first, 0, tile_bytes, kBufFlags);
+    const int cols = a.direct ? a.C : a.CP, row0 = wn * WTN + (lane >> 5) * 4;  // output channel of element (tn, e) = (0, 0)
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
         const int cr = cb + wm * WTM + tm * 32 + (lane & 31);  // row inside the run
-        if (cr >= run) continue;
-        const int ts = a.fold ? cr / a.CP : 0;
+        const int ts = a.fold ? (int)fdiv((uint32_t)cr, a.CP_div) : 0;
         const int c = cr - ts * a.CP;
         const int tapi = a.fold ? tb * a.S + ts : tb;
-        if (a.direct && c >= a.C) continue;
-        float inv_in = 0.f;
-        if (a.direct && a.lw && a.l_in) {
-            const float in = a.l_in[c];
-            inv_in = in > 0.f ? 1.0f / in : 0.f;
-        }
+        const bool ok = cr < run && c < cols;
+        const uint32_t at0 = ok ? (uint32_t)(row0 * row_pitch + tapi * tap_pitch + c) * 4u : kBufOut;
+        auto at = [&](int tn, int e) { return at0 + (uint32_t)((tn * 32 + 8 * (e >> 2) + (e & 3)) * row_pitch) * 4u; };
         if (a.direct && a.lw) {  // uniform: regulariser folded in
             // every weight and norm this lane needs is fetched before the first store: the stores may alias the loads
             // as far as the compiler knows, and interleaved they would each wait out a full memory round trip
+            const __amdgpu_buffer_rsrc_t w_srd =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.lw) + first, 0, tile_bytes, kBufFlags);
+            const float in = a.l_in && ok ? a.l_in[c] : 0.f;
+            const float inv_in = in > 0.f ? 1.0f / in : 0.f;
             float wv[TN][16], io[TN][16];
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    const int k = n0 + wn * WTN + tn * 32 + 8 * (e >> 2) + hi4 + (e & 3);
-                    const int kc = k < a.K ? k : a.K - 1;
-                    wv[tn][e] = a.lw[((int64_t)kc * a.RS + tapi) * a.wpitch + c];
-                    io[tn][e] = a.l_on ? a.l_on[kc] : 0.f;
+                    wv[tn][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(w_srd, at(tn, e), 0, 0));
+                    io[tn][e] = a.l_on ? a.l_on[min(n0 + row0 + tn * 32 + 8 * (e >> 2) + (e & 3), a.K - 1)] : 0.f;
                 }
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    const int k = n0 + wn * WTN + tn * 32 + 8 * (e >> 2) + hi4 + (e & 3);
-                    if (k >= a.K) continue;
                     const float inv_out = io[tn][e] > 0.f ? 1.0f / io[tn][e] : 0.f;
-                    out[((int64_t)k * a.RS + tapi) * a.wpitch + c] =
-                        acc[tm][tn][e] + a.l_lambda * (wv[tn][e] * (inv_out + inv_in));
+                    const float v = acc[tm][tn][e] + a.l_lambda * (wv[tn][e] * (inv_out + inv_in));
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), o_srd, at(tn, e), 0, 0);
                 }
             continue;
         }
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn) {
+        for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int k = n0 + wn * WTN + tn * 32 + 8 * g + hi4 + i;
-                    if (k >= a.K) continue;
-                    const float v = acc[tm][tn][4 * g + i];
-                    if (a.direct)
-                        out[((int64_t)k * a.RS + tapi) * a.wpitch + c] = v;
-                    else
-                        out[(int64_t)k * a.out_row_pitch + tapi * a.CP + c] = v;
-                }
-            }
-        }
+            for (int e = 0; e < 16; ++e)
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[tm][tn][e]), o_srd, at(tn, e), 0, kWgStoreAux);
     }
 #endif
 }
@@ -2404,9 +2401,9 @@ inline hipError_t launch_conv3x3_res(Res3Args& a, bool flip, hipStream_t st) {
     if (tiles <= 0 || tiles > 0x3fffffff) return hipErrorInvalidValue;
     a.tiles = (int)tiles;
     a.run = (int)((tiles + kR3Slots - 1) / kR3Slots);
-    a.x_div = make_fastdiv((uint32_t)a.tiles_x);
-    a.y_div = make_fastdiv((uint32_t)a.tiles_y);
-    a.bx_div = make_fastdiv((uint32_t)a.nbx);
+    a.x_div = make_fastdiv((int64_t)a.tiles_x);
+    a.y_div = make_fastdiv((int64_t)a.tiles_y);
+    a.bx_div = make_fastdiv((int64_t)a.nbx);
     const unsigned grid = (unsigned)((tiles + a.run - 1) / a.run);
     typedef void (*kern_t)(const Res3Args);
     static const kern_t kerns[2][4][2] = {
