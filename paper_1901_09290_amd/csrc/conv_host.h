@@ -2,6 +2,8 @@
 // tile-configuration choice and the split plan of the weight gradient.
 #pragma once
 
+#include <math.h>
+
 #include "conv_kernels.h"
 
 namespace pt {
@@ -211,10 +213,10 @@ inline int pick_tile(int n) {
     return (r64 < r128 && r128 * 5 > (int64_t)n * 6) ? 64 : 128;
 }
 
-// What a reduction step and a split cost, fitted to ResNet-50 layers on the chip (us): a step of the 128 x 128 tile takes
-// 0.30 with one workgroup on the CU (smaller tiles: in proportion to their MFMAs, but no less than 0.6 of it), a
-// split's tile of fp32 partial sums is written and read again at about 4 TB/s, and a second launch is not free.
-constexpr float kWgStepUs = 0.30f, kWgPartialUsPerByte = 2.f / 4e6f, kWgReduceUs = 2.f;
+// What a reduction step and a split cost in a call with several layers, fitted to ResNet-50 layers on the chip (us): a step of
+// the 128 x 128 tile takes 0.30 with one workgroup on the CU (smaller tiles: in proportion to their MFMAs, but no less than
+// 0.6 of it), a split's tile of fp32 partial sums is written and read again at about 4 TB/s.
+constexpr float kWgStepUs = 0.30f, kWgPartialUsPerByte = 2.f / 4e6f;
 constexpr int kWgMinSteps = 4;    // per workgroup
 constexpr int kWgSlots = 256;     // one workgroup per CU: a second one on the CU finishes no more steps per microsecond
 inline float wgrad_step_us(const WgradPlan& p) {
@@ -222,7 +224,7 @@ inline float wgrad_step_us(const WgradPlan& p) {
     return kWgStepUs * (r > 0.6f ? r : 0.6f);
 }
 
-inline WgradPlan plan_wgrad_tiles(const pt_conv_desc* d, bool dl) {
+inline WgradPlan plan_wgrad_tiles(const pt_conv_desc* d, bool dl, int cfg = -1) {  // cfg: tile configuration, -1 = by the sizes
     // the direct kernel addresses the 128 rows of an output tile with 31 bits
     const int64_t row = (int64_t)d->R * d->S * (round_up(d->C, 8) > d->w_cpitch ? round_up(d->C, 8) : d->w_cpitch);
     dl = dl && row <= (1 << 22);
@@ -236,8 +238,8 @@ inline WgradPlan plan_wgrad_tiles(const pt_conv_desc* d, bool dl) {
     p.fold = dl && p.CP < 64 && d->S > 1 && d->x_cpitch == p.CP && d->w_cpitch == p.CP;
     if (dl) {
         const int run = p.fold ? d->S * p.CP : p.CP;  // contiguous elements of one tile row block
-        p.BM = pick_tile(run);
-        p.BN = pick_tile(p.KP);
+        p.BM = cfg >= 0 ? kWgCfgBM[cfg] : pick_tile(run);
+        p.BN = cfg >= 0 ? kWgCfgBN[cfg] : pick_tile(p.KP);
         while (kWgCfgBM[p.cfg] != p.BM || kWgCfgBN[p.cfg] != p.BN) ++p.cfg;
         p.tiles_per_tap = (int)ceil_div(run, p.BM);
         p.tiles_m = (p.fold ? d->R : d->R * d->S) * p.tiles_per_tap;
@@ -264,24 +266,51 @@ inline void set_wgrad_splits(const pt_conv_desc* d, WgradPlan& p, int64_t splits
     p.ws_bytes = p.splits > 1 ? (size_t)round_up((int64_t)p.splits * d->K * p.Mtot * 4, 256) : 0;
 }
 
-// A call with one layer: the number of splits that takes the least time by the costs above, in one round of workgroups.
-// (A ResNet-50's 53 layers called one after the other take 2056 us at 96 workgroups a call, 1433 us filling the chip.)
+// A call with one layer: tile configuration and splits that take the least time by what 292 shapes cost (8 to 2048 channels, 6
+// to 56 pixels a side, batch 4 to 128, each in all configurations and at 48 to 512 workgroups; us): a step, a round of 256
+// workgroups (pipeline fill, stores), a megabyte of operands fetched into LDS by all workgroups together, a megabyte of
+// partial sums written and read, the second launch.  Chosen so the calls take 1.4 % more than the best measured of each
+// shape.  Against 128-wide tiles wherever they waste little, random shapes gain 10 % (14 x 14 128 -> 128 3 x 3 from 28 x 28,
+// batch 64: 128 x 128 tiles 19.7 us, 64 x 64 tiles 15.8; 14 x 14 256 -> 256 3 x 3 the other way round, 28 and 42).
+// Tiles smaller than the sizes ask for go unsplit up to 24 steps only (1536 pixels; 10 x 10 256 -> 256 3 x 3 at batch 15: 9.5 us
+// against 14.0 split).  They would be faster up to some 50 (14 x 14 at batch 10: 10.8 against 14.5; 1 % over all shapes), but
+// what pt_conv_bwd_weight_plan says of such layers, few splits and a wide reduction, is relied on.
+struct WgradCost {
+    float step, round;
+};
+constexpr WgradCost kWgCost[kWgConfigs] = {{0.24f, 1.35f}, {0.28f, 1.15f}, {0.30f, 1.45f}, {0.24f, 0.3f}};
+constexpr int kWgUnsplitSteps = 24;
+constexpr float kWgPartialUsPerMB = 0.77f, kWgSecondUs = 1.0f, kWgOperandUsPerMB = 0.045f;
 inline WgradPlan plan_wgrad(const pt_conv_desc* d, bool dl) {
-    WgradPlan p = plan_wgrad_tiles(d, dl);
-    const int tiles = p.tiles_m * p.tiles_n;
-    const float step = wgrad_step_us(p), part = (float)tiles * p.BM * p.BN * 4 * kWgPartialUsPerByte;
-    int64_t best = 1;
+    const WgradPlan own = plan_wgrad_tiles(d, dl);
+    const bool direct = own.dl;
+    WgradPlan best = own;
+    const float part = (float)d->K * best.Mtot * 4e-6f * kWgPartialUsPerMB;  // of one split
     float best_us = 1e30f;
-    for (int64_t s = 1; s == 1 || s * tiles <= kWgSlots; ++s) {
-        const int64_t rounds = ceil_div(s * tiles, kWgSlots);
-        const float us = (float)(rounds * ceil_div(p.iters_total, s)) * step + (s > 1 ? (float)s * part + kWgReduceUs : 0.f);
-        if (us < best_us) {
-            best_us = us;
-            best = s;
+    for (int cfg = 0; cfg < (direct ? kWgConfigs : 1); ++cfg) {
+        const WgradPlan p = plan_wgrad_tiles(d, dl, direct ? cfg : -1);
+        const WgradCost cost = direct ? kWgCost[cfg] : WgradCost{kWgStepUs, 0.85f};
+        const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n, most = p.iters_total / kWgMinSteps;
+        const float operands = (float)tiles * p.iters_total * p.bkp * (p.BM + p.BN) * 2e-6f * kWgOperandUsPerMB;
+        // none; around the optimum of steps / s + s * part without rounds; as many as fill one round or two
+        const int64_t mid = (int64_t)fminf(sqrtf((float)p.iters_total * cost.step / part), 1e6f);
+        const int64_t tries[7] = {1, mid - 1, mid, mid + 1, mid + mid / 4, kWgSlots / tiles, 2 * kWgSlots / tiles};
+        for (int64_t s : tries) {
+            if (s > most) s = most;
+            if (s > 2 * kWgSlots / tiles) s = 2 * kWgSlots / tiles;
+            if (s < 1) s = 1;
+            WgradPlan q = p;
+            set_wgrad_splits(d, q, s);
+            if (q.splits == 1 && most > 1 && q.iters_total > kWgUnsplitSteps && direct && (p.BM != own.BM || p.BN != own.BN)) continue;
+            const float us = (float)ceil_div(q.splits * tiles, kWgSlots) * ((float)q.iters_per_split * cost.step + cost.round) +
+                             (q.splits > 1 ? (float)q.splits * part + kWgSecondUs : 0.f) + operands;
+            if (us < best_us) {
+                best_us = us;
+                best = q;
+            }
         }
     }
-    set_wgrad_splits(d, p, best);
-    return p;
+    return best;
 }
 
 // The resident-weights kernel takes 3 x 3 filters at stride 1 and padding 1 with at most 64 channels on either side,

@@ -489,3 +489,53 @@ def test_batched_input_gradients_match_single_calls():
     torch.cuda.synchronize()
     for s, a, b in zip(specs, dxs, singles):
         assert torch.equal(a, b), s
+
+
+WGRAD_TILES = [
+    # N   H   W   C    K   R st pad   tile      splits: one call alone, ragged in both channel counts, every tile form
+    ((21, 6, 6, 89, 66, 3, 2, 1), (64, 64), (1, 1)),        # unsplit: the epilogue writes dw (and the regulariser)
+    ((9, 9, 9, 577, 319, 3, 2, 1), (128, 64), (1, 1)),
+    ((18, 6, 8, 434, 485, 3, 2, 1), (64, 128), (1, 1)),
+    ((5, 8, 10, 693, 341, 3, 2, 1), (128, 128), (1, 1)),
+    ((23, 10, 11, 109, 69, 1, 2, 0), (64, 64), (2, 4)),     # partial sums: one wavefront per 256 outputs, ...
+    ((3, 26, 26, 298, 69, 3, 1, 1), (64, 128), (2, 4)),
+    ((2, 33, 34, 681, 11, 3, 1, 1), (128, 64), (2, 4)),
+    ((7, 22, 23, 649, 218, 1, 1, 0), (64, 64), (5, 8)),     # ... two, ...
+    ((4, 34, 35, 353, 26, 3, 1, 1), (128, 64), (9, 16)),    # ... four
+    ((13, 22, 24, 113, 596, 1, 1, 0), (64, 64), (9, 16)),
+]
+
+
+@pytest.mark.parametrize("case,tile,splits", WGRAD_TILES, ids=lambda c: "x".join(map(str, c)))
+def test_weight_gradient_tile_forms(case, tile, splits):
+    """Every tile form of a weight gradient called alone, written directly and through one, two and four groups of splits,
+    without and with the regulariser folded in."""
+    from gpu_util import CONV_TOL, dev_bf16, dev_f32, DEV, pitch8, rel_err, workspace
+    from paper_1901_09290_amd import binding as B
+    spec = _spec(*case)
+    xp, yp = pitch8(spec.C), pitch8(spec.K)
+    d = B.desc_of(spec, xp, yp, xp)
+    info = B.conv_bwd_weight_plan(d, True)
+    assert (info.tile_m, info.tile_n) == tile and splits[0] <= info.splits <= splits[1], (info.tile_m, info.tile_n, info.splits)
+    rng = np.random.Generator(np.random.PCG64(1000 + sum(case)))
+    t = wl.conv_tensors(spec, rng, want=("x", "dy"))
+    w = (rng.standard_normal((spec.K, spec.R, spec.S, spec.C)) * 0.05).astype(np.float32)
+    w[0] = 0.0
+    xd, dyd, wd = dev_bf16(t["x"], xp), dev_bf16(t["dy"], yp), dev_f32(w, xp)
+    on, inn = (torch.from_numpy(n.astype(np.float32)).to(DEV) for n in oracle.group_norms(w))
+    ws = workspace(max(B.conv_bwd_weight_lasso_workspace_bytes(d), B.conv_bwd_weight_workspace_bytes(d)))
+    ref = oracle.conv_bwd_weight(oracle.shape_of(spec), t["x"], t["dy"])
+    dw = torch.full((spec.K, spec.R, spec.S, xp), float("nan"), dtype=torch.float32, device=DEV)
+    B.conv_bwd_weight(d, xd, dyd, dw, ws)
+    assert rel_err(dw.cpu().numpy()[..., : spec.C], ref) <= CONV_TOL
+    B.conv_bwd_weight_lasso(d, xd, dyd, wd, on, inn, 0.5, 3, dw, ws)
+    ref = oracle.group_lasso_grad(w, on.cpu().numpy(), inn.cpu().numpy(), 0.5, 3, ref)
+    assert rel_err(dw.cpu().numpy()[..., : spec.C], ref) <= CONV_TOL
+    if xp != spec.C:
+        assert bool(torch.isnan(dw[..., spec.C:]).all())
+
+
+def test_weight_gradient_rows_past_the_direct_kernels_addressing():
+    """A dw row of more than 2^22 elements (a wide pitch): the register-staged kernel takes the layer."""
+    spec = _spec(2, 9, 9, 24, 3, 1, 1, 0)
+    _check_full(spec, 1100, 24, 8, (1 << 22) + 8)
