@@ -24,6 +24,7 @@ constexpr int kMaxC = 2048;  // 64 lanes x (8 float4 column groups | 32 scalar c
 #ifndef PT_NORM_JOBS
 #define PT_NORM_JOBS 64  // 64 x 88 bytes + 16 = 5.5 KiB of kernel arguments
 #endif
+constexpr int kNormBatches = 2, kNormMaxChunkRows = kThreads * 8 * kNormBatches;  // rows of a chunk, see plan_norm_chunks
 constexpr int kMaxJobs = PT_NORM_JOBS;  // layers per launch (the table rides in the kernel arguments)
 
 struct NormJob {
@@ -46,6 +47,18 @@ struct NormJobs {
     int n;
 };
 static_assert(sizeof(NormJobs) <= 8192, "kernel-argument table");
+// One layer by itself: its kernel arguments are one read away instead of two, and the launch copies 96 bytes instead of 6 KB
+// (16 x 16 channels 3 x 3: group norms 6.0 us in two launches -> 3.6 in one, gradient 3.8 -> 3.1 us).
+struct NormJob1 {
+    NormJob j;
+    float* ws;
+    float thr;
+};
+__device__ __forceinline__ const NormJob& norm_job(const NormJobs& jobs, const int (&first)[kMaxJobs], int& block) {
+    const int ji = job_of_block(first, block);
+    block -= first[ji];
+    return jobs.j[ji];
+}
 
 struct LassoJob {
     const float* w;
@@ -64,6 +77,15 @@ struct LassoJobs {
     int first[kMaxLassoJobs];  // first workgroup of each job
     int n;
 };
+struct LassoJob1 {
+    LassoJob j;
+};
+__device__ __forceinline__ const LassoJob& lasso_job(const LassoJobs& jobs, int& block) {
+    const int ji = job_of_block(jobs.first, block);
+    block -= jobs.first[ji];
+    return jobs.j[ji];
+}
+__device__ __forceinline__ const LassoJob& lasso_job(const LassoJob1& jobs, int&) { return jobs.j; }
 
 template <int VEC>
 __device__ __forceinline__ void load_vec(const float* p, float (&v)[VEC]) {
@@ -91,13 +113,20 @@ __host__ __device__ inline NormLayout norm_layout(int C) {
     return l;
 }
 
+__device__ __forceinline__ void store_norm(float* norm, uint8_t* zero, int i, float sumsq, float thr) {
+    const float n = sqrtf(sumsq);
+    norm[i] = n;
+    if (zero) zero[i] = n < thr ? 1 : 0;  // the comparison of pt_zero_groups
+}
+
 // One workgroup = one chunk of whole rows of one layer (vector path: 16-byte aligned rows).  A thread keeps eight
 // 16-byte loads in flight: 8 / CG rows at a time, CG column groups each.  Row sums: per thread over its columns,
 // then a shuffle tree over the TX lanes of the row.  Column sums: in registers over the rows a thread visits, then
 // over the rows of a wavefront by shuffles and over the four wavefronts through LDS, all in a fixed order.
-template <int CG>
+// WHOLE: the chunk is the whole layer; its row sums stay in LDS and the norms are finished here.
+template <int CG, bool WHOLE>
 __device__ __forceinline__ void norms_partial_body(const NormJob& J, float* __restrict__ ws, int chunk, int txlog2,
-                                                   float (*colred)[1024]) {
+                                                   float (*colred)[1024], float* rows_lds, float thr) {
     constexpr int U = 8 / CG;  // rows in flight per thread
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int TX = 1 << txlog2, TY = kThreads >> txlog2;
@@ -109,8 +138,8 @@ __device__ __forceinline__ void norms_partial_body(const NormJob& J, float* __re
     const int Lv = (C + 3) >> 2;
     const float* __restrict__ w = J.w;
     uint16_t* __restrict__ shadow = J.shadow;
-    float* __restrict__ rowsq = ws + J.ws_off;
-    float* __restrict__ colpart = rowsq + rows;
+    float* __restrict__ rowsq = WHOLE ? rows_lds : ws + J.ws_off;
+    float* __restrict__ colpart = WHOLE ? nullptr : rowsq + rows;
 
     float acc[CG][4];
     bool col_ok[CG];
@@ -202,32 +231,55 @@ __device__ __forceinline__ void norms_partial_body(const NormJob& J, float* __re
         // with fewer than 64 lanes per row every wavefront holds full sums of its own rows; all four are added
         for (int f = tid; f < PER * TX * 4; f += kThreads) {
             const int c = rnd * PER * TX * 4 + f;
-            if (c < C) colpart[(size_t)chunk * C + c] = ((colred[0][f] + colred[1][f]) + colred[2][f]) + colred[3][f];
+            if (c < C) {
+                const float sum = ((colred[0][f] + colred[1][f]) + colred[2][f]) + colred[3][f];
+                if constexpr (WHOLE) store_norm(J.in_norm, J.zero_in, c, sum, thr);
+                else colpart[(size_t)chunk * C + c] = sum;
+            }
+        }
+    }
+    if constexpr (WHOLE) {  // (the row sums are behind the barriers above)
+        for (int k = tid; k < J.K; k += kThreads) {
+            float sum = 0.f;
+            for (int t = 0; t < J.RS; ++t) sum += rowsq[k * J.RS + t];
+            store_norm(J.out_norm, J.zero_out, k, sum, thr);
         }
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_group_norms_partial_vec(const NormJobs jobs) {
-    __shared__ float colred[4][1024];
-    const int ji = job_of_block(jobs.first, blockIdx.x);
-    const NormJob& J = jobs.j[ji];
-    const int chunk = blockIdx.x - jobs.first[ji];
+template <bool WHOLE>
+__device__ __forceinline__ void norms_partial(const NormJob& J, float* ws, int chunk, float (*colred)[1024], float* rows_lds, float thr) {
     const NormLayout l = norm_layout(J.C);
     switch (l.cglog2) {  // uniform
-        case 0: norms_partial_body<1>(J, jobs.ws, chunk, l.txlog2, colred); break;
-        case 1: norms_partial_body<2>(J, jobs.ws, chunk, l.txlog2, colred); break;
-        case 2: norms_partial_body<4>(J, jobs.ws, chunk, l.txlog2, colred); break;
-        default: norms_partial_body<8>(J, jobs.ws, chunk, l.txlog2, colred); break;
+        case 0: norms_partial_body<1, WHOLE>(J, ws, chunk, l.txlog2, colred, rows_lds, thr); break;
+        case 1: norms_partial_body<2, WHOLE>(J, ws, chunk, l.txlog2, colred, rows_lds, thr); break;
+        case 2: norms_partial_body<4, WHOLE>(J, ws, chunk, l.txlog2, colred, rows_lds, thr); break;
+        default: norms_partial_body<8, WHOLE>(J, ws, chunk, l.txlog2, colred, rows_lds, thr); break;
     }
+}
+__global__ __launch_bounds__(kThreads) void k_group_norms_partial_vec(const NormJobs jobs) {
+    __shared__ float colred[4][1024];
+    int chunk = blockIdx.x;
+    const NormJob& J = norm_job(jobs, jobs.first, chunk);
+    norms_partial<false>(J, jobs.ws, chunk, colred, nullptr, 0.f);
+}
+__global__ __launch_bounds__(kThreads) void k_group_norms_partial_vec_one(const NormJob1 job) {
+    __shared__ float colred[4][1024];
+    norms_partial<false>(job.j, job.ws, blockIdx.x, colred, nullptr, 0.f);
+}
+// A layer of one chunk (up to 16 K elements): norms, masks and bf16 copy in one launch of one workgroup.
+__global__ __launch_bounds__(kThreads) void k_group_norms_whole(const NormJob1 job) {
+    __shared__ float colred[4][1024];
+    __shared__ float rows_lds[kNormMaxChunkRows];
+    norms_partial<true>(job.j, nullptr, 0, colred, rows_lds, job.thr);
 }
 
 // Element-wise path (rows that are not 16-byte aligned): one element per lane and column group, one row at a time.
 __global__ __launch_bounds__(kThreads) void k_group_norms_partial_elem(const NormJobs jobs) {
     constexpr int kColsPerThread = kMaxC / 64;
     __shared__ float colred[kThreads];
-    const int ji = job_of_block(jobs.first, blockIdx.x);
-    const NormJob& J = jobs.j[ji];
-    const int chunk = blockIdx.x - jobs.first[ji];
+    int chunk = blockIdx.x;
+    const NormJob& J = norm_job(jobs, jobs.first, chunk);
     const int tid = threadIdx.x;
     int txlog2 = 0;
     while ((1 << txlog2) < J.C && txlog2 < 6) ++txlog2;
@@ -280,37 +332,53 @@ __global__ __launch_bounds__(kThreads) void k_group_norms_partial_elem(const Nor
     }
 }
 
-// Sixteen lanes per group (K filters, then C input channels of each job): the lanes stride over the R*S row
-// sums of a filter / the per-chunk partials of a channel, then a fixed shuffle tree adds the 16 lane sums.
-// The order of additions depends only on the shapes, so results are run-to-run identical.  Jobs with mask
-// pointers also get their zero masks here: zero[g] = (norm[g] < thr), the comparison of pt_zero_groups.
-constexpr int kFinLanes = 16, kFinGroups = kThreads / kFinLanes;
-__global__ __launch_bounds__(kThreads) void k_group_norms_finish(const NormJobs jobs) {
-    const int ji = job_of_block(jobs.fin, blockIdx.x);
-    const NormJob& J = jobs.j[ji];
-    const float* __restrict__ rowsq = jobs.ws + J.ws_off;
+// The second level: first the K filters of a job, a thread each (their R*S row sums are contiguous), then its C input
+// channels, 32 of them to a workgroup, whose per-chunk partials eight groups of lanes add (chunks g, g + 8, ...) and the
+// eight sums in ascending order.  Eight loads in flight: bound by their latency (ResNet-50, 53 layers, 3 MB: 8.2 us with
+// sixteen lanes on a group, each reading 16 of a 64-byte segment, 4.8 us so).  The order of additions depends only on
+// the shapes, so results are run-to-run identical.  Jobs with mask pointers also get their zero masks here.
+constexpr int kFinCols = 32, kFinSlices = kThreads / kFinCols;
+__host__ __device__ inline int64_t fin_blocks_of(int K, int C) { return (K + kThreads - 1) / kThreads + (C + kFinCols - 1) / kFinCols; }
+// Sum of p[i * stride], i = first, first + step, ... < n; loads past the end repeat the last one and are left out.
+__device__ __forceinline__ float sum_strided(const float* __restrict__ p, int64_t stride, int first, int step, int n) {
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int i = first; i < n; i += 8 * step) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = p[(int64_t)min(i + u * step, n - 1) * stride];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s[u & 3] += i + u * step < n ? v[u] : 0.f;
+    }
+    return (s[0] + s[1]) + (s[2] + s[3]);
+}
+__device__ __forceinline__ void norms_finish(const NormJob& J, const float* __restrict__ ws, float thr, int block, float (*red)[kFinCols]) {
+    const float* __restrict__ rowsq = ws + J.ws_off;
     const float* __restrict__ colpart = rowsq + (int64_t)J.K * J.RS;
-    const int l = threadIdx.x & (kFinLanes - 1);
-    const int g = (blockIdx.x - jobs.fin[ji]) * kFinGroups + (threadIdx.x / kFinLanes);
-    const bool live = g < J.K + J.C;
-    float s = 0.f;
-    if (live && g < J.K) {
-        for (int t = l; t < J.RS; t += kFinLanes) s += rowsq[(size_t)g * J.RS + t];
-    } else if (live) {
-        const int c = g - J.K;
-        for (int b = l; b < J.n_chunks; b += kFinLanes) s += colpart[(size_t)b * J.C + c];
+    const int row_blocks = (J.K + kThreads - 1) / kThreads, tid = threadIdx.x;
+    if (block < row_blocks) {  // uniform
+        const int k = block * kThreads + tid;
+        if (k < J.K) store_norm(J.out_norm, J.zero_out, k, sum_strided(rowsq + (int64_t)k * J.RS, 1, 0, 1, J.RS), thr);
+        return;
     }
-    for (int off = kFinLanes / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (live && l == 0) {
-        const float nrm = sqrtf(s);
-        if (g < J.K) {
-            J.out_norm[g] = nrm;
-            if (J.zero_out) J.zero_out[g] = nrm < jobs.thr ? 1 : 0;
-        } else {
-            J.in_norm[g - J.K] = nrm;
-            if (J.zero_in) J.zero_in[g - J.K] = nrm < jobs.thr ? 1 : 0;
-        }
+    const int l = tid % kFinCols, g = tid / kFinCols, c = (block - row_blocks) * kFinCols + l;
+    red[g][l] = c < J.C ? sum_strided(colpart + c, J.C, g, kFinSlices, J.n_chunks) : 0.f;
+    __syncthreads();
+    if (g == 0 && c < J.C) {
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < kFinSlices; ++i) s += red[i][l];
+        store_norm(J.in_norm, J.zero_in, c, s, thr);
     }
+}
+__global__ __launch_bounds__(kThreads) void k_group_norms_finish(const NormJobs jobs) {
+    __shared__ float red[kFinSlices][kFinCols];
+    int block = blockIdx.x;
+    const NormJob& J = norm_job(jobs, jobs.fin, block);
+    norms_finish(J, jobs.ws, jobs.thr, block, red);
+}
+__global__ __launch_bounds__(kThreads) void k_group_norms_finish_one(const NormJob1 job) {
+    __shared__ float red[kFinSlices][kFinCols];
+    norms_finish(job.j, job.ws, job.thr, blockIdx.x, red);
 }
 
 // UPDATE = false: dw += lambda * d(penalty)/dw.   UPDATE = true: the optimizer step with the regulariser folded in,
@@ -318,11 +386,10 @@ __global__ __launch_bounds__(kThreads) void k_group_norms_finish(const NormJobs 
 struct StepParams {
     float lr, mu, wd;
 };
-template <int VEC, bool UPDATE>
-__global__ __launch_bounds__(kThreads) void k_group_lasso_grad(const LassoJobs jobs, float lambda, StepParams sp) {
-    const int ji = job_of_block(jobs.first, blockIdx.x);
-    const LassoJob& J = jobs.j[ji];
-    const int chunk = blockIdx.x - jobs.first[ji];
+template <int VEC, bool UPDATE, typename JOBS>
+__global__ __launch_bounds__(kThreads) void k_group_lasso_grad(const JOBS jobs, float lambda, StepParams sp) {
+    int chunk = blockIdx.x;
+    const LassoJob& J = lasso_job(jobs, chunk);
     const int tid = threadIdx.x;
     const int TX = 1 << J.txlog2, TY = kThreads >> J.txlog2;
     const int tx = tid & (TX - 1), ty = tid >> J.txlog2;
@@ -412,7 +479,6 @@ static ChunkPlan plan_chunks(int64_t rows, int C, bool vec) {
 
 // Vector norms pass: a workgroup streams whole batches of TY * U rows (256 threads x eight 16-byte loads, 8 K
 // elements when every lane has a column), kNormBatches of them per chunk.
-constexpr int kNormBatches = 2;
 static ChunkPlan plan_norm_chunks(int64_t rows, int C) {
     const NormLayout l = norm_layout(C);
     const int batch_rows = (kThreads >> l.txlog2) * (8 >> l.cglog2);
@@ -465,6 +531,21 @@ int32_t launch_norms(const NormLayer* layers, int n, void* ws, size_t ws_bytes, 
         int64_t blocks = 0, fin_blocks = 0;
         auto flush = [&]() -> int32_t {
             if (jobs.n == 0) return PT_OK;
+            if (jobs.n == 1 && want_vec) {  // a layer by itself
+                const NormJob1 one{jobs.j[0], jobs.ws, jobs.thr};
+                if (one.j.n_chunks == 1) {
+                    hipLaunchKernelGGL(k_group_norms_whole, dim3(1), dim3(kThreads), 0, st, one);
+                } else {
+                    hipLaunchKernelGGL(k_group_norms_partial_vec_one, dim3((unsigned)blocks), dim3(kThreads), 0, st, one);
+                    const int32_t rc = launch_status();
+                    if (rc != PT_OK) return rc;
+                    hipLaunchKernelGGL(k_group_norms_finish_one, dim3((unsigned)fin_blocks), dim3(kThreads), 0, st, one);
+                }
+                jobs.n = 0;
+                blocks = 0;
+                fin_blocks = 0;
+                return launch_status();
+            }
             end_table(jobs.first, jobs.n);
             end_table(jobs.fin, jobs.n);
             if (want_vec) hipLaunchKernelGGL(k_group_norms_partial_vec, dim3((unsigned)blocks), dim3(kThreads), 0, st, jobs);
@@ -497,7 +578,7 @@ int32_t launch_norms(const NormLayer* layers, int n, void* ws, size_t ws_bytes, 
                 J.K = L.K; J.RS = L.RS; J.C = L.C; J.cpitch = L.cpitch;
                 J.n_chunks = cp.n_chunks; J.rows_per_chunk = cp.rows_per_chunk;
                 blocks += cp.n_chunks;
-                fin_blocks += ceil_div((int64_t)L.K + L.C, kFinGroups);
+                fin_blocks += fin_blocks_of(L.K, L.C);
                 if (jobs.n == kMaxJobs) {
                     const int32_t rc = flush();
                     if (rc != PT_OK) return rc;
@@ -625,14 +706,16 @@ static int32_t launch_lasso(const LassoLayer* layers, int n, bool update, float 
         auto flush = [&]() -> int32_t {
             if (jobs.n == 0) return PT_OK;
             end_table(jobs.first, jobs.n);
-            if (want_vec && update)
-                hipLaunchKernelGGL((k_group_lasso_grad<4, true>), dim3(blocks), dim3(kThreads), 0, st, jobs, lambda, sp);
+            if (want_vec && jobs.n == 1 && !update)  // a layer by itself
+                hipLaunchKernelGGL((k_group_lasso_grad<4, false, LassoJob1>), dim3(blocks), dim3(kThreads), 0, st, LassoJob1{jobs.j[0]}, lambda, sp);
+            else if (want_vec && update)
+                hipLaunchKernelGGL((k_group_lasso_grad<4, true, LassoJobs>), dim3(blocks), dim3(kThreads), 0, st, jobs, lambda, sp);
             else if (want_vec)
-                hipLaunchKernelGGL((k_group_lasso_grad<4, false>), dim3(blocks), dim3(kThreads), 0, st, jobs, lambda, sp);
+                hipLaunchKernelGGL((k_group_lasso_grad<4, false, LassoJobs>), dim3(blocks), dim3(kThreads), 0, st, jobs, lambda, sp);
             else if (update)
-                hipLaunchKernelGGL((k_group_lasso_grad<1, true>), dim3(blocks), dim3(kThreads), 0, st, jobs, lambda, sp);
+                hipLaunchKernelGGL((k_group_lasso_grad<1, true, LassoJobs>), dim3(blocks), dim3(kThreads), 0, st, jobs, lambda, sp);
             else
-                hipLaunchKernelGGL((k_group_lasso_grad<1, false>), dim3(blocks), dim3(kThreads), 0, st, jobs, lambda, sp);
+                hipLaunchKernelGGL((k_group_lasso_grad<1, false, LassoJobs>), dim3(blocks), dim3(kThreads), 0, st, jobs, lambda, sp);
             jobs.n = 0;
             blocks = 0;
             return launch_status();

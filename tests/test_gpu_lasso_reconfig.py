@@ -700,3 +700,19 @@ def test_sweep_refused_for_an_empty_edge_leaves_the_outputs():
     torch.cuda.synchronize()
     assert e.value.status == -2 and m.new_counts.tolist() == [19, 0]
     assert all((t == 3.0).all() for t in outs)
+
+
+@pytest.mark.parametrize("shape", [(64, 4, 4, 16), (205, 5, 1, 16), (114, 3, 3, 16), (4096, 1, 1, 4), (511, 2, 1, 5), (1, 1, 1, 1),
+                                   (32, 1, 1, 256), (33, 1, 1, 256), (4, 2, 2, 2048), (700, 3, 3, 200)])
+def test_norms_of_a_layer_by_itself(shape):
+    """One chunk (norms finished by the workgroup that reads the layer), one row more, and many chunks: against the oracle, and
+    bit for bit the same however often they are taken."""
+    from gpu_util import F32_TOL, pitch8, rel_err
+    w = np.random.Generator(np.random.PCG64(sum(shape))).standard_normal(shape, dtype=np.float32) * np.float32(0.05)
+    w[0] = 0.0
+    pitch = pitch8(shape[-1])
+    _, on, inn, _ = _norms_gpu(w, pitch, shadow=True)
+    ron, rin = oracle.group_norms(w)
+    assert rel_err(on.cpu().numpy(), ron) <= F32_TOL and rel_err(inn.cpu().numpy(), rin) <= F32_TOL and on[0].item() == 0.0
+    _, on2, inn2, _ = _norms_gpu(w, pitch)
+    assert torch.equal(on, on2) and torch.equal(inn, inn2)
