@@ -333,7 +333,7 @@ extern "C" int32_t pt_conv_fwd(const pt_conv_desc* d, const uint16_t* x, const u
     if (res3_fwd_ok(d, x, w, y)) {  // early 3 x 3 layer: the filter bank stays in LDS
         const int cinp = (int)round_up(d->C, 8);
         Res3Args r{x, w, y, d->N, d->H, d->W, d->C, cinp, d->x_cpitch, d->K, d->w_cpitch, d->y_cpitch, 0, 0, 0, 0, 0, 0, 0};
-        return hip_status(launch_conv3x3_res(r, false, (hipStream_t)stream));
+        return hip_status(launch_conv3x3_res(r, kRes3Fwd, (hipStream_t)stream));
     }
     IgemmArgs a = make_fwd_args(d, x, w, y);
     const bool vec = d->x_cpitch % 8 == 0 && d->w_cpitch % 8 == 0 && aligned16(x) && aligned16(w);
@@ -393,7 +393,7 @@ static int32_t bwd_data_classes(const pt_conv_desc* d, const uint16_t* dy, const
     if (res3_bwd_ok(d, dy, wt, dx)) {  // the same kernel on dy with the k-innermost filter copy and mirrored taps
         const int kp = (int)round_up(d->K, 8);
         Res3Args r{dy, wt, dx, d->N, d->H, d->W, d->K, kp, d->y_cpitch, d->C, kp, d->x_cpitch, 0, 0, 0, 0, 0, 0, 0};
-        return hip_status(launch_conv3x3_res(r, true, st));
+        return hip_status(launch_conv3x3_res(r, kRes3Bwd, st));
     }
     // A filter no larger than the stride reaches only some stride-parity classes of input pixels.  When class
     // (0, 0) is the only one with taps, its launch also clears the other classes (they tile into cells anchored at
@@ -565,6 +565,10 @@ extern "C" int32_t pt_conv_bwd_data(const pt_conv_desc* d, const uint16_t* dy, c
     hipStream_t st = (hipStream_t)stream;
     const int RS = d->R * d->S;
     const int kpitch = (int)round_up(d->K, 8);
+    if (res3_bwd_ok(d, dy, w, dx) && d->w_cpitch % 8 == 0) {  // transposes the filter bank itself
+        Res3Args r{dy, w, dx, d->N, d->H, d->W, d->K, kpitch, d->y_cpitch, d->C, d->w_cpitch, d->x_cpitch, 0, 0, 0, 0, 0, 0, 0};
+        return hip_status(launch_conv3x3_res(r, kRes3BwdKrsc, st));
+    }
     uint16_t* wt = (uint16_t*)ws;
     hipLaunchKernelGGL(k_transpose_w, dim3((unsigned)ceil_div(d->C, 32), (unsigned)ceil_div(kpitch, 32), RS), dim3(256),
                        0, st, w, d->K, RS, d->C, d->w_cpitch, wt, kpitch);

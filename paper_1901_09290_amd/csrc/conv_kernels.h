@@ -2193,6 +2193,7 @@ struct Res3Args {
     uint32_t pw_magic;                       // divides by the patch's width (fast_div)
     int tiles_x, tiles_y, tiles, run;
     FastDiv x_div, y_div, bx_div;            // by tiles_x, tiles_y, nbx
+    FastDiv cj_div;                          // by the 8-channel chunks of the output (KRSC)
 };
 constexpr int kR3TH = 4, kR3MaxNB = 7, kR3Waves = 8, kR3PatchPixels = (kR3TH + 2) * (8 * kR3MaxNB + 2);
 constexpr int kR3WRow = 9 * 128 + 16, kR3WBytes = 64 * kR3WRow;
@@ -2205,7 +2206,11 @@ static_assert(kR3Lds <= 160 * 1024 && (64 * (kR3WRow / 16)) % 64 == 0, "LDS plan
 // Compile-time so that the 9 * NCB steps of a tile are one straight line of code: with a branch per step every fragment
 // read is waited out before its MFMA (27 us against 34 us for the implicit-GEMM kernel on 56 x 56 x 64 -> 64;
 // straight-line with the reads of step s + 1 issued before the MFMAs of step s: see the numbers in the notes).
-template <bool FLIP, int NCB, bool KB1>
+// KRSC (input gradient only): Wt is the layer's own filter bank [Cin = K][9][wp] with the output channel of this launch
+// innermost, and the bank is transposed on its way into LDS: the loads of a workgroup's share all in flight, its 16-byte
+// rows written as 2-byte elements.  A small layer is spared the launch that makes the k-innermost copy (16 x 16 channels,
+// 16 x 16, batch 4: input gradient 2.6 + 4.1 us in two launches -> 4.4 us).
+template <bool FLIP, int NCB, bool KB1, bool KRSC = false>
 __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr uint32_t kBufOut = 0xffffffffu, kBufFlags = 0x00020000u;
@@ -2222,7 +2227,33 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
     if (first >= last) return;  // whole workgroup
 
     // ---- filter bank -> LDS, once ---------------------------------------------------------------------------------
-    {
+    if constexpr (KRSC) {
+        constexpr int ROWS = KB1 ? 64 : 32, ITEMS = 16 * NCB * 9 * (ROWS / 8), IT = (ITEMS + 511) / 512;
+        const int ncj = (a.Mout + 7) >> 3, items = a.Cin * 9 * ncj;
+        uint4 v[IT];
+        int k9[IT], cj[IT];
+#pragma unroll
+        for (int i = 0; i < IT; ++i) {
+            const int it = min(tid + 512 * i, items - 1);
+            k9[i] = (int)fdiv((uint32_t)it, a.cj_div);  // k * 9 + tap
+            cj[i] = it - k9[i] * ncj;
+            v[i] = *reinterpret_cast<const uint4*>(a.Wt + k9[i] * a.wp + cj[i] * 8);
+        }
+        // channels past the reduction's last one multiply zeros
+        for (int sl = tid; sl < ROWS * WSLOTS; sl += 512) *reinterpret_cast<uint4*>(wl + sl * 16) = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < IT; ++i) {
+            if (tid + 512 * i < items) {
+                const int k = (int)__umulhi((uint32_t)k9[i], 0x1c71c71du), t = k9[i] - k * 9;  // (exact below 2^29)
+                uint16_t* dst = reinterpret_cast<uint16_t*>(wl + cj[i] * 8 * kR3WRow + t * 128 + k * 2);
+                const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+                for (int e = 0; e < 8; ++e) dst[e * (kR3WRow / 2)] = (uint16_t)(w[e >> 1] >> ((e & 1) * 16));
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): written before the first tile's barrier
+    } else {
         const __amdgpu_buffer_rsrc_t w_srd = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint16_t*>(a.Wt), 0, (uint32_t)(a.Mout * 9 * a.wp) * 2u, kBufFlags);
 #pragma unroll
@@ -2396,7 +2427,8 @@ inline int64_t r3_tile(Res3Args& a) {
     return cols * a.tiles_y;
 }
 
-inline hipError_t launch_conv3x3_res(Res3Args& a, bool flip, hipStream_t st) {
+enum Res3Kind { kRes3Fwd = 0, kRes3Bwd = 1, kRes3BwdKrsc = 2 };
+inline hipError_t launch_conv3x3_res(Res3Args& a, Res3Kind kind, hipStream_t st) {
     const int64_t tiles = r3_tile(a);
     if (tiles <= 0 || tiles > 0x3fffffff) return hipErrorInvalidValue;
     a.tiles = (int)tiles;
@@ -2404,18 +2436,23 @@ inline hipError_t launch_conv3x3_res(Res3Args& a, bool flip, hipStream_t st) {
     a.x_div = make_fastdiv((int64_t)a.tiles_x);
     a.y_div = make_fastdiv((int64_t)a.tiles_y);
     a.bx_div = make_fastdiv((int64_t)a.nbx);
+    a.cj_div = make_fastdiv((a.Mout + 7) / 8);
     const unsigned grid = (unsigned)((tiles + a.run - 1) / a.run);
     typedef void (*kern_t)(const Res3Args);
-    static const kern_t kerns[2][4][2] = {
+    static const kern_t kerns[3][4][2] = {
         {{k_conv3x3_res<false, 1, false>, k_conv3x3_res<false, 1, true>}, {k_conv3x3_res<false, 2, false>, k_conv3x3_res<false, 2, true>},
          {k_conv3x3_res<false, 3, false>, k_conv3x3_res<false, 3, true>}, {k_conv3x3_res<false, 4, false>, k_conv3x3_res<false, 4, true>}},
         {{k_conv3x3_res<true, 1, false>, k_conv3x3_res<true, 1, true>}, {k_conv3x3_res<true, 2, false>, k_conv3x3_res<true, 2, true>},
-         {k_conv3x3_res<true, 3, false>, k_conv3x3_res<true, 3, true>}, {k_conv3x3_res<true, 4, false>, k_conv3x3_res<true, 4, true>}}};
-    static LdsOptIn opt_in[2][4][2];
+         {k_conv3x3_res<true, 3, false>, k_conv3x3_res<true, 3, true>}, {k_conv3x3_res<true, 4, false>, k_conv3x3_res<true, 4, true>}},
+        {{k_conv3x3_res<true, 1, false, true>, k_conv3x3_res<true, 1, true, true>},
+         {k_conv3x3_res<true, 2, false, true>, k_conv3x3_res<true, 2, true, true>},
+         {k_conv3x3_res<true, 3, false, true>, k_conv3x3_res<true, 3, true, true>},
+         {k_conv3x3_res<true, 4, false, true>, k_conv3x3_res<true, 4, true, true>}}};
+    static LdsOptIn opt_in[3][4][2];
     const int ncb = (a.CinP + 15) / 16, kb1 = a.Mout > 32 ? 1 : 0;
     if (ncb < 1 || ncb > 4) return hipErrorInvalidValue;
-    const kern_t kern = kerns[flip ? 1 : 0][ncb - 1][kb1];
-    if (hipError_t e = opt_in[flip ? 1 : 0][ncb - 1][kb1].ensure(reinterpret_cast<const void*>(kern), kR3Lds); e != hipSuccess) return e;
+    const kern_t kern = kerns[kind][ncb - 1][kb1];
+    if (hipError_t e = opt_in[kind][ncb - 1][kb1].ensure(reinterpret_cast<const void*>(kern), kR3Lds); e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(512), kR3Lds, st, a);
     return hipSuccess;
 }

@@ -539,3 +539,27 @@ def test_weight_gradient_rows_past_the_direct_kernels_addressing():
     """A dw row of more than 2^22 elements (a wide pitch): the register-staged kernel takes the layer."""
     spec = _spec(2, 9, 9, 24, 3, 1, 1, 0)
     _check_full(spec, 1100, 24, 8, (1 << 22) + 8)
+
+
+@pytest.mark.parametrize("C,K,pad_zero", [(8, 8, False), (64, 48, False), (16, 64, False), (48, 64, False), (40, 24, False),
+                                          (9, 17, True), (33, 56, True), (63, 45, True), (1, 64, True), (64, 3, True)])
+@pytest.mark.parametrize("extra", [0, 8])
+def test_early_3x3_input_gradient_transposes_the_filter_bank_itself(C, K, pad_zero, extra):
+    """pt_conv_bwd_data, where the kernel reads the filter bank as it is, against the same kernel on the k-innermost copy: bit
+    for bit; NaN in the filters' channel padding reaches nothing, the workspace is not needed for the result."""
+    from gpu_util import DEV, dev_bf16, host_bf16, pitch8, workspace
+    from paper_1901_09290_amd import binding as B
+    spec = _spec(3, 14, 19, C, K, 3, 1, 1)
+    t = wl.conv_tensors(spec, np.random.Generator(np.random.PCG64(C * 64 + K)), want=("dy", "w"))
+    xp, yp, wp = pitch8(C), pitch8(K), pitch8(C) + extra
+    d = B.desc_of(spec, xp, yp, wp, B.CONV_PAD_ZERO if pad_zero else 0)
+    dy, w = dev_bf16(t["dy"], yp, pad=0) if pad_zero else dev_bf16(t["dy"], yp), dev_bf16(t["w"], wp)
+    wt = torch.zeros((C, 9, yp), dtype=torch.bfloat16, device=DEV)
+    B.weights_to_crsk_batched([B.layer_crsk(w, wt, K, 9, C, wp)])
+    dx = [torch.zeros((3, 14, 19, xp), dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+    B.conv_bwd_data(d, dy, w, dx[0], workspace(B.conv_bwd_data_workspace_bytes(d)))
+    B.conv_bwd_data_crsk(d, dy, wt, dx[1])
+    torch.cuda.synchronize()
+    a, b = (host_bf16(v, C) for v in dx)
+    assert np.isfinite(a).all() and np.array_equal(a, b)
+
