@@ -655,6 +655,31 @@ def test_planned_compaction_reads_the_counts_on_the_device(C, keep_n):
     assert torch.equal(vo[:keep_n], v[sel]) and (vo[keep_n:] == 7).all()
 
 
+@pytest.mark.parametrize("sizes", [[(1, 40), (40000, 264), (1, 8), (7, 2048), (9, 2048), (3000, 2048), (2, 16), (20000, 104)],
+                                   [(100, 1000 + 8 * i) for i in range(60)]])
+def test_activation_gather_over_many_tensors(sizes):
+    """Runs of a launch's tensors are handed out with a fixed stride: a workgroup's next run may lie several tensors on,
+    or in a tensor of less than one run (8 rows of 4 KB, an odd count of them, a single row)."""
+    from gpu_util import DEV
+    jobs, want = [], []
+    for i, (pixels, C) in enumerate(sizes):
+        gen = np.random.Generator(np.random.PCG64(i))
+        n = max(1, C * 2 // 3)
+        idx = torch.from_numpy(np.sort(gen.choice(C, n, replace=False)).astype(np.int32)).to(DEV)
+        x = torch.randint(-32768, 32767, (pixels, C), dtype=torch.int16, device=DEV)
+        out = torch.full((pixels, (n + 7) // 8 * 8 + 8), 7, dtype=torch.int16, device=DEV)
+        cnt = torch.tensor([n], dtype=torch.int32, device=DEV)
+        jobs.append(B.planned_nhwc(x.view(torch.bfloat16), pixels, C, C, idx, cnt, out.view(torch.bfloat16)))
+        want.append((x, idx, out, n, cnt))
+    B.compact_planned(jobs)
+    torch.cuda.synchronize()
+    for x, idx, out, n, _ in want:
+        op, pixels = (n + 7) // 8 * 8, x.shape[0]
+        got = out.view(-1)[: pixels * op].view(pixels, op)
+        assert torch.equal(got[:, :n], x[:, idx.long()]) and not got[:, n:].any()
+        assert (out.view(-1)[pixels * op:] == 7).all()
+
+
 @pytest.mark.parametrize("n_counts,zero_at", [(1, 0), (1, None), (64, 63), (65, 64), (130, 127), (130, None), (0, None)])
 def test_guarded_compaction_writes_all_or_nothing(n_counts, zero_at):
     """One count of 0 anywhere (before, at and past the 64 that one load covers) keeps all three kinds of gather from
