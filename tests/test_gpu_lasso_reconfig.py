@@ -530,6 +530,31 @@ def test_apply_zero_bit_exact():
                 assert np.isnan(got[..., C:]).all()                            # padding untouched
 
 
+@pytest.mark.parametrize("n", [2, 11])
+def test_optimizer_step_of_many_layers_equals_the_layers_one_by_one(n):
+    """A launch of more than 256 MB of w, dw and mom takes a form of its own: bit for bit what calls of one layer (26 MB)
+    leave, padding untouched (rows that end inside a vector included)."""
+    from gpu_util import DEV
+    K, RS, lam, lr, mu, wd = 650, 9, 1e-3, 0.1, 0.9, 1e-4
+    calls = {}
+    for single in (True, False):
+        jobs = calls.setdefault(single, ([], []))
+        gen = torch.Generator(device=DEV).manual_seed(n)
+        for i in range(n):
+            C, pitch = 369 + i, 376 if i < 8 else 384
+            t = [torch.randn((K, RS, pitch), device=DEV, generator=gen) for _ in range(3)]
+            for x in t:
+                x[..., C:] = 7.0
+            norms = [torch.rand(k, device=DEV, generator=gen) + 0.5 for k in (K, C)]
+            jobs[0].append((t, norms))
+            jobs[1].append(B.layer_update(*t, *norms, K, RS, C, pitch, 3))
+        for part in [[j] for j in jobs[1]] if single else [jobs[1]]:
+            B.sgd_momentum_lasso_batched(part, lam, lr, mu, wd)
+    torch.cuda.synchronize()
+    for (one, _), (many, _) in zip(calls[True][0], calls[False][0]):
+        assert all(torch.equal(a, b) for a, b in zip(one, many))
+
+
 def test_optimizer_step_matches_oracle():
     """One launch updates several layers (vector and element-wise loaders, padded pitches, first-layer
     exemption): weights and momentum against the fp64 oracle at 1e-5; dw and pitch padding untouched; a second
