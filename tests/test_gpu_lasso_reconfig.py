@@ -766,3 +766,24 @@ def test_norms_of_a_layer_by_itself(shape):
     assert rel_err(on.cpu().numpy(), ron) <= F32_TOL and rel_err(inn.cpu().numpy(), rin) <= F32_TOL and on[0].item() == 0.0
     _, on2, inn2, _ = _norms_gpu(w, pitch)
     assert torch.equal(on, on2) and torch.equal(inn, inn2)
+
+
+@pytest.mark.parametrize("shape", [(513, 1, 1, 16), (4096, 1, 1, 16), (4097, 1, 1, 16), (128, 1, 1, 300), (129, 1, 1, 300),
+                                   (17, 1, 1, 300), (33, 1, 1, 300), (8, 1, 1, 2048), (9, 1, 1, 2048)])
+def test_norms_around_the_sizes_where_the_chunks_change(shape):
+    """Chunks of one batch of rows up to eight batches, of two batches beyond: by itself and in a call of several layers,
+    against the oracle and each other."""
+    from gpu_util import DEV, F32_TOL, rel_err, workspace
+    K, R, S, C = shape
+    w = np.random.Generator(np.random.PCG64(K + C)).standard_normal(shape, dtype=np.float32)
+    pitch = (C + 7) // 8 * 8
+    wd, on, inn, _ = _norms_gpu(w, pitch, shadow=True)
+    ron, rin = oracle.group_norms(w)
+    assert rel_err(on.cpu().numpy(), ron) <= F32_TOL and rel_err(inn.cpu().numpy(), rin) <= F32_TOL
+    on2, inn2 = (torch.zeros((3, k), device=DEV) for k in (K, C))
+    layers = [B.layer_weights(wd, K, R * S, C, pitch, on2[i], inn2[i], None) for i in range(3)]
+    B.group_norms_batched(layers, workspace(B.group_norms_batched_workspace_bytes(layers)))
+    torch.cuda.synchronize()
+    for i in range(3):
+        assert rel_err(on2[i].cpu().numpy(), ron) <= F32_TOL and rel_err(inn2[i].cpu().numpy(), rin) <= F32_TOL
+        assert torch.equal(on2[i], on2[0]) and torch.equal(inn2[i], inn2[0])
