@@ -410,7 +410,7 @@ struct StepParams {
 // Bound by HBM and by how many loads are in flight: a thread sends out those of four rows before the first store (which the
 // compiler would otherwise not let a later row's loads pass), and walks filters and rows of a filter without divisions.
 // HINT: what goes past the caches; the gradient pass 0 = nothing, the optimizer step 1 = the loads of dw and mom, or, when w,
-// dw and mom of the launch do not fit the chip's last cache anyway, 2 = every access.  Norms, value and step, row by row
+// dw and mom of the call do not fit the chip's last cache anyway, 2 = every access.  Norms, value and step, row by row
 // without hints / four rows with 0 / 1 / 2: published ResNet-50 (282 MB) 141 / 133 / 140 / 125 us, pruned ones (113 MB)
 // 92.1 / 87.8 / 81.4 / 86.1 and 83.7 / 80.7 / 74.2 / 78.2, pruned ResNet-32 (2 MB) 31.0 / 30.3 / 30.5 / 30.8.  Two and eight
 // rows: 1 to 4 and 3 to 8 % slower.
@@ -486,13 +486,13 @@ struct ChunkPlan {
     int txlog2, rows_per_chunk, n_chunks;
 };
 
-// Gradient / optimizer pass and the element-wise norms pass: TX lanes across a row, about 16 K elements per workgroup.
-static ChunkPlan plan_chunks(int64_t rows, int C, bool vec) {
+// Gradient / optimizer pass and the element-wise norms pass: TX lanes across a row, about `elements` per workgroup.
+static ChunkPlan plan_chunks(int64_t rows, int C, bool vec, int elements = 16384) {
     const int Lv = vec ? (C + 3) / 4 : C;
     int l = 0;
     while ((1 << l) < Lv && l < 6) ++l;
     const int TY = kThreads >> l;
-    int64_t rpc = ceil_div(16384, C);
+    int64_t rpc = ceil_div(elements, C);
     rpc = round_up(rpc, TY);
     ChunkPlan p;
     p.txlog2 = l;
@@ -724,7 +724,22 @@ struct LassoLayer {
     int32_t K, RS, C, w_cpitch;
     uint32_t flags;
 };
+// Elements per workgroup of the gradient / optimizer pass over `total` elements: 1280 workgroups or more of 1 K (one round of
+// loads a thread: a small network's pass is a chain of them) to 16 K elements, or 32 K each where everything passes by the
+// caches.  Norms, value and step with 1 / 2 / 4 / 8 / 16 / 32 K: pruned ResNet-32 (0.15 M elements) 20.5 / 20.7 / 27 / 28 /
+// 31 / 26 us (4 K and 16 K also seen at 26), pruned ResNet-50 (9.4 M) 90.1 / 80.4 / 75.4 / 78.1 / 80.9 / 94.5, published
+// (23.5 M) 171 / 161 / 141 / 128.5 / 125.5 / 121.6.
+static bool past_caches(int64_t elements) { return elements * 12 > kInfinityCacheBytes; }  // w, dw, mom
+static int lasso_chunk(int64_t total, bool update) {
+    if (update && past_caches(total)) return 32768;
+    int chunk = 1024;
+    while (chunk < 16384 && total / (2 * chunk) >= 1280) chunk *= 2;
+    return chunk;
+}
 static int32_t launch_lasso(const LassoLayer* layers, int n, bool update, float lambda, StepParams sp, hipStream_t st) {
+    int64_t total = 0;
+    for (int i = 0; i < n; ++i) total += (int64_t)layers[i].K * layers[i].RS * layers[i].w_cpitch;
+    const int chunk = lasso_chunk(total, update);
     for (int pass = 0; pass < 2; ++pass) {
         const bool want_vec = pass == 0;
         LassoJobs jobs;
@@ -736,9 +751,7 @@ static int32_t launch_lasso(const LassoLayer* layers, int n, bool update, float 
             if (want_vec && jobs.n == 1 && !update)  // a layer by itself
                 hipLaunchKernelGGL((k_group_lasso_grad<4, false, LassoJob1>), dim3(blocks), dim3(kThreads), 0, st, LassoJob1{jobs.j[0]}, lambda, sp);
             else if (want_vec && update) {
-                int64_t bytes = 0;
-                for (int i = 0; i < jobs.n; ++i) bytes += (int64_t)jobs.j[i].K * jobs.j[i].RS * jobs.j[i].cpitch * 12;
-                const auto kern = bytes > kInfinityCacheBytes ? k_group_lasso_grad<4, true, LassoJobs, 2> : k_group_lasso_grad<4, true, LassoJobs, 1>;
+                const auto kern = past_caches(total) ? k_group_lasso_grad<4, true, LassoJobs, 2> : k_group_lasso_grad<4, true, LassoJobs, 1>;
                 hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), 0, st, jobs, lambda, sp);
             }
             else if (want_vec)
@@ -756,7 +769,7 @@ static int32_t launch_lasso(const LassoLayer* layers, int n, bool update, float 
             const bool vec = (L.w_cpitch % 4 == 0) && (((uintptr_t)L.w & 15) == 0) && (((uintptr_t)L.dw & 15) == 0) &&
                              (!update || ((uintptr_t)L.mom & 15) == 0);
             if (vec != want_vec) continue;
-            const ChunkPlan cp = plan_chunks((int64_t)L.K * L.RS, L.C, vec);
+            const ChunkPlan cp = plan_chunks((int64_t)L.K * L.RS, L.C, vec, chunk);
             jobs.first[jobs.n] = blocks;
             LassoJob& J = jobs.j[jobs.n++];
             J.w = L.w; J.out_norm = L.out_norm; J.in_norm = L.in_norm; J.dw = L.dw; J.mom = L.mom;

@@ -787,3 +787,25 @@ def test_norms_around_the_sizes_where_the_chunks_change(shape):
     for i in range(3):
         assert rel_err(on2[i].cpu().numpy(), ron) <= F32_TOL and rel_err(inn2[i].cpu().numpy(), rin) <= F32_TOL
         assert torch.equal(on2[i], on2[0]) and torch.equal(inn2[i], inn2[0])
+
+
+@pytest.mark.parametrize("C,total", [(300, 2 << 20), (300, 3 << 20), (300, 6 << 20), (300, 12 << 20), (2045, 3 << 20), (5, 1 << 20)])
+def test_optimizer_step_for_every_chunk_size(C, total):
+    """One layer in chunks of 1 K to 16 K elements by its size: against the plain update in float64 at the tolerance of the
+    oracle's test, dw untouched."""
+    from gpu_util import DEV, F32_TOL
+    RS, lam, lr, mu, wd = 3, 1e-3, 0.1, 0.9, 1e-4
+    pitch = (C + 7) // 8 * 8
+    K = total // (RS * pitch) + 1
+    gen = torch.Generator(device=DEV).manual_seed(C)
+    w, dw, mom = (torch.randn((K, RS, pitch), device=DEV, generator=gen) for _ in range(3))
+    on, inn = (torch.rand(k, device=DEV, generator=gen) + 0.5 for k in (K, C))
+    W, G, M = (t[..., :C].double() for t in (w, dw, mom))
+    dw0 = dw.clone()
+    M = mu * M + G + wd * W + lam * W * (1.0 / on.double()[:, None, None] + 1.0 / inn.double())
+    W = W - lr * M
+    B.sgd_momentum_lasso_batched([B.layer_update(w, dw, mom, on, inn, K, RS, C, pitch, 3)], lam, lr, mu, wd)
+    torch.cuda.synchronize()
+    for got, ref in ((w, W), (mom, M)):
+        assert ((got[..., :C].double() - ref).norm() / ref.norm()).item() <= F32_TOL
+    assert torch.equal(dw, dw0)
