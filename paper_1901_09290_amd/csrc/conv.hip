@@ -30,22 +30,59 @@
 
 namespace pt {
 
-// w[K][RS][wpitch] -> wt[C][RS][kpitch]  (bf16), for the input-gradient GEMM.
-__global__ void k_transpose_w(const uint16_t* __restrict__ w, int K, int RS, int C, int wpitch,
-                              uint16_t* __restrict__ wt, int kpitch) {
-    __shared__ uint16_t tile[32][33];
-    const int rs = blockIdx.z;
-    const int k0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-    for (int i = ty; i < 32; i += 8) {
-        const int k = k0 + i, c = c0 + tx;
-        tile[i][tx] = (k < K && c < C) ? w[((int64_t)k * RS + rs) * wpitch + c] : (uint16_t)0;
+// w[K][RS][wpitch] -> wt[C][RS][kpitch]  (bf16), for the input-gradient GEMM.  A workgroup takes 64 filters x 64 channels of
+// one tap: whole 128-byte lines in and out, 16 bytes a lane, through LDS rows of 33 dwords.  Bound by HBM and by the launch:
+// the copies of ResNet-50 (47 MB in, 47 MB out) 46.7 us as 32 x 32 tiles with two bytes a lane, 20.3 so; pruned 22.3 and 13.
+constexpr int kTrTile = 64, kTrPitch = 66;
+__device__ __forceinline__ void transpose_tile(const uint16_t* __restrict__ w, uint16_t* __restrict__ wt, int K, int RS, int C,
+                                               int wpitch, int kpitch, int k0, int c0, int rs, uint16_t* tile) {
+    const bool vec_in = wpitch % 8 == 0 && ((uintptr_t)w & 15) == 0, vec_out = ((uintptr_t)wt & 15) == 0;  // uniform
+    const int row = threadIdx.x >> 3, at = (threadIdx.x & 7) * 8;
+    uint16_t v[2][8];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int k = k0 + row + 32 * i, c = c0 + at;
+        uint4 q = make_uint4(0u, 0u, 0u, 0u);
+        if (k < K && c < C) {
+            const uint16_t* src = w + ((int64_t)k * RS + rs) * wpitch + c;
+            if (vec_in && c + 8 <= C) {
+                q = *reinterpret_cast<const uint4*>(src);
+            } else {
+                uint32_t h[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) h[e] = c + e < C ? src[e] : 0u;
+                q = make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
+            }
+        }
+        const uint32_t d[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[i][e] = (uint16_t)(d[e >> 1] >> (16 * (e & 1)));
     }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) tile[(at + e) * kTrPitch + row + 32 * i] = v[i][e];
     __syncthreads();
-    for (int i = ty; i < 32; i += 8) {
-        const int c = c0 + i, k = k0 + tx;
-        if (c < C && k < kpitch) wt[((int64_t)c * RS + rs) * kpitch + k] = tile[tx][i];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int cl = row + 32 * i, c = c0 + cl, k = k0 + at;
+        if (c >= C || k >= kpitch) continue;  // (kpitch is a multiple of 8)
+        const uint32_t* src = reinterpret_cast<const uint32_t*>(tile + cl * kTrPitch + at);
+        const uint4 q = make_uint4(src[0], src[1], src[2], src[3]);
+        uint16_t* dst = wt + ((int64_t)c * RS + rs) * kpitch + k;
+        if (vec_out) {
+            *reinterpret_cast<uint4*>(dst) = q;
+        } else {
+            const uint32_t d[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) dst[e] = (uint16_t)(d[e >> 1] >> (16 * (e & 1)));
+        }
     }
+}
+__global__ __launch_bounds__(256) void k_transpose_w(const uint16_t* __restrict__ w, int K, int RS, int C, int wpitch,
+                                                     uint16_t* __restrict__ wt, int kpitch) {
+    __shared__ __attribute__((aligned(16))) uint16_t tile[kTrTile * kTrPitch];
+    transpose_tile(w, wt, K, RS, C, wpitch, kpitch, blockIdx.y * kTrTile, blockIdx.x * kTrTile, blockIdx.z, tile);
 }
 
 // The same transposition for many layers in one launch (descriptors in the kernel arguments).
@@ -53,36 +90,22 @@ constexpr int kMaxTransposeJobs = 64;
 struct TransposeJob {
     const uint16_t* w;
     uint16_t* wt;
-    int K, RS, C, wpitch, kpitch, blk0, nbx, nby;
+    int K, RS, C, wpitch, kpitch, nbx, nby, pad;
 };
 struct TransposeJobs {
     TransposeJob j[kMaxTransposeJobs];
+    int first[kMaxTransposeJobs];  // first workgroup of each job
     int n;
 };
 __global__ __launch_bounds__(256) void k_transpose_w_multi(const TransposeJobs jobs) {
-    __shared__ uint16_t tile[32][33];
-    int lo = 0, hi = jobs.n - 1;  // last job whose blk0 <= blockIdx.x
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (jobs.j[mid].blk0 <= (int)blockIdx.x) lo = mid;
-        else hi = mid - 1;
-    }
-    const TransposeJob& jb = jobs.j[lo];
-    int b = blockIdx.x - jb.blk0;
+    __shared__ __attribute__((aligned(16))) uint16_t tile[kTrTile * kTrPitch];
+    const int ji = job_of_block(jobs.first, blockIdx.x);
+    const TransposeJob jb = jobs.j[ji];
+    int b = blockIdx.x - jobs.first[ji];
     const int bx = b % jb.nbx;
     b /= jb.nbx;
     const int by = b % jb.nby, rs = b / jb.nby;
-    const int k0 = by * 32, c0 = bx * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int i = ty; i < 32; i += 8) {
-        const int k = k0 + i, c = c0 + tx;
-        tile[i][tx] = (k < jb.K && c < jb.C) ? jb.w[((int64_t)k * jb.RS + rs) * jb.wpitch + c] : (uint16_t)0;
-    }
-    __syncthreads();
-    for (int i = ty; i < 32; i += 8) {
-        const int c = c0 + i, k = k0 + tx;
-        if (c < jb.C && k < jb.kpitch) jb.wt[((int64_t)c * jb.RS + rs) * jb.kpitch + k] = tile[tx][i];
-    }
+    transpose_tile(jb.w, jb.wt, jb.K, jb.RS, jb.C, jb.wpitch, jb.kpitch, by * kTrTile, bx * kTrTile, rs, tile);
 }
 
 // Zero the destination pixels of a stride-parity class that no output pixel reaches.  One thread clears
@@ -570,7 +593,7 @@ extern "C" int32_t pt_conv_bwd_data(const pt_conv_desc* d, const uint16_t* dy, c
         return hip_status(launch_conv3x3_res(r, kRes3BwdKrsc, st));
     }
     uint16_t* wt = (uint16_t*)ws;
-    hipLaunchKernelGGL(k_transpose_w, dim3((unsigned)ceil_div(d->C, 32), (unsigned)ceil_div(kpitch, 32), RS), dim3(256),
+    hipLaunchKernelGGL(k_transpose_w, dim3((unsigned)ceil_div(d->C, kTrTile), (unsigned)ceil_div(kpitch, kTrTile), RS), dim3(256),
                        0, st, w, d->K, RS, d->C, d->w_cpitch, wt, kpitch);
     rc = launch_status();
     if (rc != PT_OK) return rc;
@@ -619,6 +642,7 @@ extern "C" int32_t pt_weights_to_crsk_batched(const pt_layer_crsk* layers, int32
     int64_t blocks = 0;
     auto flush = [&]() -> int32_t {
         if (t.n == 0) return PT_OK;
+        end_table(t.first, t.n);
         hipLaunchKernelGGL(k_transpose_w_multi, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, t);
         t.n = 0;
         blocks = 0;
@@ -627,13 +651,14 @@ extern "C" int32_t pt_weights_to_crsk_batched(const pt_layer_crsk* layers, int32
     for (int i = 0; i < n; ++i) {
         const pt_layer_crsk& l = layers[i];
         const int kpitch = (int)round_up(l.K, 8);
-        const int nbx = (int)ceil_div(l.C, 32), nby = (int)ceil_div(kpitch, 32);
+        const int nbx = (int)ceil_div(l.C, kTrTile), nby = (int)ceil_div(kpitch, kTrTile);
         const int64_t nb = (int64_t)nbx * nby * l.RS;
         if (blocks + nb > 0x3fffffff) {
             const int32_t rc = flush();
             if (rc != PT_OK) return rc;
         }
-        t.j[t.n++] = TransposeJob{l.w, l.wt, l.K, l.RS, l.C, l.w_cpitch, kpitch, (int)blocks, nbx, nby};
+        t.first[t.n] = (int)blocks;
+        t.j[t.n++] = TransposeJob{l.w, l.wt, l.K, l.RS, l.C, l.w_cpitch, kpitch, nbx, nby, 0};
         blocks += nb;
         if (t.n == kMaxTransposeJobs) {
             const int32_t rc = flush();

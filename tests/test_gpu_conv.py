@@ -359,6 +359,30 @@ def test_cfg2_resnet32_distinct_layers_full_tensor():
               flush=True)
 
 
+@pytest.mark.parametrize("K,RS,C,pitch,shift_in,shift_out", [
+    (1, 1, 1, 8, 0, 0), (8, 9, 8, 8, 0, 0), (63, 2, 65, 72, 0, 0), (64, 3, 64, 64, 0, 0), (65, 1, 63, 64, 0, 0), (200, 1, 136, 136, 0, 0),
+    (71, 2, 37, 40, 0, 0), (130, 9, 70, 70, 0, 0), (66, 1, 129, 131, 0, 0), (64, 1, 72, 72, 1, 0), (64, 2, 72, 72, 0, 1), (9, 4, 77, 80, 3, 5)])
+def test_transposed_weight_copy(K, RS, C, pitch, shift_in, shift_out):
+    """Edges of the 64 x 64 tiles, rows that are no multiple of 16 bytes and buffers that do not start on one (`shift`, in
+    elements), as the middle one of three jobs: exact, padding of k zero, nothing else written."""
+    import torch
+    from gpu_util import DEV
+    from paper_1901_09290_amd import binding as B
+    kp = (K + 7) // 8 * 8
+    src = torch.randint(-32768, 32767, (K * RS * pitch + shift_in,), dtype=torch.int16, device=DEV)
+    dst = torch.full((3, C * RS * kp + shift_out + 8), 7, dtype=torch.int16, device=DEV)
+    w = src[shift_in:]
+    job = lambda i: B.layer_crsk(w.view(torch.bfloat16), dst[i, shift_out:].view(torch.bfloat16), K, RS, C, pitch)
+    B.weights_to_crsk_batched([job(0), job(1), job(2)])
+    torch.cuda.synchronize()
+    want = torch.zeros((C, RS, kp), dtype=torch.int16, device=DEV)
+    want[..., :K] = w.view(K, RS, pitch)[..., :C].permute(2, 1, 0)
+    for i in range(3):
+        got = dst[i, shift_out:]
+        assert torch.equal(got[: want.numel()].view(want.shape), want)
+        assert (got[want.numel():] == 7).all() and (dst[i, :shift_out] == 7).all()
+
+
 @pytest.mark.parametrize("case", [(2, 15, 15, 40, 136, 3, 2, 1), (2, 10, 10, 37, 51, 3, 1, 1), (2, 16, 16, 64, 128, 1, 2, 0)])
 def test_bwd_data_from_pretransposed_weights(case):
     """pt_weights_to_crsk_batched + pt_conv_bwd_data_crsk: the transposed copy is an exact permutation
