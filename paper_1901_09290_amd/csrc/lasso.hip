@@ -144,10 +144,9 @@ __device__ __forceinline__ void store_norm(float* norm, uint8_t* zero, int i, fl
 // 16-byte loads in flight: 8 / CG rows at a time, CG column groups each.  Row sums: per thread over its columns,
 // then a shuffle tree over the TX lanes of the row.  Column sums: in registers over the rows a thread visits, then
 // over the rows of a wavefront by shuffles and over the four wavefronts through LDS, all in a fixed order.
-// WHOLE: the chunk is the whole layer; its row sums stay in LDS and the norms are finished here.
-template <int CG, bool WHOLE>
-__device__ __forceinline__ void norms_partial_body(const NormJob& J, float* __restrict__ ws, int chunk, int txlog2,
-                                                   float (*colred)[1024], float* rows_lds, float thr) {
+template <int CG>
+__device__ __forceinline__ void norms_partial_body(const NormJob& J, float* __restrict__ rowsq, float* __restrict__ colpart,
+                                                   int chunk, int txlog2, float (*colred)[1024]) {
     constexpr int U = 8 / CG;  // rows in flight per thread
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int TX = 1 << txlog2, TY = kThreads >> txlog2;
@@ -159,8 +158,6 @@ __device__ __forceinline__ void norms_partial_body(const NormJob& J, float* __re
     const int Lv = (C + 3) >> 2;
     const float* __restrict__ w = J.w;
     uint16_t* __restrict__ shadow = J.shadow;
-    float* __restrict__ rowsq = WHOLE ? rows_lds : ws + J.ws_off;
-    float* __restrict__ colpart = WHOLE ? nullptr : rowsq + rows;
 
     float acc[CG][4];
     bool col_ok[CG];
@@ -253,48 +250,36 @@ __device__ __forceinline__ void norms_partial_body(const NormJob& J, float* __re
         for (int f = tid; f < PER * TX * 4; f += kThreads) {
             const int c = rnd * PER * TX * 4 + f;
             if (c < C) {
-                const float sum = ((colred[0][f] + colred[1][f]) + colred[2][f]) + colred[3][f];
-                if constexpr (WHOLE) store_norm(J.in_norm, J.zero_in, c, sum, thr);
-                else colpart[(size_t)chunk * C + c] = sum;
+                colpart[(size_t)chunk * C + c] = ((colred[0][f] + colred[1][f]) + colred[2][f]) + colred[3][f];
             }
-        }
-    }
-    if constexpr (WHOLE) {  // (the row sums are behind the barriers above)
-        for (int k = tid; k < J.K; k += kThreads) {
-            float sum = 0.f;
-            for (int t = 0; t < J.RS; ++t) sum += rowsq[k * J.RS + t];
-            store_norm(J.out_norm, J.zero_out, k, sum, thr);
         }
     }
 }
 
-template <bool WHOLE>
-__device__ __forceinline__ void norms_partial(const NormJob& J, float* ws, int chunk, float (*colred)[1024], float* rows_lds, float thr) {
+__device__ __forceinline__ void norms_partial(const NormJob& J, float* rowsq, float* colpart, int chunk, float (*colred)[1024]) {
     const NormLayout l = norm_layout(J.C);
     switch (l.cglog2) {  // uniform
-        case 0: norms_partial_body<1, WHOLE>(J, ws, chunk, l.txlog2, colred, rows_lds, thr); break;
-        case 1: norms_partial_body<2, WHOLE>(J, ws, chunk, l.txlog2, colred, rows_lds, thr); break;
-        case 2: norms_partial_body<4, WHOLE>(J, ws, chunk, l.txlog2, colred, rows_lds, thr); break;
-        default: norms_partial_body<8, WHOLE>(J, ws, chunk, l.txlog2, colred, rows_lds, thr); break;
+        case 0: norms_partial_body<1>(J, rowsq, colpart, chunk, l.txlog2, colred); break;
+        case 1: norms_partial_body<2>(J, rowsq, colpart, chunk, l.txlog2, colred); break;
+        case 2: norms_partial_body<4>(J, rowsq, colpart, chunk, l.txlog2, colred); break;
+        default: norms_partial_body<8>(J, rowsq, colpart, chunk, l.txlog2, colred); break;
     }
+}
+// The same with this job's scratch in the workspace.
+__device__ __forceinline__ void norms_partial(const NormJob& J, float* ws, int chunk, float (*colred)[1024]) {
+    float* rowsq = ws + J.ws_off;
+    norms_partial(J, rowsq, rowsq + (int64_t)J.K * J.RS, chunk, colred);
 }
 __global__ __launch_bounds__(kThreads) void k_group_norms_partial_vec(const NormJobs jobs) {
     __shared__ float colred[4][1024];
     int chunk = blockIdx.x;
     const NormJob& J = norm_job(jobs, jobs.first, chunk);
-    norms_partial<false>(J, jobs.ws, chunk, colred, nullptr, 0.f);
+    norms_partial(J, jobs.ws, chunk, colred);
 }
 __global__ __launch_bounds__(kThreads) void k_group_norms_partial_vec_one(const NormJob1 job) {
     __shared__ float colred[4][1024];
-    norms_partial<false>(job.j, job.ws, blockIdx.x, colred, nullptr, 0.f);
+    norms_partial(job.j, job.ws, blockIdx.x, colred);
 }
-// A layer of up to two batches (16 K elements): norms, masks and bf16 copy in one launch of one workgroup.
-__global__ __launch_bounds__(kThreads) void k_group_norms_whole(const NormJob1 job) {
-    __shared__ float colred[4][1024];
-    __shared__ float rows_lds[kNormMaxChunkRows];
-    norms_partial<true>(job.j, nullptr, 0, colred, rows_lds, job.thr);
-}
-
 // Element-wise path (rows that are not 16-byte aligned): one element per lane and column group, one row at a time.
 __global__ __launch_bounds__(kThreads) void k_group_norms_partial_elem(const NormJobs jobs) {
     constexpr int kColsPerThread = kMaxC / 64;
@@ -400,6 +385,27 @@ __global__ __launch_bounds__(kThreads) void k_group_norms_finish(const NormJobs 
 __global__ __launch_bounds__(kThreads) void k_group_norms_finish_one(const NormJob1 job) {
     __shared__ float red[kFinSlices][kFinCols];
     norms_finish(job.j, job.ws, job.thr, blockIdx.x, red);
+}
+// A layer of up to two chunks (16 K elements): norms, masks and bf16 copy in one launch of one workgroup, with the row sums
+// and column partials in LDS.  The additions are those of the two launches (a chunk's partial is its slice's only one, so the
+// slices in ascending order are the chunks in ascending order), and a layer has the same norms, bit for bit, by itself and
+// among others: a group at the threshold of a detection cannot be zero by one route only.
+static_assert(kNormBatches <= kFinSlices, "one chunk a slice");
+__global__ __launch_bounds__(kThreads) void k_group_norms_whole(const NormJob1 job) {
+    __shared__ float colred[4][1024];
+    __shared__ float rowsq[kNormMaxChunkRows], colpart[kNormBatches * kMaxC];
+    const NormJob& J = job.j;
+    for (int chunk = 0; chunk < J.n_chunks; ++chunk) {
+        norms_partial(J, rowsq, colpart, chunk, colred);
+        __syncthreads();
+    }
+    for (int c = threadIdx.x; c < J.C; c += kThreads) {
+        float s = colpart[c];
+        if (J.n_chunks > 1) s += colpart[J.C + c];
+        store_norm(J.in_norm, J.zero_in, c, s, job.thr);
+    }
+    for (int k = threadIdx.x; k < J.K; k += kThreads)
+        store_norm(J.out_norm, J.zero_out, k, sum_strided(rowsq + k * J.RS, 1, 0, 1, J.RS), job.thr);
 }
 
 // UPDATE = false: dw += lambda * d(penalty)/dw.   UPDATE = true: the optimizer step with the regulariser folded in,
@@ -559,8 +565,7 @@ int32_t launch_norms(const NormLayer* layers, int n, void* ws, size_t ws_bytes, 
             if (jobs.n == 0) return PT_OK;
             if (jobs.n == 1 && want_vec) {  // a layer by itself
                 NormJob1 one{jobs.j[0], jobs.ws, jobs.thr};
-                if (one.j.n_chunks <= kNormBatches) {  // (the layers that one chunk of two batches holds)
-                    one.j.rows_per_chunk *= one.j.n_chunks;
+                if (one.j.n_chunks <= kNormBatches) {  // a few chunks of one batch
                     hipLaunchKernelGGL(k_group_norms_whole, dim3(1), dim3(kThreads), 0, st, one);
                 } else {
                     hipLaunchKernelGGL(k_group_norms_partial_vec_one, dim3((unsigned)blocks), dim3(kThreads), 0, st, one);

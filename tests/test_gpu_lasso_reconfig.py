@@ -789,6 +789,35 @@ def test_norms_around_the_sizes_where_the_chunks_change(shape):
         assert torch.equal(on2[i], on2[0]) and torch.equal(inn2[i], inn2[0])
 
 
+@pytest.mark.parametrize("shape,pitch", [((64, 3, 3, 16), 16), ((205, 5, 1, 16), 16), ((114, 3, 3, 16), 16), ((32, 3, 3, 61), 64),
+                                         ((33, 1, 1, 256), 256), ((8, 1, 1, 2047), 2048), ((129, 1, 1, 300), 304),
+                                         ((64, 3, 3, 128), 128), ((40, 3, 3, 21), 21)])
+def test_norms_of_one_layer_are_bit_for_bit_those_of_the_batched_call(shape, pitch):
+    """One to two chunks (one launch when the layer is by itself), more, and unaligned rows: norms taken alone, in a call of
+    three layers and by detection are the same bits, so a group at the threshold is zero by every route or by none."""
+    from gpu_util import DEV, workspace
+    K, R, S, C = shape
+    RS = R * S
+    w = np.random.Generator(np.random.PCG64(K * C)).standard_normal(shape, dtype=np.float32)
+    wd, on, inn, _ = _norms_gpu(w, pitch)
+    on3, inn3 = (torch.zeros((3, k), device=DEV) for k in (K, C))
+    layers = [B.layer_weights(wd, K, RS, C, pitch, on3[i], inn3[i], None) for i in range(3)]
+    B.group_norms_batched(layers, workspace(B.group_norms_batched_workspace_bytes(layers)))
+    torch.cuda.synchronize()
+    for i in range(3):
+        assert torch.equal(on3[i], on) and torch.equal(inn3[i], inn)
+    for thr in (float(on[K // 2]), float(inn[C // 2])):
+        for n in (1, 2):
+            on2, inn2 = (torch.zeros((n, k), device=DEV) for k in (K, C))
+            zo, zi = (torch.full((n, k), 7, dtype=torch.uint8, device=DEV) for k in (K, C))
+            jobs = [B.layer_detect(wd, K, RS, C, pitch, on2[i], inn2[i], zo[i], zi[i]) for i in range(n)]
+            B.group_norms_detect_batched(jobs, thr, workspace(B.group_norms_detect_batched_workspace_bytes(jobs)))
+            torch.cuda.synchronize()
+            for i in range(n):
+                assert torch.equal(on2[i], on) and torch.equal(inn2[i], inn)
+                assert torch.equal(zo[i], (on < thr).to(torch.uint8)) and torch.equal(zi[i], (inn < thr).to(torch.uint8))
+
+
 @pytest.mark.parametrize("C,total", [(300, 2 << 20), (300, 3 << 20), (300, 6 << 20), (300, 12 << 20), (2045, 3 << 20), (5, 1 << 20)])
 def test_optimizer_step_for_every_chunk_size(C, total):
     """One layer in chunks of 1 K to 16 K elements by its size: against the plain update in float64 at the tolerance of the
