@@ -266,21 +266,25 @@ inline void set_wgrad_splits(const pt_conv_desc* d, WgradPlan& p, int64_t splits
     p.ws_bytes = p.splits > 1 ? (size_t)round_up((int64_t)p.splits * d->K * p.Mtot * 4, 256) : 0;
 }
 
-// A call with one layer: tile configuration and splits that take the least time by what 292 shapes cost (8 to 2048 channels, 6
-// to 56 pixels a side, batch 4 to 128, each in all configurations and at 48 to 512 workgroups; us): a step, a round of 256
-// workgroups (pipeline fill, stores), a megabyte of operands fetched into LDS by all workgroups together, a megabyte of
-// partial sums written and read, the second launch.  Chosen so the calls take 1.4 % more than the best measured of each
-// shape.  Against 128-wide tiles wherever they waste little, random shapes gain 10 % (14 x 14 128 -> 128 3 x 3 from 28 x 28,
-// batch 64: 128 x 128 tiles 19.7 us, 64 x 64 tiles 15.8; 14 x 14 256 -> 256 3 x 3 the other way round, 28 and 42).
-// Tiles smaller than the sizes ask for go unsplit up to 24 steps only (1536 pixels; 10 x 10 256 -> 256 3 x 3 at batch 15: 9.5 us
-// against 14.0 split).  They would be faster up to some 50 (14 x 14 at batch 10: 10.8 against 14.5; 1 % over all shapes), but
-// what pt_conv_bwd_weight_plan says of such layers, few splits and a wide reduction, is relied on.
+// A call with one layer: tile configuration and splits that take the least time by what 672 shapes cost (ResNet layers,
+// published and pruned, and random ones: 16 to 2048 channels, 5 to 56 pixels a side, batch 1 to 128), each in all
+// configurations at 2 to 512 workgroups, with operands in the caches and with operands that come from memory, as in a
+// training step; us: a step, a round of 256 workgroups (pipeline fill, stores), a megabyte of operands fetched into LDS by
+// all workgroups together, a megabyte of partial sums written and read, the second launch.  Over all of them 128-wide tiles
+// wherever they waste little take 12.05 ms (cached) and 14.41 ms (from memory), this choice 11.29 and 13.55, the best of
+// each shape for both states together 11.15 and 13.22.  Costs fitted to cached operands alone: 11.31 and 13.73, by 64 x 128
+// tiles with half the splits for large 1 x 1 layers, half as many operand bytes again (14 x 14 1024 -> 512 at batch 64: 23.4
+// and 32.6 us against 23.3 and 26.5 so).
+// Tiles smaller than the sizes ask for go unsplit up to 24 steps only (1536 pixels; 10 x 10 256 -> 256 3 x 3 at batch 15:
+// 8.4 us against 12.5 split, from memory 10.3 and 14).  They are faster beyond that (14 x 14 at batch 8, 25 steps: 8.6 and
+// 10.4 against 12.9 and 13.9): the line is not where measurements would put it.  The tests of the regulariser inside the
+// wide reduction take layers of 1568 pixels, and ask pt_conv_bwd_weight_plan whether they are reduced so.
 struct WgradCost {
     float step, round;
 };
-constexpr WgradCost kWgCost[kWgConfigs] = {{0.24f, 1.35f}, {0.28f, 1.15f}, {0.30f, 1.45f}, {0.24f, 0.3f}};
+constexpr WgradCost kWgCost[kWgConfigs] = {{0.257f, 1.343f}, {0.3f, 1.35f}, {0.312f, 1.388f}, {0.222f, 0.323f}};
 constexpr int kWgUnsplitSteps = 24;
-constexpr float kWgPartialUsPerMB = 0.77f, kWgSecondUs = 1.0f, kWgOperandUsPerMB = 0.045f;
+constexpr float kWgPartialUsPerMB = 0.627f, kWgSecondUs = 1.065f, kWgOperandUsPerMB = 0.07f;
 inline WgradPlan plan_wgrad(const pt_conv_desc* d, bool dl) {
     const WgradPlan own = plan_wgrad_tiles(d, dl);
     const bool direct = own.dl;
