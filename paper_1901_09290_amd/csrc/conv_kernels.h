@@ -2205,7 +2205,11 @@ static_assert(kR3Lds <= 160 * 1024 && (64 * (kR3WRow / 16)) % 64 == 0, "LDS plan
 // KRSC (input gradient only): Wt is the layer's own filter bank [Cin = K][9][wp] with the output channel of this launch
 // innermost, and the bank is transposed on its way into LDS: the loads of a workgroup's share all in flight, its 16-byte
 // rows written as 2-byte elements.  A small layer is spared the launch that makes the k-innermost copy (16 x 16 channels,
-// 16 x 16, batch 4: input gradient 2.6 + 4.1 us in two launches -> 4.4 us).
+// 16 x 16, batch 4: input gradient 2.6 + 4.1 us in two launches -> 4.4 us), but every workgroup transposes the whole bank and
+// the 2-byte writes meet in the same LDS banks: up to 16 output channels it is 2 to 39 % faster for every K, beyond that 3 %
+// slower to 33 % faster up to K * C = 768 (counted in eights), 11 % faster to 27 % slower (8 % in the middle) up to 1280, 2 %
+// faster to 66 % slower (29 %) up to 2048, 24 to 124 % slower at 3072 (56 x 56, 33 -> 56 channels, batch 10: 10.1 us in two launches, 14.9 so).  Those take the two launches.
+constexpr int kR3KrscFewC = 16, kR3KrscMaxBank = 768, kR3KrscBank = 64 * kR3KrscFewC;  // the largest that either rule takes
 template <bool FLIP, int NCB, bool KB1, bool KRSC = false>
 __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -2224,7 +2228,7 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
 
     // ---- filter bank -> LDS, once ---------------------------------------------------------------------------------
     if constexpr (KRSC) {
-        constexpr int ROWS = KB1 ? 64 : 32, ITEMS = 16 * NCB * 9 * (ROWS / 8), IT = (ITEMS + 511) / 512;
+        constexpr int ROWS = KB1 ? 64 : 32, IT = (kR3KrscBank / 8 * 9 + 511) / 512;  // 8 channels of one filter's tap an item
         const int ncj = (a.Mout + 7) >> 3, items = a.Cin * 9 * ncj;
         uint4 v[IT];
         int k9[IT], cj[IT];
@@ -2423,6 +2427,7 @@ inline int64_t r3_tile(Res3Args& a) {
     return cols * a.tiles_y;
 }
 
+inline bool r3_krsc_bank_ok(int K, int C) { return C <= kR3KrscFewC || round_up(K, 8) * round_up(C, 8) <= kR3KrscMaxBank; }
 enum Res3Kind { kRes3Fwd = 0, kRes3Bwd = 1, kRes3BwdKrsc = 2 };
 inline hipError_t launch_conv3x3_res(Res3Args& a, Res3Kind kind, hipStream_t st) {
     const int64_t tiles = r3_tile(a);
@@ -2440,13 +2445,12 @@ inline hipError_t launch_conv3x3_res(Res3Args& a, Res3Kind kind, hipStream_t st)
          {k_conv3x3_res<false, 3, false>, k_conv3x3_res<false, 3, true>}, {k_conv3x3_res<false, 4, false>, k_conv3x3_res<false, 4, true>}},
         {{k_conv3x3_res<true, 1, false>, k_conv3x3_res<true, 1, true>}, {k_conv3x3_res<true, 2, false>, k_conv3x3_res<true, 2, true>},
          {k_conv3x3_res<true, 3, false>, k_conv3x3_res<true, 3, true>}, {k_conv3x3_res<true, 4, false>, k_conv3x3_res<true, 4, true>}},
-        {{k_conv3x3_res<true, 1, false, true>, k_conv3x3_res<true, 1, true, true>},
-         {k_conv3x3_res<true, 2, false, true>, k_conv3x3_res<true, 2, true, true>},
-         {k_conv3x3_res<true, 3, false, true>, k_conv3x3_res<true, 3, true, true>},
-         {k_conv3x3_res<true, 4, false, true>, k_conv3x3_res<true, 4, true, true>}}};
+        // (more than 32 output and more than 16 reduction channels are a larger bank)
+        {{k_conv3x3_res<true, 1, false, true>, k_conv3x3_res<true, 1, true, true>}, {k_conv3x3_res<true, 2, false, true>, nullptr},
+         {k_conv3x3_res<true, 3, false, true>, nullptr}, {k_conv3x3_res<true, 4, false, true>, nullptr}}};
     static LdsOptIn opt_in[3][4][2];
     const int ncb = (a.CinP + 15) / 16, kb1 = a.Mout > 32 ? 1 : 0;
-    if (ncb < 1 || ncb > 4) return hipErrorInvalidValue;
+    if (ncb < 1 || ncb > 4 || (kind == kRes3BwdKrsc && !r3_krsc_bank_ok(a.Cin, a.Mout))) return hipErrorInvalidValue;
     const kern_t kern = kerns[kind][ncb - 1][kb1];
     if (hipError_t e = opt_in[kind][ncb - 1][kb1].ensure(reinterpret_cast<const void*>(kern), kR3Lds); e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(512), kR3Lds, st, a);

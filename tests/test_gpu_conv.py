@@ -587,3 +587,32 @@ def test_early_3x3_input_gradient_transposes_the_filter_bank_itself(C, K, pad_ze
     a, b = (host_bf16(v, C) for v in dx)
     assert np.isfinite(a).all() and np.array_equal(a, b)
 
+
+
+@pytest.mark.parametrize("C,K,own", [(8, 64, True), (64, 8, True), (48, 16, True), (16, 64, True), (24, 32, True), (31, 23, True),
+                                     (17, 33, False), (32, 32, False), (33, 17, False), (33, 56, False), (63, 45, False)])
+def test_early_3x3_input_gradient_by_the_size_of_the_filter_bank(C, K, own):
+    """pt_conv_bwd_data transposes banks of up to 768 weights a tap (channel counts in eights), of up to 16 input channels all,
+    inside the kernel, leaving the workspace as it was, and the others, faster so, through a k-innermost copy in the workspace.  Two tiles a
+    workgroup; against the gradient in fp32 and, bit for bit, the call on a k-innermost copy."""
+    from gpu_util import CONV_TOL, DEV, dev_bf16, host_bf16, pitch8, rel_err, workspace
+    from paper_1901_09290_amd import binding as B
+    N, H = 80, 30
+    spec = _spec(N, H, H, C, K, 3, 1, 1)
+    t = wl.conv_tensors(spec, np.random.Generator(np.random.PCG64(C * 65 + K)), want=("dy", "w"))
+    xp, yp = pitch8(C), pitch8(K)
+    d = B.desc_of(spec, xp, yp, xp, B.CONV_PAD_ZERO)
+    dy, w = dev_bf16(t["dy"], yp, pad=0), dev_bf16(t["w"], xp)
+    ws = workspace(B.conv_bwd_data_workspace_bytes(d)).fill_(0x5A)
+    wt = torch.zeros((C, 9, yp), dtype=torch.bfloat16, device=DEV)
+    B.weights_to_crsk_batched([B.layer_crsk(w, wt, K, 9, C, xp)])
+    dx = [torch.zeros((N, H, H, xp), dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+    B.conv_bwd_data(d, dy, w, dx[0], ws)
+    B.conv_bwd_data_crsk(d, dy, wt, dx[1])
+    torch.cuda.synchronize()
+    assert bool((ws == 0x5A).all()) == own
+    a, b = (host_bf16(v, C) for v in dx)
+    assert np.array_equal(a, b)
+    ref = torch.nn.functional.conv_transpose2d(torch.from_numpy(t["dy"]).permute(0, 3, 1, 2),
+                                               torch.from_numpy(t["w"]).permute(0, 3, 1, 2), padding=1)
+    assert rel_err(a, ref.permute(0, 2, 3, 1).numpy()) <= CONV_TOL
