@@ -117,19 +117,23 @@ inline void igemm_fold(IgemmArgs& a) {
 }
 
 // Which kernel takes the problems of a call that fill less than one round of 128 x 128 tiles (`as`: one problem, or the
-// stride-parity classes of an input gradient, which share a launch).  Estimated times in us, least squares over 150 ResNet-50
-// shapes at batch 1 to 100, 96 to 224 pixels, published and pruned widths (chosen: 977 us in all, the best of the three for
-// each: 976, always one of them: 1199, 1131, 1930): up to 256 workgroups take `steps` steps of t1 and f1 for set-up and
-// stores, up to 512 (two on a CU, or one after the other) t2 and f2.  0 = k_igemm_dl at 128 x 64, 1 = k_igemm_small at
-// 64 x 64, 2 = at 32 x 32.
+// stride-parity classes of an input gradient, which share a launch).  Estimated times in us: up to 256 workgroups take `steps`
+// steps of t1 and f1 for set-up and stores, up to 512 (two on a CU, or one after the other) t2 and f2.  Fitted to 1591 calls
+// (ResNet layers at batch 1 to 256, published and pruned, and random shapes), each in all four forms, with operands in the
+// caches and from memory, so that few calls lose in either state.  Chosen: 14.24 ms cached and 16.65 from memory, the best
+// form for both states together 14.26 and 16.48, always one of them 18.4 / 17.4 / 26.6 / 21.2 and 23.6 / 22.2 / 27.3 / 24.7.
+// 0 = k_igemm_dl at 128 x 64, 1 = k_igemm_small at 64 x 64, 2 = at 32 x 32 in three stages (96 KB of LDS: one workgroup on the
+// CU), 3 = at 32 x 32 in two (64 KB: two on the CU, and room beside a weight gradient).  Without the last, more than 256
+// workgroups with long reductions lost up to 40 % (8 x 9 165 <- 1974 3 x 3 stride 2, batch 22: 23.6 -> 32.9 us, 38 -> 50).
 inline int pick_igemm_kernel(const IgemmArgs* as, int n) {
     struct Est { int bm, bn, nb; float t1, t2, f1, f2; };
-    constexpr Est est[3] = {{128, 64, 1, 0.30f, 0.52f, 0.54f, 1.05f},
-                            {64, 64, 1, 0.22f, 0.38f, 0.78f, 1.72f},
-                            {32, 32, 4, 0.50f, 0.98f, 1.05f, 4.39f}};
+    constexpr Est est[4] = {{128, 64, 1, 0.30f, 0.52f, 0.54f, 1.05f},
+                            {64, 64, 1, 0.22f, 0.43f, 0.77f, 1.72f},
+                            {32, 32, 4, 0.50f, 0.98f, 1.22f, 4.39f},
+                            {32, 32, 4, 0.72f, 0.70f, 0.76f, 3.47f}};
     int best = 0;
     float best_us = 1e30f;
-    for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < 4; ++k) {
         int64_t tiles = 0, tile_steps = 0, longest = 0;
         for (int i = 0; i < n; ++i) {
             const IgemmArgs& a = as[i];
@@ -152,7 +156,7 @@ inline int pick_igemm_kernel(const IgemmArgs* as, int n) {
     }
     return best;
 }
-constexpr int kIgemmLarge = 3;  // beyond pick_igemm_kernel's range: 128 x 128 tiles fill the chip
+constexpr int kIgemmLarge = 4;  // beyond pick_igemm_kernel's range: 128 x 128 tiles fill the chip
 inline bool igemm_small_ok(const IgemmArgs& a) {  // no undefined channel padding, no statistics epilogue, a bit per tap
     return !a.stats && a.TR * a.TSm < 32 && ((a.fold ? a.Creal : a.Cred) % 8 == 0 || a.pad_zero);
 }
@@ -178,7 +182,8 @@ inline hipError_t launch_igemm(IgemmArgs& a, bool vec, hipStream_t st, IgemmDlPl
     IgemmDlPlan own;
     IgemmDlPlan& p = plan ? *plan : own;
     hipError_t e;
-    if (kernel == 2) e = plan_igemm_small_cfg<32, 32, 4, 3>(a, p);
+    if (kernel == 3) e = plan_igemm_small_cfg<32, 32, 4, 2>(a, p);
+    else if (kernel == 2) e = plan_igemm_small_cfg<32, 32, 4, 3>(a, p);
     else if (kernel == 1) e = plan_igemm_small_cfg<64, 64, 1, 3>(a, p);
     // very many pixel tiles and a narrow output (the stem): tall tiles, so half as many workgroups pay set-up and fill
     else if (a.Nout <= 64 && tiles128 >= 4096 && !a.stats) e = plan_igemm_dl_cfg<256, 64, 4, 2, 2>(a, p);

@@ -1033,7 +1033,8 @@ inline hipError_t plan_igemm_dl_cfg(IgemmArgs& a, IgemmDlPlan& plan) {
 // 324 -> 263, 3 x 3, batch 10: 13.4 -> 11.2 us with the third stage; 14 x 14 655 -> 207, 1 x 1: 7.0 -> 6.4 us).  64 x 64 tiles
 // move half as much per flop as 32 x 32 and need 0.22 us a step with three stages (48 KB, three workgroups on the CU; five
 // and eight stages: 0.1 us longer for each, the longer body is fetched once more); 32 x 32 tiles, few and with long
-// reductions, 0.50 us for four steps with three stages (96 KB, one workgroup; two stages: 0.70 us, four: as three).
+// reductions, 0.50 us for four steps with three stages (96 KB, one workgroup on the CU; four stages the same), 0.70 us with two
+// (64 KB, two workgroups): the form for short reductions and for more tiles than CUs.
 template <int BM, int BN, int NB, int STAGES>
 __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problems) {
 #if defined(__HIP_DEVICE_COMPILE__)

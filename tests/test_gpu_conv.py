@@ -515,6 +515,18 @@ def test_batched_input_gradients_match_single_calls():
         assert torch.equal(a, b), s
 
 
+@pytest.mark.parametrize("case", [(2, 4, 4, 205, 56, 1, 1, 0), (3, 9, 9, 400, 70, 1, 1, 0), (2, 5, 6, 455, 15, 1, 1, 0),
+                                  (18, 21, 22, 210, 14, 5, 1, 2),    # forward: 260 tiles of 25 stages
+                                  # the four classes of an input gradient: one stage, two, 512 tiles of up to seven
+                                  (3, 6, 6, 25, 20, 3, 2, 1), (1, 8, 9, 68, 78, 3, 2, 1), (5, 14, 14, 500, 407, 3, 2, 1)])
+def test_small_tiles_in_two_stages(case):
+    """Tiles of 32 x 32 with two stages in LDS: reductions of one and two stages, and long ones where there are more tiles
+    than CUs."""
+    from gpu_util import pitch8
+    spec = _spec(*case)
+    _check_full(spec, 600 + sum(case), pitch8(spec.C), pitch8(spec.K), pitch8(spec.C), pad_zero=True)
+
+
 WGRAD_TILES = [
     # N   H   W   C    K   R st pad   tile      splits: one call alone, ragged in both channel counts, every tile form
     ((21, 6, 6, 89, 66, 3, 2, 1), (64, 64), (1, 1)),        # unsplit: the epilogue writes dw (and the regulariser)
