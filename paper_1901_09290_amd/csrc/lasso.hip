@@ -48,7 +48,7 @@ struct NormJobs {
 };
 static_assert(sizeof(NormJobs) <= 8192, "kernel-argument table");
 // One layer by itself: its kernel arguments are one read away instead of two, and the launch copies 96 bytes instead of 6 KB
-// (16 x 16 channels 3 x 3: group norms 6.0 us in two launches -> 3.6 in one, gradient 3.8 -> 3.1 us).
+// (16 x 16 channels 3 x 3: group norms 7.4 us in two launches -> 4.0 in one, gradient 3.8 -> 3.1 us).
 struct NormJob1 {
     NormJob j;
     float* ws;
@@ -140,15 +140,16 @@ __device__ __forceinline__ void store_norm(float* norm, uint8_t* zero, int i, fl
     if (zero) zero[i] = n < thr ? 1 : 0;  // the comparison of pt_zero_groups
 }
 
-// One workgroup = one chunk of whole rows of one layer (vector path: 16-byte aligned rows).  A thread keeps eight
+// kThreads threads (tid) = one chunk of whole rows of one layer (vector path: 16-byte aligned rows).  A thread keeps eight
 // 16-byte loads in flight: 8 / CG rows at a time, CG column groups each.  Row sums: per thread over its columns,
 // then a shuffle tree over the TX lanes of the row.  Column sums: in registers over the rows a thread visits, then
-// over the rows of a wavefront by shuffles and over the four wavefronts through LDS, all in a fixed order.
-template <int CG>
-__device__ __forceinline__ void norms_partial_body(const NormJob& J, float* __restrict__ rowsq, float* __restrict__ colpart,
-                                                   int chunk, int txlog2, float (*colred)[1024]) {
+// over the rows of a wavefront by shuffles and over the four wavefronts through LDS, all in a fixed order; put(c, sum)
+// takes them.  The row sums are behind the last barrier.
+template <int CG, typename PUT>
+__device__ __forceinline__ void norms_partial_body(const NormJob& J, float* __restrict__ rowsq, const PUT& put, int chunk,
+                                                   int txlog2, float (*colred)[1024], int tid) {
     constexpr int U = 8 / CG;  // rows in flight per thread
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     const int TX = 1 << txlog2, TY = kThreads >> txlog2;
     const int tx = tid & (TX - 1), ty = tid >> txlog2;
     const int64_t rows = (int64_t)J.K * J.RS;
@@ -249,26 +250,26 @@ __device__ __forceinline__ void norms_partial_body(const NormJob& J, float* __re
         // with fewer than 64 lanes per row every wavefront holds full sums of its own rows; all four are added
         for (int f = tid; f < PER * TX * 4; f += kThreads) {
             const int c = rnd * PER * TX * 4 + f;
-            if (c < C) {
-                colpart[(size_t)chunk * C + c] = ((colred[0][f] + colred[1][f]) + colred[2][f]) + colred[3][f];
-            }
+            if (c < C) put(c, ((colred[0][f] + colred[1][f]) + colred[2][f]) + colred[3][f]);
         }
     }
 }
 
-__device__ __forceinline__ void norms_partial(const NormJob& J, float* rowsq, float* colpart, int chunk, float (*colred)[1024]) {
+template <typename PUT>
+__device__ __forceinline__ void norms_partial(const NormJob& J, float* rowsq, const PUT& put, int chunk, float (*colred)[1024], int tid) {
     const NormLayout l = norm_layout(J.C);
     switch (l.cglog2) {  // uniform
-        case 0: norms_partial_body<1>(J, rowsq, colpart, chunk, l.txlog2, colred); break;
-        case 1: norms_partial_body<2>(J, rowsq, colpart, chunk, l.txlog2, colred); break;
-        case 2: norms_partial_body<4>(J, rowsq, colpart, chunk, l.txlog2, colred); break;
-        default: norms_partial_body<8>(J, rowsq, colpart, chunk, l.txlog2, colred); break;
+        case 0: norms_partial_body<1>(J, rowsq, put, chunk, l.txlog2, colred, tid); break;
+        case 1: norms_partial_body<2>(J, rowsq, put, chunk, l.txlog2, colred, tid); break;
+        case 2: norms_partial_body<4>(J, rowsq, put, chunk, l.txlog2, colred, tid); break;
+        default: norms_partial_body<8>(J, rowsq, put, chunk, l.txlog2, colred, tid); break;
     }
 }
-// The same with this job's scratch in the workspace.
+// The same by a workgroup, with this job's scratch in the workspace.
 __device__ __forceinline__ void norms_partial(const NormJob& J, float* ws, int chunk, float (*colred)[1024]) {
     float* rowsq = ws + J.ws_off;
-    norms_partial(J, rowsq, rowsq + (int64_t)J.K * J.RS, chunk, colred);
+    float* __restrict__ colpart = rowsq + (int64_t)J.K * J.RS + (int64_t)chunk * J.C;
+    norms_partial(J, rowsq, [=](int c, float sum) { colpart[c] = sum; }, chunk, colred, threadIdx.x);
 }
 __global__ __launch_bounds__(kThreads) void k_group_norms_partial_vec(const NormJobs jobs) {
     __shared__ float colred[4][1024];
@@ -387,25 +388,36 @@ __global__ __launch_bounds__(kThreads) void k_group_norms_finish_one(const NormJ
     norms_finish(job.j, job.ws, job.thr, blockIdx.x, red);
 }
 // A layer of up to two chunks (16 K elements): norms, masks and bf16 copy in one launch of one workgroup, with the row sums
-// and column partials in LDS.  The additions are those of the two launches (a chunk's partial is its slice's only one, so the
-// slices in ascending order are the chunks in ascending order), and a layer has the same norms, bit for bit, by itself and
-// among others: a group at the threshold of a detection cannot be zero by one route only.
+// and column partials in LDS and kThreads threads to a chunk, which all reach the same barriers (32 x 32 channels 3 x 3: 9.1 us
+// in two launches, 7.0 with one chunk after the other, 4.8 so).  The additions are those of the two launches (a chunk's partial is its slice's only
+// one, so the slices in ascending order are the chunks in ascending order), and a layer has the same norms, bit for bit, by
+// itself and among others: a group at the threshold of a detection cannot be zero by one route only.
 static_assert(kNormBatches <= kFinSlices, "one chunk a slice");
-__global__ __launch_bounds__(kThreads) void k_group_norms_whole(const NormJob1 job) {
-    __shared__ float colred[4][1024];
+__global__ __launch_bounds__(kThreads * kNormBatches) void k_group_norms_whole(const NormJob1 job) {
+    __shared__ float colred[kNormBatches][4][1024];
     __shared__ float rowsq[kNormMaxChunkRows], colpart[kNormBatches * kMaxC];
     const NormJob& J = job.j;
-    for (int chunk = 0; chunk < J.n_chunks; ++chunk) {
-        norms_partial(J, rowsq, colpart, chunk, colred);
-        __syncthreads();
+    const int chunk = __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads);  // blockDim.x = n_chunks * kThreads
+    auto put = [&](int c, float sum) {
+        if (J.n_chunks > 1) colpart[chunk * J.C + c] = sum;
+        else store_norm(J.in_norm, J.zero_in, c, sum, job.thr);
+    };
+    norms_partial(J, rowsq, put, chunk, colred[chunk], threadIdx.x % kThreads);
+    for (int k = threadIdx.x; k < J.K; k += blockDim.x) {
+        float s[4] = {0.f, 0.f, 0.f, 0.f};  // sum_strided's four sums, without its loads past the end
+        for (int t = 0; t < J.RS; ++t) {
+            const float v = rowsq[k * J.RS + t];
+            s[3] += (t & 3) == 3 ? v : 0.f;
+            s[2] += (t & 3) == 2 ? v : 0.f;
+            s[1] += (t & 3) == 1 ? v : 0.f;
+            s[0] += (t & 3) == 0 ? v : 0.f;
+        }
+        store_norm(J.out_norm, J.zero_out, k, (s[0] + s[1]) + (s[2] + s[3]), job.thr);
     }
-    for (int c = threadIdx.x; c < J.C; c += kThreads) {
-        float s = colpart[c];
-        if (J.n_chunks > 1) s += colpart[J.C + c];
-        store_norm(J.in_norm, J.zero_in, c, s, job.thr);
-    }
-    for (int k = threadIdx.x; k < J.K; k += kThreads)
-        store_norm(J.out_norm, J.zero_out, k, sum_strided(rowsq + k * J.RS, 1, 0, 1, J.RS), job.thr);
+    if (J.n_chunks == 1) return;
+    __syncthreads();
+    for (int c = threadIdx.x; c < J.C; c += blockDim.x)
+        store_norm(J.in_norm, J.zero_in, c, colpart[c] + colpart[J.C + c], job.thr);
 }
 
 // UPDATE = false: dw += lambda * d(penalty)/dw.   UPDATE = true: the optimizer step with the regulariser folded in,
@@ -566,7 +578,7 @@ int32_t launch_norms(const NormLayer* layers, int n, void* ws, size_t ws_bytes, 
             if (jobs.n == 1 && want_vec) {  // a layer by itself
                 NormJob1 one{jobs.j[0], jobs.ws, jobs.thr};
                 if (one.j.n_chunks <= kNormBatches) {  // a few chunks of one batch
-                    hipLaunchKernelGGL(k_group_norms_whole, dim3(1), dim3(kThreads), 0, st, one);
+                    hipLaunchKernelGGL(k_group_norms_whole, dim3(1), dim3(kThreads * one.j.n_chunks), 0, st, one);
                 } else {
                     hipLaunchKernelGGL(k_group_norms_partial_vec_one, dim3((unsigned)blocks), dim3(kThreads), 0, st, one);
                     const int32_t rc = launch_status();
