@@ -818,6 +818,32 @@ def test_norms_of_one_layer_are_bit_for_bit_those_of_the_batched_call(shape, pit
                 assert torch.equal(zo[i], (on < thr).to(torch.uint8)) and torch.equal(zi[i], (inn < thr).to(torch.uint8))
 
 
+def test_first_optimizer_step_inside_a_graph():
+    """A network whose first optimizer step is captured: every replay carries the momentum on, as eager steps do."""
+    from gpu_util import DEV
+    from paper_1901_09290_amd import harness as hz
+    specs, _ = wl.resnet32_layers(2, 8)
+    nets = [hz.Network(hz.build_network(specs[:5], seed=3)) for _ in range(2)]
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(4)
+    for l, m in zip(*(n.layers for n in nets)):
+        l.dw.normal_(generator=gen)
+        m.dw.copy_(l.dw)
+        l.out_norm.fill_(1.0), l.in_norm.fill_(1.0), m.out_norm.fill_(1.0), m.in_norm.fill_(1.0)
+    step = lambda net: net.optimizer_step(1e-4, 0.1, 0.9, 1e-4)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        step(nets[1])
+    for i in range(4):
+        step(nets[0])
+        graph.replay()
+        torch.cuda.synchronize()
+        for l, m, a, b in zip(nets[0].layers, nets[1].layers, nets[0].mom, nets[1].mom):
+            assert torch.equal(l.w_master, m.w_master) and torch.equal(a, b), i
+
+
 @pytest.mark.parametrize("C,total", [(300, 2 << 20), (300, 3 << 20), (300, 6 << 20), (300, 12 << 20), (2045, 3 << 20), (5, 1 << 20)])
 def test_optimizer_step_for_every_chunk_size(C, total):
     """One layer in chunks of 1 K to 16 K elements by its size: against the plain update in float64 at the tolerance of the
