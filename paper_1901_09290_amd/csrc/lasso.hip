@@ -13,6 +13,7 @@
 // Two levels, fixed order, no atomics: a workgroup owns whole rows of a chunk and writes one
 // sum-of-squares per row and one partial per column; the finish kernel adds the R*S row sums of each
 // filter and the per-chunk column partials in ascending order.
+#include <exception>
 #include <vector>
 #include "common.h"
 #include "norms.h"
@@ -680,6 +681,17 @@ __global__ __launch_bounds__(1024) void k_group_lasso_penalty(const PenaltyJobs 
 
 using namespace pt;
 
+// A host table of n layers; false where there is no memory for it (no exception leaves a C entry point).
+template <typename T>
+static bool make_table(std::vector<T>& v, int32_t n) {
+    try {
+        v.resize((size_t)n);
+    } catch (const std::exception&) {
+        return false;
+    }
+    return true;
+}
+
 extern "C" int32_t pt_group_norms_batched_workspace_bytes(const pt_layer_weights* layers, int32_t n, size_t* bytes) {
     if (!bytes || (n > 0 && !layers)) return PT_ERR_NULL;
     if (n < 0) return PT_ERR_SHAPE;
@@ -697,7 +709,8 @@ extern "C" int32_t pt_group_norms_batched(const pt_layer_weights* layers, int32_
     if (n < 0) return PT_ERR_SHAPE;
     if (n == 0) return PT_OK;
     if (!layers || !ws) return PT_ERR_NULL;
-    std::vector<NormLayer> v((size_t)n);
+    std::vector<NormLayer> v;
+    if (!make_table(v, n)) return PT_ERR_UNSUPPORTED;
     for (int i = 0; i < n; ++i) {
         const pt_layer_weights& L = layers[i];
         v[i] = NormLayer{L.w, L.out_norm, L.in_norm, L.w_shadow, nullptr, nullptr, L.K, L.RS, L.C, L.w_cpitch};
@@ -722,7 +735,8 @@ extern "C" int32_t pt_group_norms_detect_batched(const pt_layer_detect* layers, 
     if (n < 0) return PT_ERR_SHAPE;
     if (n == 0) return PT_OK;
     if (!layers || !ws) return PT_ERR_NULL;
-    std::vector<NormLayer> v((size_t)n);
+    std::vector<NormLayer> v;
+    if (!make_table(v, n)) return PT_ERR_UNSUPPORTED;
     for (int i = 0; i < n; ++i) {
         const pt_layer_detect& L = layers[i];
         if (!L.zero_out || !L.zero_in) return PT_ERR_NULL;
@@ -815,7 +829,8 @@ extern "C" int32_t pt_group_lasso_grad_batched(const pt_layer_lasso* layers, int
         if (L.K <= 0 || L.RS <= 0 || L.C <= 0 || L.w_cpitch < L.C) return PT_ERR_SHAPE;
         if (L.flags & ~3u) return PT_ERR_UNSUPPORTED;
     }
-    std::vector<LassoLayer> v((size_t)n);
+    std::vector<LassoLayer> v;
+    if (!make_table(v, n)) return PT_ERR_UNSUPPORTED;
     for (int i = 0; i < n; ++i) {
         const pt_layer_lasso& L = layers[i];
         v[i] = LassoLayer{L.w, L.out_norm, L.in_norm, L.dw, nullptr, L.K, L.RS, L.C, L.w_cpitch, L.flags};
@@ -834,7 +849,8 @@ extern "C" int32_t pt_sgd_momentum_lasso_batched(const pt_layer_update* layers, 
         if (L.K <= 0 || L.RS <= 0 || L.C <= 0 || L.w_cpitch < L.C) return PT_ERR_SHAPE;
         if (L.flags & ~3u) return PT_ERR_UNSUPPORTED;
     }
-    std::vector<LassoLayer> v((size_t)n);
+    std::vector<LassoLayer> v;
+    if (!make_table(v, n)) return PT_ERR_UNSUPPORTED;
     for (int i = 0; i < n; ++i) {
         const pt_layer_update& L = layers[i];
         v[i] = LassoLayer{L.w, L.out_norm, L.in_norm, const_cast<float*>(L.dw), L.mom, L.K, L.RS, L.C, L.w_cpitch, L.flags};

@@ -247,6 +247,19 @@ def test_batched_gradient_call_reports_a_plan_that_does_not_fit_memory():
     assert subprocess.run([sys.executable, "-c", code], cwd=ROOT).returncode == 0
 
 
+@pytest.mark.parametrize("name,args", [("pt_group_norms_batched", "C.c_void_p(4096), C.c_size_t(0)"),
+                                       ("pt_group_norms_detect_batched", "C.c_float(0), C.c_void_p(4096), C.c_size_t(0)")])
+def test_batched_norms_report_a_table_that_does_not_fit_memory(name, args):
+    """More layers than there is memory for: a status, not an exception that ends the process."""
+    code = ("import ctypes as C, resource\n"
+            "from paper_1901_09290_amd import binding as B\n"
+            f"f = B.lib().{name}\n"
+            "f.argtypes = None\n"
+            "resource.setrlimit(resource.RLIMIT_AS, (16 << 30, 16 << 30))\n"
+            f"assert f(C.c_void_p(4096), C.c_int32(1 << 30), {args}, None) == -4\n")
+    assert subprocess.run([sys.executable, "-c", code], cwd=ROOT).returncode == 0
+
+
 def test_crsk_calls_validate_on_the_host(lib):
     fake = 256
     assert lib.pt_weights_to_crsk_batched(None, 0, None) == 0
