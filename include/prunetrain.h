@@ -113,7 +113,8 @@ int32_t pt_conv_bwd_data(const pt_conv_desc* d, const uint16_t* dy, const uint16
 
 /* The input-gradient GEMM reduces over k, so it reads the filter bank with k innermost:
  *   wt[c][r][s][k] = w[k][r][s][c], bf16, k pitch = K rounded up to a multiple of 8 (padding written as 0).
- * pt_conv_bwd_data builds this copy in its workspace on every call.  A training step can instead convert
+ * pt_conv_bwd_data builds this copy in its workspace on every call (but for small 3 x 3 filter banks, which its kernel
+ * transposes itself).  A training step can instead convert
  * all layers once per iteration (the weights change once per iteration) with pt_weights_to_crsk_batched -
  * `layers` is a HOST array whose pointers are device pointers, wt 16-byte aligned - and call
  * pt_conv_bwd_data_crsk, which has the semantics of pt_conv_bwd_data and needs no workspace. */
@@ -149,7 +150,8 @@ int32_t pt_conv_bwd_weight(const pt_conv_desc* d, const uint16_t* x, const uint1
 #define PT_WGRAD_REDUCE_NONE 0 /* unsplit: no second pass (with the regulariser: added in the main kernel's epilogue, or
                                   by a pass over one slab when the main kernel cannot) */
 #define PT_WGRAD_REDUCE_DEEP 1 /* many slices over few outputs: one output per lane, slices spread over wavefronts */
-#define PT_WGRAD_REDUCE_WIDE 2 /* few slices over many outputs: four outputs per thread, slices in ascending order */
+#define PT_WGRAD_REDUCE_WIDE 2 /* few slices over many outputs: four outputs per thread; every first, second or fourth
+                                  slice is added in ascending order, then those one, two or four sums are */
 typedef struct pt_wgrad_plan_info {
     int32_t splits, tiles, reduce_kind, tile_m, tile_n;
 } pt_wgrad_plan_info;

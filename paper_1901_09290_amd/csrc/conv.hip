@@ -635,6 +635,7 @@ extern "C" int32_t pt_weights_to_crsk_batched(const pt_layer_crsk* layers, int32
         const pt_layer_crsk& l = layers[i];
         if (!l.w || !l.wt) return PT_ERR_NULL;
         if (l.K <= 0 || l.RS <= 0 || l.C <= 0 || l.w_cpitch < l.C) return PT_ERR_SHAPE;
+        // (tiles of 32 x 32: what one launch held with the kernel's former tiles, kept as the limit of a layer)
         if ((int64_t)ceil_div(l.C, 32) * ceil_div(round_up(l.K, 8), 32) * l.RS > 0x3fffffff) return PT_ERR_UNSUPPORTED;
     }
     TransposeJobs t;

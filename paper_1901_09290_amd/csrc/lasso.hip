@@ -755,11 +755,13 @@ struct LassoLayer {
     int32_t K, RS, C, w_cpitch;
     uint32_t flags;
 };
-// Elements per workgroup of the gradient / optimizer pass over `total` elements: 1280 workgroups or more of 1 K (one round of
-// loads a thread: a small network's pass is a chain of them) to 16 K elements, or 32 K each where everything passes by the
-// caches.  Norms, value and step with 1 / 2 / 4 / 8 / 16 / 32 K: pruned ResNet-32 (0.15 M elements) 20.5 / 20.7 / 27 / 28 /
-// 31 / 26 us (4 K and 16 K also seen at 26), pruned ResNet-50 (9.4 M) 90.1 / 80.4 / 75.4 / 78.1 / 80.9 / 94.5, published
-// (23.5 M) 171 / 161 / 141 / 128.5 / 125.5 / 121.6.
+// Elements per workgroup of the gradient / optimizer pass over `total` elements, which plan_chunks rounds up to as many rows as
+// a workgroup takes at a time (8 K elements at 2048 channels): the most of 1 to 16 K with which there are 1280 workgroups, or
+// 1 K (a small network's pass is a chain of rounds of loads, and at 1 K and 2 K a thread of a narrow layer has one and two
+// rows: of the four it loads, the others are its chunk's last one again), or 32 K where everything passes by the caches.
+// Norms, value and step with 1 / 2 / 4 / 8 / 16 / 32 K: pruned ResNet-32 (0.15 M elements) 20.5 / 20.7 / 27 / 28 / 31 / 26 us
+// (4 K and 16 K also seen at 26), pruned ResNet-50 (9.4 M) 90.1 / 80.4 / 75.4 / 78.1 / 80.9 / 94.5, published (23.5 M) 171 /
+// 161 / 141 / 128.5 / 125.5 / 121.6.
 static bool past_caches(int64_t elements) { return elements * 12 > kInfinityCacheBytes; }  // w, dw, mom
 static int lasso_chunk(int64_t total, bool update) {
     if (update && past_caches(total)) return 32768;

@@ -126,7 +126,9 @@ __global__ void k_compact_nhwc(const uint16_t* __restrict__ x, int64_t pixels, i
 // writes one 16-byte store.  Channels of the last vector past Cp are written as zero: rows without holes keep
 // the memory system from merging partial lines (measured: stores of ragged rows with holes ran at half the
 // rate of whole rows).
-// Bound by HBM, reads and writes together: without its LDS reads the kernel takes 1 % less, without the stores 23 %.  A
+// Bound by its memory instructions one after the other: without its LDS reads the kernel takes 1 % less, without the stores
+// 23 %.  The wait for a run's loads counts every memory instruction before the next run's loads, so it also waits for the
+// stores of the run before, with one run of loads in flight: reads and writes take turns in a workgroup.  A
 // byte is read once and written once, so loads and stores are both marked as not to be kept (the loads alone: 5 % slower
 // than neither, the stores alone: no change, both: 4 % faster), and runs are whole 128-byte lines.  Sweep of the pruned
 // ResNet-50 at batch 64: 377 -> 360 us, at batch 40: 273 -> 254.  Runs of 64 KB, one workgroup of 512 threads a CU: 351 and

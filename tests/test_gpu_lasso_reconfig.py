@@ -864,3 +864,33 @@ def test_optimizer_step_for_every_chunk_size(C, total):
     for got, ref in ((w, W), (mom, M)):
         assert ((got[..., :C].double() - ref).norm() / ref.norm()).item() <= F32_TOL
     assert torch.equal(dw, dw0)
+
+
+@pytest.mark.parametrize("total", [41 << 19, 43 << 19])
+def test_optimizer_step_of_the_largest_chunks(total):
+    """21.5 M elements, the most that chunks of 16 K take, and 22.5 M, in chunks of 32 K that pass by the caches."""
+    test_optimizer_step_for_every_chunk_size(300, total)
+
+
+@pytest.mark.parametrize("C,total", [(300, 1 << 20), (300, 3 << 20), (300, 6 << 20), (300, 12 << 20), (300, 21 << 20), (2045, 3 << 20),
+                                     (5, 1 << 20)])
+@pytest.mark.parametrize("n", [1, 2])
+def test_gradient_for_every_chunk_size(C, total, n):
+    """A layer by itself and two in one call, in chunks of 1 K to 16 K elements by their size: against the plain sum in
+    float64 at the tolerance of the oracle's test."""
+    from gpu_util import DEV, F32_TOL
+    RS, lam = 3, 0.5
+    pitch = (C + 7) // 8 * 8
+    K = total // (RS * pitch * n) + 1
+    gen = torch.Generator(device=DEV).manual_seed(C + n)
+    w, dw = (torch.randn((n, K, RS, pitch), device=DEV, generator=gen) for _ in range(2))
+    on, inn = (torch.rand((n, k), device=DEV, generator=gen) + 0.5 for k in (K, C))
+    ref = dw[..., :C].double() + lam * w[..., :C].double() * (1.0 / on.double()[:, :, None, None] + 1.0 / inn.double()[:, None, None, :])
+    pad = dw[..., C:].clone()
+    if n == 1:
+        B.group_lasso_grad(w, on, inn, lam, 3, dw, K, RS, C, pitch)
+    else:
+        B.group_lasso_grad_batched([B.layer_lasso(w[i], on[i], inn[i], dw[i], K, RS, C, pitch, 3) for i in range(n)], lam)
+    torch.cuda.synchronize()
+    assert ((dw[..., :C].double() - ref).norm() / ref.norm()).item() <= F32_TOL
+    assert torch.equal(dw[..., C:], pad)
