@@ -288,6 +288,9 @@ struct WgradCost {
     float step, round;
 };
 constexpr WgradCost kWgCost[kWgConfigs] = {{0.257f, 1.343f}, {0.3f, 1.35f}, {0.312f, 1.388f}, {0.222f, 0.323f}};
+// The register-staged kernel on rows that are not 16-byte aligned (element-wise loads): 2.3 us a step.  Over 240 shapes at odd
+// pitches its calls take 15.8 ms (cached) and 17.0 ms (from memory) so, with the 0.30 us of an aligned step 17.2 and 18.6.
+constexpr WgradCost kWgStagedCost = {2.3f, 0.7f};
 constexpr int kWgUnsplitSteps = 24;
 constexpr float kWgPartialUsPerMB = 0.627f, kWgSecondUs = 1.065f, kWgOperandUsPerMB = 0.07f;
 inline WgradPlan plan_wgrad(const pt_conv_desc* d, bool dl) {
@@ -298,7 +301,7 @@ inline WgradPlan plan_wgrad(const pt_conv_desc* d, bool dl) {
     float best_us = 1e30f;
     for (int cfg = 0; cfg < (direct ? kWgConfigs : 1); ++cfg) {
         const WgradPlan p = plan_wgrad_tiles(d, dl, direct ? cfg : -1);
-        const WgradCost cost = direct ? kWgCost[cfg] : WgradCost{kWgStepUs, 0.85f};
+        const WgradCost cost = direct ? kWgCost[cfg] : kWgStagedCost;
         const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n, most = p.iters_total / kWgMinSteps;
         const float operands = (float)tiles * p.iters_total * p.bkp * (p.BM + p.BN) * 2e-6f * kWgOperandUsPerMB;
         // none; around the optimum of steps / s + s * part without rounds; as many as fill one round or two

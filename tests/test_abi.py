@@ -235,6 +235,16 @@ def test_weight_gradient_plan_of_large_1x1_layers(lib, shape):
     assert (info.tile_m, info.tile_n) == (128, 128) and info.splits > 1
 
 
+@pytest.mark.parametrize("shape", [(6, 10, 12, 620, 779, 1, 1), (4, 11, 13, 977, 734, 1, 1), (4, 11, 12, 77, 710, 3, 1),
+                                   (3, 24, 24, 1009, 68, 3, 2), (38, 11, 11, 1007, 170, 3, 2)])
+def test_weight_gradient_plan_at_odd_pitches(lib, shape):
+    """Few steps of unaligned rows over few tiles: split, since a step of them takes as long as eight aligned ones (unsplit,
+    these calls take 1.8 to 2.8 times as long)."""
+    N, H, W, Cc, K, R, stride = shape
+    d = B.conv_desc(N, H, W, Cc, K, R, R, stride, R // 2, Cc | 1, K | 1, Cc | 1)
+    assert B.conv_bwd_weight_plan(d, True).splits > 1
+
+
 def test_batched_gradient_call_reports_a_plan_that_does_not_fit_memory():
     """More layers than the address space has room to plan: a status, not an exception that ends the process (the layers
     themselves are not looked at before)."""
