@@ -45,6 +45,7 @@ inline IgemmArgs make_fwd_args(const pt_conv_desc* d, const uint16_t* x, const u
     a.zf_h = a.zf_w = 1;
     a.M = d->N * d->P * d->Q;
     a.gW = make_fastdiv((int64_t)d->Q); a.gH = make_fastdiv((int64_t)d->P);
+    a.sW = make_smalldiv(d->Q); a.sH = make_smalldiv(d->P);
     a.srcH = d->H; a.srcW = d->W; a.apitch = d->x_cpitch;
     a.h_mul = d->stride_h; a.h_add = -d->pad_h; a.w_mul = d->stride_w; a.w_add = -d->pad_w;
     a.tr_step = 1; a.ts_step = 1; a.TR = d->R; a.TS = d->S;
@@ -85,6 +86,7 @@ inline IgemmArgs make_bwd_data_args(const pt_conv_desc* d, const BwdClass& c, in
     a.zf_h = a.zf_w = 1;
     a.M = d->N * c.gH * c.gW;
     a.gW = make_fastdiv((int64_t)c.gW); a.gH = make_fastdiv((int64_t)c.gH);
+    a.sW = make_smalldiv(c.gW); a.sH = make_smalldiv(c.gH);
     a.srcH = d->P; a.srcW = d->Q; a.apitch = d->y_cpitch;
     a.h_mul = 1; a.h_add = (ca + d->pad_h - c.r0) / d->stride_h;
     a.w_mul = 1; a.w_add = (cb + d->pad_w - c.s0) / d->stride_w;
@@ -394,6 +396,7 @@ inline WgradArgs make_wgrad_args(const pt_conv_desc* d, const WgradPlan& p, cons
     a.X = x; a.DY = dy;
     a.pixels = d->N * d->P * d->Q;
     a.Q = make_fastdiv((int64_t)d->Q); a.P = make_fastdiv((int64_t)d->P);
+    a.sQ = make_smalldiv(d->Q); a.sP = make_smalldiv(d->P);
     a.H = d->H; a.W = d->W; a.xpitch = d->x_cpitch; a.ypitch = d->y_cpitch;
     a.stride_h = d->stride_h; a.stride_w = d->stride_w; a.pad_h = d->pad_h; a.pad_w = d->pad_w;
     a.S = d->S; a.RS = d->R * d->S; a.C = d->C; a.CP = p.CP; a.KP = p.KP; a.Mtot = p.Mtot; a.K = d->K;

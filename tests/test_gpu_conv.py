@@ -515,6 +515,13 @@ def test_batched_input_gradients_match_single_calls():
         assert torch.equal(a, b), s
 
 
+@pytest.mark.parametrize("case", [(3, 5, 1, 19, 13, 1, 1, 0), (3, 1, 6, 19, 13, 1, 1, 0), (7, 1, 1, 21, 35, 1, 1, 0),
+                                  (5, 3, 2, 9, 17, 3, 2, 1), (2, 33, 31, 11, 7, 3, 1, 1)])
+def test_odd_pitches_and_images_one_pixel_wide_or_high(case):
+    """The register-staged kernels' pixel divisions: by one, by two and by what is no power of two."""
+    _check_full(_spec(*case), 700 + sum(case))
+
+
 @pytest.mark.parametrize("case", [(2, 4, 4, 205, 56, 1, 1, 0), (3, 9, 9, 400, 70, 1, 1, 0), (2, 5, 6, 455, 15, 1, 1, 0),
                                   (18, 21, 22, 210, 14, 5, 1, 2),    # forward: 260 tiles of 25 stages
                                   # the four classes of an input gradient: one stage, two, 512 tiles of up to seven
