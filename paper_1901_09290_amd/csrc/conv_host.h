@@ -127,12 +127,14 @@ inline void igemm_fold(IgemmArgs& a) {
 // 0 = k_igemm_dl at 128 x 64, 1 = k_igemm_small at 64 x 64, 2 = at 32 x 32 in three stages (96 KB of LDS: one workgroup on the
 // CU), 3 = at 32 x 32 in two (64 KB: two on the CU, and room beside a weight gradient).  Without the last, more than 256
 // workgroups with long reductions lost up to 40 % (8 x 9 165 <- 1974 3 x 3 stride 2, batch 22: 23.6 -> 32.9 us, 38 -> 50).
+// The figures of 64 x 64 tiles are 1 / 0.9 of their own, so that near ties go against them: the traffic of 128 x 64 tiles disturbs
+// a weight gradient running beside them less, and 32 x 32 tiles lose less when operands come from memory.
 inline int pick_igemm_kernel(const IgemmArgs* as, int n) {
     struct Est { int bm, bn, nb; float t1, t2, f1, f2; };
     constexpr Est est[4] = {{128, 64, 1, 0.30f, 0.52f, 0.54f, 1.05f},
-                            {64, 64, 1, 0.22f, 0.43f, 0.77f, 1.72f},
+                            {64, 64, 1, 0.244f, 0.478f, 0.856f, 1.91f},
                             {32, 32, 4, 0.50f, 0.98f, 1.22f, 4.39f},
-                            {32, 32, 4, 0.72f, 0.70f, 0.76f, 3.47f}};
+                            {32, 32, 4, 0.72f, 0.73f, 0.76f, 3.47f}};
     int best = 0;
     float best_us = 1e30f;
     for (int k = 0; k < 4; ++k) {
@@ -150,8 +152,7 @@ inline int pick_igemm_kernel(const IgemmArgs* as, int n) {
         const float last_steps = full ? avg : (float)longest;
         const float last = rem == 0 ? 0.f : rem <= 256 ? last_steps * est[k].t1 + est[k].f1 : last_steps * est[k].t2 + est[k].f2;
         const float us = (float)full * (avg * est[k].t2 + est[k].f2) + last;
-        // (a near tie goes to the larger tiles: their traffic disturbs a weight gradient running beside them less)
-        if (us < best_us * (k == 1 ? 0.9f : 1.f)) {
+        if (us < best_us) {
             best_us = us;
             best = k;
         }
