@@ -164,6 +164,37 @@ inline bool igemm_small_ok(const IgemmArgs& a) {  // no undefined channel paddin
     return !a.stats && a.TR * a.TSm < 32 && ((a.fold ? a.Creal : a.Cred) % 8 == 0 || a.pad_zero);
 }
 
+// Which deep form of the direct kernel takes a problem, 0 = none: 1 = 128 x 128 and 2 = 256 x 128 in three stages, 3 = 128 x 64 in
+// three.  `kernel` = what takes it otherwise.
+// A forward call by itself: by estimated times (us).  The other forms, two workgroups on a CU: rounds of 512 tiles t2 a step and
+// f2, a last one of up to 256 t1 and f1.  The deep forms hold a CU each (96 and 144 KB of LDS): rounds of 256 tiles.  Fitted to 820
+// calls (random layers of at least 4 steps and 128 tiles of 128 x 64, batch 4 to 128, 65 to 2048 output channels), each in all
+// forms with operands in the caches and from memory: without the deep forms 34.0 ms together, so 31.3, the best form for each
+// 31.0; 7 of them more than 4 % slower than without, at most 1.09 times.  Layers of ResNet-50, batch 64, from memory: 14 x 14
+// 1024 -> 256 16.6 -> 13.5 us, 3 x 3 256 -> 256 23.8 -> 20.3, 28 x 28 3 x 3 128 -> 128 20.3 -> 19.3.  128 x 64 tiles in six stages won
+// nothing over them in three with the loads between the MFMAs (80 calls of 25 steps and more in one round: 5471 and 5426 us).
+// Problems that share a launch stay with the other forms: two problems of one round each are two rounds here.
+// Input gradients run beside weight gradients, which must find LDS beside them: forms 1 and 2, faster by themselves, make the
+// training step of ResNet-50 0.3 to 1 % longer there.  Form 3 takes the 72 KB that 128 x 64 tiles take anyway, and 40 steps and
+// more in one round (pruned step 2680 -> 2644 us; twelve such calls by themselves 1112 -> 1094 us from memory, 956 -> 928 in the
+// caches).
+inline int pick_igemm_deep(const IgemmArgs& a, int kernel, bool alone) {
+    if (!igemm_small_ok(a) || a.fold || a.Nout <= 64) return 0;
+    const int64_t nk = a.TR * a.TS * ceil_div(a.CredP, 64);
+    const int64_t t128 = ceil_div(a.M, 128) * ceil_div(a.Nout, 128), t64 = ceil_div(a.M, 128) * ceil_div(a.Nout, 64);
+    if (a.edge_prio) return a.d_linear && nk >= 40 && t64 > 128 && t64 <= 256 ? 3 : 0;
+    if (!alone || nk < 4 || t64 < 128 || (kernel != 0 && kernel != kIgemmLarge)) return 0;
+    auto shared = [&](int64_t tiles, float t2, float f2, float t1, float f1) {
+        const int64_t rem = tiles % 512, full = tiles / 512 + (rem > 256);
+        return (float)full * ((float)nk * t2 + f2) + (rem > 0 && rem <= 256 ? (float)nk * t1 + f1 : 0.f);
+    };
+    auto own = [&](int64_t tiles, float t1, float f1) { return (float)ceil_div(tiles, 256) * ((float)nk * t1 + f1); };
+    const float without = kernel == 0 ? shared(t64, 0.65f, 3.29f, 0.33f, 0.97f) : shared(t128, 0.77f, 4.21f, 0.90f, 1.05f);
+    const float tall = own(ceil_div(a.M, 256) * ceil_div(a.Nout, 128), 0.66f, 5.26f), square = own(t128, 0.46f, 2.61f);
+    if (fminf(tall, square) >= 0.98f * without) return 0;
+    return square <= tall ? 1 : 2;
+}
+
 // Kernel and tile configuration.  `vec`: all operand rows are 16-byte aligned (pitches are multiples of 8
 // elements) - then the direct global->LDS kernels are used, with a tall pixel tile for narrow outputs and small tiles
 // where there are few.
@@ -184,8 +215,12 @@ inline hipError_t launch_igemm(IgemmArgs& a, bool vec, hipStream_t st, IgemmDlPl
     if (kernel < 0) kernel = tiles128 >= 256 ? kIgemmLarge : igemm_small_ok(a) ? pick_igemm_kernel(&a, 1) : 0;
     IgemmDlPlan own;
     IgemmDlPlan& p = plan ? *plan : own;
+    const int deep = pick_igemm_deep(a, kernel, plan == nullptr);
     hipError_t e;
-    if (kernel == 3) e = plan_igemm_small_cfg<32, 32, 4, 2>(a, p);
+    if (deep == 1) e = plan_igemm_dl_cfg<128, 128, 2, 4, 3, true>(a, p);
+    else if (deep == 2) e = plan_igemm_dl_cfg<256, 128, 4, 2, 3, true>(a, p);
+    else if (deep == 3) e = plan_igemm_dl_cfg<128, 64, 4, 2, 3, true>(a, p);
+    else if (kernel == 3) e = plan_igemm_small_cfg<32, 32, 4, 2>(a, p);
     else if (kernel == 2) e = plan_igemm_small_cfg<32, 32, 4, 3>(a, p);
     else if (kernel == 1) e = plan_igemm_small_cfg<64, 64, 1, 3>(a, p);
     // very many pixel tiles and a narrow output (the stem): tall tiles, so half as many workgroups pay set-up and fill

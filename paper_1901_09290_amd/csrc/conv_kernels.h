@@ -445,6 +445,14 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
+// The same, and until this wave's LDS reads have returned.
+template <int N>
+__device__ __forceinline__ void wait_vmcnt_lds() {
+    static_assert(N >= 0 && N < 64, "vmcnt range");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
+}
+
 __device__ __forceinline__ uint32_t swap_lane_pair(uint32_t v) {  // lanes 2i and 2i + 1 trade values
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, true);
 }
@@ -465,12 +473,22 @@ __device__ __forceinline__ TapSkip tap_skip(const IgemmArgs& a, int gi, int gj) 
     return {(int)~(uint32_t)valid, (int)~(uint32_t)(valid >> 32)};
 }
 
+// DEEP = a step's fragments are read into registers during the step before it.  Its LDS is then free for the loads of step
+// STAGES later from the step's own barrier on, a stage earlier than otherwise, and no MFMA waits for the LDS behind a barrier.
+// For reductions long enough to pay for the first reads, on launches of about one workgroup per CU (pick_igemm_deep).
+// In every form a step sends out a later step's loads between its MFMAs, a quarter with each 16 channels: the 64 or more
+// load instructions of a workgroup take the CU's address unit 16 clocks each, and ahead of the fragment reads they held
+// those, and the MFMAs, back for half a step.  Forward, 3 x 3, batch 64, operands from memory / in the caches: 128 x 64 tiles,
+// 7 x 7 512 -> 512 29.4 / 28.1 -> 28.1 / 23.6 us; deep, 128 x 128 tiles in three stages, 14 x 14 256 -> 256 23.9 / 21.8 -> 20.3 / 17.6
+// us (MFMAs alone, without loads and reads: 12.2), 1 x 1 1024 -> 256 16.7 / 11.1 -> 13.5 / 9.7; deep, 256 x 128, 28 x 28
+// 128 -> 128 20.3 / 18.1 -> 19.3 / 17.3.  Bound now by fragment reads and MFMAs, which with one barrier a step overlap to 0.31 us
+// of a 128 x 128 x 64 step (MFMAs alone 0.23), and on 128 x 64 tiles by the operands from the L2 (20 TB/s).
 // TAIL = some run of channels ends inside an 8-chunk whose remaining elements are undefined.
 // STATS = also reduce the stored outputs to per-channel sums and sums of squares (see IgemmArgs::stats).
 // AV = the caller has established that every tap of every row lies inside the source image (no validity tests).
 // FOLD = the problem may be a folded one (without AV; with a branch for it in the loop the loads no longer share a block with
 // the step's LDS reads and MFMAs: 22.8 instead of 22.2 us on 14 x 14 x 256 -> 256, 3 x 3, batch 64).
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool RAGGED, bool TAIL, bool STATS, bool AV, bool FOLD>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool RAGGED, bool TAIL, bool STATS, bool AV, bool FOLD, bool DEEP>
 __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN problems) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
     const IgemmArgs a = problems.a[blockIdx.y];  // (a copy: the fields then live in scalar registers as kernel arguments do)
@@ -483,7 +501,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
     constexpr int WTM = BM / WGM, WTN = BN / WGN;
     constexpr int TM = WTM / 32, TN = WTN / 32;
     static_assert(NW % 2 == 0 && GA % NW == 0 && GB % NW == 0 && LA >= 1 && LB >= 1 && TM >= 1 && TN >= 1, "tile config");
-    static_assert(STAGES >= 2 && (STAGES - 2) * LPT < 64, "stages");
+    static_assert(STAGES >= 2 && (STAGES - 1) * LPT < 64 && !(DEEP && (TAIL || STATS || FOLD)), "stages");
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_b[];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -558,8 +576,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
     };
     set_tap(0);
 
-    auto issue = [&](int stage) {
-        uint8_t* sbase = smem_b + stage * STAGE_BYTES;
+    // Loads number j with j * parts / LPT == part of the next step to issue, into LDS at byte `at`; the last part moves on to
+    // the step after it.
+    auto issue_part = [&](uint32_t at, int part, int parts) {
+        uint8_t* sbase = smem_b + at;
         uint32_t sa, sb;
         bool last;
         if constexpr (AV) {
@@ -572,17 +592,20 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
             last = blk == 1;
             // (uniform) folded: the tap depends on the lane's chunk; past the last chunk it means nothing
             if constexpr (FOLD) {
-                if (a.fold) set_tap(tap + (int)fdiv((uint32_t)(f_cb + kvoff), a.Cfold));
+                if (a.fold && part == 0) set_tap(tap + (int)fdiv((uint32_t)(f_cb + kvoff), a.Cfold));
             }
         }
         const uint32_t zero = RAGGED ? past & (last ? ~0u : 0u) : 0u;
-#pragma unroll
-        for (int j = 0; j < LA; ++j)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_srd, (lds_void_ptr)(sbase + (wave + NW * j) * 1024), 16, a_now[j] | zero, sa, 0, 0);
-#pragma unroll
-        for (int j = 0; j < LB; ++j)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(b_srd, (lds_void_ptr)(sbase + BM * 128 + (wave + NW * j) * 1024), 16,
-                                                     b_v[j] | zero, sb, 0, 0);
+        static_for<0, LPT>([&](auto j_c) {
+            constexpr int J = decltype(j_c)::value;
+            if (J * parts / LPT != part) return;
+            if constexpr (J < LA)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(a_srd, (lds_void_ptr)(sbase + (wave + NW * J) * 1024), 16, a_now[J] | zero, sa, 0, 0);
+            else
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(b_srd, (lds_void_ptr)(sbase + BM * 128 + (wave + NW * (J - LA)) * 1024), 16,
+                                                         b_v[J - LA] | zero, sb, 0, 0);
+        });
+        if (part != parts - 1) return;
         if constexpr (AV) {
             i_cb += BK;
             if (i_cb >= a.CredP) {
@@ -626,34 +649,55 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
         all_live = all_live && m_live[tm];
     }
 
-    auto compute = [&](int stage, auto check_tag) {
-        constexpr bool CHECK = decltype(check_tag)::value;
-        const uint8_t* sA = smem_b + stage * STAGE_BYTES;
-        const uint8_t* sB = sA + BM * 128;
-        // One stage = BK/16 sub-steps of (fragment reads, MFMAs); all sub-steps always run (chunks past the channel
-        // count were fetched as zeros) and the body has no branches: a branch per sub-step costs the
-        // compiler's schedule far more than the work it would skip.
-        bf16x8 fw[2][TN], fp[2][TM];
-        auto read_frags = [&](int ks, int b) {
-            const int pc = (((ks * 2 + kc0) ^ swz) << 4);
+    // A step = BK / 16 sub-steps of (MFMAs, fragment reads, a part of a later step's loads).
+    constexpr int NF = DEEP ? 4 : 2;  // sub-steps whose fragments are in registers
+    bf16x8 fw[NF][TN], fp[NF][TM];
+    auto read_frags = [&](uint32_t at, int ks, int b) {
+        const uint32_t pc = (uint32_t)(((ks * 2 + kc0) ^ swz) << 4);
+        const uint8_t* sA = smem_b + (at + (uint32_t)(wm * WTM + l32) * 128u + pc);
+        const uint8_t* sB = smem_b + (at + (uint32_t)(BM + wn * WTN + l32) * 128u + pc);
 #pragma unroll
-            for (int tn = 0; tn < TN; ++tn)
-                fw[b][tn] = *reinterpret_cast<const bf16x8*>(sB + (wn * WTN + tn * 32 + l32) * 128 + pc);
+        for (int tn = 0; tn < TN; ++tn) fw[b][tn] = *reinterpret_cast<const bf16x8*>(sB + tn * 4096);
 #pragma unroll
-            for (int tm = 0; tm < TM; ++tm)
-                fp[b][tm] = *reinterpret_cast<const bf16x8*>(sA + (wm * WTM + tm * 32 + l32) * 128 + pc);
-        };
-        read_frags(0, 0);
-#pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            if (ks + 1 < BK / 16) read_frags(ks + 1, (ks + 1) & 1);
+        for (int tm = 0; tm < TM; ++tm) fp[b][tm] = *reinterpret_cast<const bf16x8*>(sA + tm * 4096);
+    };
+    auto step = [&](uint32_t at, uint32_t next, uint32_t to, auto issue_tag, auto check_tag) {
+        constexpr bool CHECK = decltype(check_tag)::value, ISSUE = decltype(issue_tag)::value;
+        if constexpr (!DEEP) {
+            read_frags(at, 0, 0);
+            read_frags(at, 1, 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        static_for<0, 4>([&](auto ks_c) {
+            constexpr int KS = decltype(ks_c)::value, F = KS % NF;
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
                 for (int tm = 0; tm < TM; ++tm)
                     if (!CHECK || (n_live[tn] && m_live[tm]))
-                        acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[ks & 1][tn], fp[ks & 1][tm], acc[tn][tm],
-                                                                              0, 0, 0);
+                        acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[F][tn], fp[F][tm], acc[tn][tm], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (DEEP) read_frags(next, KS, KS);
+            else if constexpr (KS < 2) read_frags(at, KS + 2, KS);
+            if constexpr (ISSUE) issue_part(to, KS, 4);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        c_cb += BK;
+        if (c_cb >= a.CredP) c_cb = 0;
+    };
+
+    auto compute = [&](uint32_t at, auto check_tag) {
+        constexpr bool CHECK = decltype(check_tag)::value;
+        read_frags(at, 0, 0);
+#pragma unroll
+        for (int ks = 0; ks < BK / 16; ++ks) {
+            if (ks + 1 < BK / 16) read_frags(at, ks + 1, (ks + 1) & 1);
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+                for (int tm = 0; tm < TM; ++tm)
+                    if (!CHECK || (n_live[tn] && m_live[tm]))
+                        acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[ks & 1][tn], fp[ks & 1][tm], acc[tn][tm], 0, 0, 0);
         }
         c_cb += BK;
         if (c_cb >= a.CredP) c_cb = 0;
@@ -663,14 +707,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
     // last 8-chunk of every run of channels, in both operands.  The lane that fetched such a chunk overwrites them
     // with zeros in LDS once its loads have landed (writes only: nothing is read back) and before the barrier that
     // publishes the stage.  Which chunks of the current block have a tail comes from a table in the arguments.
-    auto clear_tails = [&](int stage) {
+    auto clear_tails = [&](uint32_t at) {
         asm volatile("" ::: "memory");  // keep the stores below behind the wait for the landed loads
         const int slot = a.fold ? (c_cb >> 6) : (c_cb + BK > a.Cred ? 0 : 7);
         const uint32_t bits = (uint32_t)(a.tail_kv >> (slot * 8)) & 0xffu;
         if (bits == 0) return;  // wave-uniform
         if ((bits >> kv) & 1u) {
             const int n = a.tail_nvalid;  // uniform, 1..7: bytes [2n, 16) of the chunk are cleared with <= 3 stores
-            uint8_t* mine = smem_b + stage * STAGE_BYTES + wave * 1024 + lane * 16;
+            uint8_t* mine = smem_b + at + wave * 1024 + lane * 16;
 #pragma unroll
             for (int j = 0; j < LA + LB; ++j) {
                 uint8_t* p = mine + (j < LA ? NW * j * 1024 : BM * 128 + NW * (j - LA) * 1024);
@@ -691,25 +735,59 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
 
     const int nk = a.nk;
     auto main_loop = [&](auto check_tag) {
-        for (int kt0 = 0; kt0 < nk; kt0 += STAGES) {
-#pragma unroll
-            for (int s = 0; s < STAGES; ++s) {
-                const int kt = kt0 + s;
-                if (kt < nk) {
-                    // loads of steps kt+1 .. kt+STAGES-2 may stay in flight; near the end just drain
-                    if (kt + STAGES - 2 < nk) wait_vmcnt<(STAGES - 2) * LPT>();
-                    else wait_vmcnt<0>();
-                    if constexpr (TAIL) clear_tails(s);
+        auto after = [](uint32_t v) { return v == (STAGES - 1) * STAGE_BYTES ? 0u : v + STAGE_BYTES; };
+        int kt = 0;
+        if constexpr (DEEP) {
+            uint32_t at = 0;  // LDS of the step computed
+            if (nk >= STAGES) wait_vmcnt<(STAGES - 1) * LPT>();
+            else wait_vmcnt<0>();
+            barrier_nofence();
+            static_for<0, 4>([&](auto ks_c) { read_frags(0, decltype(ks_c)::value, decltype(ks_c)::value); });
+            for (; kt + STAGES < nk; ++kt) {
+                wait_vmcnt_lds<(STAGES - 2) * LPT>();
+                barrier_nofence();
+                step(at, after(at), at, std::true_type{}, check_tag);
+                at = after(at);
+            }
+            for (; kt < nk; ++kt) {
+                if (kt + STAGES - 1 < nk) wait_vmcnt_lds<(STAGES - 2) * LPT>();
+                else wait_vmcnt_lds<0>();
+                barrier_nofence();
+                step(at, after(at), at, std::false_type{}, check_tag);
+                at = after(at);
+            }
+        } else {
+            // Whole rounds of the stages with nothing to test, and the last steps one by one.  With two stages the loads of the
+            // next step go out ahead of this one's reads: they have only this step to arrive in.
+            for (; STAGES >= 3 && kt + 2 * STAGES - 2 < nk; kt += STAGES) {
+                static_for<0, STAGES>([&](auto s_c) {
+                    constexpr uint32_t S = decltype(s_c)::value;
+                    wait_vmcnt<(STAGES - 2) * LPT>();
+                    if constexpr (TAIL) clear_tails(S * STAGE_BYTES);
                     barrier_nofence();  // stage s complete for every wave; stage (s-1) free again
-                    if (kt + STAGES - 1 < nk) issue((s + STAGES - 1) % STAGES);
-                    compute(s, check_tag);
-                }
+                    step(S * STAGE_BYTES, 0, (S + STAGES - 1) % STAGES * STAGE_BYTES, std::true_type{}, check_tag);
+                });
+            }
+            for (; kt < nk; kt += STAGES) {
+                static_for<0, STAGES>([&](auto s_c) {
+                    constexpr uint32_t S = decltype(s_c)::value;
+                    const int k = kt + (int)S;
+                    if (k < nk) {
+                        // loads of steps k+1 .. k+STAGES-2 may stay in flight; near the end just drain
+                        if (k + STAGES - 2 < nk) wait_vmcnt<(STAGES - 2) * LPT>();
+                        else wait_vmcnt<0>();
+                        if constexpr (TAIL) clear_tails(S * STAGE_BYTES);
+                        barrier_nofence();
+                        if (k + STAGES - 1 < nk) issue_part((S + STAGES - 1) % STAGES * STAGE_BYTES, 0, 1);
+                        compute(S * STAGE_BYTES, check_tag);
+                    }
+                });
             }
         }
     };
 #pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s)
-        if (s < nk) issue(s);
+    for (int s = 0; s < (DEEP ? STAGES : STAGES - 1); ++s)
+        if (s < nk) issue_part(s * STAGE_BYTES, 0, 1);
     // waves inside the reduction loop go first at the CU's issue arbiter: ahead of a co-resident workgroup's set-up
     // or stores, and ahead of weight-gradient waves sharing the CU from another stream (+0.4 % on the step)
     __builtin_amdgcn_s_setprio(2);
@@ -964,7 +1042,7 @@ inline bool igemm_buffer_args(IgemmArgs& a) {
     return (img * a.srcH * a.srcW * a.apitch + a.a_guard) * 2 < 0xffffff00ll && (int64_t)a.Nout * a.b_taps * a.bpitch * 2 < 0xffffff00ll;
 }
 
-template <int BM, int BN, int WGM, int WGN, int STAGES>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool DEEP = false>
 inline hipError_t plan_igemm_dl_cfg(IgemmArgs& a, IgemmDlPlan& plan) {
     constexpr int NT = 64 * WGM * WGN;
     constexpr size_t lds = (size_t)STAGES * (BM + BN) * 128;
@@ -982,6 +1060,7 @@ inline hipError_t plan_igemm_dl_cfg(IgemmArgs& a, IgemmDlPlan& plan) {
         variant += 3;
     }
     a.tiles_m = (int)ceil_div(a.M, BM);
+    if (DEEP && (variant > 1 || a.fold)) return hipErrorInvalidValue;
     if (!igemm_buffer_args(a)) return hipErrorInvalidValue;
     // every tap of every row inside the source image?  coordinates are monotone in the grid index and in the tap
     auto inside = [](int lo, int hi, int n) { return lo >= 0 && hi >= 0 && lo < n && hi < n; };
@@ -991,21 +1070,23 @@ inline hipError_t plan_igemm_dl_cfg(IgemmArgs& a, IgemmDlPlan& plan) {
     a.a_all_valid = inside(h_first, h_last, a.srcH) && inside(h_first + rr, h_last + rr, a.srcH) &&
                     inside(w_first, w_last, a.srcW) && inside(w_first + ss, w_last + ss, a.srcW);
     const bool av = a.a_all_valid && variant != 2;
-    static const igemm_dl_kern_t kerns[3][5] = {{k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, false, false, false>,
-                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, false, false, false>,
-                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, true, false, false, false>,
-                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, true, false, false>,
-                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, true, false, false>},
-                                                {k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, false, true, false>,
-                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, false, true, false>,
+    // (the deep form: no tails, no statistics, no folded mode)
+    constexpr bool D = DEEP, T = !DEEP;
+    static const igemm_dl_kern_t kerns[3][5] = {{k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, false, false, false, D>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, false, false, false, D>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, T, false, false, false, D>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, T, false, false, D>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, T, false, false, D>},
+                                                {k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, false, true, false, D>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, false, true, false, D>,
                                                  nullptr,
-                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, true, true, false>,
-                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, true, true, false>},
-                                                {k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, false, false, true>,
-                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, false, false, true>,
-                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, true, false, false, true>,
-                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, true, false, true>,
-                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, true, false, true>}};
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, T, true, false, D>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, T, true, false, D>},
+                                                {k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, false, false, T, D>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, false, false, T, D>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, T, false, false, T, D>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, false, false, T, false, T, D>,
+                                                 k_igemm_dl<BM, BN, WGM, WGN, STAGES, true, false, T, false, T, D>}};
     static LdsOptIn opt_in[3][5];
     const int tests = a.fold ? 2 : 0, rows[3] = {av ? 1 : tests, tests, 2};
     for (int l = 0; l < 3; ++l) {

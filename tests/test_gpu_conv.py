@@ -165,6 +165,23 @@ def test_few_tiles_with_long_reductions(case, pad_zero):
     _check_full(spec, 700 + sum(case), pitch8(spec.C), pitch8(spec.K), pitch8(spec.C), pad_zero=pad_zero)
 
 
+DEEP = [
+    # forward in 128 x 128 tiles: 1 x 1 and 3 x 3, ragged on every side (256 tiles, 5 and 18 steps), a stride, 4 steps
+    ((5, 20, 20, 300, 1990, 1, 1, 0), True), ((5, 20, 20, 70, 1990, 3, 1, 1), True), ((8, 31, 31, 256, 1921, 1, 2, 0), True),
+    # ... in 256 x 128 tiles (294 tiles of 128 x 128, 154 of these), whole and ragged
+    ((7, 19, 20, 72, 1697, 3, 1, 1), True), ((7, 19, 20, 1024, 1696, 1, 1, 0), False),
+    # input gradient in 128 x 64 tiles, 45 and 40 steps; one step too few
+    ((2, 17, 18, 1697, 290, 3, 1, 1), True), ((2, 17, 18, 1696, 2560, 1, 1, 0), False), ((2, 17, 18, 1696, 2496, 1, 1, 0), False),
+]
+
+
+@pytest.mark.parametrize("case,pad_zero", DEEP, ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else str(c))
+def test_fragments_a_step_ahead(case, pad_zero):
+    from gpu_util import pitch8
+    spec = _spec(*case)
+    _check_full(spec, 700 + sum(case), pitch8(spec.C), pitch8(spec.K), pitch8(spec.C), pad_zero=pad_zero)
+
+
 FIRST_LAYER = [
     # image-like inputs (at most 4 channels at a pitch of 8, zero padding vouched for): the first-layer forward kernel
     (2, 33, 35, 1, 20, 3, 1, 1),      # one channel, 3 x 3 at stride 1 (one step per filter row)
