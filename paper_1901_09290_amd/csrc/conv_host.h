@@ -120,24 +120,21 @@ inline void igemm_fold(IgemmArgs& a) {
 
 // Which kernel takes the problems of a call that fill less than one round of 128 x 128 tiles (`as`: one problem, or the
 // stride-parity classes of an input gradient, which share a launch).  Estimated times in us: up to 256 workgroups take `steps`
-// steps of t1 and f1 for set-up and stores, up to 512 (two on a CU, or one after the other) t2 and f2.  Fitted to 1591 calls
-// (ResNet layers at batch 1 to 256, published and pruned, and random shapes), each in all four forms, with operands in the
-// caches and from memory, so that few calls lose in either state.  Chosen: 14.24 ms cached and 16.65 from memory, the best
-// form for both states together 14.26 and 16.48, always one of them 18.4 / 17.4 / 26.6 / 21.2 and 23.6 / 22.2 / 27.3 / 24.7.
-// 0 = k_igemm_dl at 128 x 64, 1 = k_igemm_small at 64 x 64, 2 = at 32 x 32 in three stages (96 KB of LDS: one workgroup on the
-// CU), 3 = at 32 x 32 in two (64 KB: two on the CU, and room beside a weight gradient).  Without the last, more than 256
-// workgroups with long reductions lost up to 40 % (8 x 9 165 <- 1974 3 x 3 stride 2, batch 22: 23.6 -> 32.9 us, 38 -> 50).
-// The figures of 64 x 64 tiles are 1 / 0.9 of their own, so that near ties go against them: the traffic of 128 x 64 tiles disturbs
-// a weight gradient running beside them less, and 32 x 32 tiles lose less when operands come from memory.
+// steps of t1 and f1 for set-up and stores, up to 512 (two on a CU, or one after the other) t2 and f2.  Fitted to 480 calls
+// (random layers, 16 to 2048 channels, batch 1 to 128), each in all forms, with operands in the caches and from memory.  Mean of
+// both states: always one of them 7.68 / 7.42 / 8.35 ms, the best form for each call 6.0, chosen 5.99 (before the steps of the
+// small tiles were shortened, with three stages of 64 x 64 tiles and two and three of 32 x 32 in fours: 6.92); 24 of the calls are
+// more than 4 % slower than then, at most 1.1 times.
+// 0 = k_igemm_dl at 128 x 64, 1 = k_igemm_small at 64 x 64, 2 = at 32 x 32: all of them two workgroups on a CU.
 inline int pick_igemm_kernel(const IgemmArgs* as, int n) {
     struct Est { int bm, bn, nb; float t1, t2, f1, f2; };
-    constexpr Est est[4] = {{128, 64, 1, 0.30f, 0.52f, 0.54f, 1.05f},
-                            {64, 64, 1, 0.244f, 0.478f, 0.856f, 1.91f},
-                            {32, 32, 4, 0.50f, 0.98f, 1.22f, 4.39f},
-                            {32, 32, 4, 0.72f, 0.73f, 0.76f, 3.47f}};
+    constexpr int FORMS = 3;
+    constexpr Est est[FORMS] = {{128, 64, 1, 0.346f, 0.554f, 0.705f, 1.57f},
+                                {64, 64, 1, 0.213f, 0.408f, 0.946f, 2.20f},
+                                {32, 32, 2, 0.229f, 0.293f, 0.860f, 1.99f}};
     int best = 0;
     float best_us = 1e30f;
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < FORMS; ++k) {
         int64_t tiles = 0, tile_steps = 0, longest = 0;
         for (int i = 0; i < n; ++i) {
             const IgemmArgs& a = as[i];
@@ -159,13 +156,13 @@ inline int pick_igemm_kernel(const IgemmArgs* as, int n) {
     }
     return best;
 }
-constexpr int kIgemmLarge = 4;  // beyond pick_igemm_kernel's range: 128 x 128 tiles fill the chip
+constexpr int kIgemmLarge = 3;  // beyond pick_igemm_kernel's range: 128 x 128 tiles fill the chip
 inline bool igemm_small_ok(const IgemmArgs& a) {  // no undefined channel padding, no statistics epilogue, a bit per tap
     return !a.stats && a.TR * a.TSm < 32 && ((a.fold ? a.Creal : a.Cred) % 8 == 0 || a.pad_zero);
 }
 
-// Which deep form of the direct kernel takes a problem, 0 = none: 1 = 128 x 128 and 2 = 256 x 128 in three stages, 3 = 128 x 64 in
-// three.  `kernel` = what takes it otherwise.
+// Which deep form of the direct kernel takes a problem, 0 = none: 1 = 128 x 128 and 2 = 256 x 128 in three stages.  `kernel` = what
+// takes it otherwise.
 // A forward call by itself: by estimated times (us).  The other forms, two workgroups on a CU: rounds of 512 tiles t2 a step and
 // f2, a last one of up to 256 t1 and f1.  The deep forms hold a CU each (96 and 144 KB of LDS): rounds of 256 tiles.  Fitted to 820
 // calls (random layers of at least 4 steps and 128 tiles of 128 x 64, batch 4 to 128, 65 to 2048 output channels), each in all
@@ -174,16 +171,13 @@ inline bool igemm_small_ok(const IgemmArgs& a) {  // no undefined channel paddin
 // 1024 -> 256 16.6 -> 13.5 us, 3 x 3 256 -> 256 23.8 -> 20.3, 28 x 28 3 x 3 128 -> 128 20.3 -> 19.3.  128 x 64 tiles in six stages won
 // nothing over them in three with the loads between the MFMAs (80 calls of 25 steps and more in one round: 5471 and 5426 us).
 // Problems that share a launch stay with the other forms: two problems of one round each are two rounds here.
-// Input gradients run beside weight gradients, which must find LDS beside them: forms 1 and 2, faster by themselves, make the
-// training step of ResNet-50 0.3 to 1 % longer there.  Form 3 takes the 72 KB that 128 x 64 tiles take anyway, and 40 steps and
-// more in one round (pruned step 2680 -> 2644 us; twelve such calls by themselves 1112 -> 1094 us from memory, 956 -> 928 in the
-// caches).
+// Input gradients run beside weight gradients, which must find LDS beside them: the deep forms, faster by themselves, make the
+// training step of ResNet-50 0.3 to 1 % longer there.
 inline int pick_igemm_deep(const IgemmArgs& a, int kernel, bool alone) {
-    if (!igemm_small_ok(a) || a.fold || a.Nout <= 64) return 0;
+    if (!alone || a.edge_prio || !igemm_small_ok(a) || a.fold || a.Nout <= 64) return 0;
     const int64_t nk = a.TR * a.TS * ceil_div(a.CredP, 64);
     const int64_t t128 = ceil_div(a.M, 128) * ceil_div(a.Nout, 128), t64 = ceil_div(a.M, 128) * ceil_div(a.Nout, 64);
-    if (a.edge_prio) return a.d_linear && nk >= 40 && t64 > 128 && t64 <= 256 ? 3 : 0;
-    if (!alone || nk < 4 || t64 < 128 || (kernel != 0 && kernel != kIgemmLarge)) return 0;
+    if (nk < 4 || t64 < 128 || (kernel != 0 && kernel != kIgemmLarge)) return 0;
     auto shared = [&](int64_t tiles, float t2, float f2, float t1, float f1) {
         const int64_t rem = tiles % 512, full = tiles / 512 + (rem > 256);
         return (float)full * ((float)nk * t2 + f2) + (rem > 0 && rem <= 256 ? (float)nk * t1 + f1 : 0.f);
@@ -219,10 +213,8 @@ inline hipError_t launch_igemm(IgemmArgs& a, bool vec, hipStream_t st, IgemmDlPl
     hipError_t e;
     if (deep == 1) e = plan_igemm_dl_cfg<128, 128, 2, 4, 3, true>(a, p);
     else if (deep == 2) e = plan_igemm_dl_cfg<256, 128, 4, 2, 3, true>(a, p);
-    else if (deep == 3) e = plan_igemm_dl_cfg<128, 64, 4, 2, 3, true>(a, p);
-    else if (kernel == 3) e = plan_igemm_small_cfg<32, 32, 4, 2>(a, p);
-    else if (kernel == 2) e = plan_igemm_small_cfg<32, 32, 4, 3>(a, p);
-    else if (kernel == 1) e = plan_igemm_small_cfg<64, 64, 1, 3>(a, p);
+    else if (kernel == 2) e = plan_igemm_small_cfg<32, 32, 2, 4>(a, p);
+    else if (kernel == 1) e = plan_igemm_small_cfg<64, 64, 1, 4>(a, p);
     // very many pixel tiles and a narrow output (the stem): tall tiles, so half as many workgroups pay set-up and fill
     else if (a.Nout <= 64 && tiles128 >= 4096 && !a.stats) e = plan_igemm_dl_cfg<256, 64, 4, 2, 2>(a, p);
     else if (a.Nout <= 64 || kernel != kIgemmLarge) e = plan_igemm_dl_cfg<128, 64, 4, 2, 3>(a, p);

@@ -551,12 +551,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
         const_cast<uint16_t*>(a.A) + ((int64_t)a.a_smin - a.a_guard), 0, kBufRecords, kBufFlags);
     const __amdgpu_buffer_rsrc_t b_srd = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.B), 0, kBufRecords, kBufFlags);
 
-    // With taps outside the image the next step to issue is kept as running scalar offsets, to which a step adds one of three
-    // constants (next 64 channels, next filter column, next filter row), and which lanes read zeros, which changes with the
-    // tap only, is worked out once per tap.  14 x 14 x 256 -> 256, 3 x 3, batch 64: 22.8 us; both recomputed in every step 23.1,
-    // the test alone in every step 24.0.  With none outside (mostly 1 x 1 layers of few steps) there is no test, and what the
-    // constants take ahead of the first load is not won back: 28 x 28 x 512 -> 128 12.96 us with them, 12.70 with the offsets
-    // from tap and block.
+    // With taps outside the image the next step to issue is kept as running scalar offsets, to which a step adds 64 channels and,
+    // behind a branch at the end of a tap's last step, a constant (next filter column, next filter row); which lanes read zeros,
+    // which changes with the tap only, is worked out there too.  14 x 14 x 256 -> 256, 3 x 3, batch 64: 22.8 us; both recomputed in
+    // every step 23.1, the test alone in every step 24.0; selects instead of the branch 0 to 2 % slower.  With none outside (mostly
+    // 1 x 1 layers of few steps) there is no test, and what the constants take ahead of the first load is not won back: 28 x 28 x
+    // 512 -> 128 12.96 us with them, 12.70 with the offsets from tap and block.
     const int nblk = (a.CredP + BK - 1) / BK;
     const int ts_a = a.ts_step * a.apitch * 2, ts_b = a.b_ts_stride * a.bpitch * 2, back = (nblk - 1) * BK * 2;
     const int col_a = ts_a - back, col_b = ts_b - back;
@@ -613,15 +613,21 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
                 if (++i_ts == a.TS) { i_ts = 0; ++i_tr; }
             }
         } else {
-            // (selects, not branches: the counters stay in scalar registers)
-            const bool last_col = col == 1;
-            s_a += (uint32_t)(last ? (last_col ? row_a : col_a) : BK * 2);
-            s_b += (uint32_t)(last ? (last_col ? row_b : col_b) : BK * 2);
-            blk = last ? nblk : blk - 1;
-            col = last ? (last_col ? a.TS : col - 1) : col;
-            tap += last ? (FOLD && a.fold ? a.TSm : 1) : 0;
-            f_cb = last ? 0 : f_cb + BK;
-            if (last) set_tap(tap);
+            if (last) {
+                const bool last_col = col == 1;
+                s_a += (uint32_t)(last_col ? row_a : col_a);
+                s_b += (uint32_t)(last_col ? row_b : col_b);
+                blk = nblk;
+                col = last_col ? a.TS : col - 1;
+                tap += FOLD && a.fold ? a.TSm : 1;
+                f_cb = 0;
+                set_tap(tap);
+            } else {
+                s_a += BK * 2;
+                s_b += BK * 2;
+                --blk;
+                f_cb += BK;
+            }
         }
     };
     // ---- MFMA state ---------------------------------------------------------------------------
@@ -1118,13 +1124,12 @@ inline hipError_t plan_igemm_dl_cfg(IgemmArgs& a, IgemmDlPlan& plan) {
 // Same arguments, addressing and LDS layout as k_igemm_dl (one 64-channel step = BM + BN rows of 128 bytes, chunks XOR-ed
 // with the row), every geometry in one instantiation: a bit per tap (at most 31 of them) is tested per load.  No TAIL
 // (undefined channel padding), no statistics.
-// Bound by the chain of a step: wait, barrier, fragment reads, two MFMAs or four.  The fragments are read ahead of the issue of
-// a later stage's loads, some 25 instructions that would otherwise stand between the barrier and the reads (7 x 7
-// 324 -> 263, 3 x 3, batch 10: 13.4 -> 11.2 us with the third stage; 14 x 14 655 -> 207, 1 x 1: 7.0 -> 6.4 us).  64 x 64 tiles
-// move half as much per flop as 32 x 32 and need 0.22 us a step with three stages (48 KB, three workgroups on the CU; five
-// and eight stages: 0.1 us longer for each, the longer body is fetched once more); 32 x 32 tiles, few and with long
-// reductions, 0.50 us for four steps with three stages (96 KB, one workgroup on the CU; four stages the same), 0.70 us with two
-// (64 KB, two workgroups): the form for short reductions and for more tiles than CUs.
+// Bound by a wave's own instructions, one after the other, between two barriers: wait, fragment reads, loads, two MFMAs or one.
+// The fragments are read ahead of the issue of a later stage's loads, and what only a tap's end changes stands behind a branch
+// (see issue): 7 x 7 333 -> 300, 3 x 3, batch 10: 11.2 -> 8.0 us, 14 x 14 650 -> 170, 1 x 1: 6.5 -> 5.8.  64 x 64 tiles move half
+// as much per flop as 32 x 32.  Both take 64 KB in four stages, two workgroups on the CU: 64 x 64 from memory in three stages 14 x
+// 14 256 -> 256 11.1 us, in four 10.1, in five 10.3, with two steps a stage 10.2 and 13.6; 32 x 32 in fours of steps in
+// three stages (96 KB, one on the CU) 14 x 14 171 -> 165 10.3 us, in pairs in four 8.2.
 template <int BM, int BN, int NB, int STAGES>
 __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problems) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -1151,9 +1156,11 @@ __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problem
     const int lrow = lane >> 3;
     constexpr uint32_t kBufRecords = 0xffffff00u, kBufOut = 0xffffffffu, kBufFlags = 0x00020000u;
     const int nblk = (a.CredP + 63) / 64, back = (nblk - 1) * 128;
-    uint32_t voff[LPW], voff_last[LPW], soff[LPW];  // voff_last: in the last block of a tap
-    int col_d[LPW], row_d[LPW], skip[LPW];          // skip: a bit per tap that reads zeros
+    uint32_t voff[LPW], now[LPW], past[LPW], soff[LPW];  // now: voff, or kBufOut if the tap reads zeros; past: all ones if ...
+    int col_d[LPW], row_d[LPW], skip[LPW];               // ... the last block of a tap does; skip: a bit per tap that does
     int kvoff[LPW];
+    __amdgpu_buffer_rsrc_t srd[LPW];
+    auto flag = [](int bits) { return (uint32_t)(bits << 31 >> 31); };  // bit 0, in all bits
 #pragma unroll
     for (int j = 0; j < LPW; ++j) {
         const int g = wave + NW * j;  // 8-row group of the step: the first BM / 8 are pixels
@@ -1168,38 +1175,44 @@ __global__ __launch_bounds__(512, 1) void k_igemm_small(const IgemmArgsN problem
             voff[j] = ((uint32_t)nrow * ((uint32_t)a.b_taps * a.bpitch) + (uint32_t)kvoff[j]) * 2u;
             skip[j] = (int)(~0u << (a.TR * a.TSm));
         }
-        voff_last[j] = (nblk - 1) * 64 + kvoff[j] < a.Cred ? voff[j] : kBufOut;
+        now[j] = voff[j] | flag(skip[j]);
+        past[j] = (nblk - 1) * 64 + kvoff[j] < a.Cred ? 0u : kBufOut;
         const bool px = g < BM / 8;
+        const uint16_t* base = px ? a.A + ((int64_t)a.a_smin - a.a_guard) : a.B;  // uniform
+        srd[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0, kBufRecords, kBufFlags);
         const int ts_d = px ? a.ts_step * a.apitch * 2 : a.b_ts_stride * a.bpitch * 2;
         col_d[j] = ts_d - back;
         row_d[j] = (px ? a.tr_step * a.srcW * a.apitch * 2 : a.b_tr_stride * a.bpitch * 2) - (a.TS - 1) * ts_d - back;
         soff[j] = (uint32_t)(px ? -a.a_smin * 2 : a.b_tap0 * a.bpitch * 2);
     }
-    int blk = nblk, col = a.TS, f_cb = 0, left = a.nk;
-    const int tap_bits = a.fold ? a.TSm : 1;  // taps done with a step's last block (folded: a filter row)
+    // Sends out one stage.  What only a tap's end changes stands behind a branch, at the end of a step: a wave's own instructions,
+    // one after the other, are what a step takes (70 of them 0.24 us), and with the branch there are 30.
+    int blk = nblk, col = a.TS, f_cb = 0;
     auto issue = [&](int at) {  // at: byte offset of the stage
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             uint8_t* sbase = smem_b + at + b * SUB;
-            const bool last = blk == 1, last_col = col == 1;
+            const uint32_t last = blk == 1 ? ~0u : 0u;
 #pragma unroll
             for (int j = 0; j < LPW; ++j) {
-                const int g = wave + NW * j;
-                const uint16_t* base = g < BM / 8 ? a.A + ((int64_t)a.a_smin - a.a_guard) : a.B;  // uniform
-                const __amdgpu_buffer_rsrc_t srd = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0, kBufRecords, kBufFlags);
-                uint32_t v = last ? voff_last[j] : voff[j];
-                int tap = 0;
-                if (a.fold) tap = (int)fdiv((uint32_t)(f_cb + kvoff[j]), a.Cfold);  // uniform: the tap depends on the lane's chunk
-                v |= (uint32_t)((skip[j] >> (tap & 31)) << 31 >> 31);              // all ones (kBufOut) if it reads zeros
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(srd, (lds_void_ptr)(sbase + g * 1024), 16, v, soff[j], 0, 0);
-                const uint32_t next = soff[j] + (uint32_t)(last ? (last_col ? row_d[j] : col_d[j]) : 128);
-                soff[j] = left > 1 ? next : 0u;
-                skip[j] >>= last ? tap_bits : 0;  // (sign-extended: past the last step every tap reads zeros)
+                uint32_t v = now[j];
+                if (a.fold) v = voff[j] | flag(skip[j] >> ((int)fdiv((uint32_t)(f_cb + kvoff[j]), a.Cfold) & 31));  // uniform: the tap depends on the lane's chunk
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(srd[j], (lds_void_ptr)(sbase + (wave + NW * j) * 1024), 16, v | (past[j] & last), soff[j], 0, 0);
+                soff[j] += 128u;
             }
-            --left;
-            blk = last ? nblk : blk - 1;
-            col = last ? (last_col ? a.TS : col - 1) : col;
-            f_cb = last ? 0 : f_cb + 64;
+            f_cb += 64;
+            if (--blk == 0) {  // uniform (past the last step every tap reads zeros: skip is sign-extended)
+                const bool last_col = --col == 0;
+#pragma unroll
+                for (int j = 0; j < LPW; ++j) {
+                    soff[j] += (uint32_t)((last_col ? row_d[j] : col_d[j]) - 128);
+                    skip[j] >>= a.fold ? a.TSm : 1;  // folded: a filter row
+                    now[j] = voff[j] | flag(skip[j]);
+                }
+                blk = nblk;
+                col = last_col ? a.TS : col;
+                f_cb = 0;
+            }
         }
     };
     const int kg = wave / WT, wt = wave - kg * WT;  // part of the reduction, block of the tile

@@ -170,7 +170,7 @@ DEEP = [
     ((5, 20, 20, 300, 1990, 1, 1, 0), True), ((5, 20, 20, 70, 1990, 3, 1, 1), True), ((8, 31, 31, 256, 1921, 1, 2, 0), True),
     # ... in 256 x 128 tiles (294 tiles of 128 x 128, 154 of these), whole and ragged
     ((7, 19, 20, 72, 1697, 3, 1, 1), True), ((7, 19, 20, 1024, 1696, 1, 1, 0), False),
-    # input gradient in 128 x 64 tiles, 45 and 40 steps; one step too few
+    # input gradients of 45, 40 and 39 steps in 135 tiles of 128 x 64
     ((2, 17, 18, 1697, 290, 3, 1, 1), True), ((2, 17, 18, 1696, 2560, 1, 1, 0), False), ((2, 17, 18, 1696, 2496, 1, 1, 0), False),
 ]
 
@@ -180,6 +180,15 @@ def test_fragments_a_step_ahead(case, pad_zero):
     from gpu_util import pitch8
     spec = _spec(*case)
     _check_full(spec, 700 + sum(case), pitch8(spec.C), pitch8(spec.K), pitch8(spec.C), pad_zero=pad_zero)
+
+
+@pytest.mark.parametrize("C", [60, 64, 128, 200, 256, 320, 512, 590])
+@pytest.mark.parametrize("R", [1, 3])
+def test_small_tiles_around_their_number_of_stages(C, R):
+    """Reductions of one step to past two rounds of the small tiles' stages, with one block of channels a tap and several."""
+    from gpu_util import pitch8
+    spec = _spec(2, 7, 8, C, 70 if R == 3 else 40, R, 1, R // 2)
+    _check_full(spec, 800 + C + R, pitch8(spec.C), pitch8(spec.K), pitch8(spec.C), pad_zero=True)
 
 
 FIRST_LAYER = [
@@ -544,7 +553,7 @@ def test_odd_pitches_and_images_one_pixel_wide_or_high(case):
                                   # the four classes of an input gradient: one stage, two, 512 tiles of up to seven
                                   (3, 6, 6, 25, 20, 3, 2, 1), (1, 8, 9, 68, 78, 3, 2, 1), (5, 14, 14, 500, 407, 3, 2, 1)])
 def test_small_tiles_in_two_stages(case):
-    """Tiles of 32 x 32 with two stages in LDS: reductions of one and two stages, and long ones where there are more tiles
+    """Tiles of 32 x 32: reductions of one and two stages, and long ones where there are more tiles
     than CUs."""
     from gpu_util import pitch8
     spec = _spec(*case)
