@@ -2275,16 +2275,26 @@ __global__ __launch_bounds__(512, 1) void k_wgrad_dl(const WgradArgs a) {
 // ------------------------------------------------------------------------------------------- //
 // The early 3 x 3 layers of a network (many pixels, few channels) have nine reduction steps per tile in the
 // implicit-GEMM kernel, and a workgroup there spends as long on its set-up, its first loads and its stores as on the
-// steps.  Here ONE workgroup per CU keeps the whole filter bank in LDS ([64 outputs][9 taps][64 channels] bf16, rows
-// padded by 16 bytes so that the 32 rows a fragment read touches spread over all banks) and walks over a run of tiles of
-// nby x nbx blocks of 4 x 8 output pixels (at most eight blocks, a patch of at most 348 pixels: see r3_tile).  Per tile the
-// input patch with its halo, (4*nby + 2) x (8*nbx + 2) pixels x 128 bytes, goes to one of two LDS buffers by 16-byte
-// global->LDS loads (out-of-image pixels and channels past the count fetch zeros), the next tile's patch while the
-// current one is multiplied.  Wave b of the eight owns block b: 4 x 8 pixels x 64 outputs, two accumulator blocks; per
+// steps.  Here ONE workgroup per CU keeps the whole filter bank in LDS ([32 or 64 outputs][9 taps][16 * NCB channels] bf16,
+// rows padded by 16 bytes, an odd number of 16-byte slots, so that the 32 rows a fragment read touches spread over all banks)
+// and walks over a run of tiles of nby x nbx blocks of 4 x 8 output pixels (at most eight blocks, a patch of at most 348
+// pixels: see r3_tile).  Per tile the input patch with its halo, (4*nby + 2) x (8*nbx + 2) pixels x 32, 64 or 128 bytes, goes
+// to one of two LDS buffers by 16-byte global->LDS loads (out-of-image pixels and channels past the count fetch zeros), the
+// next tile's patch while the current one is multiplied.  Wave b of the eight owns block b: 4 x 8 pixels x 64 outputs, two accumulator blocks; per
 // (tap, 16 channels) one 16-byte patch read and two weight reads feed two MFMAs.  The nine taps are nine windows of the same patch: nothing is fetched twice.  The 16-byte
-// chunks of a patch pixel are XOR-ed with ((column >> 1) & 3) | ((row & 1) << 2): the 16 lanes one LDS cycle serves
-// (two rows of eight pixels) then read 16 different bank groups, for every tap.  FLIP: the weights are indexed by the
-// mirrored tap (input gradient: the same kernel on dy with the k-innermost filter copy).
+// chunks of a patch pixel are XOR-ed with ((column >> 1) & 3) | ((row & 1) << 2), and with as much of that as there are
+// chunks to tell apart where a pixel has four or two: the 16 lanes one LDS cycle serves (two rows of eight pixels) then read
+// 16 different bank groups, for every tap.  FLIP: the weights are indexed by the mirrored tap (input gradient: the same
+// kernel on dy with the k-innermost filter copy).
+//   A call of few tiles is bound by what comes ahead of its first MFMA: a load instruction costs a wave some 20 instructions
+// of address and a CU's address unit 16 clocks, and one workgroup's worth of full-size bank and patch is 128 of them.  So bank
+// and patch are laid out for the channels there are, and loads of filters past the last output (their rows only reach outputs
+// that are not written) and past the end of a smaller patch are not made: 16 channels 80 -> 21 loads.  Against 64 channels'
+// worth for every call, us: 128 x 32 x 32, 16 -> 16 5.97 -> 4.82, 16 x 16, 32 -> 32 4.65 -> 3.85, 8 x 8, 64 -> 64 5.40 -> 5.24,
+// 16 x 16, 16 -> 16, batch 4 3.87 -> 2.95, 56 x 56, 64 -> 64, batch 64 23.2 -> 23.0; 54 layers forward 336 -> 299, input
+// gradients 349 -> 309, none of them slower.  The test for the end of the patch stands in the set-up alone: in the tile loop,
+// where its lanes are masked off anyway, it makes small patches 0.1 us faster and full ones 0.15 us slower.  More than one
+// workgroup a CU, which the smaller LDS would allow, is up to 25 % slower: each loads the bank again.
 struct Res3Args {
     const uint16_t* X;   // [N][H][W][ip]
     const uint16_t* Wt;  // [Mout][9][wp], reduction channel innermost
@@ -2292,16 +2302,21 @@ struct Res3Args {
     int N, H, W, Cin, CinP, ip, Mout, wp, op;  // CinP = Cin rounded up to 8
     int nbx, nby;                            // blocks of 8 columns and of 4 rows per tile
     uint32_t pw_magic;                       // divides by the patch's width (fast_div)
-    int tiles_x, tiles_y, tiles, run;
+    int tiles_x, tiles_y, tiles, run, patch_bytes;
     FastDiv x_div, y_div, bx_div;            // by tiles_x, tiles_y, nbx
     FastDiv cj_div;                          // by the 8-channel chunks of the output (KRSC)
 };
 constexpr int kR3TH = 4, kR3MaxNB = 7, kR3Waves = 8, kR3PatchPixels = (kR3TH + 2) * (8 * kR3MaxNB + 2);
-constexpr int kR3WRow = 9 * 128 + 16, kR3WBytes = 64 * kR3WRow;
-constexpr int kR3PatchSlots = kR3PatchPixels * 8, kR3PatchBytes = kR3PatchSlots * 16;
-constexpr int kR3Lds = kR3WBytes + 2 * kR3PatchBytes;
+constexpr int r3_rows(bool kb1) { return kb1 ? 64 : 32; }
+constexpr int r3_wslots(int ncb) { return 18 * ncb + 1; }                                       // 16-byte slots per filter, the last one padding
+constexpr int r3_wloads(int ncb, bool kb1) { return (r3_rows(kb1) * r3_wslots(ncb) + 63) / 64; }  // wave-level loads of 1 KB
+constexpr int r3_chunks(int ncb) { return ncb == 1 ? 2 : ncb == 2 ? 4 : 8; }                    // 16-byte slots per patch pixel
+constexpr int r3_ploads(int ncb) { return (kR3PatchPixels * r3_chunks(ncb) + 63) / 64; }
+constexpr int r3_wbytes(int ncb, bool kb1) { return r3_wloads(ncb, kb1) * 1024; }
+constexpr int r3_patch_bytes(int ncb, int pixels) { return pixels * r3_chunks(ncb) * 16; }
 constexpr int kR3Slots = 256;  // one workgroup per CU
-static_assert(kR3Lds <= 160 * 1024 && (64 * (kR3WRow / 16)) % 64 == 0, "LDS plan");
+constexpr int kR3LdsMax = r3_wbytes(4, true) + 2 * r3_patch_bytes(4, kR3PatchPixels);
+static_assert(kR3LdsMax <= 160 * 1024, "LDS plan");
 
 // NCB: 16-channel steps per tap (CinP / 16 rounded up); KB1: more than 32 outputs (the second accumulator block is live).
 // Compile-time so that the 9 * NCB steps of a tile are one straight line of code: with a branch per step every fragment
@@ -2310,7 +2325,7 @@ static_assert(kR3Lds <= 160 * 1024 && (64 * (kR3WRow / 16)) % 64 == 0, "LDS plan
 // KRSC (input gradient only): Wt is the layer's own filter bank [Cin = K][9][wp] with the output channel of this launch
 // innermost, and the bank is transposed on its way into LDS: the loads of a workgroup's share all in flight, its 16-byte
 // rows written as 2-byte elements.  A small layer is spared the launch that makes the k-innermost copy (16 x 16 channels,
-// 16 x 16, batch 4: input gradient 2.6 + 4.1 us in two launches -> 4.4 us), but every workgroup transposes the whole bank and
+// 16 x 16, batch 4: input gradient 2.6 + 2.9 us in two launches -> 3.2 us), but every workgroup transposes the whole bank and
 // the 2-byte writes meet in the same LDS banks: up to 16 output channels it is 2 to 39 % faster for every K, beyond that 3 %
 // slower to 33 % faster up to K * C = 768 (counted in eights), 11 % faster to 27 % slower (8 % in the middle) up to 1280, 2 %
 // faster to 66 % slower (29 %) up to 2048, 24 to 124 % slower at 3072 (56 x 56, 33 -> 56 channels, batch 10: 10.1 us in two launches, 14.9 so).  Those take the two launches.
@@ -2319,13 +2334,17 @@ template <bool FLIP, int NCB, bool KB1, bool KRSC = false>
 __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr uint32_t kBufOut = 0xffffffffu, kBufFlags = 0x00020000u;
-    constexpr int WSLOTS = kR3WRow / 16;                       // 16-byte slots per weight row (73, the last one padding)
-    constexpr int NWL = 64 * WSLOTS / 64, WL = (NWL + 7) / 8;  // wave-level loads of the weights, per wave
-    constexpr int NPL = (kR3PatchSlots + 63) / 64, PL = (NPL + 7) / 8;
+    constexpr int ROWS = r3_rows(KB1), WSLOTS = r3_wslots(NCB), WROW = WSLOTS * 16, WTAP = 32 * NCB;
+    constexpr int NWL = r3_wloads(NCB, KB1), WL = (NWL + 7) / 8;  // wave-level loads of the weights, per wave
+    constexpr int NCH = r3_chunks(NCB), NPL = r3_ploads(NCB), PL = (NPL + 7) / 8;
     constexpr int NKB = KB1 ? 2 : 1;  // accumulator blocks
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_b[];
     uint8_t* wl = smem_b;
-    uint8_t* pbuf = smem_b + kR3WBytes;
+    uint8_t* pbuf = smem_b + r3_wbytes(NCB, KB1);
+    // where a patch pixel's 16-byte chunks lie (see above)
+    auto chunk_xor = [](int pr, int pc) {
+        return NCH == 2 ? pr & 1 : NCH == 4 ? ((pc >> 2) & 1) | ((pr & 1) << 1) : ((pc >> 1) & 3) | ((pr & 1) << 2);
+    };
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int first = blockIdx.x * a.run, last = first + a.run < a.tiles ? first + a.run : a.tiles;
@@ -2333,7 +2352,7 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
 
     // ---- filter bank -> LDS, once ---------------------------------------------------------------------------------
     if constexpr (KRSC) {
-        constexpr int ROWS = KB1 ? 64 : 32, IT = (kR3KrscBank / 8 * 9 + 511) / 512;  // 8 channels of one filter's tap an item
+        constexpr int IT = (kR3KrscBank / 8 * 9 + 511) / 512;  // 8 channels of one filter's tap an item
         const int ncj = (a.Mout + 7) >> 3, items = a.Cin * 9 * ncj;
         uint4 v[IT];
         int k9[IT], cj[IT];
@@ -2351,10 +2370,10 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
         for (int i = 0; i < IT; ++i) {
             if (tid + 512 * i < items) {
                 const int k = (int)__umulhi((uint32_t)k9[i], 0x1c71c71du), t = k9[i] - k * 9;  // (exact below 2^29)
-                uint16_t* dst = reinterpret_cast<uint16_t*>(wl + cj[i] * 8 * kR3WRow + t * 128 + k * 2);
+                uint16_t* dst = reinterpret_cast<uint16_t*>(wl + cj[i] * 8 * WROW + t * WTAP + k * 2);
                 const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
 #pragma unroll
-                for (int e = 0; e < 8; ++e) dst[e * (kR3WRow / 2)] = (uint16_t)(w[e >> 1] >> ((e & 1) * 16));
+                for (int e = 0; e < 8; ++e) dst[e * (WROW / 2)] = (uint16_t)(w[e >> 1] >> ((e & 1) * 16));
             }
         }
         __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): written before the first tile's barrier
@@ -2363,29 +2382,29 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
             const_cast<uint16_t*>(a.Wt), 0, (uint32_t)(a.Mout * 9 * a.wp) * 2u, kBufFlags);
 #pragma unroll
         for (int i = 0; i < WL; ++i) {
-            const int idx = wave + 8 * i < NWL ? wave + 8 * i : NWL - 1;  // (past the end: the last one again)
-            const int sl = idx * 64 + lane;
-            const int m = sl / WSLOTS, wi = sl - m * WSLOTS;
-            const int t = wi >> 3, j = wi & 7;
-            const bool ok = wi < 72 && m < a.Mout && j * 8 < a.CinP;
-            const uint32_t off = ok ? (uint32_t)(((m * 9 + t) * a.wp + j * 8) * 2) : kBufOut;
-            // (the rest is never read where a tap has few steps: most lanes then have nothing to fetch)
-            if (NCB > 2 || (wi < 72 && m < (KB1 ? 64 : 32) && j < 2 * NCB))
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(w_srd, (lds_void_ptr)(wl + idx * 1024), 16, off, 0, 0, 0);
+            const int idx = wave + 8 * i;  // uniform
+            if (idx * 64 >= a.Mout * WSLOTS) break;  // (rows past the last output only reach outputs that are not written)
+            const uint32_t sl = idx * 64 + lane, m = sl / WSLOTS, wi = sl - m * WSLOTS;  // (unsigned: no sign to correct for)
+            const uint32_t t = wi / (2 * NCB), j = wi - t * (2 * NCB);
+            const bool ok = wi < WSLOTS - 1 && (int)m < a.Mout && (int)(j * 8) < a.CinP;
+            const uint32_t off = ok ? ((m * 9 + t) * a.wp + j * 8) * 2 : kBufOut;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_srd, (lds_void_ptr)(wl + idx * 1024), 16, off, 0, 0, 0);
         }
     }
     // ---- this lane's slots of a patch: the same places in every tile ---------------------------------------------------
-    const int pw = 8 * a.nbx + 2, patch_slots = (kR3TH * a.nby + 2) * pw * 8;
+    const int pw = 8 * a.nbx + 2, patch_slots = (kR3TH * a.nby + 2) * pw * NCH;
     int p_rc[PL];        // row << 16 | column; -1: fetches zeros; -2: nothing there that is ever read
     uint32_t p_rel[PL];  // byte offset of the chunk from the patch's first pixel
     int p_idx[PL];
 #pragma unroll
     for (int i = 0; i < PL; ++i) {
-        p_idx[i] = wave + 8 * i < NPL ? wave + 8 * i : NPL - 1;
-        const int sl = p_idx[i] * 64 + lane;
-        const int pr = (int)fast_div((uint32_t)sl >> 3, a.pw_magic), pc = (sl >> 3) - pr * pw, pj = sl & 7;
-        const int j = pj ^ (((pc >> 1) & 3) | ((pr & 1) << 2));  // the logical chunk that belongs at this place
-        p_rc[i] = sl >= patch_slots || j >= 2 * NCB ? -2 : j * 8 < a.CinP ? (pr << 16) | pc : -1;
+        p_idx[i] = wave + 8 * i;  // uniform
+        p_rc[i] = -2, p_rel[i] = 0;
+        if (p_idx[i] * 64 >= patch_slots) continue;
+        const uint32_t sl = p_idx[i] * 64 + lane;
+        const int pr = (int)fast_div(sl / NCH, a.pw_magic), pc = (int)(sl / NCH) - pr * pw, pj = (int)(sl % NCH);
+        const int j = pj ^ chunk_xor(pr, pc);  // the logical chunk that belongs at this place
+        p_rc[i] = (int)sl >= patch_slots || j >= 2 * NCB ? -2 : j * 8 < a.CinP ? (pr << 16) | pc : -1;
         p_rel[i] = (uint32_t)(((pr * a.W + pc) * a.ip + j * 8) * 2);
     }
     const uint32_t in_bytes = (uint32_t)(a.H * a.W * a.ip) * 2u, out_bytes = (uint32_t)(a.H * a.W * a.op) * 2u;
@@ -2402,7 +2421,7 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
         const __amdgpu_buffer_rsrc_t x_srd = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint16_t*>(a.X) + (int64_t)img * a.H * a.W * a.ip, 0, in_bytes, kBufFlags);
         const uint32_t xs = (uint32_t)((ih0 * a.W + iw0) * a.ip * 2);
-        uint8_t* dst = pbuf + buf * kR3PatchBytes;
+        uint8_t* dst = pbuf + buf * a.patch_bytes;
 #pragma unroll
         for (int i = 0; i < PL; ++i) {
             const int ih = ih0 + (p_rc[i] >> 16), iw = iw0 + (p_rc[i] & 0xffff);
@@ -2422,10 +2441,10 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
         const int pr = pr0 + t / 3, pc = pc0 + t % 3;
-        pb[t] = (uint32_t)((pr * pw + pc) * 128);
-        pk[t] = (uint32_t)((((pc >> 1) & 3) | ((pr & 1) << 2)) << 4);
+        pb[t] = (uint32_t)((pr * pw + pc) * (NCH * 16));
+        pk[t] = (uint32_t)(chunk_xor(pr, pc) << 4);
     }
-    const uint8_t* wa = wl + l32 * kR3WRow + h * 16;
+    const uint8_t* wa = wl + l32 * WROW + h * 16;
     const uint32_t hc = (uint32_t)(h << 4);
 
     issue(first, 0);
@@ -2450,13 +2469,13 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
             for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[kb][v] = 0.f;
-            const uint8_t* pp = pbuf + buf * kR3PatchBytes;
+            const uint8_t* pp = pbuf + buf * a.patch_bytes;
             bf16x8 xb[2], w0[2], w1[2];
             auto read_frags = [&](auto s_c) {
                 constexpr int S = decltype(s_c)::value, t = S / NCB, cb = S % NCB, B = S & 1, tw = FLIP ? 8 - t : t;
                 xb[B] = *reinterpret_cast<const bf16x8*>(pp + pb[t] + (((uint32_t)(cb << 5) | hc) ^ pk[t]));
-                w0[B] = *reinterpret_cast<const bf16x8*>(wa + tw * 128 + cb * 32);
-                if constexpr (KB1) w1[B] = *reinterpret_cast<const bf16x8*>(wa + 32 * kR3WRow + tw * 128 + cb * 32);
+                w0[B] = *reinterpret_cast<const bf16x8*>(wa + tw * WTAP + cb * 32);
+                if constexpr (KB1) w1[B] = *reinterpret_cast<const bf16x8*>(wa + 32 * WROW + tw * WTAP + cb * 32);
             };
             read_frags(std::integral_constant<int, 0>{});
             static_for<0, 9 * NCB>([&](auto s_c) {
@@ -2535,6 +2554,8 @@ inline int64_t r3_tile(Res3Args& a) {
 inline bool r3_krsc_bank_ok(int K, int C) { return C <= kR3KrscFewC || round_up(K, 8) * round_up(C, 8) <= kR3KrscMaxBank; }
 enum Res3Kind { kRes3Fwd = 0, kRes3Bwd = 1, kRes3BwdKrsc = 2 };
 inline hipError_t launch_conv3x3_res(Res3Args& a, Res3Kind kind, hipStream_t st) {
+    const int ncb = (a.CinP + 15) / 16, kb1 = a.Mout > 32 ? 1 : 0;
+    if (ncb < 1 || ncb > 4 || (kind == kRes3BwdKrsc && !r3_krsc_bank_ok(a.Cin, a.Mout))) return hipErrorInvalidValue;
     const int64_t tiles = r3_tile(a);
     if (tiles <= 0 || tiles > 0x3fffffff) return hipErrorInvalidValue;
     a.tiles = (int)tiles;
@@ -2554,11 +2575,11 @@ inline hipError_t launch_conv3x3_res(Res3Args& a, Res3Kind kind, hipStream_t st)
         {{k_conv3x3_res<true, 1, false, true>, k_conv3x3_res<true, 1, true, true>}, {k_conv3x3_res<true, 2, false, true>, nullptr},
          {k_conv3x3_res<true, 3, false, true>, nullptr}, {k_conv3x3_res<true, 4, false, true>, nullptr}}};
     static LdsOptIn opt_in[3][4][2];
-    const int ncb = (a.CinP + 15) / 16, kb1 = a.Mout > 32 ? 1 : 0;
-    if (ncb < 1 || ncb > 4 || (kind == kRes3BwdKrsc && !r3_krsc_bank_ok(a.Cin, a.Mout))) return hipErrorInvalidValue;
     const kern_t kern = kerns[kind][ncb - 1][kb1];
-    if (hipError_t e = opt_in[kind][ncb - 1][kb1].ensure(reinterpret_cast<const void*>(kern), kR3Lds); e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), kR3Lds, st, a);
+    a.patch_bytes = r3_patch_bytes(ncb, (kR3TH * a.nby + 2) * (8 * a.nbx + 2));
+    const int lds = r3_wbytes(ncb, kb1) + (a.run > 1 ? 2 : 1) * a.patch_bytes;
+    if (hipError_t e = opt_in[kind][ncb - 1][kb1].ensure(reinterpret_cast<const void*>(kern), kR3LdsMax); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, st, a);
     return hipSuccess;
 }
 

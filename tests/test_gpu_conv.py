@@ -250,6 +250,16 @@ def test_early_3x3_layers_with_resident_weights(case, pad_zero):
     _check_full(spec, 950 + sum(case), pitch8(spec.C), pitch8(spec.K), pitch8(spec.C), pad_zero=pad_zero)
 
 
+@pytest.mark.parametrize("C", [9, 16, 17, 32, 33, 48, 49, 64])
+@pytest.mark.parametrize("K", [7, 32, 33, 50, 64])
+@pytest.mark.parametrize("N,H,W", [(3, 10, 12), (70, 12, 33)], ids=["one_tile", "runs"])
+def test_early_3x3_layers_around_the_layouts_of_bank_and_patch(C, K, N, H, W):
+    """One to four 16-channel steps a tap, one and two output blocks, loads of bank and patch left out; one patch buffer and two."""
+    from gpu_util import pitch8
+    spec = _spec(N, H, W, C, K, 3, 1, 1)
+    _check_full(spec, 1700 + C + K, pitch8(C), pitch8(K), pitch8(C), pad_zero=True)
+
+
 BATCHED_FWD = [
     # independent forward convolutions in one call: pairs that share a launch of the direct kernel (same tile shape and
     # variant: a block's first convolution and its strided shortcut), pairs that do not, and the other kernels mixed in
