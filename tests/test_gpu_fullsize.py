@@ -215,6 +215,26 @@ def test_cfg2_resnet32_train_step_on_side_streams_against_oracle(norms_head, bra
     check(new_w)
 
 
+def test_weight_copies_in_line_or_aside_give_the_same_step(monkeypatch):
+    """The k-innermost weight copies on the caller's stream (a network of few weights) and beside the forward pass: two steps
+    with an optimizer step between them, so that the second needs new copies."""
+    from paper_1901_09290_amd import harness as hz
+    specs, _ = wl.resnet32_layers(N=4)
+    rng = np.random.Generator(np.random.PCG64(3))
+    host = [wl.conv_tensors(s, rng) for s in specs]
+    results = []
+    for most in (hz.CRSK_INLINE_MAX_WEIGHTS, 0):
+        monkeypatch.setattr(hz, "CRSK_INLINE_MAX_WEIGHTS", most)
+        net = hz.Network([hz.ConvLayer(s, host=t) for s, t in zip(specs, host)])
+        assert net.crsk_aside == (most == 0) and net.norm_jobs_tail is None
+        net.train_step(50.0)
+        net.optimizer_step(0.0, 1e-4, 0.0, 0.0)
+        net.train_step(50.0)
+        torch.cuda.synchronize()
+        results.append([t.clone() for l in net.layers for t in (l.y, l.dx, l.dw) if t is not None])
+    assert all(torch.equal(a, b) for a, b in zip(*results))
+
+
 # ---------------------------------------------------------------------------------------------- #
 # reconfiguration chain on whole networks
 # ---------------------------------------------------------------------------------------------- #
