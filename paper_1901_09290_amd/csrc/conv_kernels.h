@@ -1941,8 +1941,8 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
     for (int j = 0; j < LY; ++j) y_s[j] = (uint32_t)(it0 * BKP + (wave + NW * j) * RPLY) * (uint32_t)a.ypitch * 2u;
     const uint32_t x_step = (uint32_t)(BKP * a.xpitch) * 2u, y_step = (uint32_t)(BKP * a.ypitch) * 2u;
 
-    // issues the loads of the next reduction step (steps are issued in order) into `stage`
-    auto issue = [&](int stage) {
+    // issue the loads of the next reduction step (steps are issued in order, x before dy) into `stage`
+    auto issue_x = [&](int stage) {
         uint8_t* sbase = smem_b + stage * STAGE_BYTES;
         const bool whole = p_left >= BKP;  // uniform: every pixel of the step lies inside the slice
         if constexpr (XMODE == 0) {
@@ -1984,10 +1984,13 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
                 x_s[j] += x_step;
             }
         }
+    };
+    auto issue_y = [&](int stage) {
+        uint8_t* sbase = smem_b + stage * STAGE_BYTES;
         uint32_t vy[LY];
 #pragma unroll
         for (int j = 0; j < LY; ++j) vy[j] = y_v;
-        if (!whole) {
+        if (p_left < BKP) {
 #pragma unroll
             for (int j = 0; j < LY; ++j) vy[j] = yrel0 < p_left - NW * j * RPLY ? y_v : kBufOut;
         }
@@ -2079,11 +2082,13 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
     typedef std::integral_constant<int, 0> none;
 
     const int nk = it1 - it0;
-    const bool late = STAGES >= 3 && NW >= 8 && (wave & 4) != 0;
     // Loads run STAGES - 1 steps ahead and are issued at every step, also past the slice's end (they then fetch
     // zeros into a stage nobody multiplies): the number of loads in flight is the same at every wait.
 #pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s) issue(s);
+    for (int s = 0; s < STAGES - 1; ++s) {
+        issue_x(s);
+        issue_y(s);
+    }
     if constexpr (AHEAD) {
         // Fragments are read two sub-steps ahead of their MFMAs, across the barrier between stages: sub-step ks of stage t
         // multiplies what was read during stage t - 1 and then reads sub-step ks of stage t + 1.  A read behind the barrier
@@ -2102,10 +2107,13 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
                 if constexpr (AHEAD) wait_vmcnt<(STAGES - 3) * LPT>();  // the next stage has landed ...
                 else wait_vmcnt<(STAGES - 2) * LPT>();                  // this stage has landed ...
                 barrier_nofence();  // ... for every wave, and nobody reads the previous one any more
-                // Waves w and w+4 share a SIMD.  With three or more stages one of them issues the new stage's
-                // loads before its MFMAs and the other after, so the two phases overlap on the SIMD instead of
-                // running in lockstep.  The target buffer is the one consumed in the previous step either way.
-                if (!late) issue((s + STAGES - 1) % STAGES);
+                // A later step's loads go out between this step's MFMAs, x behind the first sub-step's and dy behind the last's,
+                // into the buffer consumed in the previous step.  A CU's address unit takes 16 clocks for each of a step's 16
+                // to 24 load instructions, which then do not hold up the fragment reads of the waves that come after.  Against all
+                // loads ahead of the MFMAs in one of the two waves of a SIMD and behind them in the other: 256 -> 256, 3 x 3, 14 x 14, batch
+                // 64 27.5 -> 27.0 us, 371 -> 115, 1 x 1, 28 x 28 15.9 -> 15.85, train step of ResNet-50 3308 -> 3288; all of them behind
+                // the first sub-step 27.4, 15.8 and 3285.  Both orders as branches on the wave: 60 us, 26 and 4627.
+                const int to = (s + STAGES - 1) % STAGES;
                 const uint32_t cur = (uint32_t)(s * STAGE_BYTES), nxt = (uint32_t)(((s + 1) % STAGES) * STAGE_BYTES);
                 if constexpr (!AHEAD) issue_reads(std::integral_constant<int, 0>{}, cur);
                 static_for<0, NKS>([&](auto ks_c) {
@@ -2121,8 +2129,9 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
                     } else {
                         multiply(buf{}, none{});
                     }
+                    if constexpr (KS == 0) issue_x(to);
                 });
-                if (late) issue((s + STAGES - 1) % STAGES);
+                issue_y(to);
             }
         }
     }
