@@ -126,16 +126,20 @@ __global__ void k_compact_nhwc(const uint16_t* __restrict__ x, int64_t pixels, i
 // writes one 16-byte store.  Channels of the last vector past Cp are written as zero: rows without holes keep
 // the memory system from merging partial lines (measured: stores of ragged rows with holes ran at half the
 // rate of whole rows).
-// Bound by its memory instructions one after the other: without its LDS reads the kernel takes 1 % less, without the stores
-// 23 %.  The wait for a run's loads counts every memory instruction before the next run's loads, so it also waits for the
-// stores of the run before, with one run of loads in flight: reads and writes take turns in a workgroup.  A
-// byte is read once and written once, so loads and stores are both marked as not to be kept (the loads alone: 5 % slower
-// than neither, the stores alone: no change, both: 4 % faster), and runs are whole 128-byte lines.  Sweep of the pruned
-// ResNet-50 at batch 64: 377 -> 360 us, at batch 40: 273 -> 254.  Runs of 64 KB, one workgroup of 512 threads a CU: 351 and
-// 261, single tensors of 1 to 256 MB 3 to 25 % slower.
-constexpr int kGatherThreads = 256;
-constexpr int kGatherChunk = 32 * 1024;                           // bytes of pixel rows per LDS buffer
-constexpr int kGatherLoads = kGatherChunk / (kGatherThreads * 16);  // 16-byte loads per thread and run (8)
+// Waves of their own load: a wave that loads and stores has both in one count, and its wait for a run's loads was also one for the
+// stores of the run before, so that reads and writes took turns in a workgroup.  Nothing waits for the stores now, but where
+// a tensor's channel indices are read, which most workgroups do for nearly every run: eight loads with a wait for each were as dear as
+// that, they go out together and ahead of the wait for the run.  Sweep of the pruned ResNet-50 at batch 64 358.8 us -> 346.6 (the
+// indices alone 353.0); one loader wave 348.6, four 346.6; three buffers of 24 KB 351.5, four or five of 16 KB 358 (bound by what a
+// run takes besides its bytes: barriers, a first LDS read), two of 40 KB, all of the CU's LDS, 345.0; 512 threads that gather 352.
+// At 0.1 to 0.4 of the channels gone: batch 16 216.7 -> 200.1, batch 40 243.7 -> 224.5, smaller ones as before (bound by the host).
+// A byte is read once and written once, so loads and stores are both marked as not to be kept (measured with one kind of wave: the
+// loads alone 5 % slower than neither, the stores alone no change, both 4 % faster), and runs are whole 128-byte lines.
+constexpr int kGatherThreads = 256;                              // that gather and store; the loader waves come after them
+constexpr int kGatherLoaders = 2;                                // waves that only load
+constexpr int kGatherChunk = 32 * 1024;                          // bytes of pixel rows per LDS buffer
+constexpr int kGatherLoads = kGatherChunk / (kGatherLoaders * 1024);  // load instructions of a loader wave per run
+static_assert(kGatherLoads < 64, "counted by vmcnt");
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_vptr;
 typedef const __attribute__((address_space(1))) void* glb_vptr;
@@ -171,7 +175,7 @@ struct GatherJobs {
     int n, total_chunks;
 };
 
-__global__ __launch_bounds__(kGatherThreads) void k_compact_nhwc_lds(const GatherJobs jobs) {
+__global__ __launch_bounds__(kGatherThreads + 64 * kGatherLoaders) void k_compact_nhwc_lds(const GatherJobs jobs) {
 #if defined(__HIP_DEVICE_COMPILE__)
     extern __shared__ __attribute__((aligned(16))) uint8_t sbuf[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -189,27 +193,49 @@ __global__ __launch_bounds__(kGatherThreads) void k_compact_nhwc_lds(const Gathe
         return lo;
     };
     // The tensor of a workgroup's next run is the one of its run before, or one soon after it.
-    int ji_load = job_of((int)blockIdx.x), ji = ji_load;
+    int ji = job_of((int)blockIdx.x);
     auto advance = [&](int& j, int g) {
         while (j + 1 < jobs.n && jobs.j[j + 1].chunk0 <= g) ++j;
     };
-    // Every wave issues exactly kGatherLoads load instructions per run (lanes past the run's end re-read its last
-    // 16 bytes into a slot nobody reads), so "at most kGatherLoads outstanding" means the previous run has landed.
-    auto issue = [&](int g, int buf) {
-        advance(ji_load, g);
-        const GatherJob& J = jobs.j[ji_load];
-        const int64_t p0 = (int64_t)(g - J.chunk0) * J.ppc;
-        const int np = (int)min((int64_t)J.ppc, J.pixels - p0);
-        const int n16 = np * (J.x_cpitch >> 3);
-        const uint8_t* src = reinterpret_cast<const uint8_t*>(J.x + p0 * J.x_cpitch);
+    if (wave >= kGatherThreads / 64) {  // a loader wave
+        const int lw = wave - kGatherThreads / 64;
+        // Exactly kGatherLoads load instructions per run (lanes past the run's end re-read its last 16 bytes into a slot
+        // nobody reads), so "at most kGatherLoads outstanding" means the previous run has landed.
+        auto issue = [&](int g, int buf) {
+            advance(ji, g);
+            const GatherJob& J = jobs.j[ji];
+            const int64_t p0 = (int64_t)(g - J.chunk0) * J.ppc;
+            const int np = (int)min((int64_t)J.ppc, J.pixels - p0);
+            const int n16 = np * (J.x_cpitch >> 3);
+            const uint8_t* src = reinterpret_cast<const uint8_t*>(J.x + p0 * J.x_cpitch);
 #pragma unroll
-        for (int k = 0; k < kGatherLoads; ++k) {
-            const int i0 = k * kGatherThreads + wave * 64;
-            const int i = min(i0 + lane, n16 - 1);
-            __builtin_amdgcn_global_load_lds((glb_vptr)(uintptr_t)(src + (size_t)i * 16),
-                                             (lds_vptr)(sbuf + buf * kGatherChunk + i0 * 16), 16, 0, 2);  // nt
+            for (int k = 0; k < kGatherLoads; ++k) {
+                const int i0 = (k * kGatherLoaders + lw) * 64;
+                const int i = min(i0 + lane, n16 - 1);
+                __builtin_amdgcn_global_load_lds((glb_vptr)(uintptr_t)(src + (size_t)i * 16),
+                                                 (lds_vptr)(sbuf + buf * kGatherChunk + i0 * 16), 16, 0, 2);  // nt
+            }
+        };
+        int g = blockIdx.x;
+        if (g < total) issue(g, 0);
+        if (jobs.guard.n && some_empty(jobs.guard)) {  // (behind the first run's loads, whose latency covers the counts')
+            __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));  // nothing may land in LDS after the workgroup has gone
+            return;
         }
-    };
+        for (int it = 0; g < total; g += gridDim.x, ++it) {
+            if (g + (int)gridDim.x < total) {
+                issue(g + gridDim.x, (it & 1) ^ 1);
+                __builtin_amdgcn_s_waitcnt((kGatherLoads & 15) | (7 << 4) | (15 << 8) | ((kGatherLoads >> 4) << 14));
+            } else {
+                __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));
+            }
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();            // this run has landed for every wave
+            __builtin_amdgcn_s_barrier();            // everyone is done with its buffer, which the next loads refill
+            asm volatile("" ::: "memory");
+        }
+        return;
+    }
 
     // gather-side state of the current tensor
     int cur = -1, ppb = 1, pp = 0, v = 0, row_bytes = 0, out_cpitch = 0;
@@ -217,24 +243,10 @@ __global__ __launch_bounds__(kGatherThreads) void k_compact_nhwc_lds(const Gathe
     bool active = false;
     uint32_t id2[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // byte offset of each source channel inside a pixel row
 
+    if (jobs.guard.n && some_empty(jobs.guard)) return;
     int g = blockIdx.x;
-    if (g < total) issue(g, 0);
-    if (jobs.guard.n && some_empty(jobs.guard)) {  // (behind the first run's loads, whose latency covers the counts')
-        __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));  // nothing may land in LDS after the workgroup has gone
-        return;
-    }
     for (int it = 0; g < total; g += gridDim.x, ++it) {
         const int buf = it & 1;
-        const bool more = g + (int)gridDim.x < total;
-        if (more) {
-            issue(g + gridDim.x, buf ^ 1);
-            __builtin_amdgcn_s_waitcnt((kGatherLoads & 15) | (7 << 4) | (15 << 8) | ((kGatherLoads >> 4) << 14));
-        } else {
-            __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));
-        }
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();            // this run has landed for every wave
-        asm volatile("" ::: "memory");
         advance(ji, g);
         const GatherJob& J = jobs.j[ji];
         if (ji != cur) {                         // uniform: a new tensor, new thread roles and channel indices
@@ -246,15 +258,24 @@ __global__ __launch_bounds__(kGatherThreads) void k_compact_nhwc_lds(const Gathe
             pp = tid / nvec;
             v = tid - pp * nvec;
             active = pp < ppb && Cp > 0;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) id2[e] = (active && v * 8 + e < Cp) ? 2u * (uint32_t)J.idx[v * 8 + e] : 0u;
             const int nlast = Cp - v * 8;        // valid channels of this thread's vector (>= 8: all)
+            if (active) {                        // (then nlast >= 1; the loads go out together: one latency, not eight)
+                const int* ix = J.idx + v * 8;
+                int c[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) c[e] = ix[min(e, nlast - 1)];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) id2[e] = e < nlast ? 2u * (uint32_t)c[e] : 0u;
+            }
             auto halves = [&](int k) { return (k < nlast ? 0xFFFFu : 0u) | (k + 1 < nlast ? 0xFFFF0000u : 0u); };
             m0 = halves(0); m1 = halves(2); m2 = halves(4); m3 = halves(6);
             row_bytes = J.x_cpitch * 2;
         }
         const int64_t p0 = (int64_t)(g - J.chunk0) * J.ppc;
         const int np = (int)min((int64_t)J.ppc, J.pixels - p0);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();            // this run has landed
+        asm volatile("" ::: "memory");
         if (active) {
             for (int p = pp; p < np; p += ppb) {
                 const uint32_t r = lds_base + (uint32_t)(buf * kGatherChunk + p * row_bytes);
@@ -614,7 +635,7 @@ static int32_t launch_gather_jobs(GatherJobs& t, hipStream_t st) {
         return PT_ERR_LAUNCH;
     }
     const unsigned grid = (unsigned)(t.total_chunks < 512 ? t.total_chunks : 512);  // two resident workgroups per CU
-    hipLaunchKernelGGL(k_compact_nhwc_lds, dim3(grid), dim3(kGatherThreads), 2 * kGatherChunk, st, t);
+    hipLaunchKernelGGL(k_compact_nhwc_lds, dim3(grid), dim3(kGatherThreads + 64 * kGatherLoaders), 2 * kGatherChunk, st, t);
     t.n = 0;
     t.total_chunks = 0;
     return launch_status();

@@ -705,6 +705,19 @@ def test_activation_gather_over_many_tensors(sizes):
         assert (out.view(-1)[pixels * op:] == 7).all()
 
 
+@pytest.mark.parametrize("n", range(9, 17))
+@pytest.mark.parametrize("C,pixels", [(16, 1024 * 512 * 5 + 1), (1000, 17)])
+def test_activation_gather_last_vector_and_many_runs(C, pixels, n):
+    """One to eight channels in the last vector of a row; five runs a workgroup and one row more, and two runs in all."""
+    from gpu_util import DEV
+    idx = torch.from_numpy(np.sort(np.random.Generator(np.random.PCG64(n)).choice(C, n, replace=False)).astype(np.int32)).to(DEV)
+    x = torch.randint(-32768, 32767, (pixels, (C + 7) // 8 * 8), dtype=torch.int16, device=DEV)
+    out = torch.full((pixels + 1, 16), 7, dtype=torch.int16, device=DEV)
+    B.compact_nhwc(x.view(torch.bfloat16), pixels, C, x.shape[1], idx, n, out.view(torch.bfloat16), 16)
+    torch.cuda.synchronize()
+    assert torch.equal(out[:pixels, :n], x[:, idx.long()]) and not out[:pixels, n:].any() and (out[pixels] == 7).all()
+
+
 @pytest.mark.parametrize("n_counts,zero_at", [(1, 0), (1, None), (64, 63), (65, 64), (130, 127), (130, None), (0, None)])
 def test_guarded_compaction_writes_all_or_nothing(n_counts, zero_at):
     """One count of 0 anywhere (before, at and past the 64 that one load covers) keeps all three kinds of gather from
