@@ -2110,9 +2110,11 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
                 // A later step's loads go out between this step's MFMAs, x behind the first sub-step's and dy behind the last's,
                 // into the buffer consumed in the previous step.  A CU's address unit takes 16 clocks for each of a step's 16
                 // to 24 load instructions, which then do not hold up the fragment reads of the waves that come after.  Against all
-                // loads ahead of the MFMAs in one of the two waves of a SIMD and behind them in the other: 256 -> 256, 3 x 3, 14 x 14, batch
-                // 64 27.5 -> 27.0 us, 371 -> 115, 1 x 1, 28 x 28 15.9 -> 15.85, train step of ResNet-50 3308 -> 3288; all of them behind
-                // the first sub-step 27.4, 15.8 and 3285.  Both orders as branches on the wave: 60 us, 26 and 4627.
+                // loads ahead of the MFMAs in one of the two waves of a SIMD and behind them in the other, us on two boxes: train step
+                // of ResNet-50 3308 -> 3288 and 3189 -> 3175, pruned 2726 -> 2719 and 2681 -> 2665; calls by themselves the same within
+                // what boxes and builds differ by (256 -> 256, 3 x 3, 14 x 14, batch 64 27.5 -> 27.0 and 26.1 -> 26.3, 371 -> 115, 1 x 1,
+                // 28 x 28 15.9 -> 15.85 and 15.5 -> 15.55).  All of them behind the first sub-step: 27.4, 15.8, steps 3285 and 2725 on
+                // the first box.  Both orders as branches on the wave around every part: 60, 26, 4627 and 3418.
                 const int to = (s + STAGES - 1) % STAGES;
                 const uint32_t cur = (uint32_t)(s * STAGE_BYTES), nxt = (uint32_t)(((s + 1) % STAGES) * STAGE_BYTES);
                 if constexpr (!AHEAD) issue_reads(std::integral_constant<int, 0>{}, cur);
