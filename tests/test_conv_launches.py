@@ -1,0 +1,47 @@
+"""CPU: which kernel a convolution call takes, by the library's own host code (see launches.py)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from launches import HERE, ROOT, of_calls
+
+
+@pytest.fixture(scope="module")
+def launches():
+    if shutil.which("gcc") is None:
+        pytest.skip("no gcc")
+    build = os.path.join(ROOT, "_build", "launches")
+    os.makedirs(build, exist_ok=True)
+    so = os.path.join(build, "recorder.so")
+    subprocess.run(["gcc", "-std=c11", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "launch_recorder.c")], check=True)
+    return lambda calls: of_calls(calls, so)
+
+
+# Calls of few tiles: (call, N, H, W, C, K, R, stride), us in 128 x 64, 64 x 64 and 32 x 32 tiles (mean of operands in the caches and
+# from memory).
+FEW_TILES = [
+    # reductions of one to four steps
+    (("fwd", 1, 11, 13, 96, 32, 1, 2), (2.88, 3.44, 3.38)), (("fwd", 2, 49, 50, 66, 28, 1, 1), (3.36, 3.81, 3.70)),
+    (("fwd", 97, 5, 6, 127, 68, 1, 1), (3.56, 4.14, 4.46)), (("fwd", 2, 28, 28, 128, 512, 1, 1), (3.74, 4.19, 7.29)),
+    (("fwd", 7, 24, 24, 192, 32, 1, 1), (3.63, 4.15, 4.05)), (("fwd", 46, 14, 14, 69, 133, 1, 2), (3.60, 3.94, 4.63)),
+    (("fwd", 1, 18, 19, 128, 1440, 1, 1), (3.79, 4.19, 4.97)), (("bwd_data", 2, 5, 7, 32, 96, 1, 1), (2.91, 3.52, 3.42)),
+    (("bwd_data", 24, 20, 22, 32, 96, 1, 1), (3.68, 4.15, 4.81)), (("bwd_data", 1, 6, 7, 63, 72, 1, 1), (3.11, 3.51, 3.39)),
+    # the four classes of a strided gradient, two to eight steps
+    (("bwd_data", 25, 15, 17, 352, 96, 3, 2), (6.53, 8.71, 16.26)),
+    # a filter smaller than its stride: a tile clears the other pixels of its cells
+    (("bwd_data", 41, 6, 8, 64, 96, 1, 2), (4.86, 3.98, 3.85)), (("bwd_data", 2, 46, 48, 608, 177, 1, 2), (6.38, 5.23, 8.17)),
+    (("bwd_data", 102, 9, 11, 185, 205, 1, 2), (6.15, 5.18, 7.79)), (("bwd_data", 2, 43, 44, 832, 96, 1, 2), (6.11, 5.13, 8.75)),
+    # six steps and more: small tiles, larger ones where there are many
+    (("bwd_data", 6, 11, 13, 64, 352, 1, 1), (4.72, 4.65, 4.08)), (("bwd_data", 2, 14, 14, 118, 655, 1, 1), (6.38, 5.83, 4.67)),
+    (("fwd", 40, 14, 14, 187, 17, 3, 1), (8.96, 9.01, 6.34)), (("fwd", 12, 9, 9, 224, 480, 3, 2), (12.74, 10.32, 6.86)),
+    (("fwd", 32, 7, 7, 820, 324, 1, 1), (7.41, 6.64, 8.88)), (("bwd_data", 37, 9, 11, 154, 80, 3, 1), (8.31, 7.48, 9.69)),
+    (("bwd_data", 3, 46, 46, 192, 704, 1, 2), (7.53, 6.25, 6.79)), (("fwd", 14, 8, 9, 441, 1161, 1, 1), (5.52, 6.65, 10.65)),
+]
+
+
+def test_few_tiles_take_the_faster_form(launches):
+    forms = [["k_igemm_dl", 128, 64], ["k_igemm_small", 64, 64], ["k_igemm_small", 32, 32]]
+    for (c, us), got in zip(FEW_TILES, launches([[*c, c[6] // 2, True] for c, _ in FEW_TILES])):
+        assert got[0]["kernel"][:3] == forms[us.index(min(us))], (c, us, got)
