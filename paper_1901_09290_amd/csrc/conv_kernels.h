@@ -2082,13 +2082,16 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
     typedef std::integral_constant<int, 0> none;
 
     const int nk = it1 - it0;
+    constexpr bool TURNS = XMODE == 1 && AHEAD;  // (see the loop)
+    [[maybe_unused]] const bool late = (wave & 4) != 0;  // waves w and w + 4 share a SIMD
+    auto issue = [&](int stage) {
+        issue_x(stage);
+        issue_y(stage);
+    };
     // Loads run STAGES - 1 steps ahead and are issued at every step, also past the slice's end (they then fetch
     // zeros into a stage nobody multiplies): the number of loads in flight is the same at every wait.
 #pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s) {
-        issue_x(s);
-        issue_y(s);
-    }
+    for (int s = 0; s < STAGES - 1; ++s) issue(s);
     if constexpr (AHEAD) {
         // Fragments are read two sub-steps ahead of their MFMAs, across the barrier between stages: sub-step ks of stage t
         // multiplies what was read during stage t - 1 and then reads sub-step ks of stage t + 1.  A read behind the barrier
@@ -2111,11 +2114,16 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
                 // into the buffer consumed in the previous step.  A CU's address unit takes 16 clocks for each of a step's 16
                 // to 24 load instructions, which then do not hold up the fragment reads of the waves that come after.  Against all
                 // loads ahead of the MFMAs in one of the two waves of a SIMD and behind them in the other, us on two boxes: train step
-                // of ResNet-50 3308 -> 3288 and 3189 -> 3175, pruned 2726 -> 2719 and 2681 -> 2665; calls by themselves the same within
-                // what boxes and builds differ by (256 -> 256, 3 x 3, 14 x 14, batch 64 27.5 -> 27.0 and 26.1 -> 26.3, 371 -> 115, 1 x 1,
-                // 28 x 28 15.9 -> 15.85 and 15.5 -> 15.55).  All of them behind the first sub-step: 27.4, 15.8, steps 3285 and 2725 on
-                // the first box.  Both orders as branches on the wave around every part: 60, 26, 4627 and 3418.
+                // of ResNet-50 3308 -> 3288 and 3189 -> 3175, pruned 2726 -> 2719 and 2681 -> 2665; calls by themselves with XMODE 0
+                // 0.5 to 4 % faster, with 2 up to 2 %.  With 1 alone on the chip the tests of an x load's row and column, some 20
+                // instructions, stand between the MFMAs as well and cost more than that: 740 such calls take 1.1 % longer, 72 of
+                // them more than 3 % (64 x 56 x 56, 50 -> 39 channels, 3 x 3: 32.5 us against 31.0).  They keep the turns of the
+                // waves.  (All loads behind the MFMAs in every wave: 7 % longer than so.  Both orders as branches on the wave
+                // around every part: 60 us where it is 27.)
                 const int to = (s + STAGES - 1) % STAGES;
+                if constexpr (TURNS) {
+                    if (!late) issue(to);
+                }
                 const uint32_t cur = (uint32_t)(s * STAGE_BYTES), nxt = (uint32_t)(((s + 1) % STAGES) * STAGE_BYTES);
                 if constexpr (!AHEAD) issue_reads(std::integral_constant<int, 0>{}, cur);
                 static_for<0, NKS>([&](auto ks_c) {
@@ -2131,9 +2139,10 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
                     } else {
                         multiply(buf{}, none{});
                     }
-                    if constexpr (KS == 0) issue_x(to);
+                    if constexpr (KS == 0 && !TURNS) issue_x(to);
                 });
-                issue_y(to);
+                if constexpr (!TURNS) issue_y(to);
+                else if (late) issue(to);
             }
         }
     }
