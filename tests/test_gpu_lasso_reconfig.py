@@ -718,6 +718,23 @@ def test_activation_gather_last_vector_and_many_runs(C, pixels, n):
     assert torch.equal(out[:pixels, :n], x[:, idx.long()]) and not out[:pixels, n:].any() and (out[pixels] == 7).all()
 
 
+@pytest.mark.parametrize("runs", [768, 769, 1024, 1025])
+@pytest.mark.parametrize("tensors", [1, 6, 7])
+def test_activation_gather_of_about_two_runs_a_workgroup(runs, tensors):
+    """Either side of the lines between which a workgroup reads both of its runs ahead of the first store: runs of 256 pixels of
+    64 channels, the last one of a tensor a pixel short."""
+    from gpu_util import DEV
+    C, n = 64, 45
+    share = [runs // tensors + (i < runs % tensors) for i in range(tensors)]
+    idx = torch.from_numpy(np.sort(np.random.Generator(np.random.PCG64(runs)).choice(C, n, replace=False)).astype(np.int32)).to(DEV)
+    xs = [torch.randint(-32768, 32767, (256 * r - 1, C), dtype=torch.int16, device=DEV) for r in share]
+    outs = [torch.full((x.shape[0] + 1, 48), 7, dtype=torch.int16, device=DEV) for x in xs]
+    B.compact_nhwc_batched([B.gather_nhwc(x.view(torch.bfloat16), x.shape[0], C, C, idx, n, o.view(torch.bfloat16), 48) for x, o in zip(xs, outs)])
+    torch.cuda.synchronize()
+    for x, o in zip(xs, outs):
+        assert torch.equal(o[:-1, :n], x[:, idx.long()]) and not o[:-1, n:].any() and (o[-1] == 7).all()
+
+
 @pytest.mark.parametrize("n_counts,zero_at", [(1, 0), (1, None), (64, 63), (65, 64), (130, 127), (130, None), (0, None)])
 def test_guarded_compaction_writes_all_or_nothing(n_counts, zero_at):
     """One count of 0 anywhere (before, at and past the 64 that one load covers) keeps all three kinds of gather from
