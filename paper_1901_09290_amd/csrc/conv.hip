@@ -448,24 +448,25 @@ static int32_t bwd_data_classes(const pt_conv_desc* d, const uint16_t* dy, const
         const BwdClass c = bwd_data_class(d, ca, cb);
         return c.gH > 0 && c.gW > 0 && c.TR > 0 && c.TS > 0;
     };
-    // several classes: one choice of kernel for all of them, by what they are together
-    int kernel = -1;
-    if (vec && with_taps > 1 && with_taps <= kIgemmMaxProblems) {
-        IgemmArgs all[kIgemmMaxProblems];
+    // several classes: one choice of kernel for each four of them, which share a launch, by what they are together (each by itself
+    // they would not all choose the same and share fewer: 24 x 24 297 <- 5, 4 x 4 at stride 3, batch 24, 15.2 us in four launches)
+    auto pick = [&](int first) {  // first class of the four, counted row by row
+        IgemmArgs some[kIgemmMaxProblems];
         int n = 0;
         int64_t tiles128 = 0;
         bool small_ok = true;
-        for (int ca = 0; ca < d->stride_h; ++ca)
-            for (int cb = 0; cb < d->stride_w; ++cb)
-                if (has_taps(ca, cb)) {
-                    all[n] = args_of(ca, cb);
-                    igemm_fold(all[n]);
-                    tiles128 += ceil_div(all[n].M, 128) * ceil_div(all[n].Nout, 128);
-                    small_ok = small_ok && igemm_small_ok(all[n]);
-                    ++n;
-                }
-        kernel = tiles128 >= 256 ? kIgemmLarge : small_ok ? pick_igemm_kernel(all, n) : 0;
-    }
+        for (int i = first; i < d->stride_h * d->stride_w && n < kIgemmMaxProblems; ++i) {
+            const int ca = i / d->stride_w, cb = i % d->stride_w;
+            if (!has_taps(ca, cb)) continue;
+            some[n] = args_of(ca, cb);
+            igemm_fold(some[n]);
+            tiles128 += ceil_div(some[n].M, 128) * ceil_div(some[n].Nout, 128);
+            small_ok = small_ok && igemm_small_ok(some[n]);
+            ++n;
+        }
+        return tiles128 >= 256 ? kIgemmLarge : small_ok ? pick_igemm_kernel(some, n) : 0;
+    };
+    int kernel = -1, seen = 0;
     for (int ca = 0; ca < d->stride_h; ++ca) {
         for (int cb = 0; cb < d->stride_w; ++cb) {
             BwdClass c = bwd_data_class(d, ca, cb);
@@ -481,6 +482,7 @@ static int32_t bwd_data_classes(const pt_conv_desc* d, const uint16_t* dy, const
                 rc = launch_status();
             } else {
                 IgemmArgs a = args_of(ca, cb);
+                if (vec && with_taps > 1 && seen++ % kIgemmMaxProblems == 0) kernel = pick(ca * d->stride_w + cb);
                 rc = pend.add(a, vec, st, kernel);
             }
             if (rc != PT_OK) return rc;

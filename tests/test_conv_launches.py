@@ -45,3 +45,11 @@ def test_few_tiles_take_the_faster_form(launches):
     forms = [["k_igemm_dl", 128, 64], ["k_igemm_small", 64, 64], ["k_igemm_small", 32, 32]]
     for (c, us), got in zip(FEW_TILES, launches([[*c, c[6] // 2, True] for c, _ in FEW_TILES])):
         assert got[0]["kernel"][:3] == forms[us.index(min(us))], (c, us, got)
+
+
+@pytest.mark.parametrize("case", [(24, 24, 24, 297, 5, 4, 3, 2), (62, 16, 16, 289, 4, 5, 3, 2), (18, 27, 27, 328, 51, 5, 3, 2),
+                                  (15, 6, 7, 13, 128, 5, 3, 2)])
+def test_classes_of_a_gradient_share_launches_whatever_their_number(launches, case):
+    """The nine classes of a gradient at stride 3, four to a launch: each four choose one form."""
+    (got,) = launches([["bwd_data", *case, True]])
+    assert [g["grid"][1] for g in got] == [4, 4, 1], got

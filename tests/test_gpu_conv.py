@@ -154,6 +154,8 @@ FEW_TILES = [
     ((8, 15, 14, 256, 512, 1, 2, 0), False),    # strided 1 x 1: zeros for the untouched pixels, cells cut by the border
     ((8, 15, 15, 253, 512, 1, 3, 0), True),     # the same at stride 3, ragged channels
     ((4, 32, 32, 5, 16, 5, 1, 2), True),        # filter rows folded
+    ((4, 24, 23, 297, 5, 4, 3, 2), True),       # nine classes, four to a launch, 64 x 64 tiles,
+    ((15, 6, 7, 13, 128, 5, 3, 2), True),       # ... 32 x 32 tiles
     ((2, 7, 7, 2048, 520, 1, 1, 0), False),     # weights the larger operand: neighbouring tiles share weights
 ]
 
