@@ -121,20 +121,22 @@ inline void igemm_fold(IgemmArgs& a) {
 // Which kernel takes the problems of a call that fill less than one round of 128 x 128 tiles (`as`: one problem, or the
 // stride-parity classes of an input gradient, which share a launch).  Estimated times in us: up to 256 workgroups take `steps`
 // steps of t1 and f1 for set-up and stores, up to 512 (two on a CU, or one after the other) t2 and f2; z = what smaller tiles
-// save where a tile also clears pixels that no tap reaches (zf_h * zf_w > 1).  Fitted to 3939 calls (random layers of 16 to
-// 2048 channels at batch 1 to 128, layers of ResNet-50 at published and pruned widths), each in all forms, mean of operands in
-// the caches and from memory: always one of them 38.61 / 37.07 / 41.63 ms, chosen 29.90, the best form of each call 29.80; 775
-// other calls 5.82 and 5.80.  What is fitted is a call's ratio to its best form: fitted to the sum of the times, in which calls of 3
-// us count for little, the choice took small tiles for reductions of one to four steps as well, where 128 x 64 tiles, with no
-// partial tiles to add, are up to a quarter faster (1 x 1, 96 -> 32 channels, 42 pixels: 3.38 -> 2.88 us), 314 of the calls
-// more than 4 % above their best form; now 45.
+// save of the stores of a 128 x 64 tile, as far as it is filled, where it also clears pixels that no tap reaches (zf_h * zf_w >
+// 1).  Fitted to 3939 calls (random layers of 16 to 2048 channels at batch 1 to 128, layers of ResNet-50 at published and pruned
+// widths), each in all forms, mean of operands in the caches and from memory: always one of them 38.61 / 37.07 / 41.63 ms,
+// chosen 29.89, the best form of each call 29.80; 775 other calls 5.82 and 5.80.  What is fitted is a call's ratio to its best
+// form: fitted to the sum of the times, in which calls of 3 us count for little, the choice took small tiles for reductions of
+// one to four steps as well, where 128 x 64 tiles, with no partial tiles to add, are up to a quarter faster (1 x 1, 96 -> 32
+// channels, 42 pixels: 3.38 -> 2.88 us), 314 of the calls more than 4 % above their best form; now 36.
 // 0 = k_igemm_dl at 128 x 64, 1 = k_igemm_small at 64 x 64, 2 = at 32 x 32: all of them two workgroups on a CU.
 inline int pick_igemm_kernel(const IgemmArgs* as, int n) {
     struct Est { int bm, bn, nb; float t1, t2, f1, f2, z; };
     constexpr int FORMS = 3;
-    constexpr Est est[FORMS] = {{128, 64, 1, 0.378f, 0.428f, 0.360f, 2.092f, 0.f},
-                                {64, 64, 1, 0.228f, 0.387f, 0.921f, 2.540f, 0.333f},
-                                {32, 32, 2, 0.231f, 0.343f, 1.164f, 1.714f, 0.476f}};
+    constexpr Est est[FORMS] = {{128, 64, 1, 0.373f, 0.423f, 0.346f, 2.114f, 0.f},
+                                {64, 64, 1, 0.232f, 0.381f, 0.877f, 2.569f, 0.477f},
+                                {32, 32, 2, 0.235f, 0.335f, 1.100f, 1.816f, 0.768f}};
+    const bool clears = as[0].zf_h * as[0].zf_w > 1;  // (then it is the only class)
+    const float filled = clears ? fminf((float)as[0].M, 128.f) * fminf((float)as[0].Nout, 64.f) / (128.f * 64.f) : 0.f;
     int best = 0;
     float best_us = 1e30f;
     for (int k = 0; k < FORMS; ++k) {
@@ -151,7 +153,7 @@ inline int pick_igemm_kernel(const IgemmArgs* as, int n) {
         const float avg = (float)tile_steps / (float)tiles;
         const float last_steps = full ? avg : (float)longest;
         const float last = rem == 0 ? 0.f : rem <= 256 ? last_steps * est[k].t1 + est[k].f1 : last_steps * est[k].t2 + est[k].f2;
-        const float us = (float)full * (avg * est[k].t2 + est[k].f2) + last - (as[0].zf_h * as[0].zf_w > 1 ? est[k].z : 0.f);
+        const float us = (float)full * (avg * est[k].t2 + est[k].f2) + last - filled * est[k].z;
         if (us < best_us) {
             best_us = us;
             best = k;

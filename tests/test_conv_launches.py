@@ -33,6 +33,8 @@ FEW_TILES = [
     # a filter smaller than its stride: a tile clears the other pixels of its cells
     (("bwd_data", 41, 6, 8, 64, 96, 1, 2), (4.86, 3.98, 3.85)), (("bwd_data", 2, 46, 48, 608, 177, 1, 2), (6.38, 5.23, 8.17)),
     (("bwd_data", 102, 9, 11, 185, 205, 1, 2), (6.15, 5.18, 7.79)), (("bwd_data", 2, 43, 44, 832, 96, 1, 2), (6.11, 5.13, 8.75)),
+    # ... few of them where it is hardly filled
+    (("bwd_data", 4, 9, 10, 35, 57, 1, 2), (3.36, 3.88, 3.94)), (("bwd_data", 1, 6, 7, 33, 98, 1, 2), (3.49, 3.77, 3.69)),
     # six steps and more: small tiles, larger ones where there are many
     (("bwd_data", 6, 11, 13, 64, 352, 1, 1), (4.72, 4.65, 4.08)), (("bwd_data", 2, 14, 14, 118, 655, 1, 1), (6.38, 5.83, 4.67)),
     (("fwd", 40, 14, 14, 187, 17, 3, 1), (8.96, 9.01, 6.34)), (("fwd", 12, 9, 9, 224, 480, 3, 2), (12.74, 10.32, 6.86)),
