@@ -55,3 +55,33 @@ def test_classes_of_a_gradient_share_launches_whatever_their_number(launches, ca
     """The nine classes of a gradient at stride 3, four to a launch: each four choose one form."""
     (got,) = launches([["bwd_data", *case, True]])
     assert [g["grid"][1] for g in got] == [4, 4, 1], got
+
+
+def _forms(launches, calls):
+    return [[g["kernel"] for g in got] for got in launches([list(c) for c in calls])]
+
+
+def test_cases_of_the_gpu_tests_reach_the_forms_they_are_for(launches):
+    """The lists of test_gpu_conv.py whose cases were chosen for one kernel."""
+    from test_gpu_conv import DEEP, TILES_32, TILES_64
+    for (call, case), got in zip(TILES_64, _forms(launches, [(call, *case, True) for call, case in TILES_64])):
+        assert [k[:3] for k in got] == [["k_igemm_small", 64, 64]], (call, case, got)
+    for case, got in zip(TILES_32, _forms(launches, [("fwd", *case, True) for case in TILES_32])):
+        assert [k[:3] for k in got] == [["k_igemm_small", 32, 32]], (case, got)
+    for case, got in zip(TILES_32[4:], _forms(launches, [("bwd_data", *case, True) for case in TILES_32[4:]])):
+        assert [k[:3] for k in got] == [["k_igemm_small", 32, 32]], (case, got)
+    deep = _forms(launches, [("fwd", *case, zero) for case, zero in DEEP])
+    for (case, _), got in zip(DEEP, deep):
+        assert [k[0] for k in got] == ["k_igemm_dl"] and got[0][-1] == 1, (case, got)
+    # (tile, ragged, no tap outside the image)
+    assert {(k[1], k[2], k[6], k[9]) for (k,) in deep} == {(m, 128, r, a) for m in (128, 256) for r in (0, 1) for a in (0, 1)}
+
+
+def test_runs_of_tiles_have_two_patch_buffers(launches):
+    """The larger images of the early 3 x 3 layers: more LDS than the same rows in one tile a workgroup take, for every layout."""
+    from test_gpu_conv import LAYOUTS
+    _, (N, H, W) = LAYOUTS["images"]
+    shapes = [(C, K) for C in LAYOUTS["C"] for K in LAYOUTS["K"]]
+    one, two = ([g[0] for g in launches([["fwd", n, H, W, C, K, 3, 1, 1, True] for C, K in shapes])] for n in (N // 2, N))
+    for shape, a, b in zip(shapes, one, two):
+        assert a["kernel"] == b["kernel"] and b["kernel"][0] == "k_conv3x3_res" and b["lds"] > a["lds"], (shape, a, b)

@@ -157,6 +157,8 @@ FEW_TILES = [
     ((4, 24, 23, 297, 5, 4, 3, 2), True),       # nine classes, four to a launch, 64 x 64 tiles,
     ((15, 6, 7, 13, 128, 5, 3, 2), True),       # ... 32 x 32 tiles
     ((2, 7, 7, 2048, 520, 1, 1, 0), False),     # weights the larger operand: neighbouring tiles share weights
+    # input gradients of 45, 40 and 39 steps in 135 tiles of 128 x 64
+    ((2, 17, 18, 1697, 290, 3, 1, 1), True), ((2, 17, 18, 1696, 2560, 1, 1, 0), False), ((2, 17, 18, 1696, 2496, 1, 1, 0), False),
 ]
 
 
@@ -172,8 +174,8 @@ DEEP = [
     ((5, 20, 20, 300, 1990, 1, 1, 0), True), ((5, 20, 20, 70, 1990, 3, 1, 1), True), ((8, 31, 31, 256, 1921, 1, 2, 0), True),
     # ... in 256 x 128 tiles (294 tiles of 128 x 128, 154 of these), whole and ragged
     ((7, 19, 20, 72, 1697, 3, 1, 1), True), ((7, 19, 20, 1024, 1696, 1, 1, 0), False),
-    # input gradients of 45, 40 and 39 steps in 135 tiles of 128 x 64
-    ((2, 17, 18, 1697, 290, 3, 1, 1), True), ((2, 17, 18, 1696, 2560, 1, 1, 0), False), ((2, 17, 18, 1696, 2496, 1, 1, 0), False),
+    # whole channel blocks with padding in both; 1 x 1, ragged, in 256 x 128 tiles
+    ((5, 20, 21, 64, 1024, 3, 1, 1), False), ((8, 17, 18, 128, 1690, 3, 1, 1), False), ((7, 19, 20, 1020, 1696, 1, 1, 0), True),
 ]
 
 
@@ -187,10 +189,24 @@ def test_fragments_a_step_ahead(case, pad_zero):
 @pytest.mark.parametrize("C", [60, 64, 128, 200, 256, 320, 512, 590])
 @pytest.mark.parametrize("R", [1, 3])
 def test_small_tiles_around_their_number_of_stages(C, R):
-    """Reductions of one step to past two rounds of the small tiles' stages, with one block of channels a tap and several."""
+    """Reductions of one step to past two rounds of the stages of 32 x 32 tiles, with one block of channels a tap and several (1 x
+    1: of up to three steps in 128 x 64 tiles)."""
     from gpu_util import pitch8
     spec = _spec(2, 7, 8, C, 70 if R == 3 else 40, R, 1, R // 2)
     _check_full(spec, 800 + C + R, pitch8(spec.C), pitch8(spec.K), pitch8(spec.C), pad_zero=True)
+
+
+# Calls in 64 x 64 tiles (four stages of a step): gradients of one to three steps that also clear pixels, forward calls of four to
+# nine, and a gradient of four classes, of two to eight.
+TILES_64 = ([("bwd_data", (16, 14, 14, 330, 64 * n - 4, 1, 2, 0)) for n in (1, 2, 3)] +
+            [("fwd", (16, 14, 14, 64 * n - 4, 130, 1, 1, 0)) for n in range(4, 10)] + [("bwd_data", (2, 28, 28, 130, 120, 3, 2, 1))])
+
+
+@pytest.mark.parametrize("call,case", TILES_64, ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else c)
+def test_tiles_of_64_by_64_around_their_number_of_stages(call, case):
+    from gpu_util import pitch8
+    spec = _spec(*case)
+    _check_full(spec, 850 + sum(case), pitch8(spec.C), pitch8(spec.K), pitch8(spec.C), pad_zero=True)
 
 
 FIRST_LAYER = [
@@ -252,9 +268,12 @@ def test_early_3x3_layers_with_resident_weights(case, pad_zero):
     _check_full(spec, 950 + sum(case), pitch8(spec.C), pitch8(spec.K), pitch8(spec.C), pad_zero=pad_zero)
 
 
-@pytest.mark.parametrize("C", [9, 16, 17, 32, 33, 48, 49, 64])
-@pytest.mark.parametrize("K", [7, 32, 33, 50, 64])
-@pytest.mark.parametrize("N,H,W", [(3, 10, 12), (70, 12, 33)], ids=["one_tile", "runs"])
+LAYOUTS = dict(C=[9, 16, 17, 32, 33, 48, 49, 64], K=[7, 32, 33, 50, 64], images=[(3, 10, 12), (91, 12, 33)])  # (273 tiles: runs of two)
+
+
+@pytest.mark.parametrize("C", LAYOUTS["C"])
+@pytest.mark.parametrize("K", LAYOUTS["K"])
+@pytest.mark.parametrize("N,H,W", LAYOUTS["images"], ids=["one_tile", "runs"])
 def test_early_3x3_layers_around_the_layouts_of_bank_and_patch(C, K, N, H, W):
     """One to four 16-channel steps a tap, one and two output blocks, loads of bank and patch left out; one patch buffer and two."""
     from gpu_util import pitch8
@@ -560,13 +579,15 @@ def test_odd_pitches_and_images_one_pixel_wide_or_high(case):
     _check_full(_spec(*case), 700 + sum(case))
 
 
-@pytest.mark.parametrize("case", [(2, 4, 4, 205, 56, 1, 1, 0), (3, 9, 9, 400, 70, 1, 1, 0), (2, 5, 6, 455, 15, 1, 1, 0),
-                                  (18, 21, 22, 210, 14, 5, 1, 2),    # forward: 260 tiles of 25 stages
-                                  # the four classes of an input gradient: one stage, two, 512 tiles of up to seven
-                                  (3, 6, 6, 25, 20, 3, 2, 1), (1, 8, 9, 68, 78, 3, 2, 1), (5, 14, 14, 500, 407, 3, 2, 1)])
-def test_small_tiles_in_two_stages(case):
-    """Tiles of 32 x 32: reductions of one and two stages, and long ones where there are more tiles
-    than CUs."""
+TILES_32 = [(2, 4, 4, 205, 56, 1, 1, 0), (3, 9, 9, 400, 70, 1, 1, 0), (2, 5, 6, 455, 15, 1, 1, 0),
+            (18, 21, 22, 210, 14, 5, 1, 2),    # forward: 260 tiles of 50 stages
+            # the four classes of an input gradient: of one stage and two, of one to four, 512 tiles of up to 14
+            (3, 6, 6, 25, 20, 3, 2, 1), (1, 8, 9, 68, 78, 3, 2, 1), (5, 14, 14, 500, 407, 3, 2, 1)]
+
+
+@pytest.mark.parametrize("case", TILES_32)
+def test_small_tiles_of_32_by_32(case):
+    """Reductions of up to the four stages (of two steps each), and long ones where there are more tiles than CUs."""
     from gpu_util import pitch8
     spec = _spec(*case)
     _check_full(spec, 600 + sum(case), pitch8(spec.C), pitch8(spec.K), pitch8(spec.C), pad_zero=True)
