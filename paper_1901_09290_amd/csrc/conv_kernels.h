@@ -476,13 +476,14 @@ __device__ __forceinline__ TapSkip tap_skip(const IgemmArgs& a, int gi, int gj) 
 // DEEP = a step's fragments are read into registers during the step before it.  Its LDS is then free for the loads of step
 // STAGES later from the step's own barrier on, a stage earlier than otherwise, and no MFMA waits for the LDS behind a barrier.
 // For reductions long enough to pay for the first reads, on launches of about one workgroup per CU (pick_igemm_deep).
-// In every form a step sends out a later step's loads between its MFMAs, a quarter with each 16 channels: the 64 or more
-// load instructions of a workgroup take the CU's address unit 16 clocks each, and ahead of the fragment reads they held
-// those, and the MFMAs, back for half a step.  Forward, 3 x 3, batch 64, operands from memory / in the caches: 128 x 64 tiles,
-// 7 x 7 512 -> 512 29.4 / 28.1 -> 28.1 / 23.6 us; deep, 128 x 128 tiles in three stages, 14 x 14 256 -> 256 23.9 / 21.8 -> 20.3 / 17.6
-// us (MFMAs alone, without loads and reads: 12.2), 1 x 1 1024 -> 256 16.7 / 11.1 -> 13.5 / 9.7; deep, 256 x 128, 28 x 28
-// 128 -> 128 20.3 / 18.1 -> 19.3 / 17.3.  Bound now by fragment reads and MFMAs, which with one barrier a step overlap to 0.31 us
-// of a 128 x 128 x 64 step (MFMAs alone 0.23), and on 128 x 64 tiles by the operands from the L2 (20 TB/s).
+// With three stages every step but the last ones sends out a later step's loads between its MFMAs, a quarter with each 16
+// channels (with two they go out ahead of the step's reads, see main_loop): the 64 or more load instructions of a workgroup
+// take the CU's address unit 16 clocks each, and ahead of the fragment reads they held those, and the MFMAs, back for half
+// a step.  Forward, 3 x 3, batch 64, operands from memory / in the caches: 128 x 64 tiles, 7 x 7 512 -> 512 29.4 / 28.1 ->
+// 28.1 / 23.6 us; deep, 128 x 128 tiles in three stages, 14 x 14 256 -> 256 23.9 / 21.8 -> 20.3 / 17.6 us (MFMAs alone,
+// without loads and reads: 12.2), 1 x 1 1024 -> 256 16.7 / 11.1 -> 13.5 / 9.7; deep, 256 x 128, 28 x 28 128 -> 128 20.3 /
+// 18.1 -> 19.3 / 17.3.  Bound now by fragment reads and MFMAs, which with one barrier a step overlap to 0.31 us of a 128 x
+// 128 x 64 step (MFMAs alone 0.23), and on 128 x 64 tiles by the operands from the L2 (20 TB/s).
 // TAIL = some run of channels ends inside an 8-chunk whose remaining elements are undefined.
 // STATS = also reduce the stored outputs to per-channel sums and sums of squares (see IgemmArgs::stats).
 // AV = the caller has established that every tap of every row lies inside the source image (no validity tests).
@@ -745,8 +746,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
         int kt = 0;
         if constexpr (DEEP) {
             uint32_t at = 0;  // LDS of the step computed
-            if (nk >= STAGES) wait_vmcnt<(STAGES - 1) * LPT>();
-            else wait_vmcnt<0>();
+            wait_vmcnt<(STAGES - 1) * LPT>();  // (there are at least STAGES steps)
             barrier_nofence();
             static_for<0, 4>([&](auto ks_c) { read_frags(0, decltype(ks_c)::value, decltype(ks_c)::value); });
             for (; kt + STAGES < nk; ++kt) {
@@ -793,7 +793,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void k_igemm_dl(const IgemmArgsN
     };
 #pragma unroll
     for (int s = 0; s < (DEEP ? STAGES : STAGES - 1); ++s)
-        if (s < nk) issue_part(s * STAGE_BYTES, 0, 1);
+        if (DEEP || s < nk) issue_part(s * STAGE_BYTES, 0, 1);
     // waves inside the reduction loop go first at the CU's issue arbiter: ahead of a co-resident workgroup's set-up
     // or stores, and ahead of weight-gradient waves sharing the CU from another stream (+0.4 % on the step)
     __builtin_amdgcn_s_setprio(2);
@@ -1066,7 +1066,7 @@ inline hipError_t plan_igemm_dl_cfg(IgemmArgs& a, IgemmDlPlan& plan) {
         variant += 3;
     }
     a.tiles_m = (int)ceil_div(a.M, BM);
-    if (DEEP && (variant > 1 || a.fold)) return hipErrorInvalidValue;
+    if (DEEP && (variant > 1 || a.fold || a.nk < STAGES)) return hipErrorInvalidValue;
     if (!igemm_buffer_args(a)) return hipErrorInvalidValue;
     // every tap of every row inside the source image?  coordinates are monotone in the grid index and in the tap
     auto inside = [](int lo, int hi, int n) { return lo >= 0 && hi >= 0 && lo < n && hi < n; };
