@@ -6,12 +6,16 @@ import subprocess
 import pytest
 
 from launches import HERE, ROOT, of_calls
+from paper_1901_09290_amd import binding as B
 
 
 @pytest.fixture(scope="module")
 def launches():
     if shutil.which("gcc") is None:
         pytest.skip("no gcc")
+    if not os.path.exists(B._SO):
+        from paper_1901_09290_amd import build as hip_build
+        hip_build.build()
     build = os.path.join(ROOT, "_build", "launches")
     os.makedirs(build, exist_ok=True)
     so = os.path.join(build, "recorder.so")
