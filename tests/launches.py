@@ -37,6 +37,8 @@ def _main():
         rec.forget()
         if call == "fwd":
             B.conv_fwd_at(d, at, at, at, (None, 0), None)
+        elif call == "fwd_stats":
+            assert B.lib().pt_conv_fwd_stats(C.byref(d), at, at, at, at, 1 << 40, None) == 0
         elif call == "bwd_data":
             B.conv_bwd_data_crsk_at(d, at, at, at, None)
         else:

@@ -32,6 +32,7 @@ FEW_TILES = [
     (("fwd", 7, 24, 24, 192, 32, 1, 1), (3.63, 4.15, 4.05)), (("fwd", 46, 14, 14, 69, 133, 1, 2), (3.60, 3.94, 4.63)),
     (("fwd", 1, 18, 19, 128, 1440, 1, 1), (3.79, 4.19, 4.97)), (("bwd_data", 2, 5, 7, 32, 96, 1, 1), (2.91, 3.52, 3.42)),
     (("bwd_data", 24, 20, 22, 32, 96, 1, 1), (3.68, 4.15, 4.81)), (("bwd_data", 1, 6, 7, 63, 72, 1, 1), (3.11, 3.51, 3.39)),
+    (("fwd", 31, 10, 12, 320, 96, 1, 1), (4.46, 4.65, 5.28)), (("bwd_data", 11, 5, 6, 1392, 316, 1, 1), (4.65, 4.75, 5.47)),
     # the four classes of a strided gradient, two to eight steps
     (("bwd_data", 25, 15, 17, 352, 96, 3, 2), (6.53, 8.71, 16.26)),
     # a filter smaller than its stride: a tile clears the other pixels of its cells
@@ -51,6 +52,19 @@ def test_few_tiles_take_the_faster_form(launches):
     forms = [["k_igemm_dl", 128, 64], ["k_igemm_small", 64, 64], ["k_igemm_small", 32, 32]]
     for (c, us), got in zip(FEW_TILES, launches([[*c, c[6] // 2, True] for c, _ in FEW_TILES])):
         assert got[0]["kernel"][:3] == forms[us.index(min(us))], (c, us, got)
+
+
+def test_near_ties_of_short_reductions_are_one_launch(launches):
+    """Four and five steps: with statistics in one launch, and a block's first convolution and its shortcut (as their gradients) in
+    the same form, so that a call of both is one launch."""
+    for case in [(27, 22, 22, 224, 32, 1, 1, 0), (90, 11, 13, 257, 22, 1, 1, 0), (2, 49, 49, 256, 64, 1, 1, 0), (7, 20, 20, 296, 655, 1, 2, 0)]:
+        (got,) = launches([["fwd_stats", *case, True]])
+        assert [g["kernel"][:3] for g in got] == [["k_igemm_dl", 128, 64]], (case, got)
+    pairs = [("fwd", (4, 56, 56, 256, 64, 1, 1, 0), (4, 56, 56, 256, 512, 1, 2, 0)), ("fwd", (10, 32, 32, 256, 64, 1, 1, 0), (10, 32, 32, 256, 512, 1, 2, 0)),
+             ("bwd_data", (8, 28, 28, 82, 293, 1, 1, 0), (8, 56, 56, 195, 293, 1, 2, 0))]
+    for call, one, other in pairs:
+        a, b = launches([[call, *one, True], [call, *other, True]])
+        assert a[0]["kernel"][:3] == b[0]["kernel"][:3], (call, one, other, a, b)
 
 
 @pytest.mark.parametrize("case", [(24, 24, 24, 297, 5, 4, 3, 2), (62, 16, 16, 289, 4, 5, 3, 2), (18, 27, 27, 328, 51, 5, 3, 2),

@@ -196,10 +196,11 @@ def test_small_tiles_around_their_number_of_stages(C, R):
     _check_full(spec, 800 + C + R, pitch8(spec.C), pitch8(spec.K), pitch8(spec.C), pad_zero=True)
 
 
-# Calls in 64 x 64 tiles (four stages of a step): gradients of one to three steps that also clear pixels, forward calls of four to
-# nine, and a gradient of four classes, of two to eight.
-TILES_64 = ([("bwd_data", (16, 14, 14, 330, 64 * n - 4, 1, 2, 0)) for n in (1, 2, 3)] +
-            [("fwd", (16, 14, 14, 64 * n - 4, 130, 1, 1, 0)) for n in range(4, 10)] + [("bwd_data", (2, 28, 28, 130, 120, 3, 2, 1))])
+# Calls in 64 x 64 tiles (four stages of a step): gradients of two to five steps that also clear pixels, forward calls of six to
+# nine, and gradients of four classes, of one to four and of two to eight.
+TILES_64 = ([("bwd_data", (16, 14, 14, 330, 64 * n - 4, 1, 2, 0)) for n in range(2, 6)] +
+            [("fwd", (16, 14, 14, 64 * n - 4, 130, 1, 1, 0)) for n in range(6, 10)] +
+            [("bwd_data", (2, 28, 28, 130, K, 3, 2, 1)) for K in (60, 120)])
 
 
 @pytest.mark.parametrize("call,case", TILES_64, ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else c)
