@@ -1903,18 +1903,35 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
     const int D1 = a.stride_h * rowp - Qs * a.xpitch;                  // carry out of q: next output row
     const int D2 = (a.H - Ps) * rowp;                                  // carry out of p: next image
     const int xrel0 = wave * RPLX + xr, yrel0 = wave * RPLY + yr;      // this lane's pixel inside a step (slot 0)
-    int x_ih[LX], x_iw[LX];
-    uint32_t x_off[LX];
+    [[maybe_unused]] int x_ih[LX], x_iw[LX];
+    [[maybe_unused]] uint32_t x_off[LX];
+    // XMODE 1 needs only whether the tap is inside the image: the pixel's place in its row and in its image, both counted
+    // cyclically from the first pixel for which it is, is below the number of those.  Two counters without a carry between
+    // them, an addition, a subtraction and an unsigned minimum a step each (what lies below zero is large).
+    [[maybe_unused]] const int Qd = (int)a.Q.d, PQ = Qd * (int)a.P.d;
+    [[maybe_unused]] const int q_lo = max(0, a.pad_w - fs), m_lo = max(0, a.pad_h - fr) * Qd;
+    [[maybe_unused]] const uint32_t q_n = (uint32_t)max(0, min(Qd, a.W + a.pad_w - fs) - q_lo);
+    [[maybe_unused]] const uint32_t m_n = (uint32_t)max(0, min((int)a.P.d, a.H + a.pad_h - fr) * Qd - m_lo);
+    [[maybe_unused]] const uint32_t q_step = (uint32_t)a.dq, m_step = (uint32_t)(a.dp * Qd + a.dq);  // BKP modulo Qd and PQ
+    [[maybe_unused]] uint32_t x_q[LX], x_m[LX];
+    if constexpr (XMODE < 2) {
 #pragma unroll
-    for (int j = 0; j < LX; ++j) {
-        const int pix = it0 * BKP + xrel0 + NW * j * RPLX;
-        const uint32_t row = fdiv((uint32_t)pix, a.Q);
-        const int q = pix - (int)row * (int)a.Q.d;
-        const uint32_t n = fdiv(row, a.P);
-        const int p = (int)row - (int)n * (int)a.P.d;
-        x_ih[j] = p * a.stride_h - a.pad_h + fr;
-        x_iw[j] = q * a.stride_w - a.pad_w + fs;
-        x_off[j] = (uint32_t)(((int)n * a.H + x_ih[j]) * a.W + (x_iw[j] - fs + fs_addr)) * (uint32_t)a.xpitch + (uint32_t)xc;
+        for (int j = 0; j < LX; ++j) {
+            const int pix = it0 * BKP + xrel0 + NW * j * RPLX;
+            const uint32_t row = fdiv((uint32_t)pix, a.Q);
+            const int q = pix - (int)row * (int)a.Q.d;
+            const uint32_t n = fdiv(row, a.P);
+            const int p = (int)row - (int)n * (int)a.P.d;
+            if constexpr (XMODE == 0) {
+                x_ih[j] = p * a.stride_h - a.pad_h + fr;
+                x_iw[j] = q * a.stride_w - a.pad_w + fs;
+                x_off[j] = (uint32_t)(((int)n * a.H + x_ih[j]) * a.W + (x_iw[j] - fs + fs_addr)) * (uint32_t)a.xpitch + (uint32_t)xc;
+            } else {
+                const int m = p * Qd + q;
+                x_q[j] = (uint32_t)(q >= q_lo ? q - q_lo : q - q_lo + Qd);
+                x_m[j] = (uint32_t)(m >= m_lo ? m - m_lo : m - m_lo + PQ);
+            }
+        }
     }
     // pixels from the next step's first one to the end of this workgroup's slice (uniform): loads past it fetch zeros,
     // so steps may be issued unconditionally
@@ -1965,13 +1982,9 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
             for (int j = 0; j < LX; ++j) {
                 v[j] = x_v;
                 if constexpr (XMODE == 1) {
-                    const bool ok = (unsigned)x_ih[j] < (unsigned)a.H && (unsigned)x_iw[j] < (unsigned)a.W;
-                    v[j] = ok ? x_v : kBufOut;
-                    const int iw = x_iw[j] + dq_s;
-                    const bool c1 = iw >= iw_wrap;
-                    x_iw[j] = iw - (c1 ? Qs : 0);
-                    const int ih = x_ih[j] + (c1 ? dp_s + 1 : dp_s);
-                    x_ih[j] = ih - (ih >= ih_wrap ? Ps : 0);
+                    v[j] = x_q[j] < q_n && x_m[j] < m_n ? x_v : kBufOut;
+                    x_q[j] = min(x_q[j] + q_step, x_q[j] + (q_step - (uint32_t)Qd));
+                    x_m[j] = min(x_m[j] + m_step, x_m[j] + (m_step - (uint32_t)PQ));
                 }
             }
             if (!whole) {
@@ -2082,7 +2095,7 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
     typedef std::integral_constant<int, 0> none;
 
     const int nk = it1 - it0;
-    constexpr bool TURNS = XMODE == 1 && AHEAD;  // (see the loop)
+    constexpr bool TURNS = XMODE == 1 && AHEAD && KSPLIT > 1;  // (see the loop)
     [[maybe_unused]] const bool late = (wave & 4) != 0;  // waves w and w + 4 share a SIMD
     auto issue = [&](int stage) {
         issue_x(stage);
@@ -2112,14 +2125,10 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
                 barrier_nofence();  // ... for every wave, and nobody reads the previous one any more
                 // A later step's loads go out between this step's MFMAs, x behind the first sub-step's and dy behind the last's,
                 // into the buffer consumed in the previous step.  A CU's address unit takes 16 clocks for each of a step's 16
-                // to 24 load instructions, which then do not hold up the fragment reads of the waves that come after.  Against all
-                // loads ahead of the MFMAs in one of the two waves of a SIMD and behind them in the other, us on two boxes: train step
-                // of ResNet-50 3308 -> 3288 and 3189 -> 3175, pruned 2726 -> 2719 and 2681 -> 2665; calls by themselves with XMODE 0
-                // 0.5 to 4 % faster, with 2 up to 2 %.  With 1 alone on the chip the tests of an x load's row and column, some 20
-                // instructions, stand between the MFMAs as well and cost more than that: 740 such calls take 1.1 % longer, 72 of
-                // them more than 3 % (64 x 56 x 56, 50 -> 39 channels, 3 x 3: 32.5 us against 31.0).  They keep the turns of the
-                // waves.  (All loads behind the MFMAs in every wave: 7 % longer than so.  Both orders as branches on the wave
-                // around every part: 60 us where it is 27.)
+                // to 24 load instructions, which then do not hold up the fragment reads of the waves that come after: 14 x 14, 256 -> 256,
+                // 3 x 3, alone, against all loads ahead of the MFMAs in one of the two waves of a SIMD and behind them in the other
+                // 22.0 -> 21.0 us, 7 x 7, 512 -> 512 30.3 -> 28.8.  With two wave groups the turns of the waves stay the better order for
+                // XMODE 1 alone on the chip (7 x 7, 239 -> 383: 17.4 and 17.6 us).  (All loads behind the MFMAs in every wave: 7 % longer.)
                 const int to = (s + STAGES - 1) % STAGES;
                 if constexpr (TURNS) {
                     if (!late) issue(to);

@@ -695,3 +695,11 @@ def test_early_3x3_input_gradient_by_the_size_of_the_filter_bank(C, K, own):
     ref = torch.nn.functional.conv_transpose2d(torch.from_numpy(t["dy"]).permute(0, 3, 1, 2),
                                                torch.from_numpy(t["w"]).permute(0, 3, 1, 2), padding=1)
     assert rel_err(a, ref.permute(0, 2, 3, 1).numpy()) <= CONV_TOL
+
+
+@pytest.mark.parametrize("R", [3, 5, 7])
+@pytest.mark.parametrize("N,H,W", [(3, 1, 1), (5, 1, 3), (4, 3, 1), (3, 2, 5), (2, 7, 33), (70, 4, 4), (1, 64, 32), (2, 65, 31)])
+def test_weight_gradient_taps_outside_small_images(R, N, H, W):
+    """'Same'-padded filters on images smaller than the filter, of one column or row, and around a reduction step's pixels:
+    which places of an image a tap may use is counted cyclically along the rows and along the images."""
+    _check_full(_spec(N, H, W, 72, 40, R, 1, R // 2))
