@@ -879,7 +879,7 @@ static int32_t plan_wgrad_batched(const pt_layer_wgrad* layers, int n, float lam
         const int32_t rc = check_wgrad_layer(out[i]);
         if (rc != PT_OK) return rc;
         if (out[i].stem) continue;
-        out[i].p = plan_wgrad_tiles(&l.d, out[i].vec);
+        out[i].p = n == 1 && workgroups ? plan_wgrad_beside(&l.d, out[i].vec) : plan_wgrad_tiles(&l.d, out[i].vec);
         total += (float)out[i].p.tiles_m * out[i].p.tiles_n * out[i].p.iters_total * wgrad_step_us(out[i].p);
     }
     const bool alone = n == 1 && !workgroups;  // one layer with the chip to itself: planned as pt_conv_bwd_weight plans it
@@ -909,7 +909,7 @@ static int32_t plan_wgrad_batched(const pt_layer_wgrad* layers, int n, float lam
             WgradPlan& p = out[i].p;
             const float piece = total / (float)(best * slots);
             if (n == 1 && workgroups)  // (two of the smaller workgroups find room on a CU beside others)
-                set_wgrad_splits(out[i].d, p, (p.cfg == 0 ? slots : slots * 5 / 3) / (p.tiles_m * p.tiles_n));
+                set_wgrad_splits(out[i].d, p, (p.cfg == 0 || p.cfg == kWgRow3 ? slots : slots * 5 / 3) / (p.tiles_m * p.tiles_n));
             else
                 set_wgrad_splits(out[i].d, p, (int64_t)(p.iters_total * wgrad_step_us(p) / piece + 0.5f));
         }

@@ -263,9 +263,12 @@ inline int pick_tile(int n) {
 // the 128 x 128 tile takes 0.30 with one workgroup on the CU (smaller tiles: in proportion to their MFMAs, but no less than
 // 0.6 of it), a split's tile of fp32 partial sums is written and read again at about 4 TB/s.
 constexpr float kWgStepUs = 0.30f, kWgPartialUsPerByte = 2.f / 4e6f;
+constexpr float kRow3Beside = 0.68f, kRow3Alone = 0.93f;
+constexpr float kRow3StepUs = 0.28f;  // of wgrad_row3_body, 64 positions
 constexpr int kWgMinSteps = 4;    // per workgroup
 constexpr int kWgSlots = 256;     // one workgroup per CU: a second one on the CU finishes no more steps per microsecond
 inline float wgrad_step_us(const WgradPlan& p) {
+    if (p.cfg == kWgRow3) return kRow3StepUs;
     const float r = (float)p.BM * p.BN * p.bkp / (128.f * 128.f * 32.f);
     return kWgStepUs * (r > 0.6f ? r : 0.6f);
 }
@@ -303,6 +306,41 @@ inline WgradPlan plan_wgrad_tiles(const pt_conv_desc* d, bool dl, int cfg = -1) 
     return p;
 }
 
+// What wgrad_row3_body takes: 3 x 3 filters at stride 1 and padding 1 whose places and offsets fit its 24 and 30 bits, from
+// 3000 pixels on: with fewer, its 2 us more of set-up and of adding up are more than it saves (5 x 13 x 13, 72 -> 40: 4.3 us in
+// 64 x 64 tiles, 7.1 so).
+constexpr int64_t kRow3MinPixels = 3000;
+inline bool wgrad_row3_ok(const pt_conv_desc* d, bool dl) {
+    const int64_t rows = (int64_t)d->N * d->H, pixels = rows * d->W, most = (int64_t)1 << 29;  // elements
+    return dl && d->R == 3 && d->S == 3 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 1 && d->pad_w == 1 &&
+           pixels >= kRow3MinPixels && pixels + rows < (1 << 24) && pixels * d->x_cpitch < most && pixels * d->y_cpitch < most;
+}
+inline WgradPlan plan_wgrad_row3(const pt_conv_desc* d, WgradPlan p) {  // p: the layer's plan in another form
+    p.cfg = kWgRow3;
+    p.fold = 0;
+    p.BM = 3 * 64;
+    p.BN = 64;
+    p.bkp = kRow3Px;
+    p.tiles_per_tap = (int)ceil_div(p.CP, 64);  // of one filter row
+    p.tiles_m = 3 * p.tiles_per_tap;
+    p.tiles_n = (int)ceil_div(d->K, 64);
+    p.iters_total = (int)ceil_div((int64_t)d->N * d->H * (d->W + 1), kRow3Px);
+    return p;
+}
+// One layer beside other kernels: the form whose workgroups spend less time on their steps together, the row form where that is
+// well below (x 0.68: 256 -> 256 at 14 x 14 0.67, 64 -> 64 at 56 x 56 0.53; 512 -> 512 at 7 x 7, where an eighth of the positions
+// are zeros, 0.71).  Times of workgroups: 14 x 14 72 of 53 us against 96 of 38, 56 x 56 153 of 52 against 96 of 36, 7 x 7 144 of 28
+// against 192 of 26.  64, 80 and 128 workgroups a layer instead of 96: step of ResNet-50 0.4 to 0.8 % longer.
+inline WgradPlan plan_wgrad_beside(const pt_conv_desc* d, bool dl) {
+    const WgradPlan p = plan_wgrad_tiles(d, dl);
+    if (wgrad_row3_ok(d, p.dl)) {
+        const WgradPlan r = plan_wgrad_row3(d, p);
+        auto work = [](const WgradPlan& q) { return (float)q.tiles_m * q.tiles_n * q.iters_total * wgrad_step_us(q); };
+        if (work(r) < kRow3Beside * work(p)) return r;
+    }
+    return p;
+}
+
 inline void set_wgrad_splits(const pt_conv_desc* d, WgradPlan& p, int64_t splits) {
     const int64_t most = p.iters_total / kWgMinSteps;
     if (splits > most) splits = most;
@@ -321,6 +359,9 @@ inline void set_wgrad_splits(const pt_conv_desc* d, WgradPlan& p, int64_t splits
 // each shape for both states together 11.15 and 13.22.  Costs fitted to cached operands alone: 11.31 and 13.73, by 64 x 128
 // tiles with half the splits for large 1 x 1 layers, half as many operand bytes again (14 x 14 1024 -> 512 at batch 64: 23.4
 // and 32.6 us against 23.3 and 26.5 so).
+// The row form (wgrad_row3_body) where it is estimated at 0.93 of the others' best: of 30 random 3 x 3 layers of 3000 pixels and
+// more it takes 14, which are 0.5 to 42 % faster than in the other forms (105 x 27 x 27, 419 -> 24: 64.6 -> 45.5 us); two with
+// estimates of 0.94 and 0.98 were 1 and 3 % slower.
 // Tiles smaller than the sizes ask for go unsplit up to 24 steps only (1536 pixels; 10 x 10 256 -> 256 3 x 3 at batch 15:
 // 8.4 us against 12.5 split, from memory 10.3 and 14).  They are faster beyond that (14 x 14 at batch 8, 25 steps: 8.6 and
 // 10.4 against 12.9 and 13.9): the line is not where measurements would put it.  The tests of the regulariser inside the
@@ -328,7 +369,7 @@ inline void set_wgrad_splits(const pt_conv_desc* d, WgradPlan& p, int64_t splits
 struct WgradCost {
     float step, round;
 };
-constexpr WgradCost kWgCost[kWgConfigs] = {{0.257f, 1.343f}, {0.3f, 1.35f}, {0.312f, 1.388f}, {0.222f, 0.323f}};
+constexpr WgradCost kWgCost[kWgConfigs + 1] = {{0.257f, 1.343f}, {0.3f, 1.35f}, {0.312f, 1.388f}, {0.222f, 0.323f}, {0.32f, 6.5f}};
 // The register-staged kernel on rows that are not 16-byte aligned (element-wise loads): 2.3 us a step.  Over 240 shapes at odd
 // pitches its calls take 15.8 ms (cached) and 17.0 ms (from memory) so, with the 0.30 us of an aligned step 17.2 and 18.6.
 constexpr WgradCost kWgStagedCost = {2.3f, 0.7f};
@@ -340,11 +381,14 @@ inline WgradPlan plan_wgrad(const pt_conv_desc* d, bool dl) {
     WgradPlan best = own;
     const float part = (float)d->K * best.Mtot * 4e-6f * kWgPartialUsPerMB;  // of one split
     float best_us = 1e30f;
-    for (int cfg = 0; cfg < (direct ? kWgConfigs : 1); ++cfg) {
-        const WgradPlan p = plan_wgrad_tiles(d, dl, direct ? cfg : -1);
+    const int forms = !direct ? 1 : wgrad_row3_ok(d, direct) ? kWgConfigs + 1 : kWgConfigs;
+    for (int cfg = 0; cfg < forms; ++cfg) {
+        const bool row3 = cfg == kWgRow3;  // (the last)
+        if (row3) best_us *= kRow3Alone;
+        const WgradPlan p = row3 ? plan_wgrad_row3(d, own) : plan_wgrad_tiles(d, dl, direct ? cfg : -1);
         const WgradCost cost = direct ? kWgCost[cfg] : kWgStagedCost;
         const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n, most = p.iters_total / kWgMinSteps;
-        const float operands = (float)tiles * p.iters_total * p.bkp * (p.BM + p.BN) * 2e-6f * kWgOperandUsPerMB;
+        const float operands = (float)tiles * p.iters_total * p.bkp * ((row3 ? 64 : p.BM) + p.BN) * 2e-6f * kWgOperandUsPerMB;
         // none; around the optimum of steps / s + s * part without rounds; as many as fill one round or two
         const int64_t mid = (int64_t)fminf(sqrtf((float)p.iters_total * cost.step / part), 1e6f);
         const int64_t tries[7] = {1, mid - 1, mid, mid + 1, mid + mid / 4, kWgSlots / tiles, 2 * kWgSlots / tiles};
@@ -354,7 +398,7 @@ inline WgradPlan plan_wgrad(const pt_conv_desc* d, bool dl) {
             if (s < 1) s = 1;
             WgradPlan q = p;
             set_wgrad_splits(d, q, s);
-            if (q.splits == 1 && most > 1 && q.iters_total > kWgUnsplitSteps && direct && (p.BM != own.BM || p.BN != own.BN)) continue;
+            if (q.splits == 1 && most > 1 && q.iters_total > kWgUnsplitSteps && direct && !row3 && (p.BM != own.BM || p.BN != own.BN)) continue;
             const float us = (float)ceil_div(q.splits * tiles, kWgSlots) * ((float)q.iters_per_split * cost.step + cost.round) +
                              (q.splits > 1 ? (float)q.splits * part + kWgSecondUs : 0.f) + operands;
             if (us < best_us) {
@@ -447,6 +491,12 @@ inline WgradArgs make_wgrad_args(const pt_conv_desc* d, const WgradPlan& p, cons
     a.dq = p.bkp % d->Q;
     a.dp = p.bkp / d->Q % d->P;
     a.dn = p.bkp / (d->P * d->Q);
+    if (a.cfg == kWgRow3) {  // a place more in every row
+        a.pixels = d->N * d->P * (d->Q + 1);
+        a.Q = make_fastdiv((int64_t)d->Q + 1);
+        a.dq = p.bkp % (d->Q + 1);
+        a.dp = p.bkp / (d->Q + 1) % d->P;
+    }
     a.wpitch = d->w_cpitch;
     a.direct = p.splits == 1;
     a.OUT = a.direct ? dw : (float*)ws;
@@ -474,12 +524,20 @@ inline hipError_t launch_wgrad_dl_one(const WgradArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(kerns[a.xmode], dim3((unsigned)(a.tiles_m * a.tiles_n * a.splits)), dim3(512), lds, st, a);
     return hipSuccess;
 }
+inline hipError_t launch_wgrad_row3(const WgradArgs& a, hipStream_t st) {
+    constexpr size_t lds = (size_t)kRow3Stages * kRow3StageBytes;
+    static LdsOptIn opt_in;
+    if (hipError_t e = opt_in.ensure(reinterpret_cast<const void*>(k_wgrad_row3), lds); e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_wgrad_row3, dim3((unsigned)(a.tiles_m * a.tiles_n * a.splits)), dim3(512), lds, st, a);
+    return hipSuccess;
+}
 template <bool AHEAD>
 inline hipError_t launch_wgrad_dl_cfg(const WgradArgs& a, hipStream_t st) {
     switch (a.cfg) {
         case 0: return launch_wgrad_dl_one<0, AHEAD>(a, st);
         case 1: return launch_wgrad_dl_one<1, AHEAD>(a, st);
         case 2: return launch_wgrad_dl_one<2, AHEAD>(a, st);
+        case kWgRow3: return launch_wgrad_row3(a, st);
         default: return launch_wgrad_dl_one<3, AHEAD>(a, st);
     }
 }

@@ -2242,6 +2242,250 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
 #endif
 }
 
+// ------------------------------------------------------------------------------------------- //
+// weight gradient of 3 x 3 filters at stride 1 and padding 1: the three taps of a filter row from one tile of x
+// ------------------------------------------------------------------------------------------- //
+// What bounds wgrad_dl_body on these layers is the way of the operands into LDS (64 bytes a clock and CU) and out of it
+// again, one after the other: a 128 x 128 tile takes 16 KB in and 48 KB out for 32 pixels, 0.22 to 0.28 us where its MFMAs
+// are 0.11, whatever the number of stages.  Here a workgroup owns one filter row (three taps) x 64 input channels x 64 output
+// channels: 12288 outputs for the operand bytes of a 64 x 64 tile.  The taps of a row read the same pixels one place
+// further, so they are three windows of the same LDS rows; what keeps a window from running into the next image row is a
+// column of zeros behind every one.  The reduction therefore counts W + 1 places a row ("positions"; 1 / W more of them), and both
+// operands hold zeros there.  Which image row a tap needs is the same for the whole workgroup: x is fetched shifted, rows
+// outside the image as zeros.
+//   Eight waves: two halves of the input channels x four of a step's 64 positions.  A wave multiplies 16 positions a step
+// (3 x fragments and 2 dy fragments for 6 MFMAs), its fragments read a step ahead; the four position groups are added
+// through LDS at the end, in a fixed order, tap by tap, by all threads (2 us with the set-up: calls of few steps stay with the
+// other forms).  A step of 64 positions is 0.28 us with operands from memory (17 KB in at some 70 bytes a ns, which is what a CU
+// gets of lines that no other has fetched before; 0.16 us without the loads, its MFMAs).  Main kernel, 64 images, 240 to 252
+// workgroups, from memory: 14 x 14, 256 -> 256 23.5 -> 21.3 us, 28 x 28, 128 -> 128 22.9 -> 21.8, 56 x 56, 64 -> 64 34.9 -> 23.1;
+// with 64 x 64 tiles 252 workgroups fetch 462 MB for the last, so 157.  Whole calls 26.6 -> 26.1, 26.1 -> 25.7, 29.7 -> 24.6, 7 x 7,
+// 512 -> 512 30.2 -> 25.7, 30 x 14 x 14, 512 -> 512 50.6 -> 39.0; training step of ResNet-50 3255 -> 3186 us, pruned 2679 -> 2638.
+// Five stages: four 1 to 2 us longer, six and eight the same.
+//   (A place of the zero column multiplies a zero of dy with the x beside it, where the other forms multiply a zero of x
+// with dy: an infinity in x reaches all three taps of its channels here.)
+// A workgroup's slice in positions; a.Q.d is W + 1 and a.pixels the number of positions.  Offsets inside a slice in 24 bits times a
+// pitch, below kBufRecords (wgrad_row3_ok).
+constexpr int kRow3Px = 64;
+constexpr int kRow3XBytes = (kRow3Px / 8 + 1) * 1024;  // 66 rows of 64 channels, in loads of eight rows
+constexpr int kRow3StageBytes = kRow3XBytes + kRow3Px * 128;
+constexpr int kRow3ReduceBytes = 64 * 1024;
+template <int STAGES>
+__device__ __forceinline__ void wgrad_row3_body(const WgradArgs& a, const int lin, uint8_t* smem_b) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
+    static_assert(STAGES >= 4 && STAGES * kRow3StageBytes >= kRow3ReduceBytes && STAGES * kRow3StageBytes <= 160 * 1024, "LDS");
+    constexpr uint32_t kBufRecords = 0x40000000u, kBufOut = 0x80000000u, kBufFlags = 0x00020000u;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wc = wave & 1, wp = wave >> 1;  // half of the input channels, quarter of a step's positions
+    const int split = (int)fdiv((uint32_t)lin, a.ntile_div);
+    const int tile = lin - split * (a.tiles_m * a.tiles_n);
+    const int mt = (int)fdiv((uint32_t)tile, a.tn_div);
+    const int n0 = (tile - mt * a.tiles_n) * 64;
+    const int fr = (int)fdiv((uint32_t)mt, a.tap_div);  // filter row
+    const int cb = (mt - fr * a.tiles_per_tap) * 64;
+    const int it0 = split * a.iters_per_split;
+    const int it1 = min(a.iters_total, it0 + a.iters_per_split);
+    const int nk = it1 - it0;
+
+    // ---- loads: a wave fetches eight positions of either operand a step, wave 0 also the two of x behind the step's last one.
+    // Row i of the x tile is position (start - 1 + i), row i of the dy tile position (start + i).
+    // (placement of the 32-byte units as in wgrad_dl_body, 128-byte rows)
+    const int lr = lane >> 3, row = wave * 8 + lr;
+    const int up = ((lane & 7) >> 1) ^ ((lr >> 1) & 1), lc = ((((up & 1) << 1) | (up >> 1)) << 1) | (lane & 1);
+    const uint32_t xcb = (uint32_t)min(cb + lc * 8, a.CP - 8) * 2u, ycb = (uint32_t)min(n0 + lc * 8, a.KP - 8) * 2u;
+    const int Qp = (int)a.Q.d, PQ = Qp * (int)a.P.d;
+    const int t0 = it0 * kRow3Px, t1 = min(a.pixels, it1 * kRow3Px);
+    const int pix0 = t0 - (int)fdiv((uint32_t)t0, a.Q);  // pixel of the slice's first position
+    // place in the row, place in the image counted cyclically from the first one whose tap row lies inside, pixel
+    const int m_lo = fr == 0 ? Qp : 0;
+    const uint32_t m_n = (uint32_t)(fr == 1 ? PQ : PQ - Qp);
+    const uint32_t q_step = (uint32_t)a.dq, m_step = (uint32_t)(a.dp * Qp + a.dq);  // positions of a step modulo Qp and PQ
+    const uint32_t p_step = (uint32_t)(kRow3Px - kRow3Px / Qp);
+    uint32_t q, m, pix;
+    {
+        const int t = t0 + row;
+        const uint32_t rw = fdiv((uint32_t)t, a.Q);
+        const uint32_t n = fdiv(rw, a.P);
+        q = (uint32_t)(t - (int)rw * Qp);
+        const int mm = ((int)rw - (int)n * (int)a.P.d) * Qp + (int)q;
+        m = (uint32_t)(mm >= m_lo ? mm - m_lo : mm - m_lo + PQ);
+        pix = (uint32_t)(t - (int)rw - pix0);
+    }
+    // positions from the step's first one to the end: of the slice for dy, for x two further (but not past the last image)
+    int y_left = t1 - t0, x_left = min(t1 + 2, a.pixels + 1) - t0;
+    const uint32_t xpb = (uint32_t)a.xpitch * 2u, ypb = (uint32_t)a.ypitch * 2u;
+    const __amdgpu_buffer_rsrc_t x_srd = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t*>(a.X) + ((int64_t)pix0 + (fr - 1) * a.W - 1) * a.xpitch, 0, kBufRecords, kBufFlags);
+    const __amdgpu_buffer_rsrc_t y_srd =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.DY) + (int64_t)pix0 * a.ypitch, 0, kBufRecords, kBufFlags);
+    typedef __attribute__((address_space(3))) uint8_t* lds_bytes;
+    const lds_bytes x_to = (lds_bytes)smem_b + wave * 1024, y_to = x_to + kRow3XBytes, halo_to = (lds_bytes)smem_b + kRow3Px * 128;
+    auto issue = [&](int stage) {
+        const uint32_t ox = __umul24(pix, xpb) + xcb, oy = __umul24(pix, ypb) + ycb;
+        const uint32_t vx = (q != 0) & (m < m_n) & (row < x_left) ? ox : kBufOut;
+        const uint32_t vy = (q != (uint32_t)(Qp - 1)) & (row < y_left) ? oy : kBufOut;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(x_srd, (lds_void_ptr)(x_to + stage * kRow3StageBytes), 16, vx, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(y_srd, (lds_void_ptr)(y_to + stage * kRow3StageBytes), 16, vy, 0, 0, 0);
+        const uint32_t qs = q + q_step;
+        pix += p_step - (qs >= (uint32_t)Qp ? 1u : 0u);
+        q = min(qs, qs - (uint32_t)Qp);
+        m = min(m + m_step, m + (m_step - (uint32_t)PQ));
+        x_left -= kRow3Px;
+        y_left -= kRow3Px;
+        if (wave == 0) {  // (its first rows of the next step)
+            const uint32_t oh = __umul24(pix, xpb) + xcb;
+            const uint32_t vh = (lr < 2) & (q != 0) & (m < m_n) & (row < x_left) ? oh : kBufOut;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(x_srd, (lds_void_ptr)(halo_to + stage * kRow3StageBytes), 16, vh, 0, 0, 0);
+        }
+    };
+    auto wait_stages = [&](auto n_c) {  // all but the loads of the last n steps have landed
+        constexpr int N = decltype(n_c)::value;
+        wait_vmcnt<3 * N>();
+        if (wave != 0) wait_vmcnt<2 * N>();
+    };
+
+    // ---- fragments (transposing reads as in wgrad_dl_body; four rows further the placement is the same)
+    const int g16 = lane >> 4, t16 = lane & 15;
+    const int tr_row = wp * 16 + (g16 >> 1) * 8 + (t16 >> 2), tr_u = g16 & 1, tr_b = (t16 & 3) * 8;
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void_ptr)smem_b;
+    auto frag_at = [&](int r, int block) {
+        const int u = tr_u + 2 * block;
+        return lds_base + (uint32_t)(r * 128 + ((((((u & 1) << 1) | (u >> 1)) ^ ((r >> 1) & 1))) << 5) + tr_b);
+    };
+    uint32_t ax[3], ay[2];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) ax[s] = frag_at(tr_row + s, wc);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) ay[b] = frag_at(tr_row, b) + kRow3XBytes;
+    f32x16 acc[3][2];
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[s][b][v] = 0.f;
+    s16x4 fx[3][2], fy[2][2][2];
+    auto read_x = [&](auto s_c, uint32_t sb) {
+        constexpr int S = decltype(s_c)::value;
+        fx[S][0] = lds_read_tr16_b64<0>(ax[S] + sb);
+        fx[S][1] = lds_read_tr16_b64<512>(ax[S] + sb);
+    };
+    auto read_y = [&](auto b_c, uint32_t sb) {
+        constexpr int B = decltype(b_c)::value;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            fy[B][b][0] = lds_read_tr16_b64<0>(ay[b] + sb);
+            fy[B][b][1] = lds_read_tr16_b64<512>(ay[b] + sb);
+        }
+    };
+    // the eight reads behind the ones that tap S needs may stay in flight
+    auto multiply = [&](auto s_c, auto b_c) {
+        constexpr int S = decltype(s_c)::value, B = decltype(b_c)::value;
+        lds_wait<8>(fx[S][0]);
+        lds_tie(fx[S][1]);
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) lds_tie(fy[B][b][h]);
+        const bf16x8 vx = join_halves(fx[S][0], fx[S][1]);
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+            acc[S][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(join_halves(fy[B][b][0], fy[B][b][1]), vx, acc[S][b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    typedef std::integral_constant<int, 0> c0;
+    typedef std::integral_constant<int, 1> c1;
+    typedef std::integral_constant<int, 2> c2;
+
+#pragma unroll
+    for (int s = 0; s < STAGES - 1; ++s) issue(s);
+    wait_stages(std::integral_constant<int, STAGES - 2>{});
+    barrier_nofence();
+    read_y(c0{}, 0u);
+    read_x(c0{}, 0u);
+    read_x(c1{}, 0u);
+    read_x(c2{}, 0u);
+    constexpr int UNROLL = STAGES % 2 ? 2 * STAGES : STAGES;  // (the dy fragments alternate between two buffers)
+    for (int kt0 = 0; kt0 < nk; kt0 += UNROLL) {
+        static_for<0, UNROLL>([&](auto u_c) {
+            constexpr int U = decltype(u_c)::value;
+            if (kt0 + U < nk) {
+                wait_stages(std::integral_constant<int, STAGES - 3>{});  // the next stage has landed ...
+                barrier_nofence();  // ... for every wave, and nobody reads the previous one any more
+                typedef std::integral_constant<int, (U & 1)> now;
+                typedef std::integral_constant<int, ((U + 1) & 1)> next;
+                constexpr uint32_t nxt = (uint32_t)((U + 1) % STAGES) * kRow3StageBytes;
+                read_y(next{}, nxt);
+                multiply(c0{}, now{});
+                read_x(c0{}, nxt);
+                issue((U + STAGES - 1) % STAGES);
+                multiply(c1{}, now{});
+                read_x(c1{}, nxt);
+                multiply(c2{}, now{});
+                read_x(c2{}, nxt);
+            }
+        });
+    }
+    lds_wait<0>(fx[0][0]);
+    wait_vmcnt<0>();  // the loads issued past the end have landed before LDS is reused
+
+    // ---- the four position groups are added tap by tap: every wave parks its two blocks of 32 input x 32 output channels,
+    // then wave w adds and stores half of block w >> 1 (rows and columns of an element as in wgrad_dl_body)
+    float4* red = reinterpret_cast<float4*>(smem_b);
+    const int row_pitch = a.direct ? a.RS * a.wpitch : a.out_row_pitch, tap_pitch = a.direct ? a.wpitch : a.CP;
+    const int64_t first = (int64_t)n0 * row_pitch + (a.direct ? 0 : (int64_t)split * a.K * a.out_row_pitch);
+    const uint32_t tile_bytes = (uint32_t)(min(a.K - n0, 64) * row_pitch) * 4u;
+    const __amdgpu_buffer_rsrc_t o_srd = __builtin_amdgcn_make_buffer_rsrc(a.OUT + first, 0, tile_bytes, kBufFlags);
+    const int blk = wave >> 1, g0 = (wave & 1) * 2;
+    const int c = cb + (blk & 1) * 32 + (lane & 31), k0 = (blk >> 1) * 32 + 4 * (lane >> 5) + 8 * g0;
+    const bool ok = c < (a.direct ? a.C : a.CP);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                red[((wp * 4 + b * 2 + wc) * 4 + g) * 64 + lane] =
+                    make_float4(acc[s][b][4 * g], acc[s][b][4 * g + 1], acc[s][b][4 * g + 2], acc[s][b][4 * g + 3]);
+        __syncthreads();
+        float v[8];
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            float4 r[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) r[w] = red[((w * 4 + blk) * 4 + g0 + g) * 64 + lane];
+            v[4 * g] = ((r[0].x + r[1].x) + r[2].x) + r[3].x;
+            v[4 * g + 1] = ((r[0].y + r[1].y) + r[2].y) + r[3].y;
+            v[4 * g + 2] = ((r[0].z + r[1].z) + r[2].z) + r[3].z;
+            v[4 * g + 3] = ((r[0].w + r[1].w) + r[2].w) + r[3].w;
+        }
+        const uint32_t at0 = ok ? (uint32_t)(k0 * row_pitch + (3 * fr + s) * tap_pitch + c) * 4u : kBufOut;
+        auto at = [&](int e) { return at0 + (uint32_t)((8 * (e >> 2) + (e & 3)) * row_pitch) * 4u; };
+        if (a.direct && a.lw) {  // uniform: regulariser folded in
+            const __amdgpu_buffer_rsrc_t w_srd =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.lw) + first, 0, tile_bytes, kBufFlags);
+            const float in = a.l_in && ok ? a.l_in[c] : 0.f;
+            const float inv_in = in > 0.f ? 1.0f / in : 0.f;
+            float wv[8], io[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                wv[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(w_srd, at(e), 0, 0));
+                io[e] = a.l_on ? a.l_on[min(n0 + k0 + 8 * (e >> 2) + (e & 3), a.K - 1)] : 0.f;
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float inv_out = io[e] > 0.f ? 1.0f / io[e] : 0.f;
+                v[e] += a.l_lambda * (wv[e] * (inv_out + inv_in));
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[e]), o_srd, at(e), 0, 0);
+    }
+#endif
+}
+
 // One launch holds the weight gradients of up to kWgMaxProblems layers of any shape: every tile configuration and address
 // mode is eight waves, so they are the branches of one kernel, and a workgroup finds its problem from the table of first
 // workgroups (multiples of 8: workgroup ids are dealt round-robin to the 8 XCDs, and each XCD takes a contiguous range of
@@ -2253,6 +2497,7 @@ struct WgradJobs {
     WgradArgs a[kWgMaxProblems];
     int first[64];
 };
+constexpr int kWgRow3 = kWgConfigs, kRow3Stages = 5;  // WgradArgs::cfg of wgrad_row3_body, which takes one layer a launch
 // tile configurations (input channels x output channels) and pixels per reduction step
 constexpr int kWgCfgBM[kWgConfigs] = {128, 64, 128, 64}, kWgCfgBN[kWgConfigs] = {128, 128, 64, 64};
 constexpr int kWgCfgBKP[kWgConfigs] = {32, 64, 64, 64};
@@ -2297,6 +2542,10 @@ template <int CFG, int XMODE, bool AHEAD>
 __global__ __launch_bounds__(512, 1) void k_wgrad_dl(const WgradArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_b[];
     wgrad_dl_cfg<CFG, XMODE, AHEAD>(a, xcd_remap(blockIdx.x, gridDim.x), smem_b);
+}
+__global__ __launch_bounds__(512, 1) void k_wgrad_row3(const WgradArgs a) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem_b[];
+    wgrad_row3_body<kRow3Stages>(a, xcd_remap(blockIdx.x, gridDim.x), smem_b);
 }
 
 // ------------------------------------------------------------------------------------------- //

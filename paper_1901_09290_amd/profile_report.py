@@ -65,11 +65,11 @@ def short(name: str) -> str:
 # Kernels of the convolution calls and the family each is counted under (a digit behind the name is part of the variant).
 FAMILIES = {"k_igemm_dl": "k_igemm_dl", "k_igemm_small": "k_igemm_small", "k_igemm": "k_igemm", "k_conv3x3_res": "k_conv3x3_res",
             "k_stem_fwd": "k_stem_fwd", "k_stem_wgrad": "k_stem_wgrad", "k_wgrad_dl": "k_wgrad_dl",
-            "k_wgrad_dl_multi": "k_wgrad_dl_multi", "k_wgrad": "k_wgrad", "k_wgrad_reduce": "k_wgrad_reduce",
+            "k_wgrad_dl_multi": "k_wgrad_dl_multi", "k_wgrad_row3": "k_wgrad_row3", "k_wgrad": "k_wgrad", "k_wgrad_reduce": "k_wgrad_reduce",
             "k_wgrad_reduce_multi": "k_wgrad_reduce", "k_stem_wgrad_reduce": "k_wgrad_reduce", "k_zero_class": "k_zero_class",
             "k_transpose_w": "k_transpose_w", "k_transpose_w_multi": "k_transpose_w", "k_tile_stats": "k_tile_stats"}
 # ... and those of them that run the matrix cores
-MAIN_FAMILIES = ("k_igemm_dl", "k_igemm_small", "k_wgrad_dl", "k_wgrad_dl_multi", "k_igemm", "k_wgrad", "k_stem_fwd",
+MAIN_FAMILIES = ("k_igemm_dl", "k_igemm_small", "k_wgrad_dl", "k_wgrad_dl_multi", "k_wgrad_row3", "k_igemm", "k_wgrad", "k_stem_fwd",
                  "k_stem_wgrad", "k_conv3x3_res")
 
 

@@ -702,4 +702,46 @@ def test_early_3x3_input_gradient_by_the_size_of_the_filter_bank(C, K, own):
 def test_weight_gradient_taps_outside_small_images(R, N, H, W):
     """'Same'-padded filters on images smaller than the filter, of one column or row, and around a reduction step's pixels:
     which places of an image a tap may use is counted cyclically along the rows and along the images."""
-    _check_full(_spec(N, H, W, 72, 40, R, 1, R // 2))
+    _check_full(_spec(N, H, W, 72, 40, R, 1, R // 2), 1200 + N + H + W + R)
+
+
+ROW3 = [
+    # N   H   W   C    K  pad_zero: 3 x 3 layers whose three taps of a filter row share a tile (3000 pixels on)
+    (26, 14, 14, 64, 64, True),       # whole tiles
+    (105, 7, 7, 129, 190, True),      # image rows of eight places, one channel in the last tile
+    (1250, 1, 4, 64, 64, False), (400, 4, 4, 120, 70, False),   # one filter row that ever falls inside; small images
+    (40, 2, 63, 45, 130, True), (14, 6, 62, 64, 64, False),     # a row is a step of places, or one less
+    (3, 41, 43, 203, 171, False),     # slices that end inside a row
+    (7, 30, 25, 64, 320, True), (64, 14, 14, 256, 256, True),
+]
+
+
+@pytest.mark.parametrize("N,H,W,C,K,pad_zero", ROW3)
+@pytest.mark.parametrize("workgroups", [0, 1, 24, 160])
+def test_weight_gradient_three_taps_from_one_tile(N, H, W, C, K, pad_zero, workgroups):
+    """The form that multiplies a filter row's taps from one tile of x, unsplit and split, written directly and through the
+    reduction, with the regulariser: against the oracle, and the same bits on a second run."""
+    from gpu_util import CONV_TOL, DEV, dev_bf16, dev_f32, pitch8, rel_err, workspace
+    from paper_1901_09290_amd import binding as B
+    spec = _spec(N, H, W, C, K, 3, 1, 1)
+    xp, yp = pitch8(C), pitch8(K)
+    rng = np.random.Generator(np.random.PCG64(1300 + N + H + W + C + K))
+    t = wl.conv_tensors(spec, rng, want=("x", "dy"))
+    w = (rng.standard_normal((K, 3, 3, C)) * 0.05).astype(np.float32)
+    pad = 0 if pad_zero else 0x7FC0
+    d = B.desc_of(spec, xp, yp, xp, B.CONV_PAD_ZERO if pad_zero else 0)
+    xd, dyd, wd = dev_bf16(t["x"], xp, pad), dev_bf16(t["dy"], yp, pad), dev_f32(w, xp)
+    on, inn = (torch.from_numpy(n.astype(np.float32)).to(DEV) for n in oracle.group_norms(w))
+    ref = oracle.conv_bwd_weight(oracle.shape_of(spec), t["x"], t["dy"])
+    ref_l = oracle.group_lasso_grad(w, on.cpu().numpy(), inn.cpu().numpy(), 0.5, 3, ref)
+    got = []
+    for weights, want in ((None, ref), (wd, ref_l), (wd, ref_l)):
+        dw = torch.full((K, 3, 3, xp), float("nan"), dtype=torch.float32, device=DEV)
+        jobs = [B.layer_wgrad(d, xd, dyd, dw, *((weights, on, inn, 3) if weights is not None else ()))]
+        ws = workspace(B.conv_bwd_weight_batched_workspace_bytes(jobs, workgroups))
+        B.conv_bwd_weight_batched(jobs, 0.5, ws, workgroups)
+        assert rel_err(dw.cpu().numpy()[..., :C], want) <= CONV_TOL
+        if xp != C:
+            assert bool(torch.isnan(dw[..., C:]).all())
+        got.append(dw)
+    assert torch.equal(got[1][..., :C], got[2][..., :C])
