@@ -201,6 +201,14 @@ int32_t pt_conv_bwd_weight_lasso(const pt_conv_desc* d, const uint16_t* x, const
                                  const float* out_norm, const float* in_norm, float lambda, uint32_t flags, float* dw,
                                  void* ws, size_t ws_bytes, void* stream);
 
+/* One layer's training step in one call: pt_group_norms (with the bf16 weights w_bf16 [K][R][S][w_cpitch]), pt_conv_fwd,
+ * pt_conv_bwd_data (dx == NULL: none) and pt_conv_bwd_weight_lasso, enqueued one after the other with their results.  The
+ * workspace is the largest of theirs; where it holds pt_conv_bwd_weight's but not pt_conv_bwd_weight_lasso's, the
+ * regulariser's gradient is added by pt_group_lasso_grad. */
+int32_t pt_conv_layer_step(const pt_conv_desc* d, const uint16_t* x, const uint16_t* dy, const float* w, uint16_t* w_bf16,
+                           float* out_norm, float* in_norm, float lambda, uint32_t flags, uint16_t* y, uint16_t* dx, float* dw,
+                           void* ws, size_t ws_bytes, void* stream);
+
 /* Weight gradients of n layers in one call, with or without the regulariser's gradient: per layer the result of
  * pt_conv_bwd_weight (w == NULL) or pt_conv_bwd_weight_lasso.  The layers share launches: together they fill the chip, so
  * that a layer's pixel axis is split over workgroups (and its partial sums written, read and added) only as far as that

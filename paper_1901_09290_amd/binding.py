@@ -42,7 +42,7 @@ EXPORTS = [
     "pt_conv_bwd_weight_batched_workspace_bytes", "pt_conv_bwd_weight_batched",
     "pt_bn_workspace_bytes", "pt_bn_fwd", "pt_bn_bwd", "pt_plan_layer_removal",
     "pt_conv_fwd_stats_workspace_bytes", "pt_conv_fwd_stats", "pt_bn_fwd_from_sums",
-    "pt_conv_bwd_weight_lasso_workspace_bytes", "pt_conv_bwd_weight_lasso",
+    "pt_conv_bwd_weight_lasso_workspace_bytes", "pt_conv_bwd_weight_lasso", "pt_conv_layer_step",
 ]
 
 
@@ -165,6 +165,7 @@ def lib() -> C.CDLL:
             "pt_conv_bwd_weight": [dp, vp, vp, vp, vp, sz, vp],
             "pt_conv_bwd_weight_lasso_workspace_bytes": [dp, C.POINTER(sz)],
             "pt_conv_bwd_weight_lasso": [dp, vp, vp, vp, vp, vp, f32, u32, vp, vp, sz, vp],
+            "pt_conv_layer_step": [dp, vp, vp, vp, vp, vp, vp, f32, u32, vp, vp, vp, vp, sz, vp],
             "pt_group_norms_workspace_bytes": [i32, i32, i32, C.POINTER(sz)],
             "pt_group_norms": [vp, i32, i32, i32, i32, vp, vp, vp, vp, sz, vp],
             "pt_group_lasso_grad": [vp, vp, vp, f32, u32, vp, i32, i32, i32, i32, vp],
@@ -331,6 +332,15 @@ def conv_bwd_weight_lasso(d: ConvDesc, x, dy, w, out_norm, in_norm, lam: float, 
     _ck("pt_conv_bwd_weight_lasso",
         lib().pt_conv_bwd_weight_lasso(C.byref(d), _ptr(x), _ptr(dy), _ptr(w), _ptr(out_norm), _ptr(in_norm), lam, flags,
                                        _ptr(dw), p, n, _stream(stream)))
+
+
+def conv_layer_step(d: ConvDesc, x, dy, w, w_bf16, out_norm, in_norm, lam: float, flags: int, y, dx, dw, ws=None,
+                    stream=None) -> None:
+    """A layer's training step: group norms, forward, input gradient (dx None: none), weight gradient with the regulariser."""
+    p, n = _ws(ws)
+    _ck("pt_conv_layer_step",
+        lib().pt_conv_layer_step(C.byref(d), x.data_ptr(), dy.data_ptr(), w.data_ptr(), w_bf16.data_ptr(), out_norm.data_ptr(),
+                                 in_norm.data_ptr(), lam, flags, y.data_ptr(), _ptr(dx), dw.data_ptr(), p, n, _stream(stream)))
 
 
 def layer_wgrad(d: ConvDesc, x, dy, dw, w=None, out_norm=None, in_norm=None, flags: int = 0) -> LayerWgrad:

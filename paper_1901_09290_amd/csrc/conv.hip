@@ -851,6 +851,24 @@ extern "C" int32_t pt_conv_bwd_weight_lasso(const pt_conv_desc* d, const uint16_
     return bwd_weight_one(d, x, dy, dw, ws, ws_bytes, stream, rl);
 }
 
+extern "C" int32_t pt_conv_layer_step(const pt_conv_desc* d, const uint16_t* x, const uint16_t* dy, const float* w,
+                                      uint16_t* w_bf16, float* out_norm, float* in_norm, float lambda, uint32_t flags,
+                                      uint16_t* y, uint16_t* dx, float* dw, void* ws, size_t ws_bytes, void* stream) {
+    int32_t rc = check_desc(d);
+    if (rc != PT_OK) return rc;
+    if (!x || !dy || !w || !w_bf16 || !out_norm || !in_norm || !y || !dw) return PT_ERR_NULL;
+    if (flags & ~(PT_LASSO_OUT | PT_LASSO_IN)) return PT_ERR_UNSUPPORTED;
+    const int RS = d->R * d->S;
+    rc = pt_group_norms(w, d->K, RS, d->C, d->w_cpitch, out_norm, in_norm, w_bf16, ws, ws_bytes, stream);
+    if (rc == PT_OK) rc = pt_conv_fwd(d, x, w_bf16, y, ws, ws_bytes, stream);
+    if (rc == PT_OK && dx) rc = pt_conv_bwd_data(d, dy, w_bf16, dx, ws, ws_bytes, stream);
+    if (rc != PT_OK) return rc;
+    rc = pt_conv_bwd_weight_lasso(d, x, dy, w, out_norm, in_norm, lambda, flags, dw, ws, ws_bytes, stream);
+    if (rc != PT_ERR_WORKSPACE) return rc;
+    rc = pt_conv_bwd_weight(d, x, dy, dw, ws, ws_bytes, stream);
+    return rc != PT_OK ? rc : pt_group_lasso_grad(w, out_norm, in_norm, lambda, flags, dw, d->K, RS, d->C, d->w_cpitch, stream);
+}
+
 // Plans the layers of a batched call and lays their workspaces out one after the other; returns the bytes needed.
 // Splits: every candidate cuts the work of the call into pieces of total / (rounds * CUs); of four, the one with the least
 // estimated time, the work spread over the CUs + half of the longest piece (the last round is that uneven) + the partial

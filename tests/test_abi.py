@@ -397,3 +397,17 @@ def test_fused_statistics_calls_validate_on_the_host(lib):
         return lib.pt_bn_fwd_from_sums(*a)
     assert f(a4=None) == -1 and f(a0=None) == -1
     assert f(a5=0) == -2 and f(a3=56) == -2 and f(a3=68) == -4 and f(a2=4096, a3=4096, a10=4096) == -4
+
+
+def test_layer_step_validates_on_the_host(lib):
+    d = B.conv_desc(2, 6, 6, 16, 16, 3, 3, 1, 1)
+    fake = 0x1000  # never dereferenced: every call below is refused before anything is launched
+    def call(**kw):
+        a = dict(d=C.byref(d), x=fake, dy=fake, w=fake, wb=fake, on=fake, inn=fake, flags=3, y=fake, dx=fake, dw=fake, ws=fake, nb=0)
+        a.update(kw)
+        return lib.pt_conv_layer_step(a["d"], a["x"], a["dy"], a["w"], a["wb"], a["on"], a["inn"], 1e-3, a["flags"], a["y"], a["dx"],
+                                      a["dw"], a["ws"], a["nb"], None)
+    for name in ("d", "x", "dy", "w", "wb", "on", "inn", "y", "dw"):
+        assert call(**{name: None}) == -1, name
+    assert call(flags=4) == -4
+    assert call() == -3   # the norms' workspace

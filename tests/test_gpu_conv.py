@@ -745,3 +745,32 @@ def test_weight_gradient_three_taps_from_one_tile(N, H, W, C, K, pad_zero, workg
             assert bool(torch.isnan(dw[..., C:]).all())
         got.append(dw)
     assert torch.equal(got[1][..., :C], got[2][..., :C])
+
+
+@pytest.mark.parametrize("case", [(4, 16, 16, 16, 16, 3, 1, 1), (2, 15, 15, 40, 136, 3, 2, 1), (64, 14, 14, 64, 64, 3, 1, 1), (2, 18, 18, 3, 16, 7, 2, 3),
+                                  (1, 7, 7, 520, 520, 3, 1, 1)], ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("small_workspace", [False, True])
+def test_layer_step_is_its_calls(case, small_workspace):
+    """A layer's step in one call against its calls one by one: outputs, input gradient and norms bit for bit, the weight gradient
+    with the regulariser in either place to F32_TOL."""
+    from gpu_util import F32_TOL, rel_err
+    from paper_1901_09290_amd import binding as B
+    from paper_1901_09290_amd import harness as hz
+    gen = torch.Generator(device=hz.DEV)
+    gen.manual_seed(7)
+    l = hz.ConvLayer(_spec(*case), gen=gen)
+    d = l.desc
+    ws = hz.make_workspace([l])
+    if small_workspace:  # without the slab that the fused weight gradient asks for
+        ws = ws[:max(256, B.conv_bwd_data_workspace_bytes(d), B.conv_bwd_weight_workspace_bytes(d),
+                     B.group_norms_workspace_bytes(l.spec.K, l.RS, l.spec.C))]
+    l.norms(ws); l.fwd(ws); l.bwd_data(ws); l.bwd_weight(ws); l.lasso(0.5)
+    want = {n: getattr(l, n).clone() for n in ("y", "dx", "dw", "out_norm", "in_norm", "w_bf16") if getattr(l, n) is not None}
+    for n in want:
+        getattr(l, n).zero_()
+    l.train_step(ws, 0.5)
+    for n, v in want.items():
+        if n == "dw":
+            assert rel_err(l.dw.cpu().numpy(), v.cpu().numpy()) <= F32_TOL
+        else:
+            assert torch.equal(getattr(l, n), v), n
