@@ -300,6 +300,13 @@ def conv_bwd_data_crsk_at(d: ConvDesc, dy: int, wt: int, dx: int, stream: Option
         raise PruneTrainError("pt_conv_bwd_data_crsk", rc)
 
 
+def conv_bwd_data_crsk_batched_at(jobs, stream: Optional[int]) -> None:
+    """conv_bwd_data_crsk_batched for a caller that has the stream's handle at hand."""
+    rc = lib().pt_conv_bwd_data_crsk_batched(*jobs, stream)
+    if rc:
+        raise PruneTrainError("pt_conv_bwd_data_crsk_batched", rc)
+
+
 def conv_fwd_jobs(descs: Sequence[ConvDesc], xs, ws, ys):
     """Argument arrays of conv_fwd_batched, built once for a fixed set of layers."""
     n = len(descs)

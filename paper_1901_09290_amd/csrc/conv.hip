@@ -375,9 +375,9 @@ struct IgemmPending {
         return r;
     }
     // launches or queues one problem
-    int32_t add(IgemmArgs& args, bool vec, hipStream_t st, int kernel = -1) {
+    int32_t add(IgemmArgs& args, bool vec, hipStream_t st, int kernel = -1, bool alone = false) {
         bool planned = false;
-        const int32_t rc = hip_status(launch_igemm(args, vec, st, &p[n], &planned, kernel));
+        const int32_t rc = hip_status(launch_igemm(args, vec, st, &p[n], &planned, kernel, alone));
         if (rc != PT_OK || !planned) return rc;
         a[n++] = args;
         return n == kIgemmMaxProblems ? flush(st) : PT_OK;
@@ -410,8 +410,9 @@ extern "C" int32_t pt_conv_fwd_batched(const pt_conv_desc* descs, const uint16_t
 }
 
 // Input gradient from weights already in [C][RS][round_up(K,8)] order: one implicit GEMM per stride-parity class.
+// `alone`: nothing else joins the call.
 static int32_t bwd_data_classes(const pt_conv_desc* d, const uint16_t* dy, const uint16_t* wt, uint16_t* dx,
-                                hipStream_t st, IgemmPending& pend) {
+                                hipStream_t st, IgemmPending& pend, bool alone = false) {
     int32_t rc = PT_OK;
     if (res3_bwd_ok(d, dy, wt, dx)) {  // the same kernel on dy with the k-innermost filter copy and mirrored taps
         const int kp = (int)round_up(d->K, 8);
@@ -483,7 +484,7 @@ static int32_t bwd_data_classes(const pt_conv_desc* d, const uint16_t* dy, const
             } else {
                 IgemmArgs a = args_of(ca, cb);
                 if (vec && with_taps > 1 && seen++ % kIgemmMaxProblems == 0) kernel = pick(ca * d->stride_w + cb);
-                rc = pend.add(a, vec, st, kernel);
+                rc = pend.add(a, vec, st, kernel, alone && d->stride_h * d->stride_w == 1);
             }
             if (rc != PT_OK) return rc;
         }
@@ -492,7 +493,7 @@ static int32_t bwd_data_classes(const pt_conv_desc* d, const uint16_t* dy, const
 }
 static int32_t bwd_data_one(const pt_conv_desc* d, const uint16_t* dy, const uint16_t* wt, uint16_t* dx, hipStream_t st) {
     IgemmPending pend;
-    const int32_t rc = bwd_data_classes(d, dy, wt, dx, st, pend);
+    const int32_t rc = bwd_data_classes(d, dy, wt, dx, st, pend, true);
     return rc == PT_OK ? pend.flush(st) : rc;
 }
 

@@ -174,7 +174,7 @@ inline bool igemm_small_ok(const IgemmArgs& a) {  // no undefined channel paddin
 
 // Which deep form of the direct kernel takes a problem, 0 = none: 1 = 128 x 128 and 2 = 256 x 128 in three stages.  `kernel` = what
 // takes it otherwise.
-// A forward call by itself: by estimated times (us).  The other forms, two workgroups on a CU: rounds of 512 tiles t2 a step and
+// A call by itself: by estimated times (us).  The other forms, two workgroups on a CU: rounds of 512 tiles t2 a step and
 // f2, a last one of up to 256 t1 and f1.  The deep forms hold a CU each (96 and 144 KB of LDS): rounds of 256 tiles.  Fitted to 820
 // calls (random layers of at least 4 steps and 128 tiles of 128 x 64, batch 4 to 128, 65 to 2048 output channels), each in all
 // forms with operands in the caches and from memory: without the deep forms 34.0 ms together, so 31.3, the best form for each
@@ -182,10 +182,13 @@ inline bool igemm_small_ok(const IgemmArgs& a) {  // no undefined channel paddin
 // 1024 -> 256 16.6 -> 13.5 us, 3 x 3 256 -> 256 23.8 -> 20.3, 28 x 28 3 x 3 128 -> 128 20.3 -> 19.3.  128 x 64 tiles in six stages won
 // nothing over them in three with the loads between the MFMAs (80 calls of 25 steps and more in one round: 5471 and 5426 us).
 // Problems that share a launch stay with the other forms: two problems of one round each are two rounds here.
-// Input gradients run beside weight gradients, which must find LDS beside them: the deep forms, faster by themselves, make the
-// training step of ResNet-50 0.3 to 1 % longer there.
+// Input gradients at stride 1 (the same loop; a strided one's classes share a launch) called by themselves as forward calls: 36
+// layers of 4 to 128 images, 21 of them 1 to 36 % faster, the others the same: 14 x 14, 256 -> 256, 3 x 3 21.3 -> 17.6 us, 225 -> 207
+// 23.1 -> 19.5, 1 x 1, 1024 -> 256 12.1 -> 10.4, 9 x 56 x 56, 517 -> 72, 3 x 3 53.2 -> 39.0.  In a batched call, also of one layer, they
+// do without: beside weight gradients, which must find LDS beside them, the deep forms make the training step of ResNet-50 0.3 to 1 %
+// longer.
 inline int pick_igemm_deep(const IgemmArgs& a, int kernel, bool alone) {
-    if (!alone || a.edge_prio || !igemm_small_ok(a) || a.fold || a.Nout <= 64) return 0;
+    if (!alone || a.d_hmul * a.d_wmul > 1 || !igemm_small_ok(a) || a.fold || a.Nout <= 64) return 0;
     const int64_t nk = a.TR * a.TS * ceil_div(a.CredP, 64);
     const int64_t t128 = ceil_div(a.M, 128) * ceil_div(a.Nout, 128), t64 = ceil_div(a.M, 128) * ceil_div(a.Nout, 64);
     if (nk < 4 || t64 < 128 || (kernel != 0 && kernel != kIgemmLarge)) return 0;
@@ -209,8 +212,9 @@ inline int pick_igemm_deep(const IgemmArgs& a, int kernel, bool alone) {
 // plan is filled in and *planned set, for launch_igemm_dl_planned to send it out together with other problems (the
 // register-staged kernel is launched at once either way, *planned cleared).
 // `kernel`: what pick_igemm_kernel said for the launch this problem will be part of, -1 = decide here.
+// `alone`: the caller sends the planned problem out by itself.
 inline hipError_t launch_igemm(IgemmArgs& a, bool vec, hipStream_t st, IgemmDlPlan* plan = nullptr, bool* planned = nullptr,
-                               int kernel = -1) {
+                               int kernel = -1, bool alone = false) {
     if (planned) *planned = false;
     if (!vec) return launch_igemm_cfg<128, 128, 32, 2, 2, 2, 2, false>(a, st);
     igemm_fold(a);
@@ -220,7 +224,7 @@ inline hipError_t launch_igemm(IgemmArgs& a, bool vec, hipStream_t st, IgemmDlPl
     if (kernel < 0) kernel = tiles128 >= 256 ? kIgemmLarge : igemm_small_ok(a) ? pick_igemm_kernel(&a, 1) : 0;
     IgemmDlPlan own;
     IgemmDlPlan& p = plan ? *plan : own;
-    const int deep = pick_igemm_deep(a, kernel, plan == nullptr);
+    const int deep = pick_igemm_deep(a, kernel, alone || plan == nullptr);
     hipError_t e;
     if (deep == 1) e = plan_igemm_dl_cfg<128, 128, 2, 4, 3, true>(a, p);
     else if (deep == 2) e = plan_igemm_dl_cfg<256, 128, 4, 2, 3, true>(a, p);

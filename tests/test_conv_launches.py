@@ -103,3 +103,14 @@ def test_runs_of_tiles_have_two_patch_buffers(launches):
     one, two = ([g[0] for g in launches([["fwd", n, H, W, C, K, 3, 1, 1, True] for C, K in shapes])] for n in (N // 2, N))
     for shape, a, b in zip(shapes, one, two):
         assert a["kernel"] == b["kernel"] and b["kernel"][0] == "k_conv3x3_res" and b["lds"] > a["lds"], (shape, a, b)
+
+
+def test_stride_1_gradients_by_themselves_take_the_deep_forms(launches):
+    """An input gradient at stride 1 takes what a forward call of the same sizes takes; a strided one's classes do without."""
+    cases = [(64, 14, 14, 256, 256, 3, 1, 1), (88, 12, 12, 152, 156, 3, 1, 1), (12, 30, 30, 377, 739, 1, 1, 0), (64, 28, 28, 128, 128, 3, 1, 1)]
+    got = _forms(launches, [("bwd_data", *c, True) for c in cases])
+    assert [k[0][-1] for k in got] == [1, 1, 1, 1], got
+    mirrored = _forms(launches, [("fwd", N, H, W, K, C, *r, True) for N, H, W, C, K, *r in cases])
+    assert [[k[:6] for k in g] for g in got] == [[k[:6] for k in g] for g in mirrored]
+    (strided,) = _forms(launches, [("bwd_data", 64, 28, 28, 256, 256, 3, 2, 1, True)])
+    assert [k[-1] for k in strided] == [0], strided

@@ -774,3 +774,25 @@ def test_layer_step_is_its_calls(case, small_workspace):
             assert rel_err(l.dw.cpu().numpy(), v.cpu().numpy()) <= F32_TOL
         else:
             assert torch.equal(getattr(l, n), v), n
+
+
+@pytest.mark.parametrize("case,pad_zero", [((N, H, W, K, C, *r), z) for (N, H, W, C, K, *r), z in DEEP if r[1] == 1],
+                         ids=lambda c: "x".join(map(str, c)) if isinstance(c, tuple) else str(c))
+def test_fragments_a_step_ahead_in_gradients(case, pad_zero):
+    """The sizes of DEEP the other way round: an input gradient by itself against the oracle, and bit for bit the batched call's,
+    which takes the forms that share a CU."""
+    from gpu_util import CONV_TOL, DEV, dev_bf16, host_bf16, pitch8, rel_err
+    from paper_1901_09290_amd import binding as B
+    spec = _spec(*case)
+    xp, yp = pitch8(spec.C), pitch8(spec.K)
+    t = wl.conv_tensors(spec, np.random.Generator(np.random.PCG64(750 + sum(case))), want=("w", "dy"))
+    pad = 0 if pad_zero else 0x7FC0
+    d = B.desc_of(spec, xp, yp, xp, B.CONV_PAD_ZERO if pad_zero else 0)
+    dy = dev_bf16(t["dy"], yp, pad)
+    wt = dev_bf16(np.ascontiguousarray(t["w"].transpose(3, 1, 2, 0)), yp, 0)
+    dx = [torch.zeros((spec.N, spec.H, spec.W, xp), dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+    B.conv_bwd_data_crsk(d, dy, wt, dx[0])
+    B.conv_bwd_data_crsk_batched(B.conv_fwd_jobs([d], [dy], [wt], [dx[1]]))
+    torch.cuda.synchronize()
+    assert torch.equal(dx[0], dx[1])
+    assert rel_err(host_bf16(dx[0], spec.C), oracle.conv_bwd_data(oracle.shape_of(spec), t["dy"], t["w"])) <= CONV_TOL
