@@ -421,7 +421,7 @@ inline WgradPlan plan_wgrad(const pt_conv_desc* d, bool dl) {
 #ifndef PT_RES3
 #define PT_RES3 3
 #endif
-constexpr int kRes3BwdMaxBank = 3072;  // K * C up to which an input-gradient call takes the kernel
+constexpr int kRes3BwdMaxBank = 3072;  // K * C up to which an input gradient in a batched call takes the kernel
 inline bool res3_shape_ok(const pt_conv_desc* d) {
     return d->R == 3 && d->S == 3 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 1 && d->pad_w == 1 && d->C <= 64 &&
            d->K <= 64 && d->x_cpitch % 8 == 0 && d->y_cpitch % 8 == 0 &&
@@ -431,11 +431,18 @@ inline bool res3_fwd_ok(const pt_conv_desc* d, const uint16_t* x, const uint16_t
     return (PT_RES3 & 1) && res3_shape_ok(d) && d->w_cpitch % 8 == 0 && aligned16(x) && aligned16(w) && aligned16(y) &&
            ((d->C % 8 == 0 && d->K % 8 == 0) || (d->flags & PT_CONV_PAD_ZERO));
 }
-inline bool res3_bwd_ok(const pt_conv_desc* d, const uint16_t* dy, const uint16_t* wt, const uint16_t* dx) {
+// A larger bank in a call by itself, against 128 x 64 and 64 x 64 tiles: images whose tiles give (nearly) all eight waves work.  Up to 32
+// columns 2 to 25 % faster (100 x 32 x 32, 64 -> 64: 15.5 -> 12.4 us, 10 x 14 x 14 5.2 -> 4.8); seven or eight column blocks from
+// 192 tiles on 8 to 30 % (56 x 56, batch 64: 25.2 -> 19.4, batch 14 8.1 -> 7.1), with fewer 5 to 12 % slower (batch 10, 4), as are
+// five and six column blocks by 5 to 15 % (24 x 48 x 48: 8.6 and 10.1).  Wider images, of several tiles a row, were not looked at.
+inline bool res3_bwd_large_ok(const pt_conv_desc* d) {
+    return d->W <= 32 || (d->W > 48 && d->W <= 64 && (int64_t)d->N * ((d->H + 3) / 4) >= 192);
+}
+inline bool res3_bwd_ok(const pt_conv_desc* d, const uint16_t* dy, const uint16_t* wt, const uint16_t* dx, bool alone) {
     // (input-gradient launches share the chip with weight gradients on other streams, and a workgroup that holds a CU's
     // whole LDS for the length of the launch shuts those out: with the full 64 x 64 filter bank the train step gets
-    // 25 us slower, with the smaller banks of a pruned network 25 us faster - so only those take it here)
-    return (PT_RES3 & 2) && res3_shape_ok(d) && (PT_RES3 & 4 || d->C * d->K <= kRes3BwdMaxBank) && aligned16(dy) &&
+    // 25 us slower, with the smaller banks of a pruned network 25 us faster - so only those take it in batched calls)
+    return (PT_RES3 & 2) && res3_shape_ok(d) && ((alone && res3_bwd_large_ok(d)) || PT_RES3 & 4 || d->C * d->K <= kRes3BwdMaxBank) && aligned16(dy) &&
            aligned16(wt) && aligned16(dx) &&
            ((d->C % 8 == 0 && d->K % 8 == 0) || (d->flags & PT_CONV_PAD_ZERO));
 }

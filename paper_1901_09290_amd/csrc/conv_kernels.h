@@ -2563,7 +2563,7 @@ __global__ __launch_bounds__(512, 1) void k_wgrad_row3(const WgradArgs a) {
 // chunks of a patch pixel are XOR-ed with ((column >> 1) & 3) | ((row & 1) << 2), and with as much of that as there are
 // chunks to tell apart where a pixel has four or two: the 16 lanes one LDS cycle serves (two rows of eight pixels) then read
 // 16 different bank groups, for every tap.  FLIP: the weights are indexed by the mirrored tap (input gradient: the same
-// kernel on dy with the k-innermost filter copy).
+// kernel on dy with the k-innermost filter copy).  The sums run over the filters' taps in their order, as in k_igemm_dl: the same bits.
 //   A call of few tiles is bound by what comes ahead of its first MFMA: a load instruction costs a wave some 20 instructions
 // of address and a CU's address unit 16 clocks, and one workgroup's worth of full-size bank and patch is 128 of them.  So bank
 // and patch are laid out for the channels there are, and loads of filters past the last output (their rows only reach outputs
@@ -2750,7 +2750,7 @@ __global__ __launch_bounds__(512) void k_conv3x3_res(const Res3Args a) {
             const uint8_t* pp = pbuf + buf * a.patch_bytes;
             bf16x8 xb[2], w0[2], w1[2];
             auto read_frags = [&](auto s_c) {
-                constexpr int S = decltype(s_c)::value, t = S / NCB, cb = S % NCB, B = S & 1, tw = FLIP ? 8 - t : t;
+                constexpr int S = decltype(s_c)::value, tw = S / NCB, cb = S % NCB, B = S & 1, t = FLIP ? 8 - tw : tw;
                 xb[B] = *reinterpret_cast<const bf16x8*>(pp + pb[t] + (((uint32_t)(cb << 5) | hc) ^ pk[t]));
                 w0[B] = *reinterpret_cast<const bf16x8*>(wa + tw * WTAP + cb * 32);
                 if constexpr (KB1) w1[B] = *reinterpret_cast<const bf16x8*>(wa + 32 * WROW + tw * WTAP + cb * 32);

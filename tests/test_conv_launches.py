@@ -114,3 +114,11 @@ def test_stride_1_gradients_by_themselves_take_the_deep_forms(launches):
     assert [[k[:6] for k in g] for g in got] == [[k[:6] for k in g] for g in mirrored]
     (strided,) = _forms(launches, [("bwd_data", 64, 28, 28, 256, 256, 3, 2, 1, True)])
     assert [k[-1] for k in strided] == [0], strided
+
+
+def test_early_3x3_gradients_by_themselves_keep_their_weights_in_lds(launches):
+    """Banks of more than 3072 weights a tap: where the tiles fill the eight waves."""
+    resident = [(100, 32, 32, 64, 64), (10, 14, 14, 64, 64), (64, 56, 56, 64, 64), (14, 56, 56, 63, 57)]
+    others = [(10, 56, 56, 64, 64), (24, 48, 48, 64, 64), (6, 33, 33, 64, 64), (2, 112, 112, 64, 64)]
+    got = _forms(launches, [("bwd_data", *c, 3, 1, 1, True) for c in resident + others])
+    assert [k[0][0] == "k_conv3x3_res" for k in got] == [True] * 4 + [False] * 4, got

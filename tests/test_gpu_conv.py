@@ -796,3 +796,24 @@ def test_fragments_a_step_ahead_in_gradients(case, pad_zero):
     torch.cuda.synchronize()
     assert torch.equal(dx[0], dx[1])
     assert rel_err(host_bf16(dx[0], spec.C), oracle.conv_bwd_data(oracle.shape_of(spec), t["dy"], t["w"])) <= CONV_TOL
+
+
+@pytest.mark.parametrize("N,H,W,C,K,pad_zero", [(3, 14, 19, 64, 64, False), (49, 16, 56, 64, 56, False), (50, 15, 63, 59, 61, True), (2, 1, 1, 64, 64, False)])
+def test_early_3x3_input_gradient_with_a_large_bank(N, H, W, C, K, pad_zero):
+    """Resident weights in a gradient by itself: against the oracle, and against the batched call, which takes other tiles (bit for bit
+    where those add a pixel's products in one run)."""
+    from gpu_util import CONV_TOL, DEV, dev_bf16, host_bf16, pitch8, rel_err
+    from paper_1901_09290_amd import binding as B
+    spec = _spec(N, H, W, C, K, 3, 1, 1)
+    xp, yp = pitch8(C), pitch8(K)
+    t = wl.conv_tensors(spec, np.random.Generator(np.random.PCG64(N + H + W)), want=("w", "dy"))
+    d = B.desc_of(spec, xp, yp, xp, B.CONV_PAD_ZERO if pad_zero else 0)
+    dy, wt = dev_bf16(t["dy"], yp, 0 if pad_zero else 0x7FC0), dev_bf16(np.ascontiguousarray(t["w"].transpose(3, 1, 2, 0)), yp, 0)
+    dx = [torch.zeros((N, H, W, xp), dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+    B.conv_bwd_data_crsk(d, dy, wt, dx[0])
+    B.conv_bwd_data_crsk_batched(B.conv_fwd_jobs([d], [dy], [wt], [dx[1]]))
+    ref = oracle.conv_bwd_data(oracle.shape_of(spec), t["dy"], t["w"])
+    for v in dx:
+        assert rel_err(host_bf16(v, C), ref) <= CONV_TOL
+    if N * H * W >= 256 * 128:
+        assert torch.equal(dx[0], dx[1])
