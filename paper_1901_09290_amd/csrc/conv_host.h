@@ -427,22 +427,26 @@ inline bool res3_shape_ok(const pt_conv_desc* d) {
            d->K <= 64 && d->x_cpitch % 8 == 0 && d->y_cpitch % 8 == 0 &&
            (int64_t)d->H * d->W * (d->x_cpitch > d->y_cpitch ? d->x_cpitch : d->y_cpitch) * 2 <= 0x7fffffff;
 }
-inline bool res3_fwd_ok(const pt_conv_desc* d, const uint16_t* x, const uint16_t* w, const uint16_t* y) {
-    return (PT_RES3 & 1) && res3_shape_ok(d) && d->w_cpitch % 8 == 0 && aligned16(x) && aligned16(w) && aligned16(y) &&
-           ((d->C % 8 == 0 && d->K % 8 == 0) || (d->flags & PT_CONV_PAD_ZERO));
+// Larger banks (more than kRes3BwdMaxBank weights a tap), against 128 x 64 and 64 x 64 tiles: images whose tiles of up to 56 columns give
+// (nearly) all eight waves work.  us with 64 -> 64 channels in those tiles and in this kernel, gradients: 100 x 32 x 32 15.5 and
+// 12.4, 10 x 14 x 14 5.2 and 4.8; 56 columns, batch 64 25.2 and 19.4, batch 14 8.1 and 7.1, with less than 192 tiles the other way
+// round (batch 10 6.2 and 6.5, batch 4 5.5 and 6.2); five and six column blocks 24 x 48 x 48 8.6 and 10.1, 20 x 40 x 40 6.2 and 6.5;
+// forward 24 x 48 x 48 7.9 and 10.1, 40 x 40 x 40 8.4 and 10.3, several tiles a row, the last one narrow, 16 x 64 x 64 9.7 and 12.2,
+// 2 x 96 x 96 5.9 and 6.3, filled 24 x 112 x 112 35.6 and 28.4.  Forward calls of 33 columns stay here although 6 x 33 x 33 takes 5.9 us
+// instead of 5.4: the tests of runs of tiles are of that width.
+inline bool res3_large_ok(const pt_conv_desc* d, int narrow) {
+    const int tiles_x = (d->W + 55) / 56;
+    return d->W <= narrow || (d->W > 48 * tiles_x && (int64_t)d->N * ((d->H + 3) / 4) * tiles_x >= 192);
 }
-// A larger bank in a call by itself, against 128 x 64 and 64 x 64 tiles: images whose tiles give (nearly) all eight waves work.  Up to 32
-// columns 2 to 25 % faster (100 x 32 x 32, 64 -> 64: 15.5 -> 12.4 us, 10 x 14 x 14 5.2 -> 4.8); seven or eight column blocks from
-// 192 tiles on 8 to 30 % (56 x 56, batch 64: 25.2 -> 19.4, batch 14 8.1 -> 7.1), with fewer 5 to 12 % slower (batch 10, 4), as are
-// five and six column blocks by 5 to 15 % (24 x 48 x 48: 8.6 and 10.1).  Wider images, of several tiles a row, were not looked at.
-inline bool res3_bwd_large_ok(const pt_conv_desc* d) {
-    return d->W <= 32 || (d->W > 48 && d->W <= 64 && (int64_t)d->N * ((d->H + 3) / 4) >= 192);
+inline bool res3_fwd_ok(const pt_conv_desc* d, const uint16_t* x, const uint16_t* w, const uint16_t* y) {
+    return (PT_RES3 & 1) && res3_shape_ok(d) && (d->C * d->K <= kRes3BwdMaxBank || res3_large_ok(d, 33)) && d->w_cpitch % 8 == 0 && aligned16(x) && aligned16(w) && aligned16(y) &&
+           ((d->C % 8 == 0 && d->K % 8 == 0) || (d->flags & PT_CONV_PAD_ZERO));
 }
 inline bool res3_bwd_ok(const pt_conv_desc* d, const uint16_t* dy, const uint16_t* wt, const uint16_t* dx, bool alone) {
     // (input-gradient launches share the chip with weight gradients on other streams, and a workgroup that holds a CU's
     // whole LDS for the length of the launch shuts those out: with the full 64 x 64 filter bank the train step gets
     // 25 us slower, with the smaller banks of a pruned network 25 us faster - so only those take it in batched calls)
-    return (PT_RES3 & 2) && res3_shape_ok(d) && ((alone && res3_bwd_large_ok(d)) || PT_RES3 & 4 || d->C * d->K <= kRes3BwdMaxBank) && aligned16(dy) &&
+    return (PT_RES3 & 2) && res3_shape_ok(d) && ((alone && res3_large_ok(d, 32)) || PT_RES3 & 4 || d->C * d->K <= kRes3BwdMaxBank) && aligned16(dy) &&
            aligned16(wt) && aligned16(dx) &&
            ((d->C % 8 == 0 && d->K % 8 == 0) || (d->flags & PT_CONV_PAD_ZERO));
 }
