@@ -414,7 +414,13 @@ extern "C" int32_t pt_conv_fwd_batched(const pt_conv_desc* descs, const uint16_t
 static int32_t bwd_data_classes(const pt_conv_desc* d, const uint16_t* dy, const uint16_t* wt, uint16_t* dx,
                                 hipStream_t st, IgemmPending& pend, bool alone = false) {
     int32_t rc = PT_OK;
-    if (res3_bwd_ok(d, dy, wt, dx, alone)) {  // the same kernel on dy with the k-innermost filter copy and mirrored taps
+    bool resident = res3_bwd_ok(d, dy, wt, dx, false);
+    if (!resident && alone && res3_bwd_ok(d, dy, wt, dx, true)) {  // (only where a batched call adds in the same order: the same bits)
+        IgemmArgs a = make_bwd_data_args(d, bwd_data_class(d, 0, 0), 0, 0, dy, wt, dx);
+        igemm_fold(a);
+        resident = ceil_div(a.M, 128) >= 256 || !igemm_small_ok(a) || pick_igemm_kernel(&a, 1) == 0;
+    }
+    if (resident) {  // the same kernel on dy with the k-innermost filter copy and mirrored taps
         const int kp = (int)round_up(d->K, 8);
         Res3Args r{dy, wt, dx, d->N, d->H, d->W, d->K, kp, d->y_cpitch, d->C, kp, d->x_cpitch, 0, 0, 0, 0, 0, 0, 0};
         return hip_status(launch_conv3x3_res(r, kRes3Bwd, st));
@@ -591,7 +597,7 @@ extern "C" int32_t pt_conv_bwd_data(const pt_conv_desc* d, const uint16_t* dy, c
     hipStream_t st = (hipStream_t)stream;
     const int RS = d->R * d->S;
     const int kpitch = (int)round_up(d->K, 8);
-    if (res3_bwd_ok(d, dy, w, dx, true) && d->w_cpitch % 8 == 0 && r3_krsc_bank_ok(d->K, d->C)) {  // transposes the filter bank itself
+    if (res3_bwd_ok(d, dy, w, dx, false) && d->w_cpitch % 8 == 0 && r3_krsc_bank_ok(d->K, d->C)) {  // transposes the filter bank itself
         Res3Args r{dy, w, dx, d->N, d->H, d->W, d->K, kpitch, d->y_cpitch, d->C, d->w_cpitch, d->x_cpitch, 0, 0, 0, 0, 0, 0, 0};
         return hip_status(launch_conv3x3_res(r, kRes3BwdKrsc, st));
     }
