@@ -310,14 +310,15 @@ inline WgradPlan plan_wgrad_tiles(const pt_conv_desc* d, bool dl, int cfg = -1) 
     return p;
 }
 
-// What wgrad_row3_body takes: 3 x 3 filters at stride 1 and padding 1 whose places and offsets fit its 24 and 30 bits, from
+// What wgrad_row3_body takes: 3 x 3 filters at stride 1 and padding 1 whose places and offsets fit its 24 and 30 bits (x is addressed
+// from one pixel ahead of a slice, so the last channels of a single slice's last pixel end at (pixels + 1) * x_cpitch), from
 // 3000 pixels on: with fewer, its 2 us more of set-up and of adding up are more than it saves (5 x 13 x 13, 72 -> 40: 4.3 us in
 // 64 x 64 tiles, 7.1 so).
 constexpr int64_t kRow3MinPixels = 3000;
 inline bool wgrad_row3_ok(const pt_conv_desc* d, bool dl) {
     const int64_t rows = (int64_t)d->N * d->H, pixels = rows * d->W, most = (int64_t)1 << 29;  // elements
     return dl && d->R == 3 && d->S == 3 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 1 && d->pad_w == 1 &&
-           pixels >= kRow3MinPixels && pixels + rows < (1 << 24) && pixels * d->x_cpitch < most && pixels * d->y_cpitch < most;
+           pixels >= kRow3MinPixels && pixels + rows < (1 << 24) && (pixels + 1) * d->x_cpitch <= most && pixels * d->y_cpitch < most;
 }
 inline WgradPlan plan_wgrad_row3(const pt_conv_desc* d, WgradPlan p) {  // p: the layer's plan in another form
     p.cfg = kWgRow3;

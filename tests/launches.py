@@ -1,8 +1,8 @@
 """Which kernels the library launches for a convolution call, found without a GPU: the built library, in a process of its own,
 on launch_recorder.c in the place of the HIP runtime.
 
-`python launches.py` reads one JSON list of [call, N, H, W, C, K, R, stride, pad, zero padding] a line, channel pitches rounded
-up to 8, and writes one list of launches for each; `of_calls` does that from a test."""
+`python launches.py` reads one JSON list of [call, N, H, W, C, K, R, stride, pad, zero padding] a line ("bwd_weight_batched": and
+workgroups; a batched call of one layer), channel pitches rounded up to 8, and writes one list of launches for each; `of_calls` does that from a test."""
 import ctypes as C
 import json
 import os
@@ -31,7 +31,7 @@ def _main():
     from paper_1901_09290_amd import binding as B
     at = 1 << 20   # (an aligned address: nothing is read)
     for line in sys.stdin:
-        call, N, H, W, Ch, K, R, stride, pad, zero = json.loads(line)
+        call, N, H, W, Ch, K, R, stride, pad, zero, *more = json.loads(line)
         p8 = lambda n: (n + 7) // 8 * 8
         d = B.conv_desc(N, H, W, Ch, K, R, R, stride, pad, p8(Ch), p8(K), p8(Ch), B.CONV_PAD_ZERO if zero else 0)
         rec.forget()
@@ -41,6 +41,11 @@ def _main():
             assert B.lib().pt_conv_fwd_stats(C.byref(d), at, at, at, at, 1 << 40, None) == 0
         elif call == "bwd_data":
             B.conv_bwd_data_crsk_at(d, at, at, at, None)
+        elif call == "bwd_weight_batched":
+            jobs = (B.LayerWgrad * 1)(B.LayerWgrad(d, at, at, at, None, None, None, 0, 0))
+            size = C.c_size_t()
+            assert B.lib().pt_conv_bwd_weight_batched_workspace_bytes(jobs, 1, more[0], C.byref(size)) == 0
+            assert B.lib().pt_conv_bwd_weight_batched(jobs, 1, 0.0, more[0], at, size.value, None) == 0
         else:
             ws = B.conv_bwd_weight_workspace_bytes(d)
             assert B.lib().pt_conv_bwd_weight(C.byref(d), at, at, at, at, ws, None) == 0

@@ -126,3 +126,20 @@ def test_early_3x3_gradients_by_themselves_keep_their_weights_in_lds(launches):
     wide = [(24, 48, 48, 64, 64), (16, 64, 64, 64, 64), (2, 96, 96, 64, 60), (10, 56, 56, 64, 64)]
     got = _forms(launches, [("fwd", *c, 3, 1, 1, True) for c in resident + [(24, 112, 112, 64, 64), (24, 48, 48, 48, 64)] + wide])
     assert [k[0][0] == "k_conv3x3_res" for k in got] == [True] * 6 + [False] * 4, got
+
+
+# Sizes around the limits of the row form's offsets: (N, H, W, C, K), and whether it may take them.  Its x is addressed from one pixel
+# ahead, so all channels of the last pixel have to lie inside 2^30 bytes counted from there.
+ROW3_LIMITS = [((2891, 17, 21, 520, 520), True), ((2892, 17, 21, 520, 520), False), ((12, 91, 240, 2040, 2040), True),
+               ((12, 91, 241, 2040, 2040), False), ((2048, 16, 16, 1024, 64), False), ((2047, 16, 16, 64, 1024), True),
+               ((2048, 16, 16, 64, 1024), False), ((233016, 8, 8, 32, 32), True), ((233017, 8, 8, 32, 32), False)]
+
+
+def test_limits_of_three_taps_from_one_tile(launches):
+    """With operands beyond its 30 bits, or places beyond 24, a weight gradient takes another form, called alone and in a batched call."""
+    for (N, H, W, C, K), ok in ROW3_LIMITS:
+        pixels, last = N * H * W, 2 * ((N * H * W + 1) * C)  # (C a multiple of 8: the pitch)
+        assert ok == (last <= 1 << 30 and 2 * pixels * K < 1 << 30 and pixels + N * H < 1 << 24)
+        got = launches([["bwd_weight", N, H, W, C, K, 3, 1, 1, True], *(["bwd_weight_batched", N, H, W, C, K, 3, 1, 1, True, w] for w in (0, 96))])
+        took = ["k_wgrad_row3" in [g["kernel"][0] for g in call] for call in got]
+        assert took == [ok, ok, ok and C > 32], (N, H, W, C, K, took)  # (32 channels beside others: estimated to be slower)

@@ -747,6 +747,27 @@ def test_weight_gradient_three_taps_from_one_tile(N, H, W, C, K, pad_zero, workg
     assert torch.equal(got[1][..., :C], got[2][..., :C])
 
 
+@pytest.mark.parametrize("N", [2891, 2892])
+def test_weight_gradient_three_taps_at_the_limit_of_their_offsets(N):
+    """The last image of tensors of just under and just over 2^30 bytes, read as one slice (520 channels, 17 x 21): everything else is
+    zero, so dw is the last image's.  The larger one is past the row form's offsets."""
+    from gpu_util import CONV_TOL, DEV, dev_bf16, rel_err, workspace
+    from paper_1901_09290_amd import binding as B
+    H, W, C = 17, 21, 520
+    spec, one = _spec(N, H, W, C, C, 3, 1, 1), _spec(1, H, W, C, C, 3, 1, 1)
+    d = B.desc_of(spec, C, C, C, B.CONV_PAD_ZERO)
+    plan = B.conv_bwd_weight_plan(d)
+    assert ((plan.tile_m, plan.splits) == (192, 1)) == (N == 2891)
+    t = wl.conv_tensors(one, np.random.Generator(np.random.PCG64(1350)), want=("x", "dy"))
+    x, dy = (torch.zeros((N, H, W, C), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    x[-1:], dy[-1:] = dev_bf16(t["x"], C, 0), dev_bf16(t["dy"], C, 0)
+    dw = torch.empty((C, 3, 3, C), dtype=torch.float32, device=DEV)
+    B.conv_bwd_weight(d, x, dy, dw, workspace(B.conv_bwd_weight_workspace_bytes(d)))
+    got, want = dw.cpu().numpy(), oracle.conv_bwd_weight(oracle.shape_of(one), t["x"], t["dy"])
+    assert rel_err(got, want) <= CONV_TOL
+    assert rel_err(got[:, :, :, -40:], want[:, :, :, -40:]) <= CONV_TOL   # (the channels past the limit)
+
+
 @pytest.mark.parametrize("case", [(4, 16, 16, 16, 16, 3, 1, 1), (2, 15, 15, 40, 136, 3, 2, 1), (64, 14, 14, 64, 64, 3, 1, 1), (2, 18, 18, 3, 16, 7, 2, 3),
                                   (1, 7, 7, 520, 520, 3, 1, 1)], ids=lambda c: "x".join(map(str, c)))
 @pytest.mark.parametrize("small_workspace", [False, True])
