@@ -2262,20 +2262,25 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
 // with 64 x 64 tiles 252 workgroups fetch 462 MB for the last, so 157.  Whole calls 26.6 -> 26.1, 26.1 -> 25.7, 29.7 -> 24.6, 7 x 7,
 // 512 -> 512 30.2 -> 25.7, 30 x 14 x 14, 512 -> 512 50.6 -> 39.0; training step of ResNet-50 3255 -> 3186 us, pruned 2679 -> 2638.
 // Five stages: four 1 to 2 us longer, six and eight the same.
-//   (A place of the zero column multiplies a zero of dy with the x beside it, where the other forms multiply a zero of x
-// with dy: an infinity in x reaches all three taps of its channels here.)
+//   A place of the zero column multiplies a zero of dy with the x beside it, which is no tap's: an infinity or a NaN there
+// would reach taps that never read it.  Such a product is a NaN, and so is the tap's sum: a workgroup that finds one in its
+// outer taps runs its slice again with x cleared at those places (MASKED), so that only what a tap reads can make its
+// sum one.  The look for a NaN costs 0.2 to 0.4 us of a call's 26 (once a slice; 40 us calls beside others 0.4).  (The other way
+// round, a dy that is not finite meets a zero of x outside the image, here as in wgrad_dl_body.)
 // A workgroup's slice in positions; a.Q.d is W + 1 and a.pixels the number of positions.  Offsets inside a slice in 24 bits times a
 // pitch, below kBufRecords (wgrad_row3_ok).
 constexpr int kRow3Px = 64;
 constexpr int kRow3XBytes = (kRow3Px / 8 + 1) * 1024;  // 66 rows of 64 channels, in loads of eight rows
 constexpr int kRow3StageBytes = kRow3XBytes + kRow3Px * 128;
 constexpr int kRow3ReduceBytes = 64 * 1024;
-template <int STAGES>
-__device__ __forceinline__ void wgrad_row3_body(const WgradArgs& a, const int lin, uint8_t* smem_b) {
+// Returns whether the slice is to be run again.
+template <int STAGES, bool MASKED>
+__device__ __forceinline__ bool wgrad_row3_body(const WgradArgs& a, const int lin, uint8_t* smem_b) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
-    static_assert(STAGES >= 4 && STAGES * kRow3StageBytes >= kRow3ReduceBytes && STAGES * kRow3StageBytes <= 160 * 1024, "LDS");
+    static_assert(STAGES >= 4 && STAGES * kRow3StageBytes >= kRow3ReduceBytes + 8 * 4 && STAGES * kRow3StageBytes <= 160 * 1024, "LDS");
     constexpr uint32_t kBufRecords = 0x40000000u, kBufOut = 0x80000000u, kBufFlags = 0x00020000u;
-    const int lane = threadIdx.x & 63;
+    int lane = threadIdx.x & 63;
+    if constexpr (MASKED) asm volatile("" : "+v"(lane));  // (nothing of the first run is kept in registers for this one)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wc = wave & 1, wp = wave >> 1;  // half of the input channels, quarter of a step's positions
     const int split = (int)fdiv((uint32_t)lin, a.ntile_div);
@@ -2328,7 +2333,9 @@ __device__ __forceinline__ void wgrad_row3_body(const WgradArgs& a, const int li
         __builtin_amdgcn_raw_ptr_buffer_load_lds(x_srd, (lds_void_ptr)(x_to + stage * kRow3StageBytes), 16, vx, 0, 0, 0);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(y_srd, (lds_void_ptr)(y_to + stage * kRow3StageBytes), 16, vy, 0, 0, 0);
         const uint32_t qs = q + q_step;
-        pix += p_step - (qs >= (uint32_t)Qp ? 1u : 0u);
+        pix += p_step;
+        asm("" : "+v"(pix));  // (or the carry is subtracted from p_step first, an instruction more)
+        pix -= qs >= (uint32_t)Qp ? 1u : 0u;
         q = min(qs, qs - (uint32_t)Qp);
         m = min(m + m_step, m + (m_step - (uint32_t)PQ));
         x_left -= kRow3Px;
@@ -2358,6 +2365,13 @@ __device__ __forceinline__ void wgrad_row3_body(const WgradArgs& a, const int li
     for (int s = 0; s < 3; ++s) ax[s] = frag_at(tr_row + s, wc);
 #pragma unroll
     for (int b = 0; b < 2; ++b) ay[b] = frag_at(tr_row, b) + kRow3XBytes;
+    // MASKED: which of a lane's eight positions lie in the zero column (the places every W + 1 from there on are known as bits)
+    [[maybe_unused]] uint32_t q_frag = 0, column = 0, zeros = 0;
+    if constexpr (MASKED) {
+        const uint32_t t = (uint32_t)(t0 + wp * 16 + (lane >> 5) * 8);
+        q_frag = t - fdiv(t, a.Q) * (uint32_t)Qp;
+        for (int b = 0; b < 8; b += Qp) column |= 1u << b;
+    }
     f32x16 acc[3][2];
 #pragma unroll
     for (int s = 0; s < 3; ++s)
@@ -2388,7 +2402,13 @@ __device__ __forceinline__ void wgrad_row3_body(const WgradArgs& a, const int li
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int h = 0; h < 2; ++h) lds_tie(fy[B][b][h]);
-        const bf16x8 vx = join_halves(fx[S][0], fx[S][1]);
+        bf16x8 vx = join_halves(fx[S][0], fx[S][1]);
+        if constexpr (MASKED && S != 1) {  // (the middle tap reads the zero column there)
+            u32x4 w = __builtin_bit_cast(u32x4, vx);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] &= (zeros >> (2 * e) & 1 ? 0u : 0xffffu) | (zeros >> (2 * e + 1) & 1 ? 0u : 0xffff0000u);
+            vx = __builtin_bit_cast(bf16x8, w);
+        }
 #pragma unroll
         for (int b = 0; b < 2; ++b)
             acc[S][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(join_halves(fy[B][b][0], fy[B][b][1]), vx, acc[S][b], 0, 0, 0);
@@ -2398,41 +2418,63 @@ __device__ __forceinline__ void wgrad_row3_body(const WgradArgs& a, const int li
     typedef std::integral_constant<int, 1> c1;
     typedef std::integral_constant<int, 2> c2;
 
+    if constexpr (MASKED) {  // rare: one stage, one step after the other
+        for (int kt = 0; kt < nk; ++kt) {
+            issue(0);
+            wait_vmcnt<0>();
+            barrier_nofence();
+            read_y(c0{}, 0u);
+            read_x(c0{}, 0u);
+            read_x(c1{}, 0u);
+            read_x(c2{}, 0u);
+            lds_wait<0>(fx[2][1]);
+            zeros = q_frag + 8 < (uint32_t)Qp ? 0u : column << ((uint32_t)Qp - 1 - q_frag);
+            multiply(c0{}, c0{});
+            multiply(c1{}, c0{});
+            multiply(c2{}, c0{});
+            q_frag = min(q_frag + q_step, q_frag + (q_step - (uint32_t)Qp));
+            barrier_nofence();
+        }
+    } else {
 #pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s) issue(s);
-    wait_stages(std::integral_constant<int, STAGES - 2>{});
-    barrier_nofence();
-    read_y(c0{}, 0u);
-    read_x(c0{}, 0u);
-    read_x(c1{}, 0u);
-    read_x(c2{}, 0u);
-    constexpr int UNROLL = STAGES % 2 ? 2 * STAGES : STAGES;  // (the dy fragments alternate between two buffers)
-    for (int kt0 = 0; kt0 < nk; kt0 += UNROLL) {
-        static_for<0, UNROLL>([&](auto u_c) {
-            constexpr int U = decltype(u_c)::value;
-            if (kt0 + U < nk) {
-                wait_stages(std::integral_constant<int, STAGES - 3>{});  // the next stage has landed ...
-                barrier_nofence();  // ... for every wave, and nobody reads the previous one any more
-                typedef std::integral_constant<int, (U & 1)> now;
-                typedef std::integral_constant<int, ((U + 1) & 1)> next;
-                constexpr uint32_t nxt = (uint32_t)((U + 1) % STAGES) * kRow3StageBytes;
-                read_y(next{}, nxt);
-                multiply(c0{}, now{});
-                read_x(c0{}, nxt);
-                issue((U + STAGES - 1) % STAGES);
-                multiply(c1{}, now{});
-                read_x(c1{}, nxt);
-                multiply(c2{}, now{});
-                read_x(c2{}, nxt);
-            }
-        });
+        for (int s = 0; s < STAGES - 1; ++s) issue(s);
+        wait_stages(std::integral_constant<int, STAGES - 2>{});
+        barrier_nofence();
+        read_y(c0{}, 0u);
+        read_x(c0{}, 0u);
+        read_x(c1{}, 0u);
+        read_x(c2{}, 0u);
+        constexpr int UNROLL = STAGES % 2 ? 2 * STAGES : STAGES;  // (the dy fragments alternate between two buffers)
+        for (int kt0 = 0; kt0 < nk; kt0 += UNROLL) {
+            static_for<0, UNROLL>([&](auto u_c) {
+                constexpr int U = decltype(u_c)::value;
+                if (kt0 + U < nk) {
+                    wait_stages(std::integral_constant<int, STAGES - 3>{});  // the next stage has landed ...
+                    barrier_nofence();  // ... for every wave, and nobody reads the previous one any more
+                    typedef std::integral_constant<int, (U & 1)> now;
+                    typedef std::integral_constant<int, ((U + 1) & 1)> next;
+                    constexpr uint32_t nxt = (uint32_t)((U + 1) % STAGES) * kRow3StageBytes;
+                    read_y(next{}, nxt);
+                    multiply(c0{}, now{});
+                    read_x(c0{}, nxt);
+                    issue((U + STAGES - 1) % STAGES);
+                    multiply(c1{}, now{});
+                    read_x(c1{}, nxt);
+                    multiply(c2{}, now{});
+                    read_x(c2{}, nxt);
+                }
+            });
+        }
     }
     lds_wait<0>(fx[0][0]);
     wait_vmcnt<0>();  // the loads issued past the end have landed before LDS is reused
 
-    // ---- the four position groups are added tap by tap: every wave parks its two blocks of 32 input x 32 output channels,
-    // then wave w adds and stores half of block w >> 1 (rows and columns of an element as in wgrad_dl_body)
+    // ---- the four position groups are added tap by tap, the middle one last: every wave parks its two blocks of 32 input x 32 output
+    // channels, then wave w adds and stores half of block w >> 1 (rows and columns of an element as in wgrad_dl_body)
     float4* red = reinterpret_cast<float4*>(smem_b);
+    int* again = reinterpret_cast<int*>(smem_b + kRow3ReduceBytes);  // one of each wave
+    float probe = 0.f;
+    int run_again = 0;
     const int row_pitch = a.direct ? a.RS * a.wpitch : a.out_row_pitch, tap_pitch = a.direct ? a.wpitch : a.CP;
     const int64_t first = (int64_t)n0 * row_pitch + (a.direct ? 0 : (int64_t)split * a.K * a.out_row_pitch);
     const uint32_t tile_bytes = (uint32_t)(min(a.K - n0, 64) * row_pitch) * 4u;
@@ -2441,8 +2483,18 @@ __device__ __forceinline__ void wgrad_row3_body(const WgradArgs& a, const int li
     const int c = cb + (blk & 1) * 32 + (lane & 31), k0 = (blk >> 1) * 32 + 4 * (lane >> 5) + 8 * g0;
     const bool ok = c < (a.direct ? a.C : a.CP);
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
+    for (int i = 0; i < 3; ++i) {
+        constexpr int order[3] = {0, 2, 1};
+        const int s = order[i];
+        if (!MASKED && s == 1) {
+            const bool any = __ballot(probe != probe && c < a.C) != 0;
+            if (lane == 0) again[wave] = any;
+        }
         __syncthreads();
+        if (!MASKED && s == 1) {
+#pragma unroll
+            for (int w = 0; w < 8; ++w) run_again |= again[w];
+        }
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
@@ -2460,6 +2512,14 @@ __device__ __forceinline__ void wgrad_row3_body(const WgradArgs& a, const int li
             v[4 * g + 1] = ((r[0].y + r[1].y) + r[2].y) + r[3].y;
             v[4 * g + 2] = ((r[0].z + r[1].z) + r[2].z) + r[3].z;
             v[4 * g + 3] = ((r[0].w + r[1].w) + r[2].w) + r[3].w;
+        }
+        if (!MASKED && s != 1) {  // (a sum is a NaN if one of its terms is; padding channels may hold anything)
+            if (n0 + 64 <= a.K) {  // uniform
+                probe += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) probe += n0 + k0 + 8 * (e >> 2) + (e & 3) < a.K ? v[e] : 0.f;
+            }
         }
         const uint32_t at0 = ok ? (uint32_t)(k0 * row_pitch + (3 * fr + s) * tap_pitch + c) * 4u : kBufOut;
         auto at = [&](int e) { return at0 + (uint32_t)((8 * (e >> 2) + (e & 3)) * row_pitch) * 4u; };
@@ -2483,6 +2543,9 @@ __device__ __forceinline__ void wgrad_row3_body(const WgradArgs& a, const int li
 #pragma unroll
         for (int e = 0; e < 8; ++e) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[e]), o_srd, at(e), 0, 0);
     }
+    return __builtin_amdgcn_readfirstlane(run_again) != 0;
+#else
+    return false;
 #endif
 }
 
@@ -2545,7 +2608,11 @@ __global__ __launch_bounds__(512, 1) void k_wgrad_dl(const WgradArgs a) {
 }
 __global__ __launch_bounds__(512, 1) void k_wgrad_row3(const WgradArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_b[];
-    wgrad_row3_body<kRow3Stages>(a, xcd_remap(blockIdx.x, gridDim.x), smem_b);
+    const int lin = xcd_remap(blockIdx.x, gridDim.x);
+    if (wgrad_row3_body<kRow3Stages, false>(a, lin, smem_b)) {
+        __syncthreads();  // (everyone has seen that: the stage buffers are free)
+        wgrad_row3_body<kRow3Stages, true>(a, lin, smem_b);
+    }
 }
 
 // ------------------------------------------------------------------------------------------- //

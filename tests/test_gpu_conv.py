@@ -747,6 +747,32 @@ def test_weight_gradient_three_taps_from_one_tile(N, H, W, C, K, pad_zero, workg
     assert torch.equal(got[1][..., :C], got[2][..., :C])
 
 
+@pytest.mark.parametrize("N,H,W,C,K,workgroups", [(26, 14, 14, 64, 64, 24), (64, 14, 14, 200, 136, 96), (400, 4, 4, 120, 70, 24), (3, 41, 43, 203, 171, 0),
+                                                  (3, 40, 50, 64, 64, 1), (26, 14, 14, 64, 64, 0)])
+def test_weight_gradient_of_infinities_at_the_borders(N, H, W, C, K, workgroups):
+    """Infinities and a NaN in border pixels of x: only the taps that read them may show it, whatever form the layer takes."""
+    from gpu_util import CONV_TOL, DEV, dev_bf16, pitch8, rel_err, workspace
+    from paper_1901_09290_amd import binding as B
+    spec = _spec(N, H, W, C, K, 3, 1, 1)
+    xp, yp = pitch8(C), pitch8(K)
+    t = wl.conv_tensors(spec, np.random.Generator(np.random.PCG64(1380 + N + H)), want=("x", "dy"))
+    x = t["x"]
+    for c, (n, h, w, v) in enumerate([(0, 0, 0, np.inf), (0, H - 1, W - 1, np.inf), (N - 1, 1, W - 1, -np.inf), (N - 1, H - 1, 0, np.inf), (1, 2, 0, np.nan),
+                                      (1, 0, W - 1, np.inf), (N - 1, H - 1, W - 1, np.nan), (2, 1, 1, np.inf)]):
+        x[n, h, w, c * 7 % C] = v
+    d = B.desc_of(spec, xp, yp, xp, 0)
+    xd, dyd = dev_bf16(x, xp, 0x7FC0), dev_bf16(t["dy"], yp, 0x7FC0)
+    dw = torch.zeros((K, 3, 3, xp), dtype=torch.float32, device=DEV)
+    jobs = [B.layer_wgrad(d, xd, dyd, dw)]
+    B.conv_bwd_weight_batched(jobs, 0.0, workspace(B.conv_bwd_weight_batched_workspace_bytes(jobs, workgroups)), workgroups)
+    got, want = dw.cpu().numpy()[..., :C], oracle.conv_bwd_weight(oracle.shape_of(spec), x, t["dy"])
+    finite = np.isfinite(want)
+    assert 0 < np.sum(~finite) < finite.size // 8
+    assert np.array_equal(np.isfinite(got), finite)
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    assert rel_err(got[finite], want[finite]) <= CONV_TOL
+
+
 @pytest.mark.parametrize("N", [2891, 2892])
 def test_weight_gradient_three_taps_at_the_limit_of_their_offsets(N):
     """The last image of tensors of just under and just over 2^30 bytes, read as one slice (520 channels, 17 x 21): everything else is
