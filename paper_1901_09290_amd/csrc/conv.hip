@@ -27,6 +27,7 @@
 #include <vector>
 
 #include "conv_kernels.h"
+#include "norms.h"
 
 namespace pt {
 
@@ -865,15 +866,28 @@ extern "C" int32_t pt_conv_layer_step(const pt_conv_desc* d, const uint16_t* x, 
     if (rc != PT_OK) return rc;
     if (!x || !dy || !w || !w_bf16 || !out_norm || !in_norm || !y || !dw) return PT_ERR_NULL;
     if (flags & ~(PT_LASSO_OUT | PT_LASSO_IN)) return PT_ERR_UNSUPPORTED;
+    // everything that any of the calls would refuse, before the first of them enqueues anything
     const int RS = d->R * d->S;
+    rc = check_norm_layer(NormLayer{w, out_norm, in_norm, w_bf16, nullptr, nullptr, d->K, RS, d->C, d->w_cpitch});
+    if (rc != PT_OK) return rc;
+    if (!ws) return PT_ERR_NULL;
+    if (ws_bytes < norm_layer_ws_bytes(d->K, RS, d->C) || (dx && ws_bytes < bwd_data_ws(d))) return PT_ERR_WORKSPACE;
+    if (!aligned16(ws)) return PT_ERR_SHAPE;
+    WgradLayer L{d, x, dy, dw, ReduceLasso{w, flags & PT_LASSO_OUT ? out_norm : nullptr, flags & PT_LASSO_IN ? in_norm : nullptr, lambda},
+                 false, false, {}, 0, 0};
+    rc = check_wgrad_layer(L);
+    if (rc != PT_OK) return rc;
+    if (!L.stem) L.p = plan_wgrad(d, L.vec);
+    const bool fused = ws_bytes >= wgrad_layer_ws(L);
+    if (!fused) L.rl.w = nullptr;
+    if (ws_bytes < wgrad_layer_ws(L)) return PT_ERR_WORKSPACE;
+
     rc = pt_group_norms(w, d->K, RS, d->C, d->w_cpitch, out_norm, in_norm, w_bf16, ws, ws_bytes, stream);
     if (rc == PT_OK) rc = pt_conv_fwd(d, x, w_bf16, y, ws, ws_bytes, stream);
     if (rc == PT_OK && dx) rc = pt_conv_bwd_data(d, dy, w_bf16, dx, ws, ws_bytes, stream);
-    if (rc != PT_OK) return rc;
-    rc = pt_conv_bwd_weight_lasso(d, x, dy, w, out_norm, in_norm, lambda, flags, dw, ws, ws_bytes, stream);
-    if (rc != PT_ERR_WORKSPACE) return rc;
-    rc = pt_conv_bwd_weight(d, x, dy, dw, ws, ws_bytes, stream);
-    return rc != PT_OK ? rc : pt_group_lasso_grad(w, out_norm, in_norm, lambda, flags, dw, d->K, RS, d->C, d->w_cpitch, stream);
+    if (rc == PT_OK) rc = launch_wgrad_layers(&L, 1, false, ws, (hipStream_t)stream);
+    if (rc != PT_OK || fused) return rc;
+    return pt_group_lasso_grad(w, out_norm, in_norm, lambda, flags, dw, d->K, RS, d->C, d->w_cpitch, stream);
 }
 
 // Plans the layers of a batched call and lays their workspaces out one after the other; returns the bytes needed.

@@ -2,7 +2,7 @@
 on launch_recorder.c in the place of the HIP runtime.
 
 `python launches.py` reads one JSON list of [call, N, H, W, C, K, R, stride, pad, zero padding] a line ("bwd_weight_batched": and
-workgroups; a batched call of one layer), channel pitches rounded up to 8, and writes one list of launches for each; `of_calls` does that from a test."""
+workgroups, a batched call of one layer; "layer_step": and bytes of workspace), channel pitches rounded up to 8, and writes one list of launches for each, a status and the number of launches for a refused "layer_step"; `of_calls` does that from a test."""
 import ctypes as C
 import json
 import os
@@ -46,6 +46,11 @@ def _main():
             size = C.c_size_t()
             assert B.lib().pt_conv_bwd_weight_batched_workspace_bytes(jobs, 1, more[0], C.byref(size)) == 0
             assert B.lib().pt_conv_bwd_weight_batched(jobs, 1, 0.0, more[0], at, size.value, None) == 0
+        elif call == "layer_step":
+            rc = B.lib().pt_conv_layer_step(C.byref(d), at, at, at, at, at, at, 1e-3, 3, at, at, at, at, more[0], None)
+            if rc:
+                print(json.dumps([rc, rec.recorded()]), flush=True)
+                continue
         else:
             ws = B.conv_bwd_weight_workspace_bytes(d)
             assert B.lib().pt_conv_bwd_weight(C.byref(d), at, at, at, at, ws, None) == 0

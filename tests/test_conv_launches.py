@@ -143,3 +143,22 @@ def test_limits_of_three_taps_from_one_tile(launches):
         got = launches([["bwd_weight", N, H, W, C, K, 3, 1, 1, True], *(["bwd_weight_batched", N, H, W, C, K, 3, 1, 1, True, w] for w in (0, 96))])
         took = ["k_wgrad_row3" in [g["kernel"][0] for g in call] for call in got]
         assert took == [ok, ok, ok and C > 32], (N, H, W, C, K, took)  # (32 channels beside others: estimated to be slower)
+
+
+@pytest.mark.parametrize("case", [(4, 64, 64, 128, 128, 3, 1, 1), (64, 14, 14, 64, 64, 3, 1, 1), (2, 15, 15, 40, 136, 3, 2, 1), (1, 7, 7, 520, 520, 1, 1, 0),
+                                  (2, 18, 18, 3, 16, 7, 2, 3)], ids=lambda c: "x".join(map(str, c)))
+def test_a_layer_step_refuses_before_it_launches(launches, case):
+    """A workspace that is enough for some of the calls of a layer's step and not for others: refused with nothing launched."""
+    N, H, W, Ch, K, R, stride, pad = case
+    d = B.conv_desc(N, H, W, Ch, K, R, R, stride, pad, (Ch + 7) // 8 * 8, (K + 7) // 8 * 8, (Ch + 7) // 8 * 8, B.CONV_PAD_ZERO)
+    steps = [B.group_norms_workspace_bytes(K, R * R, Ch), B.conv_bwd_data_workspace_bytes(d), B.conv_bwd_weight_workspace_bytes(d),
+             B.conv_bwd_weight_lasso_workspace_bytes(d)]
+    sizes = sorted({max(0, n + e) for n in steps for e in (-256, 0)} | {0, 9216, 294912})
+    got = launches([["layer_step", *case, True, n] for n in sizes])
+    for n, g in zip(sizes, got):
+        if n < max(steps[:2]):
+            assert g == [-3, 0], (n, g)
+        elif n >= max(steps[:3]):
+            assert len(g) >= 4 and all("kernel" in launch for launch in g), (n, g)
+        else:  # (the weight gradient's query covers unaligned tensors too)
+            assert g == [-3, 0] or len(g) >= 4, (n, g)
