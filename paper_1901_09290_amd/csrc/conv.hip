@@ -361,7 +361,7 @@ extern "C" int32_t pt_conv_fwd(const pt_conv_desc* d, const uint16_t* x, const u
     }
     IgemmArgs a = make_fwd_args(d, x, w, y);
     const bool vec = d->x_cpitch % 8 == 0 && d->w_cpitch % 8 == 0 && aligned16(x) && aligned16(w);
-    return hip_status(launch_igemm(a, vec, (hipStream_t)stream));
+    return hip_status(launch_igemm(a, vec, (hipStream_t)stream, nullptr, nullptr, fwd_kernel(d, x, w, y)));
 }
 
 // Problems of the direct kernel waiting to be sent out together: those that chose the same instantiation share a launch.
@@ -403,7 +403,7 @@ extern "C" int32_t pt_conv_fwd_batched(const pt_conv_desc* descs, const uint16_t
             rc = pt_conv_fwd(d, x[i], w[i], y[i], nullptr, 0, stream);
         } else {
             IgemmArgs a = make_fwd_args(d, x[i], w[i], y[i]);
-            rc = pend.add(a, d->x_cpitch % 8 == 0 && d->w_cpitch % 8 == 0 && aligned16(x[i]) && aligned16(w[i]), st);
+            rc = pend.add(a, d->x_cpitch % 8 == 0 && d->w_cpitch % 8 == 0 && aligned16(x[i]) && aligned16(w[i]), st, fwd_kernel(d, x[i], w[i], y[i]));
         }
         if (rc != PT_OK) return rc;
     }
@@ -576,7 +576,7 @@ extern "C" int32_t pt_conv_fwd_stats(const pt_conv_desc* d, const uint16_t* x, c
     // so they are called as they are and the sums are taken from their output.
     IgemmArgs f = a;
     igemm_fold(f);
-    if (!stem_fwd_ok(d, x, w, y) && !res3_fwd_ok(d, x, w, y) && ceil_div(f.M, 128) * ceil_div(f.Nout, 128) < 256 &&
+    if (!stem_fwd_ok(d, x, w, y) && !res3_fwd_takes(d, x, w, y) && ceil_div(f.M, 128) * ceil_div(f.Nout, 128) < 256 &&
         igemm_small_ok(f) && pick_igemm_kernel(&f, 1) != 0) {
         rc = hip_status(launch_igemm(a, true, (hipStream_t)stream));
         if (rc != PT_OK) return rc;

@@ -439,9 +439,19 @@ inline bool res3_large_ok(const pt_conv_desc* d, int narrow) {
     const int tiles_x = (d->W + 55) / 56;
     return d->W <= narrow || (d->W > 48 * tiles_x && (int64_t)d->N * ((d->H + 3) / 4) * tiles_x >= 192);
 }
-inline bool res3_fwd_ok(const pt_conv_desc* d, const uint16_t* x, const uint16_t* w, const uint16_t* y) {
-    return (PT_RES3 & 1) && res3_shape_ok(d) && (d->C * d->K <= kRes3BwdMaxBank || res3_large_ok(d, 33)) && d->w_cpitch % 8 == 0 && aligned16(x) && aligned16(w) && aligned16(y) &&
+inline bool res3_fwd_takes(const pt_conv_desc* d, const uint16_t* x, const uint16_t* w, const uint16_t* y) {
+    return (PT_RES3 & 1) && res3_shape_ok(d) && d->w_cpitch % 8 == 0 && aligned16(x) && aligned16(w) && aligned16(y) &&
            ((d->C % 8 == 0 && d->K % 8 == 0) || (d->flags & PT_CONV_PAD_ZERO));
+}
+inline bool res3_fwd_ok(const pt_conv_desc* d, const uint16_t* x, const uint16_t* w, const uint16_t* y) {
+    return res3_fwd_takes(d, x, w, y) && (d->C * d->K <= kRes3BwdMaxBank || res3_large_ok(d, 33));
+}
+// launch_igemm's `kernel` of a forward call.  What the resident kernel takes and leaves to k_igemm_dl stays with its 128 x 64 tiles: they
+// add in the same order, and with statistics (which the small tiles would leave to a second launch) y is the same and the call one
+// launch.  us, small tiles / these / resident: 4 x 56 x 56, 64 -> 64 5.6, 5.8, 6.5 (with statistics 8.8, 6.9), 2 x 44 x 44, 64 -> 56 4.5, 5.3,
+// 6.0 (8.0, 6.4), 8 x 36 x 36, 60 -> 64 5.5, 5.9, 6.2 (8.7, 7.2).
+inline int fwd_kernel(const pt_conv_desc* d, const uint16_t* x, const uint16_t* w, const uint16_t* y) {
+    return res3_fwd_takes(d, x, w, y) ? 0 : -1;
 }
 inline bool res3_bwd_ok(const pt_conv_desc* d, const uint16_t* dy, const uint16_t* wt, const uint16_t* dx, bool alone) {
     // (input-gradient launches share the chip with weight gradients on other streams, and a workgroup that holds a CU's

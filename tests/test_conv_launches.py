@@ -162,3 +162,11 @@ def test_a_layer_step_refuses_before_it_launches(launches, case):
             assert len(g) >= 4 and all("kernel" in launch for launch in g), (n, g)
         else:  # (the weight gradient's query covers unaligned tensors too)
             assert g == [-3, 0] or len(g) >= 4, (n, g)
+
+
+def test_early_3x3_layers_with_statistics_are_one_launch(launches):
+    """Large banks on images whose columns do not fill the resident kernel's waves: the same tiles with statistics and without, alone and
+    in a batched call, and statistics in the same launch."""
+    for case in [(4, 56, 56, 64, 64), (2, 44, 44, 64, 56), (8, 36, 36, 60, 64), (1, 80, 80, 64, 64), (10, 40, 40, 57, 63), (24, 48, 48, 64, 64)]:
+        got = _forms(launches, [(call, *case, 3, 1, 1, True) for call in ("fwd", "fwd_stats", "fwd_batched")])
+        assert all(len(g) == 1 and g[0][:3] == ["k_igemm_dl", 128, 64] for g in got), (case, got)

@@ -156,6 +156,8 @@ FUSED = [
     (2, 13, 13, 45, 38, 3, 1, 1),      # ragged both ways
     (4, 28, 28, 128, 128, 3, 1, 1),    # several pixel tiles, two wave rows per tile
     (1, 1, 1, 8, 8, 1, 1, 0),
+    (2, 40, 44, 64, 60, 3, 1, 1),      # early 3 x 3 layers whose columns do not fill the resident kernel's tiles
+    (1, 50, 50, 57, 63, 3, 1, 1),
 ]
 
 
