@@ -428,23 +428,32 @@ inline bool res3_shape_ok(const pt_conv_desc* d) {
            d->K <= 64 && d->x_cpitch % 8 == 0 && d->y_cpitch % 8 == 0 &&
            (int64_t)d->H * d->W * (d->x_cpitch > d->y_cpitch ? d->x_cpitch : d->y_cpitch) * 2 <= 0x7fffffff;
 }
-// Larger banks (more than kRes3BwdMaxBank weights a tap), against 128 x 64 and 64 x 64 tiles: images whose tiles of up to 56 columns give
-// (nearly) all eight waves work.  us with 64 -> 64 channels in those tiles and in this kernel, gradients: 100 x 32 x 32 15.5 and
-// 12.4, 10 x 14 x 14 5.2 and 4.8; 56 columns, batch 64 25.2 and 19.4, batch 14 8.1 and 7.1, with less than 192 tiles the other way
-// round (batch 10 6.2 and 6.5, batch 4 5.5 and 6.2); five and six column blocks 24 x 48 x 48 8.6 and 10.1, 20 x 40 x 40 6.2 and 6.5;
-// forward 24 x 48 x 48 7.9 and 10.1, 40 x 40 x 40 8.4 and 10.3, several tiles a row, the last one narrow, 16 x 64 x 64 9.7 and 12.2,
-// 2 x 96 x 96 5.9 and 6.3, filled 24 x 112 x 112 35.6 and 28.4.  Forward calls of 33 columns stay here although 6 x 33 x 33 takes 5.9 us
-// instead of 5.4: the tests of runs of tiles are of that width.
-inline bool res3_large_ok(const pt_conv_desc* d, int narrow) {
-    const int tiles_x = (d->W + 55) / 56;
-    return d->W <= narrow || (d->W > 48 * tiles_x && (int64_t)d->N * ((d->H + 3) / 4) * tiles_x >= 192);
+// Larger banks (more than kRes3BwdMaxBank weights a tap) against the 128 x 64 tiles of k_igemm_dl, which add in the same order: by rounds of
+// either, 256 of this kernel's tiles (a CU each) and 512 of those (two a CU; up to 256 of them are half a round).  us in those and
+// here, from memory / cached, 64 -> 64 channels:
+//   up to 256 tiles: 31 x 32 x 32 6.9 / 6.1 and 6.4 / 5.8, but beyond 32 columns, where a tile is one row of blocks, 33 columns 5.9 / 5.7 and
+//   6.4 / 6.2 (batch 14), 10 x 56 x 56 6.8 / 5.9 and 7.4 / 6.6, 2 x 112 x 112 6.3 / 5.9 and 7.0 / 6.6;
+//   up to 512, one round here (224 to 256 tiles): 18 x 56 x 56 9.9 / 8.2 and 8.9 / 7.2, 64 x 32 x 32 10.4 / 8.3 and 9.0 / 7.3, 64 x 28 x 28 9.6 /
+//   7.9 and 8.5 / 7.1, with 168 of them 3 x 112 x 112 9.3 / 7.8 and 8.2 / 6.9; two rounds (280 to 400): 20 x 56 x 56 10.0 / 8.4 and 11.5 / 10.3, 80 x 28
+//   x 28 10.2 / 8.4 and 11.5 / 10.4, 100 x 24 x 24 10.1 / 8.3 and 11.0 / 10.0, 40 x 40 x 40 10.1 / 8.3 and 11.4 / 10.1;
+//   more, up to 0.8 of their tiles: 64 x 56 x 56 27.6 / 23.4 and 20.1 / 18.4, 64 x 48 x 48 21.0 / 18.0 and 16.8 / 14.7, 24 x 80 x 80 21.9 / 18.0 and
+//   19.4 / 17.5, 100 x 40 x 40 22.1 / 18.1 and 18.3 / 17.1; more of them: 40 x 70 x 70 25.4 / 21.2 and 26.2 / 24.3, 128 x 33 x 33 20.3 / 17.7 and 20.2 / 19.4.
+// 188 calls of both directions, mean of both states: always those tiles 1742 us, always these 1726, by this rule 1625, the better one of
+// each 1624.  (From memory, calls of 500 tiles in k_igemm_dl took 15 to 18 us instead of 10 in one run of five, and two rounds here less.)
+inline bool res3_large_ok(const pt_conv_desc* d) {
+    const int64_t tiles = ceil_div((int64_t)d->N * d->H * d->W, 128);
+    if (tiles <= 256) return d->W <= 32;
+    Res3Args a{};
+    a.N = d->N; a.H = d->H; a.W = d->W;
+    const int64_t own = r3_tile(a);
+    return tiles <= 512 ? own <= kR3Slots : 10 * own <= 9 * tiles;
 }
 inline bool res3_fwd_takes(const pt_conv_desc* d, const uint16_t* x, const uint16_t* w, const uint16_t* y) {
     return (PT_RES3 & 1) && res3_shape_ok(d) && d->w_cpitch % 8 == 0 && aligned16(x) && aligned16(w) && aligned16(y) &&
            ((d->C % 8 == 0 && d->K % 8 == 0) || (d->flags & PT_CONV_PAD_ZERO));
 }
 inline bool res3_fwd_ok(const pt_conv_desc* d, const uint16_t* x, const uint16_t* w, const uint16_t* y) {
-    return res3_fwd_takes(d, x, w, y) && (d->C * d->K <= kRes3BwdMaxBank || res3_large_ok(d, 33));
+    return res3_fwd_takes(d, x, w, y) && (d->C * d->K <= kRes3BwdMaxBank || res3_large_ok(d));
 }
 // launch_igemm's `kernel` of a forward call.  What the resident kernel takes and leaves to k_igemm_dl stays with its 128 x 64 tiles: they
 // add in the same order, and with statistics (which the small tiles would leave to a second launch) y is the same and the call one
@@ -457,7 +466,7 @@ inline bool res3_bwd_ok(const pt_conv_desc* d, const uint16_t* dy, const uint16_
     // (input-gradient launches share the chip with weight gradients on other streams, and a workgroup that holds a CU's
     // whole LDS for the length of the launch shuts those out: with the full 64 x 64 filter bank the train step gets
     // 25 us slower, with the smaller banks of a pruned network 25 us faster - so only those take it in batched calls)
-    return (PT_RES3 & 2) && res3_shape_ok(d) && ((alone && res3_large_ok(d, 32)) || PT_RES3 & 4 || d->C * d->K <= kRes3BwdMaxBank) && aligned16(dy) &&
+    return (PT_RES3 & 2) && res3_shape_ok(d) && ((alone && res3_large_ok(d)) || PT_RES3 & 4 || d->C * d->K <= kRes3BwdMaxBank) && aligned16(dy) &&
            aligned16(wt) && aligned16(dx) &&
            ((d->C % 8 == 0 && d->K % 8 == 0) || (d->flags & PT_CONV_PAD_ZERO));
 }

@@ -41,9 +41,9 @@ def _main():
             assert B.lib().pt_conv_fwd_stats(C.byref(d), at, at, at, at, 1 << 40, None) == 0
         elif call == "bwd_data":
             B.conv_bwd_data_crsk_at(d, at, at, at, None)
-        elif call == "fwd_batched":
-            one = (C.c_void_p * 1)(at)
-            assert B.lib().pt_conv_fwd_batched((B.ConvDesc * 1)(d), one, one, one, 1, None) == 0
+        elif call in ("fwd_batched", "bwd_data_batched"):
+            one, fn = (C.c_void_p * 1)(at), B.lib().pt_conv_fwd_batched if call == "fwd_batched" else B.lib().pt_conv_bwd_data_crsk_batched
+            assert fn((B.ConvDesc * 1)(d), one, one, one, 1, None) == 0
         elif call == "bwd_weight_batched":
             jobs = (B.LayerWgrad * 1)(B.LayerWgrad(d, at, at, at, None, None, None, 0, 0))
             size = C.c_size_t()

@@ -170,3 +170,19 @@ def test_early_3x3_layers_with_statistics_are_one_launch(launches):
     for case in [(4, 56, 56, 64, 64), (2, 44, 44, 64, 56), (8, 36, 36, 60, 64), (1, 80, 80, 64, 64), (10, 40, 40, 57, 63), (24, 48, 48, 64, 64)]:
         got = _forms(launches, [(call, *case, 3, 1, 1, True) for call in ("fwd", "fwd_stats", "fwd_batched")])
         assert all(len(g) == 1 and g[0][:3] == ["k_igemm_dl", 128, 64] for g in got), (case, got)
+
+
+# 64 -> 64 channels, 3 x 3: (N, H, W) and whether the resident kernel's rounds are fewer than those of 128 x 64 tiles
+ROUNDS = [((31, 32, 32), True), ((30, 33, 33), False), ((10, 56, 56), False), ((11, 56, 56), True), ((18, 56, 56), True), ((20, 56, 56), False),
+          ((64, 32, 32), True), ((64, 28, 28), True), ((80, 28, 28), False), ((100, 24, 24), False), ((3, 112, 112), True), ((3, 128, 128), False),
+          ((40, 40, 40), False), ((48, 40, 40), True), ((64, 48, 48), True), ((24, 80, 80), True), ((40, 70, 70), False), ((128, 33, 33), False),
+          ((64, 56, 56), True)]
+
+
+def test_early_3x3_layers_with_large_banks_by_rounds(launches):
+    """Forward calls and input gradients by themselves alike; a batched gradient leaves the resident kernel to smaller banks."""
+    calls = [[(call, *size, 64, 64, 3, 1, 1, True) for size, _ in ROUNDS] for call in ("fwd", "bwd_data", "bwd_data_batched")]
+    fwd, alone, batched = (_forms(launches, c) for c in calls)
+    for (size, resident), f, a, b in zip(ROUNDS, fwd, alone, batched):
+        want = ["k_conv3x3_res"] if resident else ["k_igemm_dl"]
+        assert [k[0] for k in f] == want and [k[0] for k in a] == want and [k[0] for k in b] == ["k_igemm_dl"], (size, f, a, b)

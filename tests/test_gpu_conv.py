@@ -269,7 +269,7 @@ def test_early_3x3_layers_with_resident_weights(case, pad_zero):
     _check_full(spec, 950 + sum(case), pitch8(spec.C), pitch8(spec.K), pitch8(spec.C), pad_zero=pad_zero)
 
 
-LAYOUTS = dict(C=[9, 16, 17, 32, 33, 48, 49, 64], K=[7, 32, 33, 50, 64], images=[(3, 10, 12), (91, 12, 33)])  # (273 tiles: runs of two)
+LAYOUTS = dict(C=[9, 16, 17, 32, 33, 48, 49, 64], K=[7, 32, 33, 50, 64], images=[(3, 10, 12), (110, 11, 55)])  # (330 tiles: runs of two)
 
 
 @pytest.mark.parametrize("C", LAYOUTS["C"])
@@ -845,7 +845,8 @@ def test_fragments_a_step_ahead_in_gradients(case, pad_zero):
     assert rel_err(host_bf16(dx[0], spec.C), oracle.conv_bwd_data(oracle.shape_of(spec), t["dy"], t["w"])) <= CONV_TOL
 
 
-@pytest.mark.parametrize("N,H,W,C,K,pad_zero", [(3, 14, 19, 64, 64, False), (49, 16, 56, 64, 56, False), (50, 15, 55, 59, 61, True), (2, 1, 1, 64, 64, False)])
+@pytest.mark.parametrize("N,H,W,C,K,pad_zero", [(3, 14, 19, 64, 64, False), (49, 16, 56, 64, 56, False), (50, 15, 55, 59, 61, True), (2, 1, 1, 64, 64, False),
+                                                  (36, 31, 32, 64, 64, False), (100, 27, 25, 61, 60, True), (20, 48, 60, 64, 64, False)])
 def test_early_3x3_input_gradient_with_a_large_bank(N, H, W, C, K, pad_zero):
     """Resident weights in a gradient by itself: against the oracle and, bit for bit, the batched call, which takes other tiles (and where
     those add in another order, so does the call by itself)."""
