@@ -55,7 +55,8 @@ __device__ __forceinline__ uint4 mask8(uint4 v, bool ok, const Mask8& k) {
 // LDS reads issued as inline assembly are ordered only by explicit waits: the compiler neither moves them nor
 // adds waits of its own.  The result registers must not be touched before lds_wait() has been applied to them.
 // Waits until at most N of this wave's LDS reads are outstanding (they return in order) and makes `first`
-// depend on the wait; lds_tie() extends the dependence to further registers.
+// depend on the wait; lds_tie() extends the dependence to further registers, also to those whose values nobody
+// wants: a read in flight would overwrite whatever else the compiler had put there.
 template <int N, typename V>
 __device__ __forceinline__ void lds_wait(V& first) {
     static_assert(N >= 0 && N < 16, "lgkmcnt range");
@@ -2155,7 +2156,16 @@ __device__ __forceinline__ void wgrad_dl_body(const WgradArgs& a, const int lin,
             }
         }
     }
-    if constexpr (AHEAD) lds_wait<0>(fx[0][0][0]);
+    if constexpr (AHEAD) {  // the fragments of the step past the end
+        lds_wait<0>(fx[0][0][0]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) lds_tie(fx[i >> 1][tm][i & 1]);
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) lds_tie(fy[i >> 1][tn][i & 1]);
+        }
+    }
     wait_vmcnt<0>();  // the loads issued past the end have landed before LDS is reused or the wave ends
 
     if constexpr (KSPLIT > 1) {
@@ -2466,7 +2476,16 @@ __device__ __forceinline__ bool wgrad_row3_body(const WgradArgs& a, const int li
             });
         }
     }
-    lds_wait<0>(fx[0][0]);
+    lds_wait<0>(fx[0][0]);  // the fragments of the step past the end
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s) lds_tie(fx[s][h]);
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int o = 0; o < 2; ++o) lds_tie(fy[b][o][h]);
+    }
     wait_vmcnt<0>();  // the loads issued past the end have landed before LDS is reused
 
     // ---- the four position groups are added tap by tap, the middle one last: every wave parks its two blocks of 32 input x 32 output
