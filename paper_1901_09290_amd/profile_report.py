@@ -74,7 +74,8 @@ MAIN_FAMILIES = ("k_igemm_dl", "k_igemm_small", "k_wgrad_dl", "k_wgrad_dl_multi"
 
 
 def family(n: str) -> Optional[str]:
-    return FAMILIES.get(re.match(r"\w*", n).group().rstrip("0123456789"))
+    kernel = re.match(r"\w*", n).group()
+    return FAMILIES.get(kernel) or FAMILIES.get(kernel.rstrip("0123456789"))
 
 
 def load_trace(path: str) -> List[dict]:

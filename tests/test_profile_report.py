@@ -83,6 +83,8 @@ def test_every_kernel_of_the_convolution_calls_has_a_family():
     kernels = {k for pair in kernels for k in pair if k}
     assert len(kernels) >= 15 and kernels == set(pr.FAMILIES)
     assert set(pr.MAIN_FAMILIES) <= set(pr.FAMILIES.values())
+    for name, counted_under in pr.FAMILIES.items():
+        assert pr.family(name) == pr.family(name + "<5, true>") == counted_under, name
     assert pr.family("k_igemm_small<64, 64, 1, 3>") == "k_igemm_small" and pr.family("k_wgrad_reduce4<true>") == "k_wgrad_reduce"
     assert pr.family("k_wgrad_dl_multi") == "k_wgrad_dl_multi" and pr.family("k_wgrad_reduce_multi") == "k_wgrad_reduce"
     assert pr.family("k_bn_sums<0>") is None and pr.family("at::native::x") is None
