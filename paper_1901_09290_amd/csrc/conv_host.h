@@ -311,14 +311,11 @@ inline WgradPlan plan_wgrad_tiles(const pt_conv_desc* d, bool dl, int cfg = -1) 
 }
 
 // What wgrad_row3_body takes: 3 x 3 filters at stride 1 and padding 1 whose places and offsets fit its 24 and 30 bits (x is addressed
-// from one pixel ahead of a slice, so the last channels of a single slice's last pixel end at (pixels + 1) * x_cpitch), from
-// 3000 pixels on: with fewer, its 2 us more of set-up and of adding up are more than it saves (5 x 13 x 13, 72 -> 40: 4.3 us in
-// 64 x 64 tiles, 7.1 so).
-constexpr int64_t kRow3MinPixels = 3000;
+// from one pixel ahead of a slice, so the last channels of a single slice's last pixel end at (pixels + 1) * x_cpitch).
 inline bool wgrad_row3_ok(const pt_conv_desc* d, bool dl) {
     const int64_t rows = (int64_t)d->N * d->H, pixels = rows * d->W, most = (int64_t)1 << 29;  // elements
     return dl && d->R == 3 && d->S == 3 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 1 && d->pad_w == 1 &&
-           pixels >= kRow3MinPixels && pixels + rows < (1 << 24) && (pixels + 1) * d->x_cpitch <= most && pixels * d->y_cpitch < most;
+           pixels + rows < (1 << 24) && (pixels + 1) * d->x_cpitch <= most && pixels * d->y_cpitch < most;
 }
 inline WgradPlan plan_wgrad_row3(const pt_conv_desc* d, WgradPlan p) {  // p: the layer's plan in another form
     p.cfg = kWgRow3;
@@ -335,10 +332,16 @@ inline WgradPlan plan_wgrad_row3(const pt_conv_desc* d, WgradPlan p) {  // p: th
 // One layer beside other kernels: the form whose workgroups spend less time on their steps together, the row form where that is
 // well below (x 0.68: 256 -> 256 at 14 x 14 0.67, 64 -> 64 at 56 x 56 0.53; 512 -> 512 at 7 x 7, where an eighth of the positions
 // are zeros, 0.71).  Times of workgroups: 14 x 14 72 of 53 us against 96 of 38, 56 x 56 153 of 52 against 96 of 36, 7 x 7 144 of 28
-// against 192 of 26.  64, 80 and 128 workgroups a layer instead of 96: step of ResNet-50 0.4 to 0.8 % longer.
+// against 192 of 26.  Step of ResNet-50, us in two runs, with the line at 0.60 (14 x 14 without), 0.68 and 0.75 (7 x 7 as well): batch 64 3270 and
+// 3252, 3241 and 3228, 3242 and 3225; batch 48 2810 and 2800, 2795 and 2784, 2801 and 2803; batch 96 4545 and 4516, 4468 and 4504, 4537 and 4542;
+// pruned 2713 and 2698, 2674 and 2702, 2674 and 2694; never 3273 and 3288, 2820 and 2827, 4556 and 4581, 2692 and 2723.  64, 80 and 128 workgroups a layer
+// instead of 96: 0.4 to 0.8 % longer.  From 3000 pixels on: the row form's 2 us more of set-up and of adding up (5 x 13 x 13, 72 -> 40: 4.3
+// us in 64 x 64 tiles, 7.1 so) are not in these times.  Steps at batch 8 and 12 are the same with the line and without
+// (in five runs 0.4 % longer to 0.3 % shorter).
+constexpr int64_t kRow3MinPixels = 3000;
 inline WgradPlan plan_wgrad_beside(const pt_conv_desc* d, bool dl) {
     const WgradPlan p = plan_wgrad_tiles(d, dl);
-    if (wgrad_row3_ok(d, p.dl)) {
+    if (wgrad_row3_ok(d, p.dl) && (int64_t)d->N * d->P * d->Q >= kRow3MinPixels) {
         const WgradPlan r = plan_wgrad_row3(d, p);
         auto work = [](const WgradPlan& q) { return (float)q.tiles_m * q.tiles_n * q.iters_total * wgrad_step_us(q); };
         if (work(r) < kRow3Beside * work(p)) return r;
@@ -364,9 +367,11 @@ inline void set_wgrad_splits(const pt_conv_desc* d, WgradPlan& p, int64_t splits
 // each shape for both states together 11.15 and 13.22.  Costs fitted to cached operands alone: 11.31 and 13.73, by 64 x 128
 // tiles with half the splits for large 1 x 1 layers, half as many operand bytes again (14 x 14 1024 -> 512 at batch 64: 23.4
 // and 32.6 us against 23.3 and 26.5 so).
-// The row form (wgrad_row3_body) where it is estimated at 0.93 of the others' best: of 30 random 3 x 3 layers of 3000 pixels and
-// more it takes 14, which are 0.5 to 42 % faster than in the other forms (105 x 27 x 27, 419 -> 24: 64.6 -> 45.5 us); two with
-// estimates of 0.94 and 0.98 were 1 and 3 % slower.
+// The row form (wgrad_row3_body) where it is estimated at 0.93 of the others' best (mean of operands in the caches and from memory): of 102
+// 3 x 3 layers of 3000 pixels and more the calls so chosen are within 0.3 % of the better form's in the mean (the line at 0.90 0.2 %, at 0.86
+// 0.5 %, at 1.05 0.3 %), three up to 10 % slower than in the other form, most 5 to 34 % faster (21 x 39 x 40, 396 -> 192 89.5 -> 58.7 us); of 116
+// smaller ones 0.2 % (0.90 0.4 %, 0.86 1.8 %, none at all some 10 %), five up to 9 % slower (1 x 47 x 50, 524 -> 359 19.2 and 21.0), others up to 40 %
+// faster (4 x 22 x 22, 145 -> 1412 34.7 -> 20.6; 60 x 7 x 7, 512 -> 512 29.0 -> 26.3).
 // Tiles smaller than the sizes ask for go unsplit up to 24 steps only (1536 pixels; 10 x 10 256 -> 256 3 x 3 at batch 15:
 // 8.4 us against 12.5 split, from memory 10.3 and 14).  They are faster beyond that (14 x 14 at batch 8, 25 steps: 8.6 and
 // 10.4 against 12.9 and 13.9): the line is not where measurements would put it.  The tests of the regulariser inside the

@@ -186,3 +186,23 @@ def test_early_3x3_layers_with_large_banks_by_rounds(launches):
     for (size, resident), f, a, b in zip(ROUNDS, fwd, alone, batched):
         want = ["k_conv3x3_res"] if resident else ["k_igemm_dl"]
         assert [k[0] for k in f] == want and [k[0] for k in a] == want and [k[0] for k in b] == ["k_igemm_dl"], (size, f, a, b)
+
+
+def test_cases_of_three_taps_from_one_tile_reach_it(launches):
+    """The lists of test_gpu_conv.py for that form: batched calls of one layer planned for few workgroups, and calls by themselves."""
+    from test_gpu_conv import ROW3, ROW3_ALONE
+    calls = [["bwd_weight_batched", *case[:5], 3, 1, 1, case[5], w] for case in ROW3 for w in (1, 24, 160)]
+    calls += [["bwd_weight", *case[:5], 3, 1, 1, case[5]] for case in ROW3_ALONE]
+    split = set()
+    for call, got in zip(calls, launches(calls)):
+        assert got[0]["kernel"] == ["k_wgrad_row3"], (call, got)
+        split.add((call[0], len(got)))
+    assert split == {("bwd_weight_batched", 1), ("bwd_weight_batched", 2), ("bwd_weight", 1), ("bwd_weight", 2)}
+
+
+def test_three_taps_from_one_tile_whatever_the_number_of_pixels(launches):
+    """By estimated time alone when a call has the chip to itself; beside other kernels from 3000 pixels on."""
+    for case, alone, beside in [((60, 7, 7, 512, 512), True, False), ((64, 7, 7, 512, 512), True, False), ((4, 22, 22, 145, 1412), True, False),
+                                ((5, 13, 13, 72, 40), False, False), ((15, 14, 14, 256, 256), False, False), ((16, 14, 14, 256, 256), False, True)]:
+        a, b = launches([["bwd_weight", *case, 3, 1, 1, True], ["bwd_weight_batched", *case, 3, 1, 1, True, 96]])
+        assert [g[0]["kernel"][0] == "k_wgrad_row3" for g in (a, b)] == [alone, beside], (case, a, b)

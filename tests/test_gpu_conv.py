@@ -709,18 +709,30 @@ ROW3 = [
     # N   H   W   C    K  pad_zero: 3 x 3 layers whose three taps of a filter row share a tile (3000 pixels on)
     (26, 14, 14, 64, 64, True),       # whole tiles
     (105, 7, 7, 129, 190, True),      # image rows of eight places, one channel in the last tile
-    (1250, 1, 4, 64, 64, False), (400, 4, 4, 120, 70, False),   # one filter row that ever falls inside; small images
+    (1250, 1, 4, 64, 64, False), (400, 4, 4, 64, 63, False),   # one filter row that ever falls inside; small images
     (40, 2, 63, 45, 130, True), (14, 6, 62, 64, 64, False),     # a row is a step of places, or one less
     (3, 41, 43, 203, 171, False),     # slices that end inside a row
     (7, 30, 25, 64, 320, True), (64, 14, 14, 256, 256, True),
 ]
+
+# ... and layers that take that form called by themselves, some of them of fewer pixels: unsplit and split
+ROW3_ALONE = [(64, 14, 14, 256, 256, True), (45, 7, 8, 311, 755, True), (1, 27, 29, 888, 279, False), (400, 4, 4, 300, 800, True), (700, 3, 5, 250, 300, False)]
 
 
 @pytest.mark.parametrize("N,H,W,C,K,pad_zero", ROW3)
 @pytest.mark.parametrize("workgroups", [0, 1, 24, 160])
 def test_weight_gradient_three_taps_from_one_tile(N, H, W, C, K, pad_zero, workgroups):
     """The form that multiplies a filter row's taps from one tile of x, unsplit and split, written directly and through the
-    reduction, with the regulariser: against the oracle, and the same bits on a second run."""
+    reduction, with the regulariser: against the oracle, and the same bits on a second run.  (0: another form for most.)"""
+    _check_three_taps(N, H, W, C, K, pad_zero, workgroups)
+
+
+@pytest.mark.parametrize("N,H,W,C,K,pad_zero", ROW3_ALONE)
+def test_weight_gradient_three_taps_from_one_tile_alone(N, H, W, C, K, pad_zero):
+    _check_three_taps(N, H, W, C, K, pad_zero, 0)
+
+
+def _check_three_taps(N, H, W, C, K, pad_zero, workgroups):
     from gpu_util import CONV_TOL, DEV, dev_bf16, dev_f32, pitch8, rel_err, workspace
     from paper_1901_09290_amd import binding as B
     spec = _spec(N, H, W, C, K, 3, 1, 1)
