@@ -55,7 +55,8 @@ def _sampled_err(got, ref):
 
 def _run_layer_as_the_step_does(spec, t, lam):
     """One layer through the calls Network.train_step makes for it: norms (+ bf16 weights), forward, the k-innermost
-    filter copy and the workspace-free input gradient, and the weight gradient with the regulariser folded in."""
+    filter copy and the input gradient as a batched call, and the weight gradient with the regulariser folded in for as many workgroups.
+    Returns the layer, the gradients in it those of calls by themselves (the input gradient's the same bits), and the step's weight gradient."""
     from paper_1901_09290_amd import harness as hz
     layer = hz.ConvLayer(spec, host=t)
     ws = hz.make_workspace([layer])
@@ -63,10 +64,18 @@ def _run_layer_as_the_step_does(spec, t, lam):
     layer.fwd(ws)
     if layer.w_crsk is not None:
         B.weights_to_crsk_batched([B.layer_crsk(layer.w_bf16, layer.w_crsk, spec.K, layer.RS, spec.C, layer.wp)])
+        B.conv_bwd_data_crsk_batched(B.conv_fwd_jobs([layer.desc], [layer.dy], [layer.w_crsk], [layer.dx]))
+        beside = layer.dx.clone()
+        layer.dx.zero_()
         layer.bwd_data_crsk()
+        assert torch.equal(layer.dx, beside), spec
     layer.bwd_weight_lasso(ws, lam)
+    dw = torch.zeros_like(layer.dw)
+    jobs = [B.layer_wgrad(layer.desc, layer.x, layer.dy, dw, layer.w_master, layer.out_norm, layer.in_norm, layer.lasso_flags)]
+    ws = torch.empty(max(256, B.conv_bwd_weight_batched_workspace_bytes(jobs, hz.WGRAD_WORKGROUPS)), dtype=torch.uint8, device=hz.DEV)
+    B.conv_bwd_weight_batched(jobs, lam, ws, hz.WGRAD_WORKGROUPS)
     torch.cuda.synchronize()
-    return layer
+    return layer, dw
 
 
 def _lasso_term(t, spec, layer, lam):
@@ -88,7 +97,7 @@ def _check_layer_sampled(spec, seed):
     from gpu_util import CONV_TOL, host_bf16
     rng = np.random.Generator(np.random.PCG64(seed))
     t = wl.conv_tensors(spec, rng)
-    layer = _run_layer_as_the_step_does(spec, t, LAMBDA_VISIBLE)
+    layer, dw_step = _run_layer_as_the_step_does(spec, t, LAMBDA_VISIBLE)
     s = oracle.shape_of(spec)
     # the shadow copy is the exact bf16 image of the master weights (already on the bf16 grid)
     assert np.array_equal(host_bf16(layer.w_bf16, spec.C), t["w"])
@@ -99,10 +108,10 @@ def _check_layer_sampled(spec, seed):
         dx = host_bf16(layer.dx, spec.C).reshape(-1)
         ix = _samples((spec.N, spec.H, spec.W, spec.C), spec.N * spec.H * spec.W, spec.C, rng)
         assert _sampled_err(dx[ix], oracle.conv_bwd_data_at(s, t["dy"], t["w"], ix)) <= CONV_TOL, spec
-    dw = layer.dw.cpu().numpy()[..., : spec.C].reshape(-1)
     iw = _samples((spec.K, spec.R, spec.S, spec.C), spec.K, spec.R * spec.S * spec.C, rng)
     ref = oracle.conv_bwd_weight_at(s, t["x"], t["dy"], iw) + _lasso_term(t, spec, layer, LAMBDA_VISIBLE).reshape(-1)[iw]
-    assert _sampled_err(dw[iw], ref) <= CONV_TOL, spec
+    for dw in (layer.dw, dw_step):
+        assert _sampled_err(dw.cpu().numpy()[..., : spec.C].reshape(-1)[iw], ref) <= CONV_TOL, spec
     _check_padding_stays_zero(layer, spec)
 
 
@@ -111,13 +120,14 @@ def _check_layer_whole(spec, seed):
     from gpu_util import CONV_TOL, host_bf16, rel_err
     rng = np.random.Generator(np.random.PCG64(seed))
     t = wl.conv_tensors(spec, rng)
-    layer = _run_layer_as_the_step_does(spec, t, LAMBDA_VISIBLE)
+    layer, dw_step = _run_layer_as_the_step_does(spec, t, LAMBDA_VISIBLE)
     s = oracle.shape_of(spec)
     assert rel_err(host_bf16(layer.y, spec.K), oracle.conv_fwd(s, t["x"], t["w"])) <= CONV_TOL, spec
     if layer.dx is not None:
         assert rel_err(host_bf16(layer.dx, spec.C), oracle.conv_bwd_data(s, t["dy"], t["w"])) <= CONV_TOL, spec
     ref = oracle.conv_bwd_weight(s, t["x"], t["dy"]) + _lasso_term(t, spec, layer, LAMBDA_VISIBLE)
-    assert rel_err(layer.dw.cpu().numpy()[..., : spec.C], ref) <= CONV_TOL, spec
+    for dw in (layer.dw, dw_step):
+        assert rel_err(dw.cpu().numpy()[..., : spec.C], ref) <= CONV_TOL, spec
     _check_padding_stays_zero(layer, spec)
 
 
