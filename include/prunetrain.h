@@ -89,9 +89,10 @@ int32_t pt_conv_bwd_weight_workspace_bytes(const pt_conv_desc* d, size_t* bytes)
 /* y[n,p,q,k] = sum_{r,s,c} x[n, p*stride_h - pad_h + r, q*stride_w - pad_w + s, c] * w[k,r,s,c].
  * x, w bf16; y bf16 (fp32 accumulator rounded once). ws: device scratch of ws_bytes (256-byte aligned).
  * An image-like first layer under PT_CONV_PAD_ZERO (C <= 4 at x_cpitch = w_cpitch = 8, y_cpitch a multiple of 8,
- * filter <= 8 x 8, stride 1 or 2, 16-byte aligned tensors) takes a kernel of its own, and so does a 3 x 3 filter at
- * stride 1 and padding 1 with at most 64 channels on either side (pitches multiples of 8, channel counts multiples
- * of 8 or PT_CONV_PAD_ZERO); same results to the same tolerance. */
+ * filter <= 8 x 8, stride 1 or 2, 16-byte aligned tensors) takes a kernel of its own; same results to the same tolerance.
+ * So does a 3 x 3 filter at stride 1 and padding 1 with at most 64 channels on either side (pitches multiples of 8,
+ * channel counts multiples of 8 or PT_CONV_PAD_ZERO), one of more than 3072 weights a tap where that kernel's tiles are
+ * fewer rounds; same bits in either. */
 int32_t pt_conv_fwd(const pt_conv_desc* d, const uint16_t* x, const uint16_t* w, uint16_t* y, void* ws,
                     size_t ws_bytes, void* stream);
 
@@ -137,10 +138,11 @@ int32_t pt_conv_bwd_data_crsk_batched(const pt_conv_desc* descs, const uint16_t*
 
 /* dw[k,r,s,c] = sum_{n,p,q} dy[n,p,q,k] * x[n, p*stride_h - pad_h + r, q*stride_w - pad_w + s, c]  (Eq. 4;
  * plain sum over the mini-batch).  x, dy bf16; dw fp32 [K][R][S][w_cpitch].  The reduction is split
- * over workgroups into ws and combined in a fixed order: results are run-to-run identical.  An image-like first
- * layer (C <= 4 at x_cpitch 8, K <= 64, filter <= 8 x 8, stride 1 or 2, 16-byte aligned x and dy) takes a kernel of
- * its own, which always writes one slab of partial sums per workgroup: ws must not be NULL there (the workspace query
- * says how much). */
+ * over workgroups into ws and combined in a fixed order: results are run-to-run identical.  A value of dy that is not
+ * finite also reaches taps that lie outside the image for it (0 times it); in an image-like first layer so may one of x.
+ * An image-like first layer (C <= 4 at x_cpitch 8, K <= 64, filter <= 8 x 8, stride 1 or 2, 16-byte aligned x and dy)
+ * takes a kernel of its own, which always writes one slab of partial sums per workgroup: ws must not be NULL there (the
+ * workspace query says how much). */
 int32_t pt_conv_bwd_weight(const pt_conv_desc* d, const uint16_t* x, const uint16_t* dy, float* dw, void* ws,
                            size_t ws_bytes, void* stream);
 
