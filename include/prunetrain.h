@@ -131,7 +131,8 @@ int32_t pt_conv_bwd_data_crsk(const pt_conv_desc* d, const uint16_t* dy, const u
 /* n independent input gradients in one call (e.g. those of a residual block's last convolution and of the block's
  * shortcut convolution, which both start from the gradient of the block's output): same results as n calls of
  * pt_conv_bwd_data_crsk, sharing launches as pt_conv_fwd_batched does.  A call by itself may take kernels that leave no room
- * beside them on a CU; a batched call, also of one layer, does not: the one for gradients beside other streams' kernels.
+ * beside them on a CU; a batched call, also of one layer, does so only for 3 x 3 filters of up to 3072 weights a tap: the one
+ * for gradients beside other streams' kernels.
  * Host arrays of n entries. */
 int32_t pt_conv_bwd_data_crsk_batched(const pt_conv_desc* descs, const uint16_t* const* dy, const uint16_t* const* wt,
                                       uint16_t* const* dx, int32_t n, void* stream);
